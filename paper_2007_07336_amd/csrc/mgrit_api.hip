@@ -164,6 +164,7 @@ struct Solver {
   float* g[MGRIT_MAX_LEVELS];
   float* R[MGRIT_MAX_LEVELS];
   bool plain_rhs = false;              // nested start: every level carries the right-hand side (first, 0, .., 0)
+  bool want_norm = false;              // somebody reads the residual norm of the cycles
   const void* W;
   int wn = 0, wn_fc = 0;               // adjoint on the caller's dense / fully connected weights as stored: W[k][n]
   const float* bias;
@@ -221,7 +222,7 @@ struct Solver {
   StepArgs fc_args(const StepArgs& a, long long g0, long long per) const {
     auto sub = [&](const PtMap& mp) { return PtMap{mp.base + g0 * mp.stride, mp.stride * per}; };
     StepArgs d = a;
-    d.xm = sub(a.xm); d.dm = sub(a.dm); d.om = sub(a.om); d.e1m = sub(a.e1m); d.e2m = sub(a.e2m);
+    d.xm = sub(a.xm); d.dm = sub(a.dm); d.om = sub(a.om); d.e1m = sub(a.e1m); d.rm = sub(a.rm);
     d.wm = PtMap{(a.wm.base + g0 * a.wm.stride) / pl.fcP, a.wm.stride * per / pl.fcP};
     d.W = Wfc; d.wn = wn_fc; d.bias = a.bias ? bfc : nullptr;
     d.M = pl.B; d.Nf = (int)pl.dfc; d.K = (int)pl.dfc; d.Himg = 0; d.Wimg = 0; d.TH = 0;
@@ -255,13 +256,16 @@ struct Solver {
       chk(launch_step(d, MGRIT_LAYER_DENSE, p->dtype, cnt, s));
     }
   }
-  // X[js] = Phi(X[js-1]) + g[js] for js = js0 + gi*jstride        (relaxation, coarsest solve)
-  void propagate(int l, long long js0, long long jstride, int groups) {
+  // states out[om] = Phi(in[im]) + g[l][js] for js = js0 + gi*jstride     (relaxation, coarsest solve)
+  void step(int l, long long js0, long long jstride, int groups, const float* in, PtMap im, float* out, PtMap om) {
     StepArgs a = base_args(l, js0, jstride);
-    a.X = X[l]; a.xm = pm(l, js0 - 1, jstride);
-    a.Out = X[l]; a.om = pm(l, js0, jstride);
+    a.X = in; a.xm = im;
+    a.Out = out; a.om = om;
     if (g[l] && !plain_rhs) { a.E1 = g[l]; a.e1m = PtMap{js0, jstride}; a.c1 = 1.0f; }
     launch(a, groups);
+  }
+  void propagate(int l, long long js0, long long jstride, int groups) {
+    step(l, js0, jstride, groups, X[l], pm(l, js0 - 1, jstride), X[l], pm(l, js0, jstride));
   }
   // One fused launch per F-relaxation sweep where it pays: dense layers of a supported width or convolution
   // layers of at most 16 float channels on images that fit one workgroup, at least two steps per interval, and
@@ -274,7 +278,13 @@ struct Solver {
     if (!sweep_supported(p->q, p->dtype)) return false;
     return sweep_blocks(pl.M, pl.Nl[l + 1]) >= 128;
   }
-  void f_relax(int l) {                                        // Sec. III-C, Fig. 3
+  // Where the current values of a level's C-points 0, m, 2m, .. are: point js = j m at p[m.base + j m.stride].
+  // They do not live in the level's own array: the relaxation leaves them in R[l], the coarse solve in X[l + 1]
+  // (it solves for their corrected values: with injection, U_C + (V_H - U_H) is V_H), and every consumer reads them
+  // there.  The level's own array receives them once, when the level is closed.
+  struct CPoints { const float* p; PtMap m; };
+
+  void f_relax(int l, const CPoints& c) {                      // Sec. III-C, Fig. 3
     const int Nc = pl.Nl[l + 1];
     const int tail = pl.Nl[l] - Nc * p->m;                     // F-points behind the last C-point (< m)
     if (use_sweep(l)) {
@@ -282,7 +292,7 @@ struct Solver {
       memset(&a, 0, sizeof(a));
       const long long mp = pl.mpow[l];
       const PtMap unit = pm(l, 0, 1);                          // storage index of sweep point js = base + js * stride
-      a.S = X[l]; a.sm = pm(l, 0, p->m);
+      a.S = c.p; a.sm = c.m;
       a.X = X[l]; a.xb = unit.base; a.xs = unit.stride * p->m; a.xk = unit.stride;
       if (g[l] && !plain_rhs) { a.G = g[l]; a.gb = 0; a.gs = p->m; }
       a.W = W; a.wn = wn; a.bias = bias; a.Dm = Dm;
@@ -296,73 +306,70 @@ struct Solver {
       } else if (err == hipSuccess) {
         chk(launch_sweep(a, p->dtype, s));
       }
-      for (int k = 1; k <= tail; ++k) propagate(l, (long long)Nc * p->m + k, p->m, 1);
+      if (tail > 0) step(l, (long long)Nc * p->m + 1, p->m, 1, c.p, PtMap{c.m.base + Nc * c.m.stride, 0}, X[l], pm(l, (long long)Nc * p->m + 1, 1));
+      for (int k = 2; k <= tail; ++k) propagate(l, (long long)Nc * p->m + k, p->m, 1);
       return;
     }
-    for (int k = 1; k < p->m; ++k) propagate(l, k, p->m, Nc + (k <= tail ? 1 : 0));
+    step(l, 1, p->m, Nc + (1 <= tail ? 1 : 0), c.p, c.m, X[l], pm(l, 1, p->m));
+    for (int k = 2; k < p->m; ++k) propagate(l, k, p->m, Nc + (k <= tail ? 1 : 0));
   }
-  void c_relax(int l) { propagate(l, p->m, p->m, pl.Nl[l + 1]); }
+  // The level's own array, complete: C-points from the level below, F-points by F-relaxation (Alg. 1 ends with the
+  // C-points; the F-layers follow by F-relaxation, Sec. III-C).
+  void close(int l) {
+    chk(launch_copy_points(X[l], pm(l, 0, p->m), X[l + 1], PtMap{0, 1}, pl.E, pl.Nl[l + 1] + 1, s));
+    f_relax(l, CPoints{X[l + 1], PtMap{0, 1}});
+  }
 
   // Nested-iteration start: the coarsest level's own equation is solved in sequence from the known
   // value; going up, the C-points of a level take the coarser level's values and (on the middle
-  // levels) the F-points follow by F-relaxation.  The fine level's F-points are left to the opening
-  // relaxation of the first cycle.
-  void nested_start(const float* first) {
-    const int m = p->m;
+  // levels) the F-points follow by F-relaxation.  The fine level's C-points are then level 1's values.
+  void nested_start() {
     plain_rhs = true;
     const int lc = pl.L - 1;
-    chk(launch_copy_points(X[lc], pm(lc, 0, 0), first, PtMap{0, 0}, pl.E, 1, s));
     for (int j = 1; j <= pl.Nl[lc]; ++j) propagate(lc, j, 1, 1);
-    for (int l = lc - 1; l >= 0; --l) {
-      chk(launch_copy_points(X[l], pm(l, 0, m), X[l + 1], PtMap{0, 1}, pl.E, pl.Nl[l + 1] + 1, s));
-      if (l > 0) f_relax(l);
-    }
+    for (int l = lc - 1; l >= 1; --l) close(l);
     plain_rhs = false;
   }
 
-  void cycle(int l, int iter, bool skip_opening_relax) {
+  // One visit of level l, up to the new values of its C-points in X[l + 1] (of all its points on the coarsest level).
+  // c: the C-points' current values (unused on the coarsest level).
+  void cycle(int l, int iter, CPoints c) {
     const int m = p->m;
     if (l == pl.L - 1) {                                        // coarsest level: serial solve
-      // X[l][0] already holds the known value: the injection copied it together with the other points
-      for (int j = 1; j <= pl.Nl[l]; ++j) propagate(l, j, 1, 1);
+      for (int j = 1; j <= pl.Nl[l]; ++j) propagate(l, j, 1, 1);   // X[l][0] holds the known value
       return;
     }
     const int Nc = pl.Nl[l + 1];
-    if (!skip_opening_relax) f_relax(l);                        // Alg. 1 step 1
-    if (p->relax == MGRIT_RELAX_FCF) { c_relax(l); f_relax(l); }
-    {                                                           // residual at the C-points, Eq. (19)
-      StepArgs a = base_args(l, m, m);
-      a.X = X[l]; a.xm = pm(l, m - 1, m);
-      a.Out = R[l]; a.om = PtMap{1, 1};
-      a.E1 = X[l]; a.e1m = pm(l, m, m); a.c1 = -1.0f;
-      if (g[l]) { a.E2 = g[l]; a.e2m = PtMap{m, m}; a.c2 = 1.0f; }
-      if (l == 0) a.norm_partial = partial;
-      launch(a, Nc);
-      // Alg. 1 step 2: injection of the C-points (the residual of point 0 is identically zero); on the fine
-      // level the same launch also sums the norm partials of the residual launch (Alg. 1 step 6)
-      if (l == 0) {
-        const int nb = launch_blocks(a, Nc);
-        const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(Nc + 1) * (double)pl.E) : 1.0;
-        chk(launch_copy_points_norm(X[l + 1], PtMap{0, 1}, X[l], pm(l, 0, m), pl.E, Nc + 1, partial, nb, scale,
-                                    hist_dev + iter, s));
-      } else {
-        chk(launch_copy_points(X[l + 1], PtMap{0, 1}, X[l], pm(l, 0, m), pl.E, Nc + 1, s));
-      }
+    f_relax(l, c);                                              // Alg. 1 step 1
+    if (p->relax == MGRIT_RELAX_FCF) {
+      step(l, m, m, Nc, X[l], pm(l, m - 1, m), R[l], PtMap{1, 1});
+      c = CPoints{R[l], PtMap{0, 1}};
+      f_relax(l, c);
     }
-    // g[l+1][0] = U[0] + R[0] is the known value at point 0 in every cycle (R[0] = 0): set once per solve
-    {                                                           // Alg. 1 step 3: S_H = L_H(U_H) + R_H
+    // Alg. 1 steps 2 and 3.  With P_j the layer step that lands on C-point j (plus the level's right-hand side) the
+    // residual there is R_j = P_j - U_j, Eq. (19), and the coarse right-hand side
+    // S_H = L_H(U_H) + R_H = U_j - Phi_H(U_{j-1}) + P_j - U_j = P_j - Phi_H(U_{j-1}): the residual itself is needed for
+    // its norm only, which the second launch takes of E1 - Ref.
+    step(l, m, m, Nc, X[l], pm(l, m - 1, m), g[l + 1], PtMap{1, 1});
+    {
       StepArgs a = base_args(l + 1, 1, 1);
-      a.X = X[l + 1]; a.xm = PtMap{0, 1};
+      a.X = c.p; a.xm = c.m;
       a.Out = g[l + 1]; a.om = PtMap{1, 1};
       a.sp = -1.0f;
-      a.E1 = X[l + 1]; a.e1m = PtMap{1, 1}; a.c1 = 1.0f;
-      a.E2 = R[l]; a.e2m = PtMap{1, 1}; a.c2 = 1.0f;
+      a.E1 = g[l + 1]; a.e1m = PtMap{1, 1}; a.c1 = 1.0f;        // in place, element by element
+      const bool norm = l == 0 && want_norm;
+      if (norm) {
+        a.Ref = c.p; a.rm = PtMap{c.m.base + c.m.stride, c.m.stride};
+        a.norm_partial = partial;
+      }
       launch(a, Nc);
+      if (norm) {
+        const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(Nc + 1) * (double)pl.E) : 1.0;
+        chk(launch_norm_final(partial, launch_blocks(a, Nc), scale, hist_dev + iter, s));
+      }
     }
-    cycle(l + 1, iter, false);                                  // solve for V_H (in place of U_H)
-    // Alg. 1 steps 4, 5: C-points += V_H - U_H, where U_H is still held by the C-points themselves
-    chk(launch_correct(X[l], pm(l, m, m), X[l + 1], PtMap{1, 1}, pl.E, Nc, s));
-    f_relax(l);
+    cycle(l + 1, iter, CPoints{c.p, PtMap{c.m.base, c.m.stride * m}});   // V_H, Alg. 1 steps 3 to 5
+    if (l + 1 < pl.L - 1) close(l + 1);
   }
 };
 
@@ -377,26 +384,40 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
   const mgrit_problem_t* p = sv.p;
   const Plan& pl = sv.pl;
   const int m = p->m;
-  // known value at sweep point 0 and initial guess of the C-points
+  // the known value, in every array that holds sweep point 0, and the initial guess of the C-points
+  float* zero_pt[2 * MGRIT_MAX_LEVELS];
+  int nz = 0;
+  Solver::CPoints c{first, PtMap{0, 0}};                                  // MGRIT_INIT_COPY: `first` everywhere
+  if (pl.L == 1) {
+    zero_pt[nz++] = sv.X[0] + sv.pm(0, 0, 0).base * pl.E;
+  } else {
+    zero_pt[nz++] = sv.X[pl.L - 1];
+    for (int l = 0; l + 1 < pl.L && p->relax == MGRIT_RELAX_FCF; ++l) zero_pt[nz++] = sv.R[l];
+    if (p->init == MGRIT_INIT_ZERO || p->init == MGRIT_INIT_USER) {
+      c = Solver::CPoints{sv.X[0], sv.pm(0, 0, m)};
+      zero_pt[nz++] = sv.X[0] + c.m.base * pl.E;
+    }
+  }
+  sv.chk(launch_spread_state(zero_pt, nz, first, pl.E, sv.s));
   if (pl.L > 1 && p->init == MGRIT_INIT_ZERO)
     sv.chk(launch_zero_points(sv.X[0], sv.pm(0, m, m), pl.E, pl.Nl[1], sv.s));
-  if (pl.L > 1 && p->init == MGRIT_INIT_COPY)
-    sv.chk(launch_copy_points(sv.X[0], sv.pm(0, m, m), first, PtMap{0, 0}, pl.E, pl.Nl[1], sv.s));
-  sv.chk(launch_copy_points(sv.X[0], sv.pm(0, 0, 0), first, PtMap{0, 0}, pl.E, 1, sv.s));
-  for (int l = 1; l < pl.L; ++l)       // right-hand side of point 0 on the coarse levels: the known value
-    sv.chk(launch_copy_points(sv.g[l], PtMap{0, 0}, first, PtMap{0, 0}, pl.E, 1, sv.s));
-  if (pl.L > 1 && p->init == MGRIT_INIT_NESTED) sv.nested_start(first);
+  if (pl.L > 1 && p->init == MGRIT_INIT_NESTED) {
+    sv.nested_start();
+    c = Solver::CPoints{sv.X[1], PtMap{0, 1}};
+  }
+  sv.want_norm = p->tol > 0.0f || resnorm_hist;
 
   int iters = 0;
   int rc = MGRIT_OK;
   if (pl.L == 1) {
-    sv.cycle(0, 0, false);
+    sv.cycle(0, 0, c);
     iters = 1;
     if (resnorm_hist) resnorm_hist[0] = 0.0;
     if (sv.err == hipSuccess && (resnorm_hist || iters_done)) sv.chk(hipStreamSynchronize(sv.s));
   } else {
     for (int k = 0; k < p->max_iter && sv.err == hipSuccess; ++k) {
-      sv.cycle(0, k, k > 0);
+      sv.cycle(0, k, c);
+      c = Solver::CPoints{sv.X[1], PtMap{0, 1}};
       ++iters;
       if (p->tol > 0.0f) {
         double v = 0.0;
@@ -408,11 +429,12 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
         if (v <= (double)p->tol) break;
       }
     }
+    if (sv.err == hipSuccess) sv.close(0);
     if (!(p->tol > 0.0f) && resnorm_hist && sv.err == hipSuccess) {
       sv.chk(hipMemcpyAsync(resnorm_hist, sv.hist_dev, sizeof(double) * iters, hipMemcpyDeviceToHost, sv.s));
       sv.chk(hipStreamSynchronize(sv.s));
       if (sv.err == hipSuccess) rc = check_finite(resnorm_hist, iters);
-    } else if (iters_done && sv.err == hipSuccess) {
+    } else if ((iters_done || resnorm_hist) && sv.err == hipSuccess) {
       sv.chk(hipStreamSynchronize(sv.s));
     }
   }

@@ -18,7 +18,7 @@ struct PtMap {
 // own layer parameters,
 //     z   = A_layer * (Dm ? Dm .* X : X) + bias
 //     phi = X + hs * act(z)                                   (Sec. II, Eq. (1))
-//     out = sp * phi + c1 * E1 + c2 * E2                      (mode PHI)
+//     out = sp * phi + c1 * E1                                (mode PHI)
 //     out = act'(z)                                           (mode DACT)
 // which covers F-/C-relaxation, the C-point residual, the FAS right-hand side and the adjoint
 // steps (Sec. III-B, III-C).  If norm_partial is set, every workgroup also writes the sum of
@@ -33,7 +33,7 @@ struct StepArgs {
   const float* bias;               // [layers][Nf] or null (same layer index as W)
   float* Out;       PtMap om;      // may be null when only the norm is wanted
   const float* E1;  PtMap e1m;  float c1;
-  const float* E2;  PtMap e2m;  float c2;
+  const float* Ref; PtMap rm;      // norm only: subtracted from E1 (null: the norm is that of out)
   float sp, hs;
   float* norm_partial;
   int mode;                        // MODE_PHI / MODE_DACT
@@ -91,16 +91,13 @@ int        step_grid_blocks(const StepArgs& a, int layer_kind, int dtype, int gr
 int        conv_tile_rows(int Himg, int Wimg, int C, int dtype);            // TH, or 0 if unsupported
 hipError_t launch_grad(const GradArgs& a, int layer_kind, int dtype, int groups, hipStream_t s);
 
-// out[om(gi)] = in[im(gi)]                      (injection restriction, initial guesses)
+// out[om(gi)] = in[im(gi)]                      (C-points handed to the finer level)
 hipError_t launch_copy_points(float* out, PtMap om, const float* in, PtMap im, long long E, int groups,
                               hipStream_t s);
-hipError_t launch_copy_points_norm(float* out, PtMap om, const float* in, PtMap im, long long E, int groups,
-                                   const float* partial, int n, double scale, double* nout, hipStream_t s);
+// out[i] = in for n <= 32 states
+hipError_t launch_spread_state(float* const* out, int n, const float* in, long long E, hipStream_t s);
 // out[om(gi)] = 0
 hipError_t launch_zero_points(float* out, PtMap om, long long E, int groups, hipStream_t s);
-// U[um(gi)] += V[vm(gi)] - U[um(gi)]  evaluated as  U + (V - U)      (C-point correction)
-hipError_t launch_correct(float* U, PtMap um, const float* V, PtMap vm, long long E, int groups,
-                          hipStream_t s);
 // partial[slot0 + block] = sum over this block's chunk of (a - b)^2 ; returns blocks used
 hipError_t launch_diff_sq(const float* a, const float* b, long long n, float* partial, int* blocks_used,
                           hipStream_t s);

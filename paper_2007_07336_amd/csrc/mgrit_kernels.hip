@@ -276,11 +276,15 @@ __device__ __forceinline__ int logical_block() {
 
 // Fused epilogue shared by the dense and the conv kernel, one 32x32 accumulator block at a time:
 // register r of lane (g, c) holds row = row0 + 8*(r/4) + 4*g + r%4, column = col0 + c.
+__device__ __forceinline__ float sq_norm(float4 v) { return (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w); }
+__device__ __forceinline__ float sq_diff(float4 a, float4 b) {
+  return sq_norm(make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w));
+}
 struct EpiPtrs {
   const float* Xp;
   float* Op_;
   const float* E1p;
-  const float* E2p;
+  const float* Rp;
   const float* bp;
 };
 __device__ __forceinline__ EpiPtrs epi_ptrs(const StepArgs& a, int gi, long long layer) {
@@ -288,7 +292,7 @@ __device__ __forceinline__ EpiPtrs epi_ptrs(const StepArgs& a, int gi, long long
   e.Xp = a.X + (a.xm.base + gi * a.xm.stride) * a.E;
   e.Op_ = a.Out ? a.Out + (a.om.base + gi * a.om.stride) * a.E : nullptr;
   e.E1p = a.E1 ? a.E1 + (a.e1m.base + gi * a.e1m.stride) * a.E : nullptr;
-  e.E2p = a.E2 ? a.E2 + (a.e2m.base + gi * a.e2m.stride) * a.E : nullptr;
+  e.Rp = a.Ref ? a.Ref + (a.rm.base + gi * a.rm.stride) * a.E : nullptr;
   e.bp = a.bias ? a.bias + layer * a.Nf : nullptr;
   return e;
 }
@@ -329,7 +333,7 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
     stage_block(tm, stage);
 #pragma unroll
     for (int h0 = 0; h0 < NIT; h0 += HB) {
-      float4 z[HB], xv[HB], e1[HB], e2[HB];
+      float4 z[HB], xv[HB], e1[HB], rf[HB];
       unsigned off[HB];
 #pragma unroll
       for (int i = 0; i < HB; ++i) {
@@ -353,12 +357,9 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
 #pragma unroll
         for (int i = 0; i < HB; ++i) e1[i] = zero;
       }
-      if (e.E2p) {
+      if (e.Rp) {
 #pragma unroll
-        for (int i = 0; i < HB; ++i) e2[i] = *reinterpret_cast<const float4*>(e.E2p + off[i]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < HB; ++i) e2[i] = zero;
+        for (int i = 0; i < HB; ++i) rf[i] = *reinterpret_cast<const float4*>(e.Rp + off[i]);
       }
 #pragma unroll
       for (int i = 0; i < HB; ++i) {
@@ -367,10 +368,10 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
           o.x = act_prime_c<ACT>(z[i].x + bv.x); o.y = act_prime_c<ACT>(z[i].y + bv.y);
           o.z = act_prime_c<ACT>(z[i].z + bv.z); o.w = act_prime_c<ACT>(z[i].w + bv.w);
         } else {
-          o.x = a.sp * (xv[i].x + a.hs * act_fn_c<ACT>(z[i].x + bv.x)) + a.c1 * e1[i].x + a.c2 * e2[i].x;
-          o.y = a.sp * (xv[i].y + a.hs * act_fn_c<ACT>(z[i].y + bv.y)) + a.c1 * e1[i].y + a.c2 * e2[i].y;
-          o.z = a.sp * (xv[i].z + a.hs * act_fn_c<ACT>(z[i].z + bv.z)) + a.c1 * e1[i].z + a.c2 * e2[i].z;
-          o.w = a.sp * (xv[i].w + a.hs * act_fn_c<ACT>(z[i].w + bv.w)) + a.c1 * e1[i].w + a.c2 * e2[i].w;
+          o.x = a.sp * (xv[i].x + a.hs * act_fn_c<ACT>(z[i].x + bv.x)) + a.c1 * e1[i].x;
+          o.y = a.sp * (xv[i].y + a.hs * act_fn_c<ACT>(z[i].y + bv.y)) + a.c1 * e1[i].y;
+          o.z = a.sp * (xv[i].z + a.hs * act_fn_c<ACT>(z[i].z + bv.z)) + a.c1 * e1[i].z;
+          o.w = a.sp * (xv[i].w + a.hs * act_fn_c<ACT>(z[i].w + bv.w)) + a.c1 * e1[i].w;
         }
         xv[i] = o;
       }
@@ -385,7 +386,7 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
           } else if (e.Op_) {
             *reinterpret_cast<float4*>(e.Op_ + (unsigned)(row * a.Nf + col)) = xv[i];
           }
-          sq += (xv[i].x * xv[i].x + xv[i].y * xv[i].y) + (xv[i].z * xv[i].z + xv[i].w * xv[i].w);
+          sq += e.Rp ? sq_diff(e1[i], rf[i]) : sq_norm(xv[i]);
         }
       }
     }
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
       if (e.bp) bv = *reinterpret_cast<const float4*>(e.bp + col);
 #pragma unroll
       for (int h0 = 0; h0 < AP; h0 += 4) {
-        float4 z[4], e1[4], e2[4];
+        float4 z[4], e1[4], rf[4];
         unsigned off[4];
         const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -651,12 +652,9 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
 #pragma unroll
           for (int u = 0; u < 4; ++u) e1[u] = zero;
         }
-        if (e.E2p) {
+        if (e.Rp) {
 #pragma unroll
-          for (int u = 0; u < 4; ++u) e2[u] = *reinterpret_cast<const float4*>(e.E2p + off[u]);
-        } else {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) e2[u] = zero;
+          for (int u = 0; u < 4; ++u) rf[u] = *reinterpret_cast<const float4*>(e.Rp + off[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -666,10 +664,10 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
             o.x = act_prime_c<ACT>(z[u].x + bv.x); o.y = act_prime_c<ACT>(z[u].y + bv.y);
             o.z = act_prime_c<ACT>(z[u].z + bv.z); o.w = act_prime_c<ACT>(z[u].w + bv.w);
           } else {
-            o.x = a.sp * (xv.x + a.hs * act_fn_c<ACT>(z[u].x + bv.x)) + a.c1 * e1[u].x + a.c2 * e2[u].x;
-            o.y = a.sp * (xv.y + a.hs * act_fn_c<ACT>(z[u].y + bv.y)) + a.c1 * e1[u].y + a.c2 * e2[u].y;
-            o.z = a.sp * (xv.z + a.hs * act_fn_c<ACT>(z[u].z + bv.z)) + a.c1 * e1[u].z + a.c2 * e2[u].z;
-            o.w = a.sp * (xv.w + a.hs * act_fn_c<ACT>(z[u].w + bv.w)) + a.c1 * e1[u].w + a.c2 * e2[u].w;
+            o.x = a.sp * (xv.x + a.hs * act_fn_c<ACT>(z[u].x + bv.x)) + a.c1 * e1[u].x;
+            o.y = a.sp * (xv.y + a.hs * act_fn_c<ACT>(z[u].y + bv.y)) + a.c1 * e1[u].y;
+            o.z = a.sp * (xv.z + a.hs * act_fn_c<ACT>(z[u].z + bv.z)) + a.c1 * e1[u].z;
+            o.w = a.sp * (xv.w + a.hs * act_fn_c<ACT>(z[u].w + bv.w)) + a.c1 * e1[u].w;
           }
           if (dact && a.dbf16) {
             __bf16* ob = reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E;
@@ -677,7 +675,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
           } else if (e.Op_) {
             *reinterpret_cast<float4*>(e.Op_ + off[u]) = o;
           }
-          sq += (o.x * o.x + o.y * o.y) + (o.z * o.z + o.w * o.w);
+          sq += e.Rp ? sq_diff(e1[u], rf[u]) : sq_norm(o);
         }
       }
     }
@@ -764,10 +762,10 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
   const unsigned eoff = eok ? (unsigned)(erow * a.Nf + ecol) : 0u;
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
   const bool dact = a.mode == MODE_DACT;
-  float4 xv = zero, e1 = zero, e2 = zero, bv = zero;
+  float4 xv = zero, e1 = zero, rf = zero, bv = zero;
   if (!dact) xv = *reinterpret_cast<const float4*>(e.Xp + eoff);
   if (e.E1p) e1 = *reinterpret_cast<const float4*>(e.E1p + eoff);
-  if (e.E2p) e2 = *reinterpret_cast<const float4*>(e.E2p + eoff);
+  if (e.Rp) rf = *reinterpret_cast<const float4*>(e.Rp + eoff);
   if (e.bp && ecol < a.Nf) bv = *reinterpret_cast<const float4*>(e.bp + ecol);
 
   // ---- k loop.  MFMA lane (c, g) feeds row m0+c of the state and row n0+c of the weights, KL consecutive k
@@ -898,16 +896,16 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
     o.x = act_prime(z.x + bv.x, a.act); o.y = act_prime(z.y + bv.y, a.act);
     o.z = act_prime(z.z + bv.z, a.act); o.w = act_prime(z.w + bv.w, a.act);
   } else {
-    o.x = a.sp * (xv.x + a.hs * act_fn(z.x + bv.x, a.act)) + a.c1 * e1.x + a.c2 * e2.x;
-    o.y = a.sp * (xv.y + a.hs * act_fn(z.y + bv.y, a.act)) + a.c1 * e1.y + a.c2 * e2.y;
-    o.z = a.sp * (xv.z + a.hs * act_fn(z.z + bv.z, a.act)) + a.c1 * e1.z + a.c2 * e2.z;
-    o.w = a.sp * (xv.w + a.hs * act_fn(z.w + bv.w, a.act)) + a.c1 * e1.w + a.c2 * e2.w;
+    o.x = a.sp * (xv.x + a.hs * act_fn(z.x + bv.x, a.act)) + a.c1 * e1.x;
+    o.y = a.sp * (xv.y + a.hs * act_fn(z.y + bv.y, a.act)) + a.c1 * e1.y;
+    o.z = a.sp * (xv.z + a.hs * act_fn(z.z + bv.z, a.act)) + a.c1 * e1.z;
+    o.w = a.sp * (xv.w + a.hs * act_fn(z.w + bv.w, a.act)) + a.c1 * e1.w;
   }
   float sq = 0.0f;
   if (eok) {
     if (dact && a.dbf16) cvt_store4(reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E + eoff, o);
     else if (e.Op_) *reinterpret_cast<float4*>(e.Op_ + eoff) = o;
-    sq = (o.x * o.x + o.y * o.y) + (o.z * o.z + o.w * o.w);
+    sq = e.Rp ? sq_diff(e1, rf) : sq_norm(o);
   }
   if (a.norm_partial) {
     const float s = block_sum(sq, red);
@@ -1442,7 +1440,7 @@ hipError_t launch_step(const StepArgs& a_in, int layer_kind, int dtype, int grou
   const double es = dtype == 0 ? 4.0 : 2.0;
   double per = (double)a.wsize * es + (a.bias ? 4.0 * a.Nf : 0.0) + 4.0 * (double)a.E;
   if (a.E1 && a.c1 != 0.0f) per += 4.0 * (double)a.E;
-  if (a.E2 && a.c2 != 0.0f) per += 4.0 * (double)a.E;
+  if (a.Ref) per += 4.0 * (double)a.E;
   if (a.Dm) per += es * (double)a.E;
   if (a.Out) per += (a.mode == MODE_DACT ? es : 4.0) * (double)a.E;
   trace_after(s, cls, worked, per * worked);
@@ -1465,16 +1463,12 @@ __global__ __launch_bounds__(NT) void zero_points_kernel(float* out, PtMap om, l
   for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < E4; i += (long long)gridDim.x * NT)
     dst[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
-__global__ __launch_bounds__(NT) void correct_kernel(float* U, PtMap um, const float* V, PtMap vm, long long E4) {
-  const long long gi = blockIdx.y;
-  float4* u = reinterpret_cast<float4*>(U) + (um.base + gi * um.stride) * E4;
-  const float4* v = reinterpret_cast<const float4*>(V) + (vm.base + gi * vm.stride) * E4;
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < E4; i += (long long)gridDim.x * NT) {
-    float4 x = u[i];
-    const float4 y = v[i];
-    x.x += y.x - x.x; x.y += y.y - x.y; x.z += y.z - x.z; x.w += y.w - x.w;
-    u[i] = x;
-  }
+// out[i] = in for every one of n places (the known value of point 0 on all the arrays that hold it)
+struct StateDst { float* p[2 * 16]; };
+__global__ __launch_bounds__(NT) void spread_state_kernel(StateDst d, const float* in, long long E4) {
+  const float4* src = reinterpret_cast<const float4*>(in);
+  float4* dst = reinterpret_cast<float4*>(d.p[blockIdx.y]);
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < E4; i += (long long)gridDim.x * NT) dst[i] = src[i];
 }
 static dim3 xfer_grid(long long E4, int groups) {
   long long bx = (E4 + NT - 1) / NT;
@@ -1493,9 +1487,12 @@ hipError_t launch_zero_points(float* out, PtMap om, long long E, int groups, hip
   hipLaunchKernelGGL(zero_points_kernel, xfer_grid(E / 4, groups), dim3(NT), 0, s, out, om, E / 4);
   return hipGetLastError();
 }
-hipError_t launch_correct(float* U, PtMap um, const float* V, PtMap vm, long long E, int groups, hipStream_t s) {
-  if (groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(correct_kernel, xfer_grid(E / 4, groups), dim3(NT), 0, s, U, um, V, vm, E / 4);
+hipError_t launch_spread_state(float* const* out, int n, const float* in, long long E, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  StateDst d;
+  if (n > (int)(sizeof(d.p) / sizeof(d.p[0]))) return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i) d.p[i] = out[i];
+  hipLaunchKernelGGL(spread_state_kernel, xfer_grid(E / 4, n), dim3(NT), 0, s, d, in, E / 4);
   return hipGetLastError();
 }
 
@@ -1539,37 +1536,6 @@ __global__ __launch_bounds__(NT) void norm_final_kernel(const float* partial, in
     __syncthreads();
   }
   if (threadIdx.x == 0) out[0] = sqrt(red[0]) * scale;
-}
-// The injection copy of the fine level and the final norm reduction of the same cycle in one launch: block
-// row `groups` (one past the copies) holds the reduction, done by its first workgroup exactly as above.
-__global__ __launch_bounds__(NT) void copy_points_norm_kernel(float* out, PtMap om, const float* in, PtMap im,
-                                                              long long E4, int groups, const float* partial, int n,
-                                                              double scale, double* nout) {
-  __shared__ double red[NT];
-  if ((int)blockIdx.y == groups) {
-    if (blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += NT) s += (double)partial[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = NT / 2; o > 0; o >>= 1) {
-      if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) nout[0] = sqrt(red[0]) * scale;
-    return;
-  }
-  const long long gi = blockIdx.y;
-  const float4* src = reinterpret_cast<const float4*>(in) + (im.base + gi * im.stride) * E4;
-  float4* dst = reinterpret_cast<float4*>(out) + (om.base + gi * om.stride) * E4;
-  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < E4; i += (long long)gridDim.x * NT) dst[i] = src[i];
-}
-hipError_t launch_copy_points_norm(float* out, PtMap om, const float* in, PtMap im, long long E, int groups,
-                                   const float* partial, int n, double scale, double* nout, hipStream_t s) {
-  if (groups <= 0) return launch_norm_final(partial, n, scale, nout, s);
-  hipLaunchKernelGGL(copy_points_norm_kernel, xfer_grid(E / 4, groups + 1), dim3(NT), 0, s, out, om, in, im, E / 4,
-                     groups, partial, n, scale, nout);
-  return hipGetLastError();
 }
 hipError_t launch_norm_final(const float* partial, int n, double scale, double* out, hipStream_t s) {
   hipLaunchKernelGGL(norm_final_kernel, dim3(1), dim3(NT), 0, s, partial, n, scale, out);
