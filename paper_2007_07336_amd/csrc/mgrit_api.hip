@@ -267,17 +267,40 @@ struct Solver {
   void propagate(int l, long long js0, long long jstride, int groups) {
     step(l, js0, jstride, groups, X[l], pm(l, js0 - 1, jstride), X[l], pm(l, js0, jstride));
   }
-  // One fused launch per F-relaxation sweep where it pays: dense layers of a supported width or convolution
-  // layers of at most 16 float channels on images that fit one workgroup, at least two steps per interval, and
-  // enough workgroups -- (interval, 32-row slice) or (interval, image) -- to occupy the chip; with fewer, the
-  // lockstep launches (which spread one step over many workgroups) are as fast.
+  // Dense layers: one fused launch per F-relaxation sweep where it pays -- a supported width, at least two steps per
+  // interval, and enough (interval, 32-row slice) workgroups to occupy the chip; with fewer, the lockstep launches (which
+  // spread one step over many workgroups) are as fast.
   bool use_sweep(int l) const {
-    if (pl.fcP || p->m < 3 || !sweep_enabled()) return false;
-    if (p->layer == MGRIT_LAYER_CONV3X3)         // workgroup = (interval, image)
-      return conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) && (long long)pl.B * pl.Nl[l + 1] >= 128;
-    if (!sweep_supported(p->q, p->dtype)) return false;
-    return sweep_blocks(pl.M, pl.Nl[l + 1]) >= 128;
+    if (pl.fcP || p->m < 3 || p->layer != MGRIT_LAYER_DENSE || !sweep_enabled()) return false;
+    return sweep_supported(p->q, p->dtype) && sweep_blocks(pl.M, pl.Nl[l + 1]) >= 128;
   }
+  // Convolution layers whose images fit on a CU: all relaxation of a level's visit is one launch (march), the closing
+  // F-relaxation and the coarsest solve are one launch each.  A chain's step takes less time than a lockstep launch of the
+  // same step at every size, also where only a few workgroups run: whole solves 372 -> 240 us (5 images of 13 x 17 pixels, 24
+  // channels, bf16), 1405 -> 828 us (64 of 28 x 28, 16 channels, float), 16.6 -> 10.8 ms (32 of 32 x 32, 64 channels, bf16).
+  bool use_march() const {
+    return !pl.fcP && p->layer == MGRIT_LAYER_CONV3X3 && sweep_enabled() &&
+           conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype);
+  }
+  // chains of level l that start at sweep point ci * stride, for every ci
+  SweepArgs sweep_args(int l, long long stride) const {
+    SweepArgs a;
+    memset(&a, 0, sizeof(a));
+    const long long mp = pl.mpow[l];
+    if (g[l] && !plain_rhs) { a.G = g[l]; a.gb = 0; a.gs = stride; }
+    a.W = W; a.wn = wn; a.bias = bias; a.Dm = Dm;
+    if (adjoint) { a.lb = p->N - mp; a.ls = -stride * mp; a.lk = -mp; }
+    else         { a.lb = 0;         a.ls = stride * mp;  a.lk = mp; }
+    a.hs = pl.hl[l]; a.act = act;
+    a.M = pl.M; a.q = pl.Nf; a.E = pl.E; a.wsize = pl.wsize;
+    if (p->layer == MGRIT_LAYER_CONV3X3) { a.M = pl.B; a.Himg = p->Himg; a.Wimg = p->Wimg; a.C = p->C; }
+    return a;
+  }
+  void keep_states(SweepArgs& a, int l, long long stride) const {   // into the level's own array
+    const PtMap unit = pm(l, 0, 1);                                 // storage index of sweep point js = base + js * stride
+    a.X = X[l]; a.xb = unit.base; a.xs = unit.stride * stride; a.xk = unit.stride;
+  }
+  void launch_march(const SweepArgs& a) { if (err == hipSuccess) chk(launch_conv_sweep(a, p->dtype, s)); }
   // Where the current values of a level's C-points 0, m, 2m, .. are: point js = j m at p[m.base + j m.stride].
   // They do not live in the level's own array: the relaxation leaves them in R[l], the coarse solve in X[l + 1]
   // (it solves for their corrected values: with injection, U_C + (V_H - U_H) is V_H), and every consumer reads them
@@ -288,24 +311,11 @@ struct Solver {
     const int Nc = pl.Nl[l + 1];
     const int tail = pl.Nl[l] - Nc * p->m;                     // F-points behind the last C-point (< m)
     if (use_sweep(l)) {
-      SweepArgs a;
-      memset(&a, 0, sizeof(a));
-      const long long mp = pl.mpow[l];
-      const PtMap unit = pm(l, 0, 1);                          // storage index of sweep point js = base + js * stride
+      SweepArgs a = sweep_args(l, p->m);
       a.S = c.p; a.sm = c.m;
-      a.X = X[l]; a.xb = unit.base; a.xs = unit.stride * p->m; a.xk = unit.stride;
-      if (g[l] && !plain_rhs) { a.G = g[l]; a.gb = 0; a.gs = p->m; }
-      a.W = W; a.wn = wn; a.bias = bias; a.Dm = Dm;
-      if (adjoint) { a.lb = p->N - mp;           a.ls = -(long long)p->m * mp; a.lk = -mp; }
-      else         { a.lb = 0;                   a.ls = (long long)p->m * mp;  a.lk = mp; }
-      a.hs = pl.hl[l]; a.act = act; a.nsteps = p->m - 1; a.nchains = Nc;
-      a.M = pl.M; a.q = pl.Nf; a.E = pl.E; a.wsize = pl.wsize;
-      if (p->layer == MGRIT_LAYER_CONV3X3) {
-        a.M = pl.B; a.Himg = p->Himg; a.Wimg = p->Wimg; a.C = p->C;
-        if (err == hipSuccess) chk(launch_conv_sweep(a, s));
-      } else if (err == hipSuccess) {
-        chk(launch_sweep(a, p->dtype, s));
-      }
+      keep_states(a, l, p->m);
+      a.nsteps = a.nlast = p->m - 1; a.nchains = Nc;
+      if (err == hipSuccess) chk(launch_sweep(a, p->dtype, s));
       if (tail > 0) step(l, (long long)Nc * p->m + 1, p->m, 1, c.p, PtMap{c.m.base + Nc * c.m.stride, 0}, X[l], pm(l, (long long)Nc * p->m + 1, 1));
       for (int k = 2; k <= tail; ++k) propagate(l, (long long)Nc * p->m + k, p->m, 1);
       return;
@@ -316,8 +326,54 @@ struct Solver {
   // The level's own array, complete: C-points from the level below, F-points by F-relaxation (Alg. 1 ends with the
   // C-points; the F-layers follow by F-relaxation, Sec. III-C).
   void close(int l) {
+    if (use_march()) {
+      // chain ci: the C-point and the F-points behind it; the last chain is the last C-point with the trailing F-points
+      SweepArgs a = sweep_args(l, p->m);
+      const int Nc = pl.Nl[l + 1];
+      a.S = X[l + 1]; a.sm = PtMap{0, 1};
+      keep_states(a, l, p->m);
+      a.store0 = 1;
+      a.nsteps = p->m - 1; a.nlast = pl.Nl[l] - Nc * p->m; a.nchains = Nc + 1;
+      launch_march(a);
+      return;
+    }
     chk(launch_copy_points(X[l], pm(l, 0, p->m), X[l + 1], PtMap{0, 1}, pl.E, pl.Nl[l + 1] + 1, s));
     f_relax(l, CPoints{X[l + 1], PtMap{0, 1}});
+  }
+
+  // The coarsest level: its points in sequence.  X[l][0] holds the known value.
+  void serial(int l) {
+    if (use_march()) {
+      SweepArgs a = sweep_args(l, 0);
+      a.S = X[l]; a.sm = pm(l, 0, 0);
+      keep_states(a, l, 0);
+      a.nsteps = a.nlast = pl.Nl[l]; a.nchains = 1;
+      launch_march(a);
+      return;
+    }
+    for (int j = 1; j <= pl.Nl[l]; ++j) propagate(l, j, 1, 1);
+  }
+
+  // Relaxation of level l from the C-points c, and the step P_j that lands on every C-point j, in one launch.  A chain
+  // starts at C-point ci.  FCF-relaxation: m - 1 F-steps, the C-step to the new value of C-point ci + 1 (kept in R[l]), and
+  // on through the next interval's F-steps to P_{ci + 2}: the new C-point is where the second F-relaxation of that interval
+  // starts.  The first interval's C-point does not change, so its second F-relaxation repeats the first and P_1 is the new
+  // value of C-point 1; the last chain ends at the last C-point.  F-relaxation: m - 1 F-steps and P_{ci + 1}.
+  void march(int l, const CPoints& c) {
+    const int m = p->m, Nc = pl.Nl[l + 1];
+    SweepArgs a = sweep_args(l, m);
+    a.S = c.p; a.sm = c.m;
+    a.nchains = Nc;
+    a.Z = g[l + 1];
+    if (p->relax == MGRIT_RELAX_FCF) {
+      a.Y = R[l]; a.yb = 1; a.ys = 1; a.kmid = m;
+      a.zb = 2; a.zs = 1; a.zfirst = 1;
+      a.nsteps = 2 * m; a.nlast = m;
+    } else {
+      a.zb = 1; a.zs = 1;
+      a.nsteps = a.nlast = m;
+    }
+    launch_march(a);
   }
 
   // Nested-iteration start: the coarsest level's own equation is solved in sequence from the known
@@ -326,7 +382,7 @@ struct Solver {
   void nested_start() {
     plain_rhs = true;
     const int lc = pl.L - 1;
-    for (int j = 1; j <= pl.Nl[lc]; ++j) propagate(lc, j, 1, 1);
+    serial(lc);
     for (int l = lc - 1; l >= 1; --l) close(l);
     plain_rhs = false;
   }
@@ -335,38 +391,51 @@ struct Solver {
   // c: the C-points' current values (unused on the coarsest level).
   void cycle(int l, int iter, CPoints c) {
     const int m = p->m;
-    if (l == pl.L - 1) {                                        // coarsest level: serial solve
-      for (int j = 1; j <= pl.Nl[l]; ++j) propagate(l, j, 1, 1);   // X[l][0] holds the known value
-      return;
-    }
+    if (l == pl.L - 1) { serial(l); return; }
     const int Nc = pl.Nl[l + 1];
-    f_relax(l, c);                                              // Alg. 1 step 1
-    if (p->relax == MGRIT_RELAX_FCF) {
-      step(l, m, m, Nc, X[l], pm(l, m - 1, m), R[l], PtMap{1, 1});
-      c = CPoints{R[l], PtMap{0, 1}};
-      f_relax(l, c);
-    }
     // Alg. 1 steps 2 and 3.  With P_j the layer step that lands on C-point j (plus the level's right-hand side) the
     // residual there is R_j = P_j - U_j, Eq. (19), and the coarse right-hand side
     // S_H = L_H(U_H) + R_H = U_j - Phi_H(U_{j-1}) + P_j - U_j = P_j - Phi_H(U_{j-1}): the residual itself is needed for
     // its norm only, which the second launch takes of E1 - Ref.
-    step(l, m, m, Nc, X[l], pm(l, m - 1, m), g[l + 1], PtMap{1, 1});
-    {
+    if (use_march()) {
+      march(l, c);                                              // Alg. 1 step 1, and P
+      if (p->relax == MGRIT_RELAX_FCF) c = CPoints{R[l], PtMap{0, 1}};
+    } else {
+      f_relax(l, c);                                            // Alg. 1 step 1
+      if (p->relax == MGRIT_RELAX_FCF) {
+        step(l, m, m, Nc, X[l], pm(l, m - 1, m), R[l], PtMap{1, 1});
+        c = CPoints{R[l], PtMap{0, 1}};
+        f_relax(l, c);
+      }
+      step(l, m, m, Nc, X[l], pm(l, m - 1, m), g[l + 1], PtMap{1, 1});
+    }
+    const bool norm = l == 0 && want_norm;
+    const PtMap next = PtMap{c.m.base + c.m.stride, c.m.stride};
+    int blocks;
+    if (use_march() && p->dtype == MGRIT_FP32) {
+      // (the coarse step here and the one of the coarse solve nearly cancel, so in float they have to round alike and both
+      // are the sweep kernel's: 1.7e-7 from the exact states with the lockstep kernel here, 1.0e-7 so)
+      SweepArgs a = sweep_args(l + 1, 1);
+      a.G = nullptr;
+      a.S = c.p; a.sm = c.m;
+      a.nsteps = a.nlast = 1; a.nchains = Nc;
+      a.tau = 1; a.Z = g[l + 1]; a.zb = 1; a.zs = 1;
+      if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = partial; }
+      launch_march(a);
+      blocks = conv_sweep_blocks(a, p->dtype);
+    } else {
       StepArgs a = base_args(l + 1, 1, 1);
       a.X = c.p; a.xm = c.m;
       a.Out = g[l + 1]; a.om = PtMap{1, 1};
       a.sp = -1.0f;
       a.E1 = g[l + 1]; a.e1m = PtMap{1, 1}; a.c1 = 1.0f;        // in place, element by element
-      const bool norm = l == 0 && want_norm;
-      if (norm) {
-        a.Ref = c.p; a.rm = PtMap{c.m.base + c.m.stride, c.m.stride};
-        a.norm_partial = partial;
-      }
+      if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = partial; }
       launch(a, Nc);
-      if (norm) {
-        const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(Nc + 1) * (double)pl.E) : 1.0;
-        chk(launch_norm_final(partial, launch_blocks(a, Nc), scale, hist_dev + iter, s));
-      }
+      blocks = launch_blocks(a, Nc);
+    }
+    if (norm) {
+      const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(Nc + 1) * (double)pl.E) : 1.0;
+      chk(launch_norm_final(partial, blocks, scale, hist_dev + iter, s));
     }
     cycle(l + 1, iter, CPoints{c.p, PtMap{c.m.base, c.m.stride * m}});   // V_H, Alg. 1 steps 3 to 5
     if (l + 1 < pl.L - 1) close(l + 1);

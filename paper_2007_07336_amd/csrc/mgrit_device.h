@@ -1,0 +1,133 @@
+// Device-side helpers shared by the kernel files: operand and accumulator types, activations, the XCD-aware
+// workgroup order and the LDS opt-in.
+#pragma once
+#include "mgrit_internal.h"
+
+namespace mgrit {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// Operand traits.  Matrix-core operands live in LDS as rows of KSTEP-multiples, k fastest.
+//   float : v_mfma_f32_32x32x2_f32, a lane feeds 4 consecutive k over 4 instructions
+//   bf16  : v_mfma_f32_32x32x16_bf16, a lane feeds 8 consecutive k per instruction
+template <typename T> struct Op;
+template <> struct Op<float> {
+  static constexpr int KSTEP = 8;   // k consumed by one mma_step
+  static constexpr int VEC = 4;     // elements per 16-byte piece
+  static constexpr int PAD = 4;     // row padding in LDS (elements)
+};
+template <> struct Op<__bf16> {
+  static constexpr int KSTEP = 16;
+  static constexpr int VEC = 8;
+  static constexpr int PAD = 8;
+};
+
+// 16-byte load of layer weights.  STREAM: non-temporal, for parameter sets larger than the 256 MB last-level
+// cache -- a weight is used once per launch and must not push out the states, which the next launch reads
+// again.  Otherwise a plain load: the whole parameter set stays cached across the launches of a solve
+// (measured: 6 % on the q=256 workload with 64 MB of weights, the other way round -0.5 % with 2 GB).
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <bool STREAM, typename T>
+__device__ __forceinline__ uint4 ld_weights(const T* p) {
+  if (STREAM) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+  }
+  return *reinterpret_cast<const uint4*>(p);
+}
+// The act' cache of the adjoint sweep (and of the parameter gradient) is stored in the weights' type: float, or
+// bf16 when the matrix-core operands are bf16 anyway (half the bytes of its many reads).  Four consecutive
+// values are loaded raw -- no conversion next to the load, which would make the compiler wait for it -- and
+// widened when they are used.
+__device__ __forceinline__ float4 ld_d4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ uint2 ld_d4(const __bf16* p) { return *reinterpret_cast<const uint2*>(p); }
+__device__ __forceinline__ float4 d4_to_f4(float4 r) { return r; }
+__device__ __forceinline__ float4 d4_to_f4(uint2 r) {
+  return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
+                     __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
+}
+template <typename T> struct DRaw;
+template <> struct DRaw<float>  { typedef float4 type; };
+template <> struct DRaw<__bf16> { typedef uint2 type; };
+__device__ __forceinline__ void cvt_store4(float* dst, float4 v) { *reinterpret_cast<float4*>(dst) = v; }
+__device__ __forceinline__ void cvt_store4(__bf16* dst, float4 v) {
+  bf16x4 o;
+  o[0] = static_cast<__bf16>(v.x);   // round to nearest even
+  o[1] = static_cast<__bf16>(v.y);
+  o[2] = static_cast<__bf16>(v.z);
+  o[3] = static_cast<__bf16>(v.w);
+  *reinterpret_cast<bf16x4*>(dst) = o;
+}
+
+__device__ __forceinline__ floatx16 zero16() {
+  floatx16 z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+  return z;
+}
+// tanh(z) = 1 - 2 / (e^{2z} + 1) on the hardware exp2 / rcp units: absolute error about 2e-7
+// (the library tanhf costs ~100 instructions per element, which dominated the epilogue).  The
+// result enters the state scaled by h, so the absolute error is what matters.
+__device__ __forceinline__ float fast_tanh(float z) {
+  const float e = __builtin_amdgcn_exp2f(z * 2.885390081777927f);      // e^{2z}; inf / 0 saturate correctly
+  return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
+}
+__device__ __forceinline__ float act_fn(float z, int act) {
+  if (act == ACT_TANH) return fast_tanh(z);
+  if (act == ACT_RELU) return fmaxf(z, 0.0f);
+  return z;
+}
+__device__ __forceinline__ float act_prime(float z, int act) {
+  if (act == ACT_TANH) { float t = fast_tanh(z); return 1.0f - t * t; }
+  if (act == ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
+  return 1.0f;
+}
+// The same with the activation as a compile-time value: the epilogues of the tiled kernels branch on it once
+// per workgroup instead of once per element (a chain of scalar compares and branches around every one of a
+// lane's 64 output values took longer than their arithmetic).
+template <int ACT> __device__ __forceinline__ float act_fn_c(float z) {
+  if (ACT == ACT_TANH) return fast_tanh(z);
+  if (ACT == ACT_RELU) return fmaxf(z, 0.0f);
+  return z;
+}
+template <int ACT> __device__ __forceinline__ float act_prime_c(float z) {
+  if (ACT == ACT_TANH) { float t = fast_tanh(z); return 1.0f - t * t; }
+  if (ACT == ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
+  return 1.0f;
+}
+
+// (In the kernels below the wavefront index is read with readfirstlane: the compiler cannot see that tid >> 6 is
+// the same in all lanes, and with a scalar index the address arithmetic and conditions that depend on it stay on
+// the scalar unit.)
+// XCD-aware workgroup order: hardware deals consecutive workgroup ids round-robin to the 8
+// XCDs; remap so that consecutive logical tiles (which share a group's state and weights)
+// land on the same XCD and meet in its L2.
+__device__ __forceinline__ int logical_block() {
+  int total = gridDim.x, L = blockIdx.x;
+  if ((total & 7) == 0) L = (L & 7) * (total >> 3) + (L >> 3);
+  return L;
+}
+
+// p / w for 0 <= p < 4096 and 1 <= w <= 256 with magic = ceil(2^20 / w): exact because p * (magic * w - 2^20) < 2^20
+__device__ __forceinline__ int div_small(int p, unsigned magic) { return (int)(((unsigned)p * magic) >> 20); }
+
+// A kernel that uses more than 64 KB of dynamic LDS has to opt in, once per device (the attribute belongs to
+// the device's copy of the kernel).  One of these per kernel instance remembers the largest size each device
+// has been raised to.
+struct LdsOptIn {
+  size_t seen[64] = {};
+  bool need(size_t smem) {
+    if (smem <= 64 * 1024) return false;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return true;
+    if (smem <= seen[dev]) return false;
+    seen[dev] = smem;
+    return true;
+  }
+};
+
+}  // namespace mgrit

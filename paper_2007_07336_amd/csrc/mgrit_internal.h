@@ -109,32 +109,43 @@ hipError_t launch_norm_final(const float* partial, int n, double scale, double* 
 hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int dtype, int layers, int Nf,
                                     hipStream_t s);
 
-// Fused F-relaxation sweep (dense layers): workgroup (interval ci, slice of 32 batch rows) starts from
-// S[sm(ci)] and performs nsteps layer steps in sequence with the state slice resident in LDS -- a dense
-// layer acts on every batch row by itself, so the slices of an interval never exchange anything:
-//   step k = 1..nsteps:  u <- u + hs * act(A_layer (Dm_layer .* u) + bias_layer) + G[gb + ci*gs + k]
-//   layer(k) = lb + ci*ls + (k-1)*lk;   the state after step k is stored to X[xb + ci*xs + k*xk]
-// One launch replaces the nsteps lockstep launches of a sweep (Sec. III-C, Fig. 3).
+// A sweep: chain ci = 0 .. nchains - 1 starts from S[sm(ci)] and performs n layer steps in sequence (n = nsteps, nlast for
+// the last chain) with the state on chip:
+//   step k = 1..n:  u <- u + hs * act(A_layer (Dm_layer .* u) + bias_layer) + G[gb + ci*gs + k]
+//   layer(k) = lb + ci*ls + (k-1)*lk
+// One launch replaces n lockstep launches (Sec. III-C, Fig. 3).  What it keeps of the states:
+//   X, xk != 0: the state after every step k, in X[xb + ci*xs + k*xk]; with store0 also the start state, k = 0
+//   Y:          the state after step kmid, in Y[yb + ci*ys]
+//   Z:          the state after the last step, in Z[zb + ci*zs], if n > kmid; chain 0's state after step kmid in Z[zfirst]
+//   tau:        float convolution layers, single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of
+//               (Z - Ref[rm(ci)])^2, Z before the update, in norm_partial[workgroup]
+// S may not be written by another chain: X, Y, Z are other arrays, or other points of the same one.
 struct SweepArgs {
   const float* S;  PtMap sm;
-  float* X;  long long xb, xs, xk;
+  float* X;  long long xb, xs, xk;  int store0;
+  float* Y;  long long yb, ys;  int kmid;
+  float* Z;  long long zb, zs, zfirst;
+  int tau;  const float* Ref;  PtMap rm;  float* norm_partial;
   const float* G;  long long gb, gs;     // optional right-hand side (null: none)
   const void* W;  const float* bias;     // weights in the problem's type; bias may be null
   int wn;                                // dense sweep, 1: W holds W[k][n] (the adjoint on the caller's weights)
   const void* Dm;                        // optional act' factors in the weights' type, [layers][E]
   long long lb, ls, lk;
   float hs;
-  int act, nsteps, nchains, M, q;
+  int act, nsteps, nlast, nchains, M, q;
   long long E, wsize;
   int Himg, Wimg, C;                     // convolution sweep only (then M = images per state)
+  int ipw;                               // ... images per workgroup (filled in by the launch wrapper)
 };
+// Dense layers: workgroup (chain, slice of 32 batch rows) -- a dense layer acts on every batch row by itself, so the
+// slices of a chain never exchange anything.  Keeps every state (X); all chains have the same length.
 bool       sweep_supported(int q, int dtype);
 int        sweep_blocks(int M, int nchains);
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s);
-// The same for 3x3 convolution layers of at most 16 float channels on images small enough for one workgroup
-// (a convolution needs its neighbours' rows, so the unit is a whole image): workgroup (interval ci, image).
+// 3x3 convolution layers: workgroup (chain, images).
 bool       conv_sweep_supported(int Himg, int Wimg, int C, int dtype);
-hipError_t launch_conv_sweep(const SweepArgs& a, hipStream_t s);
+int        conv_sweep_blocks(const SweepArgs& a, int dtype);
+hipError_t launch_conv_sweep(const SweepArgs& a, int dtype, hipStream_t s);
 
 // launch tracing (diagnostic): kernel classes, and begin / collect
 enum { TRACE_DENSE_F32_64 = 0, TRACE_DENSE_F32_128, TRACE_DENSE_BF16_64, TRACE_DENSE_BF16_128,

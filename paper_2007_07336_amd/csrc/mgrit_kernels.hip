@@ -1,7 +1,7 @@
 // HIP kernels (gfx950 / CDNA4) of the MGRIT-FAS library: layer-batched residual-block steps
 // as grouped MFMA GEMMs / implicit-GEMM 3x3 convolutions with a fused epilogue, the
 // bandwidth-bound transfer kernels, the norm reduction and the parameter-gradient kernel.
-#include "mgrit_internal.h"
+#include "mgrit_device.h"
 
 #include <stdlib.h>
 
@@ -9,10 +9,6 @@
 #include <vector>
 
 namespace mgrit {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 256;  // threads per workgroup (4 wavefronts of 64)
 
@@ -68,60 +64,6 @@ int trace_end(double* ms, long long* launches, long long* units, double* bytes, 
   }
   g_trace.used = 0;
   return 0;
-}
-
-// ------------------------------------------------------------------------------------------
-// Operand traits.  Matrix-core operands live in LDS as rows of KSTEP-multiples, k fastest.
-//   float : v_mfma_f32_32x32x2_f32, a lane feeds 4 consecutive k over 4 instructions
-//   bf16  : v_mfma_f32_32x32x16_bf16, a lane feeds 8 consecutive k per instruction
-// ------------------------------------------------------------------------------------------
-template <typename T> struct Op;
-template <> struct Op<float> {
-  static constexpr int KSTEP = 8;   // k consumed by one mma_step
-  static constexpr int VEC = 4;     // elements per 16-byte piece
-  static constexpr int PAD = 4;     // row padding in LDS (elements)
-};
-template <> struct Op<__bf16> {
-  static constexpr int KSTEP = 16;
-  static constexpr int VEC = 8;
-  static constexpr int PAD = 8;
-};
-
-// 16-byte load of layer weights.  STREAM: non-temporal, for parameter sets larger than the 256 MB last-level
-// cache -- a weight is used once per launch and must not push out the states, which the next launch reads
-// again.  Otherwise a plain load: the whole parameter set stays cached across the launches of a solve
-// (measured: 6 % on the q=256 workload with 64 MB of weights, the other way round -0.5 % with 2 GB).
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-template <bool STREAM, typename T>
-__device__ __forceinline__ uint4 ld_weights(const T* p) {
-  if (STREAM) {
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-  }
-  return *reinterpret_cast<const uint4*>(p);
-}
-// The act' cache of the adjoint sweep (and of the parameter gradient) is stored in the weights' type: float, or
-// bf16 when the matrix-core operands are bf16 anyway (half the bytes of its many reads).  Four consecutive
-// values are loaded raw -- no conversion next to the load, which would make the compiler wait for it -- and
-// widened when they are used.
-__device__ __forceinline__ float4 ld_d4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ uint2 ld_d4(const __bf16* p) { return *reinterpret_cast<const uint2*>(p); }
-__device__ __forceinline__ float4 d4_to_f4(float4 r) { return r; }
-__device__ __forceinline__ float4 d4_to_f4(uint2 r) {
-  return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
-                     __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
-}
-template <typename T> struct DRaw;
-template <> struct DRaw<float>  { typedef float4 type; };
-template <> struct DRaw<__bf16> { typedef uint2 type; };
-__device__ __forceinline__ void cvt_store4(float* dst, float4 v) { *reinterpret_cast<float4*>(dst) = v; }
-__device__ __forceinline__ void cvt_store4(__bf16* dst, float4 v) {
-  bf16x4 o;
-  o[0] = static_cast<__bf16>(v.x);   // round to nearest even
-  o[1] = static_cast<__bf16>(v.y);
-  o[2] = static_cast<__bf16>(v.z);
-  o[3] = static_cast<__bf16>(v.w);
-  *reinterpret_cast<bf16x4*>(dst) = o;
 }
 
 // One KSTEP of the contraction for a TM x TN arrangement of 32x32 blocks.  ap[tm] / bp[tn]
@@ -212,43 +154,6 @@ __device__ __forceinline__ void mma_step_wn(const __bf16* const (&ap)[TM], const
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
 }
 
-__device__ __forceinline__ floatx16 zero16() {
-  floatx16 z;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = 0.0f;
-  return z;
-}
-// tanh(z) = 1 - 2 / (e^{2z} + 1) on the hardware exp2 / rcp units: absolute error about 2e-7
-// (the library tanhf costs ~100 instructions per element, which dominated the epilogue).  The
-// result enters the state scaled by h, so the absolute error is what matters.
-__device__ __forceinline__ float fast_tanh(float z) {
-  const float e = __builtin_amdgcn_exp2f(z * 2.885390081777927f);      // e^{2z}; inf / 0 saturate correctly
-  return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
-}
-__device__ __forceinline__ float act_fn(float z, int act) {
-  if (act == ACT_TANH) return fast_tanh(z);
-  if (act == ACT_RELU) return fmaxf(z, 0.0f);
-  return z;
-}
-__device__ __forceinline__ float act_prime(float z, int act) {
-  if (act == ACT_TANH) { float t = fast_tanh(z); return 1.0f - t * t; }
-  if (act == ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
-  return 1.0f;
-}
-// The same with the activation as a compile-time value: the epilogues of the tiled kernels branch on it once
-// per workgroup instead of once per element (a chain of scalar compares and branches around every one of a
-// lane's 64 output values took longer than their arithmetic).
-template <int ACT> __device__ __forceinline__ float act_fn_c(float z) {
-  if (ACT == ACT_TANH) return fast_tanh(z);
-  if (ACT == ACT_RELU) return fmaxf(z, 0.0f);
-  return z;
-}
-template <int ACT> __device__ __forceinline__ float act_prime_c(float z) {
-  if (ACT == ACT_TANH) { float t = fast_tanh(z); return 1.0f - t * t; }
-  if (ACT == ACT_RELU) return z > 0.0f ? 1.0f : 0.0f;
-  return 1.0f;
-}
-
 __device__ __forceinline__ float block_sum(float v, float* red) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -260,18 +165,6 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   float s = (red[0] + red[1]) + (red[2] + red[3]);
   for (int i = 4; i < (int)(blockDim.x >> 6); i += 2) s += red[i] + red[i + 1];
   return s;
-}
-
-// (In the kernels below the wavefront index is read with readfirstlane: the compiler cannot see that tid >> 6 is
-// the same in all lanes, and with a scalar index the address arithmetic and conditions that depend on it stay on
-// the scalar unit.)
-// XCD-aware workgroup order: hardware deals consecutive workgroup ids round-robin to the 8
-// XCDs; remap so that consecutive logical tiles (which share a group's state and weights)
-// land on the same XCD and meet in its L2.
-__device__ __forceinline__ int logical_block() {
-  int total = gridDim.x, L = blockIdx.x;
-  if ((total & 7) == 0) L = (L & 7) * (total >> 3) + (L >> 3);
-  return L;
 }
 
 // Fused epilogue shared by the dense and the conv kernel, one 32x32 accumulator block at a time:
@@ -922,9 +815,6 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
 // ------------------------------------------------------------------------------------------
 // N16 (float only, at most 16 channels): the output-channel side uses 16x16x4 MFMA blocks, so none of the
 // matrix-core work is spent on padding columns; a wavefront then owns 4 blocks of 16 pixels.
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-// p / w for 0 <= p < 4096 and 1 <= w <= 256 with magic = ceil(2^20 / w): exact because p * (magic * w - 2^20) < 2^20
-__device__ __forceinline__ int div_small(int p, unsigned magic) { return (int)(((unsigned)p * magic) >> 20); }
 // CFIX > 0: the channel count is this compile-time value (a multiple of the MFMA's k step that fills the
 // workgroup's output columns), so the tap loop unrolls with its LDS reads ahead of the matrix instructions and
 // the weight pieces need neither masks nor divisions -- with bf16 matrix instructions a tap is 16 of them per
@@ -1228,21 +1118,6 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
     epilogue<TM, TN, true, NX>(a, gi, layer, acc, row0, img_row0 + npx, 0, L, red, reinterpret_cast<float*>(smem_raw), xreg);
   }
 }
-
-// A kernel that uses more than 64 KB of dynamic LDS has to opt in, once per device (the attribute belongs to
-// the device's copy of the kernel).  One of these per kernel instance remembers the largest size each device
-// has been raised to.
-struct LdsOptIn {
-  size_t seen[64] = {};
-  bool need(size_t smem) {
-    if (smem <= 64 * 1024) return false;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return true;
-    if (smem <= seen[dev]) return false;
-    seen[dev] = smem;
-    return true;
-  }
-};
 
 // ------------------------------------------------------------------------------------------
 // launch configuration
@@ -2602,246 +2477,6 @@ hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
                      (a.G ? 4.0 : 0.0) * (double)a.E + 4.0 * (double)a.E;
   trace_after(s, dtype == 0 ? TRACE_SWEEP_F32 : TRACE_SWEEP_BF16, (long long)a.nchains * a.nsteps,
               (double)a.nchains * (a.nsteps * per + 4.0 * (double)a.E));
-  return e;
-}
-
-// ------------------------------------------------------------------------------------------
-// Fused F-relaxation sweep for 3x3 convolution layers with at most 16 float channels.  A workgroup owns one
-// image of one coarse interval and marches through all steps of the sweep.  In LDS: the fp32 state of the image
-// St [pixel][20], its matrix-core operand P (Dm .* state) as a patch with a one-pixel frame of zeros
-// [(H+2)(W+2)][20], and the nine 16x16 weight slices of the current layer.  A step multiplies 16-pixel blocks
-// (wavefront w of eight takes blocks w, w+8, ..) with v_mfma_f32_16x16x4_f32 over the nine taps and adds h*act(.) into St
-// right away (St is not an operand, so no barrier is needed for that); after a barrier one float4 pass over
-// whole pixels adds the right-hand side, stores the new state to global memory and writes the next operand.
-// ------------------------------------------------------------------------------------------
-constexpr int CSW_CS = 20;                       // floats per pixel in LDS (16 channels + 4 padding)
-constexpr int CSW_MAXBLK = 52;                   // 16-pixel blocks per image at most
-constexpr int CSW_PASS = (CSW_MAXBLK * 16 * 4 + 511) / 512;   // float4 pieces per thread in a pass over the image at most
-constexpr int CSW_NT = 512;                      // eight wavefronts: two per SIMD hide each other's LDS and barrier waits
-static size_t conv_sweep_smem(int Himg, int Wimg) {
-  return ((size_t)Himg * Wimg + (size_t)(Himg + 2) * (Wimg + 2) + 9 * 16) * CSW_CS * sizeof(float);
-}
-bool conv_sweep_supported(int Himg, int Wimg, int C, int dtype) {
-  if (dtype != 0 || (C != 8 && C != 16) || Himg < 1 || Wimg < 1 || Wimg > 256) return false;
-  if ((Himg * Wimg + 15) / 16 > CSW_MAXBLK) return false;
-  return conv_sweep_smem(Himg, Wimg) <= (size_t)150 * 1024;
-}
-
-template <int ACT>          // the activation as a compile-time value (one branch per launch, not per state value)
-__global__ __launch_bounds__(CSW_NT) void conv_sweep_kernel(SweepArgs a, unsigned wmagic) {
-  constexpr int NT = CSW_NT;                                 // shadows the file-wide 256
-  constexpr int CS = CSW_CS;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int H = a.Himg, Wd = a.Wimg, C = a.C, HW = H * Wd, PW = Wd + 2;
-  float* St = reinterpret_cast<float*>(smem_raw);            // [HW][CS]
-  float* P = St + HW * CS;                                   // [(H+2)*(W+2)][CS]
-  float* Wt = P + (H + 2) * PW * CS;                         // [9][16][CS]
-  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, kq = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // the same in every lane: block conditions stay scalar
-  const int L = logical_block();
-  const long long ci = L / a.M;
-  const int img = L % a.M;
-  const long long img_off = (long long)img * HW * C;
-  const float* Wall = reinterpret_cast<const float*>(a.W);
-  const float* Dall = reinterpret_cast<const float*>(a.Dm);
-  auto layer_of = [&](int k) { return a.lb + ci * a.ls + (long long)(k - 1) * a.lk; };
-  const int cq = C / 4, n4 = HW * cq;                        // float4 pieces of a pixel (2 or 4) / of the image
-  const int cqs = C == 16 ? 2 : 1;                           // log2(cq)
-  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-
-  // weight slices of a layer: 9 taps x 16 rows x 4 pieces = 576 pieces of 16 bytes, rows / channels past C are zero
-  uint4 wall[2];
-  unsigned wallmask = 0;
-  auto load_w = [&](long long layer) {
-    const float* Wp = Wall + layer * a.wsize;
-    wallmask = 0;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int p = tid + NT * i;
-      const int tap = p >> 6, row = (p >> 2) & 15, kc = (p & 3) * 4;
-      const bool ok = p < 576 && row < C && kc < C;
-      wallmask |= ok ? (1u << i) : 0u;
-      wall[i] = *reinterpret_cast<const uint4*>(Wp + (ok ? (unsigned)((row * 9 + tap) * C + kc) : 0u));
-    }
-  };
-  auto store_w = [&]() {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int p = tid + NT * i;
-      if (p < 576) {
-        const int tap = p >> 6, row = (p >> 2) & 15, kc = (p & 3) * 4;
-        uint4 v = wall[i];
-        if (!((wallmask >> i) & 1u)) v = make_uint4(0, 0, 0, 0);
-        *reinterpret_cast<uint4*>(&Wt[(tap * 16 + row) * CS + kc]) = v;
-      }
-    }
-  };
-  load_w(layer_of(1));
-
-  // ---- the frame of the operand patch, and with fewer than 16 channels the channels past C, are zero for the
-  // whole sweep: cleared once (the frame alone when every channel is written)
-  if (C < 16) {
-    for (int p = tid; p < (H + 2) * PW * (CS / 4); p += NT) *reinterpret_cast<float4*>(P + 4 * p) = zero;
-  } else {
-    const int nfr = 2 * PW + 2 * H;                          // top and bottom rows, left and right columns
-    for (int p = tid; p < nfr * 4; p += NT) {
-      const int f = p >> 2, c4 = (p & 3) * 4;
-      int fy, fx;
-      if (f < PW) { fy = 0; fx = f; }
-      else if (f < 2 * PW) { fy = H + 1; fx = f - PW; }
-      else { const int t = f - 2 * PW; fy = 1 + (t >> 1); fx = (t & 1) ? PW - 1 : 0; }
-      *reinterpret_cast<float4*>(P + (fy * PW + fx) * CS + c4) = zero;
-    }
-  }
-  __syncthreads();
-  {
-    const float* sp = a.S + (a.sm.base + ci * a.sm.stride) * a.E + img_off;
-    const float* dp = Dall ? Dall + layer_of(1) * a.E + img_off : nullptr;
-    for (int p = tid; p < n4; p += NT) {
-      const int px = p >> cqs, c4 = (p - (px << cqs)) * 4;
-      const float4 v = *reinterpret_cast<const float4*>(sp + 4 * p);
-      *reinterpret_cast<float4*>(St + px * CS + c4) = v;
-      float4 o = v;
-      if (dp) { const float4 d = *reinterpret_cast<const float4*>(dp + 4 * p); o.x *= d.x; o.y *= d.y; o.z *= d.z; o.w *= d.w; }
-      const int py = div_small(px, wmagic);
-      *reinterpret_cast<float4*>(P + ((py + 1) * PW + (px - py * Wd) + 1) * CS + c4) = o;
-    }
-  }
-  store_w();
-  __syncthreads();
-
-  const int nblk = (HW + 15) / 16;
-  for (int k = 1; k <= a.nsteps; ++k) {
-    const long long layer = layer_of(k);
-    if (k < a.nsteps) load_w(layer_of(k + 1));               // next layer's slices: in flight during this step
-    float bo = 0.0f;
-    if (a.bias && r16 < C) bo = a.bias[layer * C + r16];
-    // the pass at the end of the step needs the right-hand side and the next step's act' factors: requested now,
-    // their latency passes behind the matrix instructions
-    const bool build = k < a.nsteps;
-    const float* gp = a.G ? a.G + (a.gb + ci * a.gs + k) * a.E + img_off : nullptr;
-    const float* dp = (Dall && build) ? Dall + layer_of(k + 1) * a.E + img_off : nullptr;
-    float4 gpre[CSW_PASS], dpre[CSW_PASS];
-#pragma unroll
-    for (int i = 0; i < CSW_PASS; ++i) {
-      const int p = tid + NT * i;
-      const unsigned off = p < n4 ? 4u * (unsigned)p : 0u;
-      if (gp) gpre[i] = *reinterpret_cast<const float4*>(gp + off);
-      if (dp) dpre[i] = *reinterpret_cast<const float4*>(dp + off);
-    }
-    // the nine B fragments of this lane (output channel r16, input channels 4 kq .. + 3) serve every block
-    float4 bf[9];
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap) bf[tap] = *reinterpret_cast<const float4*>(Wt + (tap * 16 + r16) * CS + 4 * kq);
-    // four blocks at a time: their accumulators are independent, so consecutive matrix instructions never
-    // wait for each other.
-    // (NV, the number of blocks of the group inside the image, is a compile-time value: a run-time count put a
-    // compare and a branch around every matrix instruction of the image's last group)
-    auto group = [&](int blk0, auto nvc) {
-      constexpr int NV = decltype(nvc)::value;
-      const float* ap[4];
-      floatx4 acc[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int p = (blk0 + 8 * i) * 16 + r16;                   // this lane's A row: pixel p (rows past the image use pixel 0)
-        if (p >= HW) p = 0;
-        const int py = div_small(p, wmagic);
-        ap[i] = P + (py * PW + (p - py * Wd)) * CS + 4 * kq;
-        acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int toff = ((tap / 3) * PW + (tap % 3)) * CS;
-        float4 af[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (i < NV) af[i] = *reinterpret_cast<const float4*>(ap[i] + toff);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (i < NV) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].x, bf[tap].x, acc[i], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (i < NV) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].y, bf[tap].y, acc[i], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (i < NV) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].z, bf[tap].z, acc[i], 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (i < NV) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].w, bf[tap].w, acc[i], 0, 0, 0);
-      }
-      // register v of a lane holds pixel 4 kq + v of the block, output channel r16.  All sixteen state values
-      // are read before the first is written back (written as one read-modify-write each, every read would wait
-      // for the write before it: the compiler cannot tell that the addresses differ).
-      float sv[4][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int pv = (blk0 + 8 * i) * 16 + 4 * kq + v;   // >= HW past the image
-          if (i < NV) sv[i][v] = St[(pv < HW ? pv : 0) * CS + r16];
-        }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int pv = (blk0 + 8 * i) * 16 + 4 * kq + v;
-          if (i < NV && pv < HW && r16 < C) St[pv * CS + r16] = sv[i][v] + a.hs * act_fn_c<ACT>(acc[i][v] + bo);
-        }
-    };
-    for (int blk0 = wave; blk0 < nblk; blk0 += 32) {
-      const int nv = (nblk - blk0 + 7) / 8;                  // the same for all lanes of the wavefront
-      if (nv >= 4)      group(blk0, std::integral_constant<int, 4>{});
-      else if (nv == 3) group(blk0, std::integral_constant<int, 3>{});
-      else if (nv == 2) group(blk0, std::integral_constant<int, 2>{});
-      else              group(blk0, std::integral_constant<int, 1>{});
-    }
-    __syncthreads();                                         // every block is done with P and has updated St
-    {
-      float* xo = a.X + (a.xb + ci * a.xs + (long long)k * a.xk) * a.E + img_off;
-#pragma unroll
-      for (int i = 0; i < CSW_PASS; ++i) {
-        const int p = tid + NT * i;
-        if (p < n4) {
-          const int px = p >> cqs, c4 = (p - (px << cqs)) * 4;
-          float4 u = *reinterpret_cast<const float4*>(St + px * CS + c4);
-          if (gp) {
-            u.x += gpre[i].x; u.y += gpre[i].y; u.z += gpre[i].z; u.w += gpre[i].w;
-            *reinterpret_cast<float4*>(St + px * CS + c4) = u;
-          }
-          *reinterpret_cast<float4*>(xo + 4 * p) = u;
-          if (build) {
-            if (dp) { u.x *= dpre[i].x; u.y *= dpre[i].y; u.z *= dpre[i].z; u.w *= dpre[i].w; }
-            const int py = div_small(px, wmagic);
-            *reinterpret_cast<float4*>(P + ((py + 1) * PW + (px - py * Wd) + 1) * CS + c4) = u;
-          }
-        }
-      }
-      if (build) store_w();
-    }
-    __syncthreads();                                         // next operand and weight slices complete
-  }
-}
-
-hipError_t launch_conv_sweep(const SweepArgs& a, hipStream_t s) {
-  if (a.nchains <= 0 || a.nsteps <= 0) return hipSuccess;
-  if (!conv_sweep_supported(a.Himg, a.Wimg, a.C, 0) || a.M < 1) return hipErrorInvalidValue;
-  const size_t smem = conv_sweep_smem(a.Himg, a.Wimg);
-  const int actc = a.act == ACT_TANH ? 0 : a.act == ACT_RELU ? 1 : 2;
-  const void* kfn = actc == 0 ? reinterpret_cast<const void*>(conv_sweep_kernel<ACT_TANH>)
-                  : actc == 1 ? reinterpret_cast<const void*>(conv_sweep_kernel<ACT_RELU>)
-                              : reinterpret_cast<const void*>(conv_sweep_kernel<ACT_IDENT>);
-  static LdsOptIn opt[3];
-  if (opt[actc].need(smem)) {
-    const hipError_t e = hipFuncSetAttribute(kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
-  const unsigned blocks = (unsigned)a.M * (unsigned)a.nchains;
-  const unsigned wmagic = ((1u << 20) + (unsigned)a.Wimg - 1u) / (unsigned)a.Wimg;
-  trace_before(s);
-  if (actc == 0)      hipLaunchKernelGGL(conv_sweep_kernel<ACT_TANH>, dim3(blocks), dim3(CSW_NT), smem, s, a, wmagic);
-  else if (actc == 1) hipLaunchKernelGGL(conv_sweep_kernel<ACT_RELU>, dim3(blocks), dim3(CSW_NT), smem, s, a, wmagic);
-  else                hipLaunchKernelGGL(conv_sweep_kernel<ACT_IDENT>, dim3(blocks), dim3(CSW_NT), smem, s, a, wmagic);
-  const hipError_t e = hipGetLastError();
-  // algorithmic bytes per layer step: weights and bias, the act' factor, the right-hand side, the state out
-  // (the state in is read once per chain)
-  const double per = 4.0 * (double)a.wsize + (a.bias ? 4.0 * a.C : 0.0) + (a.Dm ? 4.0 : 0.0) * (double)a.E +
-                     (a.G ? 4.0 : 0.0) * (double)a.E + 4.0 * (double)a.E;
-  trace_after(s, TRACE_CONV_SWEEP_F32, (long long)a.nchains * a.nsteps, (double)a.nchains * (a.nsteps * per + 4.0 * (double)a.E));
   return e;
 }
 

@@ -1,0 +1,620 @@
+// Kernels that carry one state through many layer steps in one launch (sweeps): a workgroup owns some samples of one
+// coarse interval and keeps their state on chip from step to step.
+#include "mgrit_device.h"
+
+#include <type_traits>
+
+namespace mgrit {
+
+// ------------------------------------------------------------------------------------------
+// Sweep over 3x3 convolution layers.  A convolution needs its neighbours' rows, so the unit is a whole image: a
+// workgroup of eight wavefronts owns `ipw` images of one chain and marches through its layer steps.
+//   - The float state stays in registers, in the arrangement of the accumulators of v_mfma_f32_16x16x32_bf16 with the
+//     weights as the A operand: lane (c, kq) of a 16-pixel block holds channels 16 cb + 4 kq .. + 3 of pixel c.
+//   - The matrix operand (act' .* state) of all pixels sits in LDS as bf16.  Taps that fall off the image read one
+//     pixel of zeros, chosen by a 9-bit mask per pixel, so no frame is stored and several small images can share the
+//     list of pixels.  The 16-byte pieces of a pixel are permuted by its index where the pixel pitch would put eight
+//     neighbours on the same banks.
+//   - The contraction runs over k = (tap, input channel) in steps of 32, four 8-channel pieces per step.
+// NP = 1: bf16 problems.  NP = 3: float problems; state and weights are split into three bf16 numbers each, x = x1 + x2
+// + x3 (8 + 8 + 8 significant bits, so the split is exact), and the six products that reach 2^-24 are formed on the bf16
+// matrix cores with float accumulation -- 6/16 of the time of the float instructions.  The products left out are below
+// 2^-27 of the full one, less than the rounding of a single float addition.
+// The weights of a layer: all in LDS (the next layer's are on their way in registers during a step), or, for 64 channels
+// on images too large for that (RING), tap by tap through three LDS slots.
+// What bounds it: 16 channels float -- the LDS reads of the operand (15 KB per 16 pixels and step against 480 cycles of
+// matrix instructions); 64 channels bf16 -- LDS reads and matrix instructions alike (a 64 x 64 tile per wavefront needs
+// 8 KB of fragments for 16 instructions).  Global memory sees only what a caller keeps of the states.
+// ------------------------------------------------------------------------------------------
+typedef unsigned char u8;
+
+// x = h + m + l, each representable in bf16.  The first part is rounded to nearest unless that would overflow.
+__device__ __forceinline__ void split3(float x, __bf16& h, __bf16& m, __bf16& l) {
+  h = static_cast<__bf16>(x);
+  const float r = x - static_cast<float>(h);
+  m = static_cast<__bf16>(r);
+  l = static_cast<__bf16>(r - static_cast<float>(m));
+}
+
+template <int NP, int CP>
+__device__ __forceinline__ int conv_sweep_swz(int p) {          // permutation of a pixel's 16-byte pieces
+  if (CP == 64 && NP == 1) return p & 7;                        // pitch 128 bytes
+  if (CP == 32 && NP == 1) return (p >> 1) & 3;                 // 64
+  if (CP == 32 && NP == 3) return (p >> 2) & 3;                 // 192
+  return 0;                                                     // 32, 96: eight neighbours already on distinct banks
+}
+template <int NP, int CP> constexpr int conv_sweep_ksteps() { return (9 * (CP / 8) + 3) / 4; }
+template <int NP, int CP, bool RING> constexpr size_t conv_sweep_wbytes() {
+  return (size_t)(RING ? 3 * 2 : conv_sweep_ksteps<NP, CP>()) * 4 * NP * CP * 16;
+}
+
+// TAU: the coarse right-hand side, single steps (its epilogue beside the others would cost the sweep registers)
+template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
+__global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
+  constexpr bool HD = ACT == ACT_IDENT;                         // the adjoint: act' factors, no bias
+  constexpr int NTH = 64 * NWV;
+  constexpr int CB = CP / 16, PPT = CP / 8, NPC = 9 * PPT, S = conv_sweep_ksteps<NP, CP>();
+  constexpr int PLB = CP * 2, PXB = NP * PLB;                   // LDS bytes of one part of a pixel, of a pixel
+  constexpr int GB = 4, NG = NBW / GB;                          // pixel blocks multiplied together, groups of them
+  constexpr int WSB = 4 * NP * CP * 16;                         // LDS bytes of the weights of a k step
+  constexpr int WS = RING ? 2 : S;                              // k steps loaded together: a tap or the whole layer
+  constexpr int WU = (WS * 4 * CP + NTH - 1) / NTH;             // units (8 input channels of one output channel) per thread
+  constexpr int WR = NP == 3 ? 2 : 1;                           // 16-byte loads per unit
+  constexpr bool HOLD = CP == 16 || (CP == 32 && NP == 1);      // a layer's weight fragments fit in registers
+  constexpr bool DEARLY = !RING;                                // act' factors requested at the start of a step
+  static_assert(NBW % GB == 0 && (!RING || (CP == 64 && NP == 1)), "instances");
+  typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
+  typedef typename DRaw<WT>::type DR;
+  extern __shared__ __attribute__((aligned(16))) u8 smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int H = a.Himg, Wd = a.Wimg, C = RING ? CP : a.C, HW = H * Wd;
+  const int nwg = (a.M + a.ipw - 1) / a.ipw;                    // workgroups per chain
+  const int L = logical_block();
+  const long long ci = L / nwg;
+  const int img0 = (L % nwg) * a.ipw;
+  const int npx = min(a.ipw, a.M - img0) * HW;                  // pixels of this workgroup
+  const int nblk = (npx + 15) >> 4;
+  const int nbw = nblk > wave ? (nblk - wave + NWV - 1) / NWV : 0;     // blocks wave, wave + 8, .. of this wavefront
+  const int ngr = ((nblk + NWV - 1) / NWV + GB - 1) / GB;       // groups of the wavefront with the most blocks
+  const int n = TAU ? 1 : ci == a.nchains - 1 ? a.nlast : a.nsteps;
+  const int ZP = a.ipw * HW;                                    // the pixel of zeros
+  u8* P = smem;
+  u8* Wl = smem + ((size_t)(ZP + 1) * PXB + 255) / 256 * 256;
+  float* bl = reinterpret_cast<float*>(Wl + conv_sweep_wbytes<NP, CP, RING>());     // [2][CP] bias
+  const long long img_off = (long long)img0 * HW * C;
+  auto layer_of = [&](int k) __attribute__((always_inline)) { return a.lb + ci * a.ls + (long long)(k - 1) * a.lk; };
+
+  // this lane's pixel in block b and its place in a state
+  // (cpx is made opaque to the compiler once per step: everything that follows from a lane's pixel -- the operand addresses
+  // of all taps and blocks -- is the same in every step, and kept across the step loop it would take several hundred
+  // registers)
+  int cpx = c;
+  auto px = [&](int b) __attribute__((always_inline)) { return (wave + NWV * b) * 16 + cpx; };
+  // (pixels past the last one read that one's values, channels past C those of the pixel's first block: never stored)
+  const int chl = CB == 1 && 4 * kq >= C ? 0 : 4 * kq;
+  const bool last_ok = 16 * (CB - 1) + 4 * kq < C;              // C % 8 == 0: a lane's four channels are in or out together
+  const int chlast = last_ok ? 16 * (CB - 1) : 0;
+  auto off = [&](int b, int cb) __attribute__((always_inline)) { return (unsigned)(min(px(b), npx - 1) * C + chl + (cb < CB - 1 ? 16 * cb : chlast)); };
+  // which of the nine taps of a pixel lie in its image (bit 9 and above: never)
+  unsigned mask[NBW];
+#pragma unroll
+  for (int b = 0; b < NBW; ++b) {
+    const int p = px(b), r = p % HW, y = r / Wd, x = r % Wd;
+    const unsigned xm = (x > 0 ? 1u : 0u) | 2u | (x + 1 < Wd ? 4u : 0u);
+    unsigned m = xm << 3;
+    if (y > 0) m |= xm;
+    if (y + 1 < H) m |= xm << 6;
+    mask[b] = p < npx ? m : 0u;
+  }
+
+  floatx4 st[NBW][CB];
+  {
+    const float* sp = a.S + (a.sm.base + ci * a.sm.stride) * a.E + img_off;
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) st[b][cb] = *reinterpret_cast<const floatx4*>(sp + off(b, cb));
+  }
+  auto store_state = [&](float* o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+      if (px(b) < npx) {
+#pragma unroll
+        for (int cb = 0; cb < CB - 1; ++cb) *reinterpret_cast<floatx4*>(o + off(b, cb)) = st[b][cb];
+        if (last_ok) *reinterpret_cast<floatx4*>(o + off(b, CB - 1)) = st[b][CB - 1];
+      }
+  };
+  auto place = [&](float* base, long long point) __attribute__((always_inline)) { return base + point * a.E + img_off; };
+  if (a.X && a.store0) store_state(place(a.X, a.xb + ci * a.xs));
+  if (n <= 0) return;                                           // the whole workgroup
+
+  // ---- weights: unit u = (k step, output channel, piece of the step)
+  const WT* Wall = reinterpret_cast<const WT*>(a.W);
+  u32x4 wr[WU * WR];
+  // (a unit outside the layer -- a padded channel, the k step's pieces past tap 8 -- reads the layer's first values and is
+  // cleared on its way into LDS)
+  auto unit_ok = [&](int u, int tap0) __attribute__((always_inline)) {
+    const int pc = 4 * (u / (4 * CP)) + (u & 3);
+    return u < WS * 4 * CP && tap0 + pc / PPT < 9 && (u >> 2) % CP < C && (pc % PPT) * 8 < C;
+  };
+  auto load_w = [&](u32x4 (&r)[WU * WR], const WT* Wp, int tap0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WU; ++i) {
+      if constexpr (RING) {                                     // every unit inside: a uniform base and a fixed offset
+        const int u = tid + NTH * i;
+        const unsigned e = (unsigned)(((u >> 2) & 63) * 9 * CP + (u >> 8) * 32 + (u & 3) * 8);
+        r[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(Wp + tap0 * CP) + 2u * e);
+        continue;
+      }
+      const int u = tid + NTH * i, pc = 4 * (u / (4 * CP)) + (u & 3), o = (u >> 2) % CP;
+      const unsigned e = (unsigned)((o * 9 + tap0 + pc / PPT) * C + (pc % PPT) * 8);
+      const WT* q = Wp + (unit_ok(u, tap0) ? e : 0u);
+#pragma unroll
+      for (int j = 0; j < WR; ++j) r[i * WR + j] = *reinterpret_cast<const u32x4*>(q + (NP == 3 ? 4 * j : 0));
+    }
+  };
+  auto store_w = [&](u32x4 (&r)[WU * WR], u8* dst, int tap0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WU; ++i) {
+      const int u = tid + NTH * i, s = u / (4 * CP), kg = u & 3, o = (u >> 2) % CP;
+      if (u < WS * 4 * CP) {
+        // (the slot of an output channel is permuted by the piece, so that the four pieces a quad of lanes holds go to
+        // different banks)
+        u8* q = dst + s * WSB + ((kg * NP) * CP + (o ^ (4 * kg))) * 16;
+        const unsigned keep = RING || unit_ok(u, tap0) ? ~0u : 0u;
+#pragma unroll
+        for (int j = 0; j < WR; ++j) r[i * WR + j] &= keep;
+        if constexpr (NP == 1) {
+          *reinterpret_cast<u32x4*>(q) = r[i];
+        } else {
+          bf16x8 h, m, l;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            __bf16 hh, mm, ll;
+            split3(__uint_as_float(r[i * WR + (e >> 2)][e & 3]), hh, mm, ll);
+            h[e] = hh; m[e] = mm; l[e] = ll;
+          }
+          *reinterpret_cast<bf16x8*>(q) = h;
+          *reinterpret_cast<bf16x8*>(q + CP * 16) = m;
+          *reinterpret_cast<bf16x8*>(q + 2 * CP * 16) = l;
+        }
+      }
+    }
+  };
+  const WT* Wc = Wall + layer_of(1) * a.wsize;
+  load_w(wr, Wc, 0);
+  float bnext = 0.0f;
+  auto load_bias = [&](int k) __attribute__((always_inline)) { if (a.bias && tid < CP && tid < C) bnext = a.bias[layer_of(k) * C + tid]; };
+  load_bias(1);
+
+  // ---- operand of a step: act' .* state, to LDS (a pixel's padded channels are zero)
+  DR dr[HD ? NBW : 1][HD ? CB : 1];
+  auto load_d = [&](int k) __attribute__((always_inline)) {
+    if constexpr (HD) {
+      const WT* dp = reinterpret_cast<const WT*>(a.Dm) + layer_of(k) * a.E + img_off;
+#pragma unroll
+      for (int b = 0; b < NBW; ++b)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) dr[b][cb] = ld_d4(dp + off(b, cb));
+    }
+  };
+  auto piece = [&](int p, int pc) __attribute__((always_inline)) { return (unsigned)(p * PXB + ((pc ^ conv_sweep_swz<NP, CP>(p)) << 4)); };
+  auto write_operand = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < NBW; ++b) {
+      const int p = px(b);
+      if (p < npx) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          float4 v = make_float4(st[b][cb][0], st[b][cb][1], st[b][cb][2], st[b][cb][3]);
+          if constexpr (HD) { const float4 d = d4_to_f4(dr[b][cb]); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
+          if (cb == CB - 1 && !last_ok) v = make_float4(0.f, 0.f, 0.f, 0.f);
+          // (the permutation of a pixel's pieces repeats every 16 pixels at most: it depends on the lane alone)
+          u8* q = P + p * PXB + (((2 * cb + (kq >> 1)) ^ conv_sweep_swz<NP, CP>(cpx)) << 4) + (kq & 1) * 8;
+          if constexpr (NP == 1) {
+            cvt_store4(reinterpret_cast<__bf16*>(q), v);
+          } else {
+            bf16x4 h, m, l;
+            const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              __bf16 hh, mm, ll;
+              split3(f[e], hh, mm, ll);
+              h[e] = hh; m[e] = mm; l[e] = ll;
+            }
+            *reinterpret_cast<bf16x4*>(q) = h;
+            *reinterpret_cast<bf16x4*>(q + PLB) = m;
+            *reinterpret_cast<bf16x4*>(q + 2 * PLB) = l;
+          }
+        }
+      }
+    }
+  };
+  load_d(1);
+  if (tid < PXB / 4) reinterpret_cast<float*>(P + (size_t)ZP * PXB)[tid] = 0.0f;
+  write_operand();
+  store_w(wr, Wl, 0);
+  if constexpr (RING) load_w(wr, Wc, 1);
+  if (tid < CP) bl[CP + tid] = bnext;
+  __syncthreads();
+
+  const unsigned alane = (unsigned)(((kq * NP) * CP + (c ^ (4 * kq))) * 16);      // this lane's row of a weight fragment
+  for (int k = 1; k <= n; ++k) {
+    asm volatile("" : "+v"(cpx));
+#pragma unroll
+    for (int b = 0; b < NBW; ++b) asm volatile("" : "+v"(mask[b]));
+    const WT* Wn = Wall + layer_of(k < n ? k + 1 : k) * a.wsize;                  // (past the last step: read, not used)
+    // RING: a tap is requested one tap before it is needed, which covers an L2 hit and not a miss (a layer's weights come
+    // from HBM once per XCD: 38 us per step without this, waiting for every tap).  Every line of the next layer is touched
+    // at the start of a step.
+    constexpr int NTOUCH = (9 * CP * CP * 2 + 128 * NTH - 1) / (128 * NTH);
+    unsigned touch[NTOUCH] = {};
+    if constexpr (RING) {
+      const char* wn = reinterpret_cast<const char*>(Wn);
+      const unsigned last = (unsigned)(a.wsize * sizeof(WT)) - 4u;
+#pragma unroll
+      for (int i = 0; i < NTOUCH; ++i) touch[i] = *reinterpret_cast<const unsigned*>(wn + min((unsigned)(tid + NTH * i) * 128u, last));
+    } else {
+      load_w(wr, Wn, 0);
+    }
+    if (k < n) {
+      load_bias(k + 1);
+      if constexpr (DEARLY) load_d(k + 1);
+    }
+    bf16x8 hold[HOLD ? S : 1][HOLD ? CB : 1][NP];
+    if constexpr (HOLD) {
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+          for (int q = 0; q < NP; ++q)
+            hold[s][cb][q] = *reinterpret_cast<const bf16x8*>(Wl + alane + s * WSB + q * CP * 16 + cb * 256);
+    }
+    const float* bp = bl + (k & 1) * CP;
+    const float* gp = a.G ? a.G + (a.gb + ci * a.gs + k) * a.E + img_off : nullptr;
+
+    // one k step for NV pixel blocks: base address of each block's pixel for the lane's tap and piece
+    // (NP = 3: the five small products have accumulators of their own, so that the large one's sum is rounded once per k
+    // step; they are added at the end)
+    auto mma = [&](auto nvc, floatx4 (&acc)[GB][CB], floatx4 (&low)[NP == 3 ? GB : 1][NP == 3 ? CB : 1], const unsigned (&pa)[GB], const u8* ws, int s) __attribute__((always_inline)) {
+      constexpr int NV = decltype(nvc)::value;
+      // (the fragments of one k step at a time: the other wavefront of the SIMD covers their latency, and a second set
+      // in flight would not fit beside state and accumulators)
+      if constexpr (NBW * CB + NV * CB > 16) __builtin_amdgcn_sched_barrier(0);
+      bf16x8 bfr[NV][NP];
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) bfr[i][q] = *reinterpret_cast<const bf16x8*>(P + pa[i] + q * PLB);
+      bf16x8 afr[CB][NP];
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          if constexpr (HOLD) afr[cb][q] = hold[s][cb][q];
+          else afr[cb][q] = *reinterpret_cast<const bf16x8*>(ws + alane + q * CP * 16 + cb * 256);
+        }
+      if constexpr (NP == 1) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[cb][0], bfr[i][0], acc[i][cb], 0, 0, 0);
+      } else {
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};     // smallest products first
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+#pragma unroll
+          for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+              low[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[cb][PA[t]], bfr[i][PB[t]], low[i][cb], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afr[cb][0], bfr[i][0], acc[i][cb], 0, 0, 0);
+      }
+    };
+    auto update = [&](auto grpc, auto nvc, floatx4 (&acc)[GB][CB]) __attribute__((always_inline)) {
+      constexpr int G0 = decltype(grpc)::value * GB, NV = decltype(nvc)::value;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) st[G0 + i][cb][v] += a.hs * act_fn_c<ACT>(acc[i][cb][v]);
+      }
+      if (gp) {                                                     // coarse levels only
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          floatx4 gv[NV];
+#pragma unroll
+          for (int i = 0; i < NV; ++i) gv[i] = *reinterpret_cast<const floatx4*>(gp + off(G0 + i, cb));
+#pragma unroll
+          for (int i = 0; i < NV; ++i) st[G0 + i][cb] += gv[i];
+        }
+      }
+    };
+    auto group = [&](auto grpc, auto nvc) __attribute__((always_inline)) {
+      constexpr int G0 = decltype(grpc)::value * GB, NV = decltype(nvc)::value;
+      floatx4 acc[GB][CB];
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+          if (!HD) acc[i][cb] = *reinterpret_cast<const floatx4*>(bp + 16 * cb + 4 * kq);        // the bias
+          else acc[i][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      floatx4 low[NP == 3 ? GB : 1][NP == 3 ? CB : 1];
+      if constexpr (NP == 3) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) low[i][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+      if constexpr (RING) {
+        // Software pipeline over the 18 k steps: the fragments of a step are read while the one before is multiplied.  The
+        // barrier that makes the next tap's weights visible stands between the two steps of a tap.
+        const bool last = decltype(grpc)::value + 1 >= ngr;
+        constexpr bool PIPE = NWV == 4;
+        bf16x8 af[PIPE ? 2 : 1][CB], bf[PIPE ? 2 : 1][GB];
+        unsigned pa[GB];
+        auto tap_addr = [&](int tap) __attribute__((always_inline)) {
+          const int ty = (tap * 11) >> 5, dp = (ty - 1) * Wd + (tap - 3 * ty) - 1;        // tap / 3
+#pragma unroll
+          for (int i = 0; i < GB; ++i) {
+            const int pp = (mask[G0 + i] >> tap) & 1u ? px(G0 + i) + dp : ZP;
+            pa[i] = piece(pp, kq);
+          }
+        };
+        auto read = [&](int f, const u8* ws, unsigned flip) __attribute__((always_inline)) {                 // flip 64: pieces 4 .. 7 of the pixel
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) af[f][cb] = *reinterpret_cast<const bf16x8*>(ws + alane + cb * 256);
+#pragma unroll
+          for (int i = 0; i < GB; ++i) bf[f][i] = *reinterpret_cast<const bf16x8*>(P + (pa[i] ^ flip));
+        };
+        auto mul = [&](int f) __attribute__((always_inline)) {
+#pragma unroll
+          for (int i = 0; i < GB; ++i)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[f][cb], bf[f][i], acc[i][cb], 0, 0, 0);
+        };
+        if constexpr (NV > 0) { tap_addr(0); if (PIPE) read(0, Wl, 0u); }
+        // (a rolled loop: unrolled, the kernel is larger than the 64 KB instruction cache of two CUs and takes five times as
+        // long, waiting for its instructions)
+        u8* slot = Wl;                                              // this tap's weights; the next tap's go to the next slot
+#pragma unroll 1
+        for (int tap = 0; tap < 9; ++tap) {
+          u8* next = slot == Wl + 4 * WSB ? Wl : slot + 2 * WSB;
+          store_w(wr, next, 0);
+          load_w(wr, (tap >= 7 && last) ? Wn : Wc, tap >= 7 ? tap - 7 : tap + 2);
+          if constexpr (PIPE) {
+          if constexpr (NV > 0) {
+            read(1, slot + WSB, 64u);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          __syncthreads();                                          // next tap complete
+          if constexpr (NV > 0) {
+            if (tap < 8) {
+              tap_addr(tap + 1);
+              read(0, next, 0u);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            mul(1);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          } else {
+            if constexpr (NV > 0) {
+              read(0, slot, 0u);
+              __builtin_amdgcn_sched_barrier(0);
+              mul(0);
+              __builtin_amdgcn_sched_barrier(0);
+              read(0, slot + WSB, 64u);
+              __builtin_amdgcn_sched_barrier(0);
+              mul(0);
+              if (tap < 8) tap_addr(tap + 1);
+            }
+            __syncthreads();
+          }
+          slot = next;
+        }
+      } else if constexpr (NV > 0) {
+        auto kstep = [&](int s) __attribute__((always_inline)) {
+          const int pc = 4 * s + kq, tap = pc / PPT, ty = (tap * 11) >> 5;        // tap / 3 for 0 <= tap < 16
+          const int dp = (ty - 1) * Wd + (tap - 3 * ty) - 1;
+          unsigned pa[GB];
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            const int pp = (mask[G0 + i] >> tap) & 1u ? px(G0 + i) + dp : ZP;
+            pa[i] = piece(pp, pc % PPT);
+          }
+          mma(nvc, acc, low, pa, Wl + s * WSB, s);
+        };
+        if constexpr (HOLD) {
+#pragma unroll
+          for (int s = 0; s < S; ++s) kstep(s);
+        } else {                                                    // (rolled: the instruction cache again)
+#pragma unroll 2
+          for (int s = 0; s < S; ++s) kstep(s);
+        }
+      }
+      if constexpr (NP == 3) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) acc[i][cb] += low[i][cb];
+      }
+      if constexpr (NV > 0) update(grpc, nvc, acc);
+    };
+    auto groups = [&](auto grpc) __attribute__((always_inline)) {
+      const int nv = nbw - decltype(grpc)::value * GB;              // the same for all lanes of the wavefront
+      if constexpr (RING) {                                         // every wavefront takes part in the ring's barriers
+        if (nv > 0) group(grpc, std::integral_constant<int, 4>{});  // (blocks past the last one read zeros)
+        else        group(grpc, std::integral_constant<int, 0>{});
+      } else {
+        if (nv >= 4) group(grpc, std::integral_constant<int, 4>{});
+        else if (nv == 3) group(grpc, std::integral_constant<int, CP == 16 ? 3 : 4>{});
+        else if (nv == 2) group(grpc, std::integral_constant<int, 2>{});
+        else if (nv == 1) group(grpc, std::integral_constant<int, CP == 16 ? 1 : 2>{});
+      }
+    };
+    groups(std::integral_constant<int, 0>{});
+    if constexpr (NG > 1) { if (ngr > 1) groups(std::integral_constant<int, 1>{}); }
+    if constexpr (NG > 2) { if (ngr > 2) groups(std::integral_constant<int, 2>{}); }
+    if constexpr (NG > 3) { if (ngr > 3) groups(std::integral_constant<int, 3>{}); }
+    static_assert(NG <= 4, "groups");
+
+    if constexpr (TAU) {                                            // coarse right-hand side: Z <- Z - state, and its norm
+      float* o = place(a.Z, a.zb + ci * a.zs);
+      const float* ref = a.Ref ? a.Ref + (a.rm.base + ci * a.rm.stride) * a.E + img_off : nullptr;
+      float sq = 0.0f;
+#pragma unroll
+      for (int b = 0; b < NBW; ++b) {
+        floatx4 pv[CB], rv[CB];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) pv[cb] = *reinterpret_cast<const floatx4*>(o + off(b, cb));
+        if (ref) {
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb) rv[cb] = *reinterpret_cast<const floatx4*>(ref + off(b, cb));
+        }
+        if (px(b) < npx) {
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+            if (cb < CB - 1 || last_ok) {
+              *reinterpret_cast<floatx4*>(o + off(b, cb)) = pv[cb] - st[b][cb];
+              if (ref) {
+                const floatx4 d = pv[cb] - rv[cb];
+                sq += (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+              }
+            }
+        }
+      }
+      if (a.norm_partial) {                                         // in a fixed order over the wavefronts
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) sq += __shfl_xor(sq, w, 64);
+        float* red = reinterpret_cast<float*>(P);
+        __syncthreads();                                            // the operand is not needed any more
+        if (lane == 0) red[wave] = sq;
+        __syncthreads();
+        if (tid == 0) {
+          float t = red[0];
+#pragma unroll
+          for (int w = 1; w < NWV; ++w) t += red[w];
+          a.norm_partial[L] = t;
+        }
+      }
+      break;
+    }
+    float* o1 = nullptr;                                            // where this step's state is kept: at most two places
+    float* o2 = nullptr;
+    if (a.X && a.xk) o1 = place(a.X, a.xb + ci * a.xs + (long long)k * a.xk);
+    else if (k == a.kmid) { o1 = place(a.Y, a.yb + ci * a.ys); if (ci == 0) o2 = place(a.Z, a.zfirst); }
+    else if (a.Z && k == n) o1 = place(a.Z, a.zb + ci * a.zs);
+    for (; o1; o1 = o2, o2 = nullptr) store_state(o1);
+    if constexpr (RING) {
+#pragma unroll
+      for (int i = 0; i < NTOUCH; ++i) asm volatile("" :: "v"(touch[i]));
+    }
+    if (k == n) break;
+    if constexpr (!DEARLY) load_d(k + 1);
+    __syncthreads();                                                // every wavefront is done with the operand and the weights
+    write_operand();
+    if constexpr (!RING) store_w(wr, Wl, 0);
+    if (tid < CP) bl[((k + 1) & 1) * CP + tid] = bnext;
+    Wc = Wn;
+    __syncthreads();
+  }
+}
+
+// Instances: 1 / 2 / 3 / 4 blocks of 16 channels; up to 1024 pixels per workgroup with eight pixel blocks per
+// wavefront, 512 with four.
+namespace {
+struct ConvSweepShape { int cp, np, nwv, nbw; bool ring; size_t smem; };
+size_t conv_sweep_smem(int np, int cp, bool ring, int pixels) {
+  const size_t op = ((size_t)(pixels + 1) * np * cp * 2 + 255) / 256 * 256;
+  const size_t ks = ring ? 6 : (9 * (cp / 8) + 3) / 4;
+  return op + ks * 4 * np * cp * 16 + 2 * cp * sizeof(float);
+}
+bool conv_sweep_shape(int pixels, int C, int dtype, ConvSweepShape* sh) {
+  const size_t cap = (size_t)160 * 1024;
+  sh->np = dtype == 0 ? 3 : 1;
+  sh->cp = (C + 15) / 16 * 16;
+  sh->ring = false;
+  if (sh->np == 3 && sh->cp > 32) return false;
+  sh->nwv = 8;
+  sh->nbw = (sh->np == 3 && sh->cp == 32) || sh->cp == 64 ? 4 : 8;
+  if (C == 64 && sh->np == 1 && pixels > 512) { sh->ring = true; sh->nwv = 8; sh->nbw = 8; }
+  sh->smem = conv_sweep_smem(sh->np, sh->cp, sh->ring, pixels);
+  return pixels <= sh->nwv * sh->nbw * 16 && sh->smem <= cap;
+}
+template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
+hipError_t launch_conv_sweep_t(const SweepArgs& a, unsigned blocks, size_t smem, hipStream_t s) {
+  static LdsOptIn opt;
+  const void* k = reinterpret_cast<const void*>(conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>);
+  if (opt.need(smem)) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) { opt = LdsOptIn(); return e; }
+  }
+  hipLaunchKernelGGL((conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>), dim3(blocks), dim3(64 * NWV), smem, s, a);
+  return hipGetLastError();
+}
+}  // namespace
+
+bool conv_sweep_supported(int Himg, int Wimg, int C, int dtype) {
+  ConvSweepShape sh;
+  if (Himg < 1 || Wimg < 1 || C < 8 || C > 64 || C % 8 != 0 || (long long)Himg * Wimg > 1024) return false;
+  return conv_sweep_shape(Himg * Wimg, C, dtype, &sh);
+}
+// Images per workgroup: a step has fixed costs (two barriers, the weights' way into LDS) and eight wavefronts want at least
+// a block of 16 pixels each, so small images share a workgroup as long as every CU still gets one.
+static int conv_sweep_images(int Himg, int Wimg, int C, int dtype, int B, int nchains) {
+  ConvSweepShape sh;
+  int ipw = 1;
+  while (2 * ipw <= B && 2 * ipw * Himg * Wimg <= 512 && (long long)nchains * ((B + 2 * ipw - 1) / (2 * ipw)) >= 256 &&
+         conv_sweep_shape(2 * ipw * Himg * Wimg, C, dtype, &sh))
+    ipw *= 2;
+  return ipw;
+}
+
+int conv_sweep_blocks(const SweepArgs& a, int dtype) {
+  const int ipw = conv_sweep_images(a.Himg, a.Wimg, a.C, dtype, a.M, a.nchains);
+  return (a.M + ipw - 1) / ipw * a.nchains;
+}
+hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
+  SweepArgs a = a_in;
+  if (a.nchains <= 0) return hipSuccess;
+  if (a.tau && (dtype != 0 || a.nsteps != 1 || a.nlast != 1 || !a.Z)) return hipErrorInvalidValue;
+  if ((a.act == ACT_IDENT) != (a.Dm != nullptr)) return hipErrorInvalidValue;     // the adjoint's steps, and only they
+  if (a.M < 1 || !conv_sweep_supported(a.Himg, a.Wimg, a.C, dtype)) return hipErrorInvalidValue;
+  a.ipw = conv_sweep_images(a.Himg, a.Wimg, a.C, dtype, a.M, a.nchains);
+  ConvSweepShape sh;
+  if (!conv_sweep_shape(a.ipw * a.Himg * a.Wimg, a.C, dtype, &sh)) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)((a.M + a.ipw - 1) / a.ipw) * (unsigned)a.nchains;
+  trace_before(s);
+  hipError_t e = hipErrorInvalidValue;
+#define MGRIT_CS(NP_, CP_, NWV_, NBW_, RING_, TAU_)                                                                    \
+  if (sh.np == NP_ && sh.cp == CP_ && sh.nwv == NWV_ && sh.nbw == NBW_ && sh.ring == RING_ && (a.tau != 0) == TAU_)    \
+    e = a.act == ACT_TANH   ? launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_TANH, TAU_>(a, blocks, sh.smem, s)  \
+        : a.act == ACT_RELU ? launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_RELU, TAU_>(a, blocks, sh.smem, s)  \
+                            : launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_IDENT, TAU_>(a, blocks, sh.smem, s);
+  MGRIT_CS(1, 16, 8, 8, false, false) MGRIT_CS(1, 32, 8, 8, false, false) MGRIT_CS(1, 48, 8, 8, false, false)
+  MGRIT_CS(1, 64, 8, 4, false, false) MGRIT_CS(1, 64, 8, 8, true, false)
+  MGRIT_CS(3, 16, 8, 8, false, false) MGRIT_CS(3, 32, 8, 4, false, false)
+  MGRIT_CS(3, 16, 8, 8, false, true) MGRIT_CS(3, 32, 8, 4, false, true)
+#undef MGRIT_CS
+  // algorithmic bytes: per layer step the weights and bias, the act' factor, the right-hand side and what is kept of the
+  // state; the start state once per chain
+  const double es = dtype == 0 ? 4.0 : 2.0, E4 = 4.0 * (double)a.E;
+  const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
+  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.C : 0.0) + (a.Dm ? es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
+                     (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
+  trace_after(s, TRACE_CONV_SWEEP_F32, (long long)steps,
+              steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0)));
+  return e;
+}
+
+}  // namespace mgrit

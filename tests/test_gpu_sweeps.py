@@ -1,0 +1,59 @@
+"""Sweep kernels (many layer steps in one launch) at the edges of their instances, against the CPU oracle: channel counts that
+fill and do not fill a block of 16, pixel counts around the multiples of 16, images that share a workgroup (the last
+workgroup short), the largest image and the one past it, one coarse interval, trailing F-points, m = 2.
+Tolerances (relative L2 per state / per layer gradient): float 1e-5, bf16 operands 2e-2, as in the other parity tests."""
+import numpy as np
+import pytest
+
+import mgrit_inputs as I
+from tests.gpu_util import GpuProblem, oracle_forward, oracle_adjoint, rel_l2_per_state
+
+pytestmark = pytest.mark.gpu
+TOL = {I.FP32: 1e-5, I.BF16: 2e-2}
+
+
+def _conv(C, H, W, B, N, m, levels, dtype, relax=I.RELAX_FCF, act=I.TANH, it=1):
+    name = f"sweep_conv_c{C}_{H}x{W}_B{B}_N{N}_m{m}_L{levels}_{'bf16' if dtype else 'fp32'}_{'FCF' if relax else 'F'}_{'relu' if act else 'tanh'}"
+    return I.reduced(I.cfg4(it), name=name, C=C, Himg=H, Wimg=W, B=B, N=N, m=m, max_levels=levels, dtype=dtype, relax=relax, act=act)
+
+
+CONV = [
+    _conv(8, 3, 5, 3, 7, 2, 3, I.FP32),                            # 15 pixels, half-empty channel block, m = 2, trailing
+    _conv(16, 4, 4, 21, 97, 4, 2, I.FP32, act=I.RELU, it=2),       # 16 pixels, images share workgroups, the last one short
+    _conv(16, 32, 32, 1, 8, 4, 2, I.FP32),                         # the largest image
+    _conv(24, 11, 3, 2, 9, 3, 3, I.FP32, relax=I.RELAX_F),         # 33 pixels, 24 of 32 channels
+    _conv(32, 16, 32, 1, 5, 4, 2, I.FP32, act=I.RELU),             # 512 pixels: the largest of this instance; one interval
+    _conv(32, 19, 27, 1, 4, 2, 2, I.FP32),                         # 513 pixels: lockstep launches
+    _conv(16, 7, 9, 2, 4, 4, 2, I.BF16, it=2),                     # one interval (Nc = 1)
+    _conv(40, 5, 13, 2, 11, 4, 2, I.BF16),                         # 65 pixels, 40 of 48 channels
+    _conv(48, 31, 33, 1, 6, 3, 2, I.BF16, relax=I.RELAX_F),        # 1023 pixels
+    _conv(56, 8, 8, 2, 10, 2, 4, I.BF16),                          # 56 of 64 channels
+    _conv(64, 16, 32, 1, 8, 4, 2, I.BF16, act=I.RELU),             # 512 pixels: the whole layer's weights in LDS
+    _conv(64, 27, 19, 2, 18, 4, 3, I.BF16),                        # 513 pixels: weights tap by tap
+    _conv(64, 32, 32, 1, 9, 2, 3, I.BF16, relax=I.RELAX_F, it=2),  # 1024 pixels
+]
+
+
+@pytest.mark.parametrize("wl", CONV, ids=lambda w: w.name)
+def test_conv_sweep_instances(wl):
+    print(f"\n[case] {wl.name}", flush=True)
+    data = I.generate(wl)
+    gp = GpuProblem(wl, data)
+    _, U, hist, it = gp.forward()
+    Uo, hist_o, it_o = oracle_forward(wl, data)
+    tol = TOL[wl.dtype]
+    assert it == it_o and rel_l2_per_state(U, Uo) <= tol
+    # a residual that has converged stops at the float32 rounding floor: one ulp of the largest state value per entry
+    sizes, _ = gp.M.mgrit_level_map(gp.p)
+    floor = 2.0 ** -23 * float(np.abs(Uo).max()) * np.sqrt((sizes[1] + 1) * wl.E)
+    for a, b in zip(hist, hist_o):
+        assert abs(a - b) <= (1e-3 if wl.dtype == I.FP32 else 0.2) * b + floor, (hist, hist_o)
+    if wl.dtype == I.FP32 and wl.act == I.RELU:
+        return                                   # ReLU' is a 0/1 decision that summation order can turn
+    Ul = Uo.astype(np.float32) if wl.dtype == I.FP32 else I.round_to_bf16(Uo.astype(np.float32))
+    lamN = np.random.default_rng(3).standard_normal(wl.state_shape).astype(np.float32)
+    Lam, dW, db, _, _ = gp.adjoint(Ul, lamN)
+    Lo, dWo, dbo, _, _ = oracle_adjoint(wl, data, Ul, lamN)
+    eL, eW, eb = rel_l2_per_state(Lam, Lo), rel_l2_per_state(dW, dWo), rel_l2_per_state(db, dbo)
+    print(f"{wl.name}: Lam {eL:.2e} dW {eW:.2e} db {eb:.2e}", flush=True)
+    assert eL <= tol and eW <= tol and eb <= tol, (eL, eW, eb)
