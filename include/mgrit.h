@@ -25,9 +25,8 @@
  *
  * Environment (diagnostic switches, read at every call; results agree with the default path to rounding).
  * MGRIT_NO_SWEEP=1 makes the library use one launch per layer step also where it would fuse many steps
- * into one launch (dense layers of width 128 or 256 with many coarse intervals; convolution layers whose images fit
- * on a compute unit: at most 1024 pixels, in float at most 16 channels, or 32 and 512 pixels).  MGRIT_SWEEP_WAVES=4 runs
- * the fused sweep of width 256 with four instead of eight wavefronts.  MGRIT_GRAD_NARROW=1 keeps the
+ * into one launch (dense layers of width at most 256; convolution layers whose images fit on a compute unit: at most
+ * 1024 pixels, in float at most 16 channels, or 32 and 512 pixels).  MGRIT_GRAD_NARROW=1 keeps the
  * parameter gradient of dense layers of width 512 and more on the 128x128 tiles of narrower layers.
  * MGRIT_MASKED_STEP=1 sends dense layer steps whose batch, width and contraction length are whole multiples of
  * the tile through the bounds-masked loop that ragged shapes use.

@@ -127,6 +127,10 @@ int make_plan(const mgrit_problem_t* p, Plan* pl, int fcP = 0) {
   if (pl->L > 1) {
     size_t np1 = (size_t)step_grid_blocks(a, p->layer, p->dtype, pl->Nl[1]) * pl->Nl[1];
     if (np1 > np) np = np1;
+    if (p->layer == MGRIT_LAYER_DENSE && sweep_supported(p->q)) {           // the sweep kernel's workgroups, one per slice of rows
+      np1 = (size_t)sweep_blocks(pl->M, pl->Nl[1]);
+      if (np1 > np) np = np1;
+    }
   }
   if (fcP)     // the dense launch of the fully connected groups adds its workgroups (at most 32x32 tiles of each)
     np += (size_t)((p->B + 31) / 32) * (size_t)((pl->dfc + 31) / 32) * (size_t)pl->nfc;
@@ -267,20 +271,18 @@ struct Solver {
   void propagate(int l, long long js0, long long jstride, int groups) {
     step(l, js0, jstride, groups, X[l], pm(l, js0 - 1, jstride), X[l], pm(l, js0, jstride));
   }
-  // Dense layers: one fused launch per F-relaxation sweep where it pays -- a supported width, at least two steps per
-  // interval, and enough (interval, 32-row slice) workgroups to occupy the chip; with fewer, the lockstep launches (which
-  // spread one step over many workgroups) are as fast.
-  bool use_sweep(int l) const {
-    if (pl.fcP || p->m < 3 || p->layer != MGRIT_LAYER_DENSE || !sweep_enabled()) return false;
-    return sweep_supported(p->q, p->dtype) && sweep_blocks(pl.M, pl.Nl[l + 1]) >= 128;
-  }
-  // Convolution layers whose images fit on a CU: all relaxation of a level's visit is one launch (march), the closing
-  // F-relaxation and the coarsest solve are one launch each.  A chain's step takes less time than a lockstep launch of the
-  // same step at every size, also where only a few workgroups run: whole solves 372 -> 240 us (5 images of 13 x 17 pixels, 24
-  // channels, bf16), 1405 -> 828 us (64 of 28 x 28, 16 channels, float), 16.6 -> 10.8 ms (32 of 32 x 32, 64 channels, bf16).
+  // Layers whose state fits on a CU -- convolution layers on images of at most 1024 pixels, dense layers of width at most
+  // 256: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
+  // one launch each.  A chain's step takes less time than a lockstep launch of the same step at every size, also where
+  // only a few workgroups run: whole solves 372 -> 240 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 828 us
+  // (64 of 28 x 28, 16 channels, float), 16.6 -> 10.8 ms (32 of 32 x 32, 64 channels, bf16);
+  // 250 -> 135 us (4 samples, width 8), 655 -> 540 us (128 samples, width 256, float).
   bool use_march() const {
-    return !pl.fcP && p->layer == MGRIT_LAYER_CONV3X3 && sweep_enabled() &&
-           conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype);
+    if (pl.fcP || !sweep_enabled()) return false;
+    // (a launch holds less than 2^32 threads: at most 1024 for 16 rows, 512 for an image, of every chain)
+    const long long chains = pl.L > 1 ? pl.Nl[1] + 1LL : 1LL;
+    if ((p->layer == MGRIT_LAYER_CONV3X3 ? p->B * chains * 512 : (pl.M + 15LL) / 16 * chains * 1024) >= 1LL << 32) return false;
+    return p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : sweep_supported(p->q);
   }
   // chains of level l that start at sweep point ci * stride, for every ci
   SweepArgs sweep_args(int l, long long stride) const {
@@ -300,7 +302,11 @@ struct Solver {
     const PtMap unit = pm(l, 0, 1);                                 // storage index of sweep point js = base + js * stride
     a.X = X[l]; a.xb = unit.base; a.xs = unit.stride * stride; a.xk = unit.stride;
   }
-  void launch_march(const SweepArgs& a) { if (err == hipSuccess) chk(launch_conv_sweep(a, p->dtype, s)); }
+  void launch_march(SweepArgs& a, long long units) {
+    a.units = units;
+    if (err != hipSuccess) return;
+    chk(p->layer == MGRIT_LAYER_CONV3X3 ? launch_conv_sweep(a, p->dtype, s) : launch_sweep(a, p->dtype, s));
+  }
   // Where the current values of a level's C-points 0, m, 2m, .. are: point js = j m at p[m.base + j m.stride].
   // They do not live in the level's own array: the relaxation leaves them in R[l], the coarse solve in X[l + 1]
   // (it solves for their corrected values: with injection, U_C + (V_H - U_H) is V_H), and every consumer reads them
@@ -310,16 +316,6 @@ struct Solver {
   void f_relax(int l, const CPoints& c) {                      // Sec. III-C, Fig. 3
     const int Nc = pl.Nl[l + 1];
     const int tail = pl.Nl[l] - Nc * p->m;                     // F-points behind the last C-point (< m)
-    if (use_sweep(l)) {
-      SweepArgs a = sweep_args(l, p->m);
-      a.S = c.p; a.sm = c.m;
-      keep_states(a, l, p->m);
-      a.nsteps = a.nlast = p->m - 1; a.nchains = Nc;
-      if (err == hipSuccess) chk(launch_sweep(a, p->dtype, s));
-      if (tail > 0) step(l, (long long)Nc * p->m + 1, p->m, 1, c.p, PtMap{c.m.base + Nc * c.m.stride, 0}, X[l], pm(l, (long long)Nc * p->m + 1, 1));
-      for (int k = 2; k <= tail; ++k) propagate(l, (long long)Nc * p->m + k, p->m, 1);
-      return;
-    }
     step(l, 1, p->m, Nc + (1 <= tail ? 1 : 0), c.p, c.m, X[l], pm(l, 1, p->m));
     for (int k = 2; k < p->m; ++k) propagate(l, k, p->m, Nc + (k <= tail ? 1 : 0));
   }
@@ -334,7 +330,7 @@ struct Solver {
       keep_states(a, l, p->m);
       a.store0 = 1;
       a.nsteps = p->m - 1; a.nlast = pl.Nl[l] - Nc * p->m; a.nchains = Nc + 1;
-      launch_march(a);
+      launch_march(a, pl.Nl[l] - Nc);
       return;
     }
     chk(launch_copy_points(X[l], pm(l, 0, p->m), X[l + 1], PtMap{0, 1}, pl.E, pl.Nl[l + 1] + 1, s));
@@ -348,7 +344,7 @@ struct Solver {
       a.S = X[l]; a.sm = pm(l, 0, 0);
       keep_states(a, l, 0);
       a.nsteps = a.nlast = pl.Nl[l]; a.nchains = 1;
-      launch_march(a);
+      launch_march(a, pl.Nl[l]);
       return;
     }
     for (int j = 1; j <= pl.Nl[l]; ++j) propagate(l, j, 1, 1);
@@ -373,7 +369,9 @@ struct Solver {
       a.zb = 1; a.zs = 1;
       a.nsteps = a.nlast = m;
     }
-    launch_march(a);
+    // (counted as the relaxation's lockstep launches are: the trailing F-points and the first interval's repeated sweep,
+    // which change nothing before the level is closed, among them)
+    launch_march(a, (p->relax == MGRIT_RELAX_FCF ? 2 : 1) * (long long)pl.Nl[l]);
   }
 
   // Nested-iteration start: the coarsest level's own equation is solved in sequence from the known
@@ -412,7 +410,7 @@ struct Solver {
     const bool norm = l == 0 && want_norm;
     const PtMap next = PtMap{c.m.base + c.m.stride, c.m.stride};
     int blocks;
-    if (use_march() && p->dtype == MGRIT_FP32) {
+    if (use_march() && !(p->layer == MGRIT_LAYER_CONV3X3 && p->dtype == MGRIT_BF16)) {
       // (the coarse step here and the one of the coarse solve nearly cancel, so in float they have to round alike and both
       // are the sweep kernel's: 1.7e-7 from the exact states with the lockstep kernel here, 1.0e-7 so)
       SweepArgs a = sweep_args(l + 1, 1);
@@ -421,8 +419,8 @@ struct Solver {
       a.nsteps = a.nlast = 1; a.nchains = Nc;
       a.tau = 1; a.Z = g[l + 1]; a.zb = 1; a.zs = 1;
       if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = partial; }
-      launch_march(a);
-      blocks = conv_sweep_blocks(a, p->dtype);
+      launch_march(a, Nc);
+      blocks = p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_blocks(a, p->dtype) : sweep_blocks(a.M, Nc);
     } else {
       StepArgs a = base_args(l + 1, 1, 1);
       a.X = c.p; a.xm = c.m;

@@ -105,11 +105,11 @@ template <int ACT> __device__ __forceinline__ float act_prime_c(float z) {
 // the scalar unit.)
 // XCD-aware workgroup order: hardware deals consecutive workgroup ids round-robin to the 8
 // XCDs; remap so that consecutive logical tiles (which share a group's state and weights)
-// land on the same XCD and meet in its L2.
+// land on the same XCD and meet in its L2.  With a count that is no multiple of 8 the first
+// XCDs get one more.
 __device__ __forceinline__ int logical_block() {
-  int total = gridDim.x, L = blockIdx.x;
-  if ((total & 7) == 0) L = (L & 7) * (total >> 3) + (L >> 3);
-  return L;
+  const int total = gridDim.x, L = blockIdx.x, x = L & 7, r = total & 7;
+  return x * (total >> 3) + (x < r ? x : r) + (L >> 3);
 }
 
 // p / w for 0 <= p < 4096 and 1 <= w <= 256 with magic = ceil(2^20 / w): exact because p * (magic * w - 2^20) < 2^20

@@ -117,7 +117,7 @@ hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int
 //   X, xk != 0: the state after every step k, in X[xb + ci*xs + k*xk]; with store0 also the start state, k = 0
 //   Y:          the state after step kmid, in Y[yb + ci*ys]
 //   Z:          the state after the last step, in Z[zb + ci*zs], if n > kmid; chain 0's state after step kmid in Z[zfirst]
-//   tau:        float convolution layers, single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of
+//   tau:        not for bf16 convolution layers; single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of
 //               (Z - Ref[rm(ci)])^2, Z before the update, in norm_partial[workgroup]
 // S may not be written by another chain: X, Y, Z are other arrays, or other points of the same one.
 struct SweepArgs {
@@ -133,14 +133,14 @@ struct SweepArgs {
   long long lb, ls, lk;
   float hs;
   int act, nsteps, nlast, nchains, M, q;
+  long long units;                       // layer steps of the schedule that the launch stands for (launch trace)
   long long E, wsize;
   int Himg, Wimg, C;                     // convolution sweep only (then M = images per state)
   int ipw;                               // ... images per workgroup (filled in by the launch wrapper)
 };
-// Dense layers: workgroup (chain, slice of 32 batch rows) -- a dense layer acts on every batch row by itself, so the
-// slices of a chain never exchange anything.  Keeps every state (X); all chains have the same length.
-bool       sweep_supported(int q, int dtype);
-int        sweep_blocks(int M, int nchains);
+// Dense layers of width at most 256: workgroup (chain, slice of batch rows).
+bool       sweep_supported(int q);
+int        sweep_blocks(int M, int nchains);             // workgroups of a launch
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s);
 // 3x3 convolution layers: workgroup (chain, images).
 bool       conv_sweep_supported(int Himg, int Wimg, int C, int dtype);

@@ -2200,286 +2200,6 @@ static hipError_t launch_conv_grad(const GradArgs& a, unsigned blocks, size_t sm
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------------------
-// Fused F-relaxation sweep for dense layers.  A workgroup owns 32 batch rows of one coarse interval
-// and marches through all steps of the sweep: the fp32 state slice S and its matrix-core operand
-// copy A (Dm .* S in the operand type) stay in LDS, the weights of each layer stream through two LDS
-// slabs of BK values of k (whole-line loads into a register ring of PF slabs, running ahead
-// across layer boundaries; while one slab is multiplied the next is written to the other buffer).  Every
-// wavefront loads, stages and multiplies its own weight rows only, so the slab loop has no workgroup barrier.  The raw sums of a step go through the slab buffer that has just become free, so that
-// the update -- new state to LDS and to global memory, next operand -- is one float4 pass over whole rows.  Wavefront w of NWV owns the column blocks w*NBW .. w*NBW + NBW - 1 of 32 columns;
-// q = 32 * NBW * NWV.  Width 256 runs with eight wavefronts of one column block each: two per SIMD, so that one
-// wavefront's fragment reads and float4 passes hide behind the other's matrix instructions (four wavefronts of two
-// blocks left the matrix cores idle half of the time).
-// WN: the weights are W[k][n] (the adjoint sweep on the caller's array): a slab is BK rows of k, of which a wavefront
-// loads and stages its own columns, k-major with pitch Q + 4 (float) or Q + 16 (bf16) -- no larger than the n-major
-// slab -- and the fragments come from mma_step_wn.
-// ------------------------------------------------------------------------------------------
-constexpr int SWEEP_R = 32;
-template <typename WT> struct SweepOp;
-template <> struct SweepOp<float>  { static constexpr int BK = 32; };
-template <> struct SweepOp<__bf16> { static constexpr int BK = 64; };
-
-template <typename WT, int NBW, int PF, int NWV, bool WN = false>
-__global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
-  constexpr int NT = 64 * NWV;                  // shadows the file-wide 256: NWV wavefronts
-  constexpr int R = SWEEP_R, BK = SweepOp<WT>::BK, VEC = Op<WT>::VEC, KSTEP = Op<WT>::KSTEP, PAD = Op<WT>::PAD;
-  constexpr int Q = 32 * NBW * NWV, Q4 = Q / 4;
-  constexpr int AST = Q + PAD, ST = BK + PAD;
-  constexpr int PPR = BK / VEC;                 // 16-byte pieces per weight row and slab (one 128-byte line)
-  constexpr int WROWS = 32 * NBW;               // weight rows (output columns) of a wavefront
-  constexpr int BP = WROWS * PPR / 64;          // pieces per lane and slab
-  constexpr int NSL = Q / BK;                   // slabs per layer
-  static_assert(WROWS * PPR % 64 == 0 && R * Q4 % NT == 0, "slab and slice must divide over the lanes");
-  constexpr int QP = Q + (sizeof(WT) == 2 ? 16 : 4);    // k-major slab: row pitch
-  constexpr int PPN = WROWS / VEC;                      // ... and 16-byte pieces of a wavefront's columns per k row
-  constexpr int BUF = WN ? BK * QP : Q * ST;            // elements of one slab buffer
-  static_assert(BK * QP <= Q * ST, "the k-major slab fits the n-major one's buffer");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  float* S = reinterpret_cast<float*>(smem_raw);           // [R][Q] state slice
-  WT* A = reinterpret_cast<WT*>(S + R * Q);                // [R][AST] operand of the current step
-  WT* Bs = A + R * AST;                                    // [2][Q][ST] weight slabs: row = output column, k fastest
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, c = lane & 31;
-  const int L = logical_block();
-  const int nsl = (a.M + R - 1) / R;
-  const long long ci = L / nsl;
-  const int r0 = (L % nsl) * R;
-  const int rows = min(R, a.M - r0);
-  const long long slice_off = (long long)r0 * Q;
-  const WT* Wall = reinterpret_cast<const WT*>(a.W);
-  const WT* Dall = reinterpret_cast<const WT*>(a.Dm);
-  auto layer_of = [&](int k) { return a.lb + ci * a.ls + (long long)(k - 1) * a.lk; };
-
-  // ---- weight slabs: the sweep's slabs are numbered through, it = (k - 1) * NSL + sl; PF of them are in
-  // flight in registers (a workgroup has a CU to itself, so the loaded memory latency is hidden by depth)
-  const int total = a.nsteps * NSL;
-  uint4 breg[PF][BP];
-  auto load_slab = [&](uint4 (&br)[BP], int it) {
-    const WT* Wp = Wall + layer_of(it / NSL + 1) * a.wsize + (it % NSL) * (WN ? BK * Q : BK);   // slab = k range
-#pragma unroll
-    for (int i = 0; i < BP; ++i) {
-      if constexpr (WN) {
-        const int p = lane + 64 * i, kr = p / PPN, col = wave * WROWS + (p % PPN) * VEC;
-        br[i] = ld_weights<false>(Wp + kr * Q + col);
-      } else {
-        const int p = lane + 64 * i, row = wave * WROWS + p / PPR, kc = (p % PPR) * VEC;
-        br[i] = ld_weights<false>(Wp + row * Q + kc);
-      }
-    }
-  };
-  auto store_slab = [&](const uint4 (&br)[BP], WT* dst) {
-#pragma unroll
-    for (int i = 0; i < BP; ++i) {
-      if constexpr (WN) {
-        const int p = lane + 64 * i, kr = p / PPN, col = wave * WROWS + (p % PPN) * VEC;
-        *reinterpret_cast<uint4*>(&dst[kr * QP + col]) = br[i];
-      } else {
-        const int p = lane + 64 * i, row = wave * WROWS + p / PPR, kc = (p % PPR) * VEC;
-        *reinterpret_cast<uint4*>(&dst[row * ST + kc]) = br[i];
-      }
-    }
-  };
-  // A wavefront loads, stages and multiplies only its own weight rows, so the slab pipeline needs no workgroup
-  // barrier: its LDS operations execute in order, and the fences only keep the compiler from moving the
-  // fragment reads across the stores.
-  auto wave_sync = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
-#pragma unroll
-  for (int sidx = 0; sidx < PF; ++sidx)
-    if (sidx < total) load_slab(breg[sidx], sidx);
-
-  // ---- start state -> S (rows past the batch end are zero; loads are unconditional)
-  {
-    const float* sp = a.S + (a.sm.base + ci * a.sm.stride) * a.E + slice_off;
-#pragma unroll
-    for (int i = 0; i < R * Q4 / NT; ++i) {
-      const int p = tid + NT * i, row = p / Q4, c4 = (p % Q4) * 4;
-      const bool ok = row < rows;
-      float4 v = *reinterpret_cast<const float4*>(sp + (ok ? row * Q + c4 : 0));
-      if (!ok) v = make_float4(0.f, 0.f, 0.f, 0.f);
-      *reinterpret_cast<float4*>(S + row * Q + c4) = v;
-    }
-  }
-  // The column group of a thread in the float4 passes over the slice is the same for all its pieces
-  // (256 threads are a multiple of the Q/4 pieces of a row)
-  const int c4t = (tid % Q4) * 4;
-  // operand of a step from the state slice: (Dm[layer] .* S) in the matrix-core type
-  auto build_operand = [&](long long layer) {
-    const WT* dp = Dall ? Dall + layer * a.E + slice_off : nullptr;
-#pragma unroll
-    for (int i = 0; i < R * Q4 / NT; ++i) {
-      const int row = (tid + NT * i) / Q4;
-      float4 v = *reinterpret_cast<const float4*>(S + row * Q + c4t);
-      if (dp) {
-        const float4 d = d4_to_f4(ld_d4(dp + (row < rows ? row * Q + c4t : 0)));
-        v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w;       // rows past the end hold 0 in S
-      }
-      cvt_store4(&A[row * AST + c4t], v);
-    }
-  };
-  __syncthreads();                                         // S complete
-  build_operand(layer_of(1));
-  // slab j lives in ring slot j % PF and goes to LDS buffer j % 2; a slot is reloaded with slab j + PF as
-  // soon as slab j has been written to LDS
-  static_assert(NSL % PF == 0 && PF % 2 == 0, "ring slot and LDS buffer of a slab must be compile-time values");
-  store_slab(breg[0], Bs);
-  if (PF < total) load_slab(breg[0], PF);
-  __syncthreads();                                         // the first operand is complete
-
-  for (int k = 1; k <= a.nsteps; ++k) {
-    floatx16 acc[1][NBW];
-    // bias of this thread's column group in the float4 pass: requested before the contraction, its latency
-    // would otherwise open the epilogue
-    const long long layer = layer_of(k);
-    float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (a.bias) bv = *reinterpret_cast<const float4*>(a.bias + layer * Q + c4t);
-#pragma unroll
-    for (int t = 0; t < NBW; ++t) acc[0][t] = zero16();
-    for (int sl0 = 0; sl0 < NSL; sl0 += PF) {
-#pragma unroll
-      for (int sidx = 0; sidx < PF; ++sidx) {
-        const int sl = sl0 + sidx, it = (k - 1) * NSL + sl;
-        wave_sync();                                       // slab it of this wavefront is in LDS; slab it-1 consumed
-        if (it + 1 < total) {                              // next slab (maybe the next layer's first) -> other buffer
-          store_slab(breg[(sidx + 1) % PF], Bs + ((sidx + 1) & 1) * BUF);
-          if (it + 1 + PF < total) load_slab(breg[(sidx + 1) % PF], it + 1 + PF);
-        }
-        const WT* Bcur = Bs + (sidx & 1) * BUF;
-#pragma unroll
-        for (int ks = 0; ks < BK; ks += KSTEP) {
-          const WT* ap[1] = {&A[c * AST + sl * BK + ks]};
-          if constexpr (WN) {
-            int bcol[NBW];
-#pragma unroll
-            for (int t = 0; t < NBW; ++t) bcol[t] = (wave * NBW + t) * 32 + c;
-            mma_step_wn<1, NBW>(ap, Bcur + ks * QP, QP, bcol, acc, g);
-          } else {
-            const WT* bp[NBW];
-#pragma unroll
-            for (int t = 0; t < NBW; ++t) bp[t] = &Bcur[((wave * NBW + t) * 32 + c) * ST + ks];
-            mma_step<1, NBW>(ap, bp, acc, g);
-          }
-        }
-      }
-    }
-    // ---- epilogue of step k.  The raw sums go through the weight buffer that the last slab has just left
-    // (the other one already holds the next layer's first slab), so that the update is one float4 pass over
-    // whole rows: new state to S and to global memory, and the next step's operand to A.
-    __syncthreads();                                       // every wavefront is done with that buffer and with A
-    constexpr int ZST = Q + 4;
-    float* Z = reinterpret_cast<float*>(Bs + ((NSL - 1) & 1) * BUF);          // [R][ZST], fits: 128 Q + 512 bytes in either layout
-    static_assert((size_t)BUF * sizeof(WT) >= sizeof(float) * R * ZST, "the raw sums fit a slab buffer");
-#pragma unroll
-    for (int t = 0; t < NBW; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)                          // lane holds rows 8*(r/4) + 4*g + r%4 of column n
-        Z[(8 * (r >> 2) + 4 * g + (r & 3)) * ZST + (wave * NBW + t) * 32 + c] = acc[0][t][r];
-    __syncthreads();
-    {
-      const float* gp = a.G ? a.G + (a.gb + ci * a.gs + k) * a.E + slice_off : nullptr;
-      float* xo = a.X + (a.xb + ci * a.xs + (long long)k * a.xk) * a.E + slice_off;
-      const bool build = k < a.nsteps;
-      const WT* dp = (Dall && build) ? Dall + layer_of(k + 1) * a.E + slice_off : nullptr;
-      // (the activation as a compile-time value inside the pass: one branch per step, not four per float4)
-      auto update_pass = [&](auto actc) {
-      constexpr int ACT = decltype(actc)::value;
-#pragma unroll
-      for (int i = 0; i < R * Q4 / NT; ++i) {
-        const int row = (tid + NT * i) / Q4;
-        const bool ok = row < rows;
-        const int off = ok ? row * Q + c4t : 0;
-        const float4 z = *reinterpret_cast<const float4*>(Z + row * ZST + c4t);
-        float4 u = *reinterpret_cast<const float4*>(S + row * Q + c4t);
-        u.x += a.hs * act_fn_c<ACT>(z.x + bv.x); u.y += a.hs * act_fn_c<ACT>(z.y + bv.y);
-        u.z += a.hs * act_fn_c<ACT>(z.z + bv.z); u.w += a.hs * act_fn_c<ACT>(z.w + bv.w);
-        if (gp) {
-          const float4 gv = *reinterpret_cast<const float4*>(gp + off);
-          u.x += gv.x; u.y += gv.y; u.z += gv.z; u.w += gv.w;
-        }
-        if (!ok) u = make_float4(0.f, 0.f, 0.f, 0.f);       // rows past the batch end stay zero
-        *reinterpret_cast<float4*>(S + row * Q + c4t) = u;
-        if (ok) *reinterpret_cast<float4*>(xo + off) = u;
-        if (build) {
-          if (dp) {
-            const float4 d = d4_to_f4(ld_d4(dp + off));
-            u.x *= d.x; u.y *= d.y; u.z *= d.z; u.w *= d.w;
-          }
-          cvt_store4(&A[row * AST + c4t], u);
-        }
-      }
-      };
-      if (a.act == ACT_TANH)      update_pass(std::integral_constant<int, ACT_TANH>{});
-      else if (a.act == ACT_RELU) update_pass(std::integral_constant<int, ACT_RELU>{});
-      else                        update_pass(std::integral_constant<int, ACT_IDENT>{});
-    }
-    __syncthreads();                                       // next operand complete; the sums' buffer is free again
-  }
-}
-
-static size_t sweep_smem_bytes(int q, int dtype) {
-  const size_t es = dtype == 0 ? 4 : 2, pad = dtype == 0 ? Op<float>::PAD : Op<__bf16>::PAD;
-  const size_t bk = dtype == 0 ? SweepOp<float>::BK : SweepOp<__bf16>::BK;
-  return (size_t)SWEEP_R * q * 4 + (size_t)SWEEP_R * (q + pad) * es + (size_t)2 * q * (bk + pad) * es;
-}
-bool sweep_supported(int q, int dtype) {
-  return (q == 128 || q == 256) && sweep_smem_bytes(q, dtype) <= (size_t)150 * 1024;
-}
-int sweep_blocks(int M, int nchains) { return ((M + SWEEP_R - 1) / SWEEP_R) * nchains; }
-
-template <typename WT, int NBW, int NWV, bool WN = false>
-static hipError_t launch_sweep_t(const SweepArgs& a, unsigned blocks, size_t smem, hipStream_t s) {
-  if constexpr (!WN) {
-    if (a.wn) return launch_sweep_t<WT, NBW, NWV, true>(a, blocks, smem, s);
-  }
-  // weight slabs in flight in registers: as many as a layer has, at most 4 (eight measured no faster and
-  // take 256 registers of a lane)
-  constexpr int NSLABS = 32 * NBW * NWV / SweepOp<WT>::BK;
-  constexpr int PF = NSLABS < 4 ? NSLABS : 4;
-  static LdsOptIn opt;
-  if (opt.need(smem)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(dense_sweep_kernel<WT, NBW, PF, NWV, WN>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((dense_sweep_kernel<WT, NBW, PF, NWV, WN>), dim3(blocks), dim3(64 * NWV), smem, s, a);
-  return hipGetLastError();
-}
-// MGRIT_SWEEP_WAVES=4 in the environment runs width 256 with four wavefronts of two column blocks (diagnostic)
-static bool sweep_four_waves() {
-  const char* e = getenv("MGRIT_SWEEP_WAVES");
-  return e && e[0] == '4';
-}
-hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
-  if (a.nchains <= 0 || a.nsteps <= 0) return hipSuccess;
-  if (!sweep_supported(a.q, dtype) || a.M < 1) return hipErrorInvalidValue;
-  const size_t smem = sweep_smem_bytes(a.q, dtype);
-  const unsigned blocks = (unsigned)sweep_blocks(a.M, a.nchains);
-  const bool wide = a.q == 256, w4 = sweep_four_waves();
-  trace_before(s);
-  hipError_t e = hipErrorInvalidValue;
-  if (dtype == 0) {
-    if (!wide) e = launch_sweep_t<float, 1, 4>(a, blocks, smem, s);
-    else if (w4) e = launch_sweep_t<float, 2, 4>(a, blocks, smem, s);
-    else e = launch_sweep_t<float, 1, 8>(a, blocks, smem, s);
-  } else {
-    if (!wide) e = launch_sweep_t<__bf16, 1, 4>(a, blocks, smem, s);
-    else if (w4) e = launch_sweep_t<__bf16, 2, 4>(a, blocks, smem, s);
-    else e = launch_sweep_t<__bf16, 1, 8>(a, blocks, smem, s);
-  }
-  // algorithmic bytes per layer step: weights and bias, the act' factor, the right-hand side, the state out
-  // (the state in is read once per chain)
-  const double es = dtype == 0 ? 4.0 : 2.0;
-  const double per = (double)a.wsize * es + (a.bias ? 4.0 * a.q : 0.0) + (a.Dm ? es : 0.0) * (double)a.E +
-                     (a.G ? 4.0 : 0.0) * (double)a.E + 4.0 * (double)a.E;
-  trace_after(s, dtype == 0 ? TRACE_SWEEP_F32 : TRACE_SWEEP_BF16, (long long)a.nchains * a.nsteps,
-              (double)a.nchains * (a.nsteps * per + 4.0 * (double)a.E));
-  return e;
-}
-
 // MGRIT_GRAD_NARROW=1 in the environment keeps wide dense layers on the 128x128 gradient kernel with its separate
 // bias pass (diagnostic; the tests compare both)
 static bool dense_grad_narrow_forced() {

@@ -19,7 +19,8 @@ namespace mgrit {
 // NP = 1: bf16 problems.  NP = 3: float problems; state and weights are split into three bf16 numbers each, x = x1 + x2
 // + x3 (8 + 8 + 8 significant bits, so the split is exact), and the six products that reach 2^-24 are formed on the bf16
 // matrix cores with float accumulation -- 6/16 of the time of the float instructions.  The products left out are below
-// 2^-27 of the full one, less than the rounding of a single float addition.
+// 2^-27 of the full one, less than the rounding of a single float addition.  (An infinite operand splits into inf and NaN
+// parts, so an output that would be infinite is NaN; no finite result depends on one.)
 // The weights of a layer: all in LDS (the next layer's are on their way in registers during a step), or, for 64 channels
 // on images too large for that (RING), tap by tap through three LDS slots.
 // What bounds it: 16 channels float -- the LDS reads of the operand (15 KB per 16 pixels and step against 480 cycles of
@@ -27,13 +28,31 @@ namespace mgrit {
 // 8 KB of fragments for 16 instructions).  Global memory sees only what a caller keeps of the states.
 // ------------------------------------------------------------------------------------------
 typedef unsigned char u8;
+typedef short short4w __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-// x = h + m + l, each representable in bf16.  The first part is rounded to nearest unless that would overflow.
-__device__ __forceinline__ void split3(float x, __bf16& h, __bf16& m, __bf16& l) {
-  h = static_cast<__bf16>(x);
-  const float r = x - static_cast<float>(h);
-  m = static_cast<__bf16>(r);
-  l = static_cast<__bf16>(r - static_cast<float>(m));
+// x = h + m + l, each representable in bf16 (rounded to nearest each time; exact, since a float has 24 significant
+// bits), for a vector of floats: two values per conversion instruction.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ floatx2 widen2(bf16x2 v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  return floatx2{__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u)};
+}
+template <int N, typename F, typename V>
+__device__ __forceinline__ void split3(F f, V& h, V& m, V& l) {               // f(i) = value i
+#pragma unroll
+  for (int i = 0; i < N; i += 2) {
+    const floatx2 x = floatx2{f(i), f(i + 1)};
+    const bf16x2 a = __builtin_convertvector(x, bf16x2);
+    const floatx2 wa = widen2(a), r = floatx2{x[0] - wa[0], x[1] - wa[1]};
+    const bf16x2 b = __builtin_convertvector(r, bf16x2);
+    const floatx2 wb = widen2(b);
+    const bf16x2 c = __builtin_convertvector((floatx2{r[0] - wb[0], r[1] - wb[1]}), bf16x2);
+    h[i] = a[0]; h[i + 1] = a[1];
+    m[i] = b[0]; m[i + 1] = b[1];
+    l[i] = c[0]; l[i + 1] = c[1];
+  }
 }
 
 template <int NP, int CP>
@@ -110,13 +129,6 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   }
 
   floatx4 st[NBW][CB];
-  {
-    const float* sp = a.S + (a.sm.base + ci * a.sm.stride) * a.E + img_off;
-#pragma unroll
-    for (int b = 0; b < NBW; ++b)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) st[b][cb] = *reinterpret_cast<const floatx4*>(sp + off(b, cb));
-  }
   auto store_state = [&](float* o) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < NBW; ++b)
@@ -127,7 +139,14 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       }
   };
   auto place = [&](float* base, long long point) __attribute__((always_inline)) { return base + point * a.E + img_off; };
-  if (a.X && a.store0) store_state(place(a.X, a.xb + ci * a.xs));
+  {
+    const float* sp = a.S + (a.sm.base + ci * a.sm.stride) * a.E + img_off;
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) st[b][cb] = *reinterpret_cast<const floatx4*>(sp + off(b, cb));
+  }
+  if (a.store0) store_state(place(a.X, a.xb + ci * a.xs));
   if (n <= 0) return;                                           // the whole workgroup
 
   // ---- weights: unit u = (k step, output channel, piece of the step)
@@ -170,12 +189,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
           *reinterpret_cast<u32x4*>(q) = r[i];
         } else {
           bf16x8 h, m, l;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            __bf16 hh, mm, ll;
-            split3(__uint_as_float(r[i * WR + (e >> 2)][e & 3]), hh, mm, ll);
-            h[e] = hh; m[e] = mm; l[e] = ll;
-          }
+          split3<8>([&](int e) { return __uint_as_float(r[i * WR + (e >> 2)][e & 3]); }, h, m, l);
           *reinterpret_cast<bf16x8*>(q) = h;
           *reinterpret_cast<bf16x8*>(q + CP * 16) = m;
           *reinterpret_cast<bf16x8*>(q + 2 * CP * 16) = l;
@@ -217,13 +231,8 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
             cvt_store4(reinterpret_cast<__bf16*>(q), v);
           } else {
             bf16x4 h, m, l;
-            const float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              __bf16 hh, mm, ll;
-              split3(f[e], hh, mm, ll);
-              h[e] = hh; m[e] = mm; l[e] = ll;
-            }
+            const floatx4 f = floatx4{v.x, v.y, v.z, v.w};
+            split3<4>([&](int e) { return f[e]; }, h, m, l);
             *reinterpret_cast<bf16x4*>(q) = h;
             *reinterpret_cast<bf16x4*>(q + PLB) = m;
             *reinterpret_cast<bf16x4*>(q + 2 * PLB) = l;
@@ -612,7 +621,354 @@ hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
   const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
   const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.C : 0.0) + (a.Dm ? es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
                      (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
-  trace_after(s, TRACE_CONV_SWEEP_F32, (long long)steps,
+  trace_after(s, TRACE_CONV_SWEEP_F32, a.units,
+              steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0)));
+  return e;
+}
+
+// ------------------------------------------------------------------------------------------
+// Sweep over dense layers of width at most 256.  A dense layer acts on every batch row by itself, so a workgroup owns 16 RB
+// rows of one chain and marches through its layer steps without talking to any other.
+//   - Matrix instructions as in the convolution sweep, weights as the A operand: lane (c, kq) holds features
+//     16 fb + 4 kq .. + 3 of batch row c of a block; wavefront w owns the feature blocks w FBW .. + FBW - 1.  The float
+//     state stays in registers, the operand (act' .* state) of all rows sits in LDS.
+//   - The weights of a layer stream from L2, k step by k step (32 values of k), two k steps ahead in registers and running
+//     on into the next layer; every wavefront handles its own features' weights, so the contraction has no barriers.
+//     They pass through an LDS area of the wavefront's own: fragments read straight from memory touch a 64-byte segment
+//     per lane (38 GB/s per CU against 130 for whole segments).  k-major bf16 weights take LDS's transposing read.
+//   - Everything a wavefront does in a k step depends on what it did before, so the chain's latency counts: width 256 runs
+//     with sixteen wavefronts of one feature block (four per SIMD) instead of eight of two.
+// NP = 3 (float) splits state and weights into three bf16 numbers as the convolution sweep does.
+// What bounds it, width 256 float: splitting the weights (every wavefront its own, vector instructions) and the latency of
+// a k step; a step takes 9.1 us with 32 rows (float matrix instructions and eight wavefronts before: 12.5) and 5.5 us with
+// 16 (a lockstep launch before: 5.1 .. 7.5, and the state through memory).  Global memory sees the weights once per XCD and
+// what a caller keeps of the states.
+// Requesting a layer's lines ahead of their loads did not pay: 126 us instead of 105 for 16 serial steps.
+// ------------------------------------------------------------------------------------------
+template <int NP, int FBW, bool WN> constexpr int dense_sweep_stage() {     // bytes of a wavefront's staging area
+  return NP == 3 ? (WN ? 32 * (64 * FBW + 8) : 16 * FBW * 144) : (WN ? 32 * (32 * FBW + 32) : 16 * FBW * 80);
+}
+constexpr int dense_sweep_pitch(int np, int kp) { return np * kp * 2 + 16; }   // bytes of an operand row in LDS
+
+template <int NP, int NWV, int FBW, int RB, int ACT, bool WN>
+__global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
+  constexpr bool HD = ACT == ACT_IDENT;                             // the adjoint: act' factors, no bias
+  constexpr int NTH = 64 * NWV, R = 16 * RB;
+  constexpr int STG = dense_sweep_stage<NP, FBW, WN>();
+  constexpr int NL = NP == 3 ? 2 * FBW : FBW;                       // 16-byte loads of a k step per lane
+  typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
+  typedef typename DRaw<WT>::type DR;
+  typedef u32x4 LW;
+  extern __shared__ __attribute__((aligned(16))) u8 smem[];
+  __shared__ float red[NWV];
+
+  const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = a.q, KP = (q + 63) & ~63, KS = KP / 32, OP = dense_sweep_pitch(NP, KP);   // KS is even
+  const int nsl = (a.M + R - 1) / R;
+  const int L = logical_block();
+  const long long ci = L / nsl;
+  const int r0 = (L % nsl) * R, rows = min(R, a.M - r0);
+  const int n = ci == a.nchains - 1 ? a.nlast : a.nsteps;
+  u8* A = smem;                                                     // operand [R][OP]
+  u8* Ws = smem + R * OP + wave * STG;
+  const long long sl_off = (long long)r0 * q;
+  const int f0 = wave * FBW * 16;                                   // this wavefront's first feature
+  auto layer_of = [&](int k) __attribute__((always_inline)) { return a.lb + ci * a.ls + (long long)(k - 1) * a.lk; };
+  auto place = [&](const float* base, long long point) __attribute__((always_inline)) { return const_cast<float*>(base) + point * a.E + sl_off; };
+  // (rows past the batch read the last one's values, features past the width those of feature 0: never stored)
+  auto feat = [&](int j) __attribute__((always_inline)) { return f0 + 16 * j + 4 * kq; };
+  auto off = [&](int rb, int j) __attribute__((always_inline)) { return (unsigned)(min(16 * rb + c, rows - 1) * q + (feat(j) < q ? feat(j) : 0)); };
+
+  floatx4 st[RB][FBW];
+  auto store_state = [&](float* o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < FBW; ++j)
+        if (16 * rb + c < rows && feat(j) < q) *reinterpret_cast<floatx4*>(o + off(rb, j)) = st[rb][j];
+  };
+  {
+    const float* sp = place(a.S, a.sm.base + ci * a.sm.stride);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < FBW; ++j) st[rb][j] = *reinterpret_cast<const floatx4*>(sp + off(rb, j));
+  }
+  if (a.store0) store_state(place(a.X, a.xb + ci * a.xs));
+  if (n <= 0) return;                                               // the whole workgroup
+
+  // ---- weights of a k step, straight into registers: whole 128-byte (bf16: 64-byte) pieces of the wavefront's rows, or
+  // rows of k.  Everything past the width is clamped to a valid address: its operand is zero, or its output is not stored.
+  const WT* Wall = reinterpret_cast<const WT*>(a.W);
+  // (a k step inside the width: a uniform base and offsets that stay the same; the last ones are clamped value by value)
+  unsigned wo[NL];
+  int wk[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    int f, k;
+    if constexpr (WN) { constexpr int LPR = (NP == 3 ? 4 : 2) * FBW, VEC = NP == 3 ? 4 : 8; const int p = lane + 64 * i; k = p / LPR; f = f0 + (p % LPR) * VEC; }
+    else { constexpr int LPR = NP == 3 ? 8 : 4, VEC = NP == 3 ? 4 : 8; const int p = lane + 64 * i; f = f0 + p / LPR; k = (p % LPR) * VEC; }
+    f = f < q ? f : 0;
+    wk[i] = k;
+    wo[i] = (unsigned)(WN ? k * q + f : f * q + k) * (unsigned)sizeof(WT);
+  }
+  auto load_w = [&](LW (&w)[NL], const WT* Wp, int s) __attribute__((always_inline)) {
+    const int k0 = 32 * s;
+    if (k0 + 32 <= q) {
+      const char* base = reinterpret_cast<const char*>(Wp + (size_t)k0 * (WN ? q : 1));
+#pragma unroll
+      for (int i = 0; i < NL; ++i) w[i] = *reinterpret_cast<const LW*>(base + wo[i]);
+    } else {
+      const char* base = reinterpret_cast<const char*>(Wp);
+      const unsigned step = (unsigned)(k0 * (WN ? q : 1) * (int)sizeof(WT)), row = (unsigned)((WN ? q : 1) * (int)sizeof(WT));
+#pragma unroll
+      for (int i = 0; i < NL; ++i) w[i] = *reinterpret_cast<const LW*>(base + (k0 + wk[i] < q ? wo[i] + step : wo[i] - wk[i] * row));
+    }
+  };
+  auto stage_w = [&](const LW (&w)[NL]) __attribute__((always_inline)) {
+    {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int p = lane + 64 * i;
+        if constexpr (WN && NP == 3) {
+          u32x2* d = reinterpret_cast<u32x2*>(Ws + (p / (4 * FBW)) * (64 * FBW + 8) + (p % (4 * FBW)) * 16);
+          d[0] = u32x2{w[i][0], w[i][1]}; d[1] = u32x2{w[i][2], w[i][3]};
+        } else if constexpr (WN) *reinterpret_cast<u32x4*>(Ws + (p / (2 * FBW)) * (32 * FBW + 32) + (p % (2 * FBW)) * 16) = w[i];
+        else if constexpr (NP == 3) *reinterpret_cast<u32x4*>(Ws + (p >> 3) * 144 + (p & 7) * 16) = w[i];
+        else *reinterpret_cast<u32x4*>(Ws + (p >> 2) * 80 + (p & 3) * 16) = w[i];
+      }
+    }
+  };
+  // A wavefront's staging area is its own and its LDS operations execute in order: the fences only keep the compiler from
+  // moving accesses across.
+  auto wave_sync = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  DR dr[RB][FBW];
+  auto load_d = [&](int k) __attribute__((always_inline)) {
+    if constexpr (HD) {
+      const WT* dp = reinterpret_cast<const WT*>(a.Dm) + layer_of(k) * a.E + sl_off;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < FBW; ++j) dr[rb][j] = ld_d4(dp + off(rb, j));
+    }
+  };
+  auto write_operand = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < FBW; ++j)
+        if (feat(j) < KP) {
+          float4 v = make_float4(st[rb][j][0], st[rb][j][1], st[rb][j][2], st[rb][j][3]);
+          if constexpr (HD) { const float4 d = d4_to_f4(dr[rb][j]); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
+          if (feat(j) >= q) v = make_float4(0.f, 0.f, 0.f, 0.f);
+          u8* p = A + (16 * rb + c) * OP + feat(j) * 2;
+          if constexpr (NP == 1) {
+            cvt_store4(reinterpret_cast<__bf16*>(p), v);
+          } else {
+            bf16x4 h, m, l;
+            const floatx4 f = floatx4{v.x, v.y, v.z, v.w};
+            split3<4>([&](int e) { return f[e]; }, h, m, l);
+            *reinterpret_cast<bf16x4*>(p) = h;
+            *reinterpret_cast<bf16x4*>(p + KP * 2) = m;
+            *reinterpret_cast<bf16x4*>(p + KP * 4) = l;
+          }
+        }
+  };
+  const WT* Wc = Wall + layer_of(1) * a.wsize;
+  LW w0[NL], w1[NL];
+  load_w(w0, Wc, 0);
+  load_w(w1, Wc, 1);
+  load_d(1);
+  write_operand();
+  __syncthreads();
+
+  for (int k = 1; k <= n; ++k) {
+    const WT* Wn = Wall + layer_of(k < n ? k + 1 : k) * a.wsize;    // (past the last step: read, not used)
+    floatx4 bv[FBW], gv[RB][FBW];
+    if constexpr (!HD) {
+      const float* bp = a.bias + layer_of(k) * q;
+#pragma unroll
+      for (int j = 0; j < FBW; ++j) bv[j] = *reinterpret_cast<const floatx4*>(bp + (feat(j) < q ? feat(j) : 0));
+    }
+    if (a.G) {
+      const float* gp = place(a.G, a.gb + ci * a.gs + k);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < FBW; ++j) gv[rb][j] = *reinterpret_cast<const floatx4*>(gp + off(rb, j));
+    }
+    if (k < n) load_d(k + 1);
+
+    floatx4 acc[RB][FBW], low[RB][FBW];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < FBW; ++j) { acc[rb][j] = floatx4{0.f, 0.f, 0.f, 0.f}; low[rb][j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+    auto kstep = [&](LW (&w)[NL], int s) __attribute__((always_inline)) {
+      bf16x8 af[FBW][NP];
+      {
+        stage_w(w);
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < FBW; ++j) {
+          if constexpr (NP == 3 && WN) {
+            // rows k of 64 FBW + 8 bytes: the four lane groups, eight rows apart, fall on different banks
+            const u8* p = Ws + 8 * kq * (64 * FBW + 8) + (16 * j + c) * 4;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const float*>(p + e * (64 * FBW + 8));
+            split3<8>([&](int e) { return x[e]; }, af[j][0], af[j][1 % NP], af[j][2 % NP]);
+          } else if constexpr (NP == 3) {
+            const u8* p = Ws + (16 * j + c) * 144 + kq * 32;
+            const floatx4 x0 = *reinterpret_cast<const floatx4*>(p), x1 = *reinterpret_cast<const floatx4*>(p + 16);
+            split3<8>([&](int e) { return e < 4 ? x0[e & 3] : x1[e & 3]; }, af[j][0], af[j][1 % NP], af[j][2 % NP]);
+          } else if constexpr (WN) {
+            // two transposing reads: rows k = 8 kq + 0 .. 3 and + 4 .. 7 of column c of the block
+            constexpr int P = 32 * FBW + 32;
+            typedef __attribute__((address_space(3))) short4w* lds_s4;
+            const u8* p = Ws + (8 * kq + (c >> 2)) * P + 32 * j + 8 * (c & 3);
+            const short4w lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p));
+            const short4w hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p + 4 * P));
+            af[j][0] = __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo), __builtin_bit_cast(bf16x4, hi), 0, 1, 2, 3, 4, 5, 6, 7);
+          } else {
+            af[j][0] = *reinterpret_cast<const bf16x8*>(Ws + (16 * j + c) * 80 + kq * 16);
+          }
+        }
+        wave_sync();
+      }
+      // the k step after next goes into the registers this one has left
+      if (s + 2 < KS) load_w(w, Wc, s + 2); else load_w(w, Wn, s + 2 - KS);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const u8* p = A + (16 * rb + c) * OP + 64 * s + 16 * kq;
+        bf16x8 bf[NP];
+#pragma unroll
+        for (int t = 0; t < NP; ++t) bf[t] = *reinterpret_cast<const bf16x8*>(p + t * KP * 2);
+        if constexpr (NP == 1) {
+#pragma unroll
+          for (int j = 0; j < FBW; ++j) acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[j][0], bf[0], acc[rb][j], 0, 0, 0);
+        } else {
+          constexpr int PA[5] = {2, 0, 1, 1, 0}, PB[5] = {0, 2, 1, 0, 1};         // smallest products first
+#pragma unroll
+          for (int t = 0; t < 5; ++t)
+#pragma unroll
+            for (int j = 0; j < FBW; ++j)
+              low[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[j][PA[t] % NP], bf[PB[t] % NP], low[rb][j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < FBW; ++j) acc[rb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[j][0], bf[0], acc[rb][j], 0, 0, 0);
+        }
+      }
+    };
+    for (int s = 0; s < KS; s += 2) { kstep(w0, s); kstep(w1, s + 1); }
+
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int j = 0; j < FBW; ++j) {
+        floatx4 z = acc[rb][j];
+        if constexpr (NP == 3) z += low[rb][j];
+        if constexpr (!HD) z += bv[j];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) st[rb][j][v] += a.hs * act_fn_c<ACT>(z[v]);
+        if (a.G) st[rb][j] += gv[rb][j];
+      }
+
+    if (a.tau) {                                                    // coarse right-hand side: Z <- Z - state, and its norm
+      float* o = place(a.Z, a.zb + ci * a.zs);
+      const float* ref = a.Ref ? place(a.Ref, a.rm.base + ci * a.rm.stride) : nullptr;
+      float sq = 0.0f;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int j = 0; j < FBW; ++j)
+          if (16 * rb + c < rows && feat(j) < q) {
+            const floatx4 p = *reinterpret_cast<const floatx4*>(o + off(rb, j));
+            *reinterpret_cast<floatx4*>(o + off(rb, j)) = p - st[rb][j];
+            if (ref) {
+              const floatx4 d = p - *reinterpret_cast<const floatx4*>(ref + off(rb, j));
+              sq += (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+            }
+          }
+      if (a.norm_partial) {                                         // in a fixed order over the wavefronts
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) sq += __shfl_xor(sq, w, 64);
+        if (lane == 0) red[wave] = sq;
+        __syncthreads();
+        if (tid == 0) {
+          float t = red[0];
+#pragma unroll
+          for (int w = 1; w < NWV; ++w) t += red[w];
+          a.norm_partial[L] = t;
+        }
+      }
+      break;
+    }
+    float* o1 = nullptr;                                            // where this step's state is kept: at most two places
+    float* o2 = nullptr;
+    if (a.X && a.xk) o1 = place(a.X, a.xb + ci * a.xs + (long long)k * a.xk);
+    else if (k == a.kmid) { o1 = place(a.Y, a.yb + ci * a.ys); if (ci == 0) o2 = place(a.Z, a.zfirst); }
+    else if (a.Z && k == n) o1 = place(a.Z, a.zb + ci * a.zs);
+    for (; o1; o1 = o2, o2 = nullptr) store_state(o1);
+    if (k == n) break;
+    __syncthreads();                                                // every wavefront is done with the operand
+    write_operand();
+    Wc = Wn;
+    __syncthreads();
+  }
+}
+
+namespace {
+template <int NP, int NWV, int FBW, int RB, int ACT, bool WN>
+hipError_t launch_dense_sweep_t(const SweepArgs& a, unsigned blocks, hipStream_t s) {
+  const size_t smem = (size_t)16 * RB * dense_sweep_pitch(NP, (a.q + 63) & ~63) + (size_t)NWV * dense_sweep_stage<NP, FBW, WN>();
+  static LdsOptIn opt;
+  const void* k = reinterpret_cast<const void*>(dense_sweep_kernel<NP, NWV, FBW, RB, ACT, WN>);
+  if (opt.need(smem)) {
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) { opt = LdsOptIn(); return e; }
+  }
+  hipLaunchKernelGGL((dense_sweep_kernel<NP, NWV, FBW, RB, ACT, WN>), dim3(blocks), dim3(64 * NWV), smem, s, a);
+  return hipGetLastError();
+}
+// Rows of a workgroup: 32 where that still gives three quarters of the CUs a workgroup, else 16.  A CU holds one workgroup
+// of sixteen wavefronts, and a step of 16 rows takes 5.5 us against 9.1 us for 32: twice the workgroups pay as long as they
+// all run at once (17 chains of 128 rows, three steps: 22 us in 136 workgroups), not in two rounds.
+int sweep_rows(int M, int nchains) { return (long long)((M + 31) / 32) * nchains >= 192 ? 32 : 16; }
+}  // namespace
+
+bool sweep_supported(int q) { return q >= 8 && q <= 256 && q % 8 == 0; }
+int sweep_blocks(int M, int nchains) { const int r = sweep_rows(M, nchains); return (M + r - 1) / r * nchains; }
+
+hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
+  if (a.nchains <= 0) return hipSuccess;
+  if (a.M < 1 || !sweep_supported(a.q)) return hipErrorInvalidValue;
+  if ((a.act == ACT_IDENT) != (a.Dm != nullptr) || (a.Dm == nullptr && (a.wn || !a.bias))) return hipErrorInvalidValue;  // the adjoint's steps, and only they
+  if (a.tau && (a.nsteps != 1 || a.nlast != 1 || !a.Z)) return hipErrorInvalidValue;
+  const int rows = sweep_rows(a.M, a.nchains);
+  const unsigned blocks = (unsigned)sweep_blocks(a.M, a.nchains);
+  trace_before(s);
+  hipError_t e = hipErrorInvalidValue;
+#define MGRIT_DS_RB(NP_, NWV_, FBW_, RB_)                                                                     \
+  e = a.act == ACT_TANH   ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_TANH, false>(a, blocks, s)         \
+      : a.act == ACT_RELU ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_RELU, false>(a, blocks, s)         \
+      : a.wn              ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_IDENT, true>(a, blocks, s)         \
+                          : launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_IDENT, false>(a, blocks, s)
+#define MGRIT_DS(NP_, NWV_, FBW_) { if (rows == 32) MGRIT_DS_RB(NP_, NWV_, FBW_, 2); else MGRIT_DS_RB(NP_, NWV_, FBW_, 1); }
+  // wavefronts x feature blocks of 16 that cover the width
+  if (dtype == 0) { if (a.q <= 64) MGRIT_DS(3, 4, 1) else if (a.q <= 128) MGRIT_DS(3, 8, 1) else MGRIT_DS(3, 16, 1) }
+  else            { if (a.q <= 64) MGRIT_DS(1, 4, 1) else if (a.q <= 128) MGRIT_DS(1, 8, 1) else MGRIT_DS(1, 16, 1) }
+#undef MGRIT_DS
+#undef MGRIT_DS_RB
+  const double es = dtype == 0 ? 4.0 : 2.0, E4 = 4.0 * (double)a.E;
+  const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
+  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.q : 0.0) + (a.Dm ? es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
+                     (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
+  trace_after(s, dtype == 0 ? TRACE_SWEEP_F32 : TRACE_SWEEP_BF16, a.units,
               steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0)));
   return e;
 }

@@ -45,7 +45,7 @@ def test_conv_sweep_instances(wl):
     assert it == it_o and rel_l2_per_state(U, Uo) <= tol
     # a residual that has converged stops at the float32 rounding floor: one ulp of the largest state value per entry
     sizes, _ = gp.M.mgrit_level_map(gp.p)
-    floor = 2.0 ** -23 * float(np.abs(Uo).max()) * np.sqrt((sizes[1] + 1) * wl.E)
+    floor = 2.0 ** -23 * float(np.abs(Uo).max()) * np.sqrt((sizes[min(1, len(sizes) - 1)] + 1) * wl.E)
     for a, b in zip(hist, hist_o):
         assert abs(a - b) <= (1e-3 if wl.dtype == I.FP32 else 0.2) * b + floor, (hist, hist_o)
     if wl.dtype == I.FP32 and wl.act == I.RELU:
@@ -57,3 +57,30 @@ def test_conv_sweep_instances(wl):
     eL, eW, eb = rel_l2_per_state(Lam, Lo), rel_l2_per_state(dW, dWo), rel_l2_per_state(db, dbo)
     print(f"{wl.name}: Lam {eL:.2e} dW {eW:.2e} db {eb:.2e}", flush=True)
     assert eL <= tol and eW <= tol and eb <= tol, (eL, eW, eb)
+
+
+def _dense(q, B, N, m, levels, dtype, relax=I.RELAX_FCF, act=I.TANH, it=1):
+    name = f"sweep_dense_q{q}_B{B}_N{N}_m{m}_L{levels}_{'bf16' if dtype else 'fp32'}_{'FCF' if relax else 'F'}_{'relu' if act else 'tanh'}"
+    return I.reduced(I.cfg5(it), name=name, q=q, B=B, N=N, m=m, max_levels=levels, min_coarse=1, dtype=dtype, relax=relax, act=act,
+                     head_classes=0)
+
+
+DENSE = [
+    _dense(8, 1, 7, 2, 3, I.FP32, it=2),                           # one feature block, one row, trailing F-points
+    _dense(64, 17, 12, 4, 2, I.FP32),                              # the widest of the four-wavefront instance, 17 rows
+    _dense(72, 16, 9, 3, 2, I.FP32, relax=I.RELAX_F),              # 72 of 128 features, the last k step short
+    _dense(128, 33, 5, 4, 2, I.FP32),                              # one interval
+    _dense(136, 3, 24, 2, 4, I.FP32),                              # 136 of 256
+    _dense(248, 400, 60, 4, 2, I.FP32, act=I.RELU),                # 32-row slices, the last one short
+    _dense(256, 16, 8, 4, 1, I.FP32),                              # serial propagation
+    _dense(264, 5, 8, 4, 2, I.FP32),                               # too wide: lockstep launches
+    _dense(24, 40, 13, 3, 3, I.BF16),
+    _dense(104, 500, 49, 4, 2, I.BF16, it=2),                      # 32-row slices
+    _dense(256, 15, 33, 2, 3, I.BF16, relax=I.RELAX_F),
+    _dense(200, 50, 21, 5, 2, I.BF16),
+]
+
+
+@pytest.mark.parametrize("wl", DENSE, ids=lambda w: w.name)
+def test_dense_sweep_instances(wl):
+    test_conv_sweep_instances(wl)
