@@ -323,13 +323,15 @@ struct Solver {
   // C-points; the F-layers follow by F-relaxation, Sec. III-C).
   void close(int l) {
     if (use_march()) {
-      // chain ci: the C-point and the F-points behind it; the last chain is the last C-point with the trailing F-points
+      // chain ci: the C-point and the F-points behind it; trailing F-points are a chain of their own behind the last C-point,
+      // which otherwise the last chain passes on
       SweepArgs a = sweep_args(l, p->m);
       const int Nc = pl.Nl[l + 1];
       a.S = X[l + 1]; a.sm = PtMap{0, 1};
       keep_states(a, l, p->m);
-      a.store0 = 1;
-      a.nsteps = p->m - 1; a.nlast = pl.Nl[l] - Nc * p->m; a.nchains = Nc + 1;
+      const int tail = pl.Nl[l] - Nc * p->m;
+      a.store0 = tail > 0 ? 1 : 2;
+      a.nsteps = p->m - 1; a.nlast = tail > 0 ? tail : p->m - 1; a.nchains = Nc + (tail > 0 ? 1 : 0);
       launch_march(a, pl.Nl[l] - Nc);
       return;
     }

@@ -114,7 +114,8 @@ hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int
 //   step k = 1..n:  u <- u + hs * act(A_layer (Dm_layer .* u) + bias_layer) + G[gb + ci*gs + k]
 //   layer(k) = lb + ci*ls + (k-1)*lk
 // One launch replaces n lockstep launches (Sec. III-C, Fig. 3).  What it keeps of the states:
-//   X, xk != 0: the state after every step k, in X[xb + ci*xs + k*xk]; with store0 also the start state, k = 0
+//   X, xk != 0: the state after every step k, in X[xb + ci*xs + k*xk]; with store0 also the start state, k = 0,
+//               and with store0 = 2 the point behind the last chain, S[sm(nchains)] to X[xb + nchains*xs]
 //   Y:          the state after step kmid, in Y[yb + ci*ys]
 //   Z:          the state after the last step, in Z[zb + ci*zs], if n > kmid; chain 0's state after step kmid in Z[zfirst]
 //   tau:        not for bf16 convolution layers; single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of

@@ -139,14 +139,15 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       }
   };
   auto place = [&](float* base, long long point) __attribute__((always_inline)) { return base + point * a.E + img_off; };
-  {
-    const float* sp = a.S + (a.sm.base + ci * a.sm.stride) * a.E + img_off;
+  // the start state (store0 = 2: the last chain first passes on the point behind it)
+  for (int t = a.store0 == 2 && ci == a.nchains - 1 ? 1 : 0; t >= 0; --t) {
+    const float* sp = a.S + (a.sm.base + (ci + t) * a.sm.stride) * a.E + img_off;
 #pragma unroll
     for (int b = 0; b < NBW; ++b)
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) st[b][cb] = *reinterpret_cast<const floatx4*>(sp + off(b, cb));
+    if (a.store0) store_state(place(a.X, a.xb + (ci + t) * a.xs));
   }
-  if (a.store0) store_state(place(a.X, a.xb + ci * a.xs));
   if (n <= 0) return;                                           // the whole workgroup
 
   // ---- weights: unit u = (k step, output channel, piece of the step)
@@ -688,14 +689,15 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
       for (int j = 0; j < FBW; ++j)
         if (16 * rb + c < rows && feat(j) < q) *reinterpret_cast<floatx4*>(o + off(rb, j)) = st[rb][j];
   };
-  {
-    const float* sp = place(a.S, a.sm.base + ci * a.sm.stride);
+  // the start state (store0 = 2: the last chain first passes on the point behind it)
+  for (int t = a.store0 == 2 && ci == a.nchains - 1 ? 1 : 0; t >= 0; --t) {
+    const float* sp = place(a.S, a.sm.base + (ci + t) * a.sm.stride);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int j = 0; j < FBW; ++j) st[rb][j] = *reinterpret_cast<const floatx4*>(sp + off(rb, j));
+    if (a.store0) store_state(place(a.X, a.xb + (ci + t) * a.xs));
   }
-  if (a.store0) store_state(place(a.X, a.xb + ci * a.xs));
   if (n <= 0) return;                                               // the whole workgroup
 
   // ---- weights of a k step, straight into registers: whole 128-byte (bf16: 64-byte) pieces of the wavefront's rows, or
