@@ -256,19 +256,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
 #pragma unroll
     for (int b = 0; b < NBW; ++b) asm volatile("" : "+v"(mask[b]));
     const WT* Wn = Wall + layer_of(k < n ? k + 1 : k) * a.wsize;                  // (past the last step: read, not used)
-    // RING: a tap is requested one tap before it is needed, which covers an L2 hit and not a miss (a layer's weights come
-    // from HBM once per XCD: 38 us per step without this, waiting for every tap).  Every line of the next layer is touched
-    // at the start of a step.
-    constexpr int NTOUCH = (9 * CP * CP * 2 + 128 * NTH - 1) / (128 * NTH);
-    unsigned touch[NTOUCH] = {};
-    if constexpr (RING) {
-      const char* wn = reinterpret_cast<const char*>(Wn);
-      const unsigned last = (unsigned)(a.wsize * sizeof(WT)) - 4u;
-#pragma unroll
-      for (int i = 0; i < NTOUCH; ++i) touch[i] = *reinterpret_cast<const unsigned*>(wn + min((unsigned)(tid + NTH * i) * 128u, last));
-    } else {
-      load_w(wr, Wn, 0);
-    }
+    if constexpr (!RING) load_w(wr, Wn, 0);
     if (k < n) {
       load_bias(k + 1);
       if constexpr (DEARLY) load_d(k + 1);
@@ -365,11 +353,10 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
           for (int cb = 0; cb < CB; ++cb) low[i][cb] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
       if constexpr (RING) {
-        // Software pipeline over the 18 k steps: the fragments of a step are read while the one before is multiplied.  The
-        // barrier that makes the next tap's weights visible stands between the two steps of a tap.
+        // Tap by tap: a tap's weights are requested two taps and written to LDS one tap before their use, and the barrier at
+        // the end of a tap makes the next one's visible.
         const bool last = decltype(grpc)::value + 1 >= ngr;
-        constexpr bool PIPE = NWV == 4;
-        bf16x8 af[PIPE ? 2 : 1][CB], bf[PIPE ? 2 : 1][GB];
+        bf16x8 af[CB], bf[GB];
         unsigned pa[GB];
         auto tap_addr = [&](int tap) __attribute__((always_inline)) {
           const int ty = (tap * 11) >> 5, dp = (ty - 1) * Wd + (tap - 3 * ty) - 1;        // tap / 3
@@ -379,19 +366,18 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
             pa[i] = piece(pp, kq);
           }
         };
-        auto read = [&](int f, const u8* ws, unsigned flip) __attribute__((always_inline)) {                 // flip 64: pieces 4 .. 7 of the pixel
+        auto kstep = [&](const u8* ws, unsigned flip) __attribute__((always_inline)) {                 // flip 64: pieces 4 .. 7 of the pixel
 #pragma unroll
-          for (int cb = 0; cb < CB; ++cb) af[f][cb] = *reinterpret_cast<const bf16x8*>(ws + alane + cb * 256);
+          for (int cb = 0; cb < CB; ++cb) af[cb] = *reinterpret_cast<const bf16x8*>(ws + alane + cb * 256);
 #pragma unroll
-          for (int i = 0; i < GB; ++i) bf[f][i] = *reinterpret_cast<const bf16x8*>(P + (pa[i] ^ flip));
-        };
-        auto mul = [&](int f) __attribute__((always_inline)) {
+          for (int i = 0; i < GB; ++i) bf[i] = *reinterpret_cast<const bf16x8*>(P + (pa[i] ^ flip));
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int i = 0; i < GB; ++i)
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[f][cb], bf[f][i], acc[i][cb], 0, 0, 0);
+            for (int cb = 0; cb < CB; ++cb) acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[cb], bf[i], acc[i][cb], 0, 0, 0);
         };
-        if constexpr (NV > 0) { tap_addr(0); if (PIPE) read(0, Wl, 0u); }
+        if constexpr (NV > 0) tap_addr(0);
         // (a rolled loop: unrolled, the kernel is larger than the 64 KB instruction cache of two CUs and takes five times as
         // long, waiting for its instructions)
         u8* slot = Wl;                                              // this tap's weights; the next tap's go to the next slot
@@ -400,36 +386,13 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
           u8* next = slot == Wl + 4 * WSB ? Wl : slot + 2 * WSB;
           store_w(wr, next, 0);
           load_w(wr, (tap >= 7 && last) ? Wn : Wc, tap >= 7 ? tap - 7 : tap + 2);
-          if constexpr (PIPE) {
           if constexpr (NV > 0) {
-            read(1, slot + WSB, 64u);
+            kstep(slot, 0u);
             __builtin_amdgcn_sched_barrier(0);
-            mul(0);
-            __builtin_amdgcn_sched_barrier(0);
+            kstep(slot + WSB, 64u);
+            if (tap < 8) tap_addr(tap + 1);
           }
           __syncthreads();                                          // next tap complete
-          if constexpr (NV > 0) {
-            if (tap < 8) {
-              tap_addr(tap + 1);
-              read(0, next, 0u);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            mul(1);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-          } else {
-            if constexpr (NV > 0) {
-              read(0, slot, 0u);
-              __builtin_amdgcn_sched_barrier(0);
-              mul(0);
-              __builtin_amdgcn_sched_barrier(0);
-              read(0, slot + WSB, 64u);
-              __builtin_amdgcn_sched_barrier(0);
-              mul(0);
-              if (tap < 8) tap_addr(tap + 1);
-            }
-            __syncthreads();
-          }
           slot = next;
         }
       } else if constexpr (NV > 0) {
@@ -525,10 +488,6 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     else if (k == a.kmid) { o1 = place(a.Y, a.yb + ci * a.ys); if (ci == 0) o2 = place(a.Z, a.zfirst); }
     else if (a.Z && k == n) o1 = place(a.Z, a.zb + ci * a.zs);
     for (; o1; o1 = o2, o2 = nullptr) store_state(o1);
-    if constexpr (RING) {
-#pragma unroll
-      for (int i = 0; i < NTOUCH; ++i) asm volatile("" :: "v"(touch[i]));
-    }
     if (k == n) break;
     if constexpr (!DEARLY) load_d(k + 1);
     __syncthreads();                                                // every wavefront is done with the operand and the weights
