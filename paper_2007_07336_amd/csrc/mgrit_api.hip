@@ -273,16 +273,22 @@ struct Solver {
   }
   // Layers whose state fits on a CU -- convolution layers on images of at most 1024 pixels, dense layers of width at most
   // 256: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
-  // one launch each.  A chain's step takes less time than a lockstep launch of the same step at every size, also where
-  // only a few workgroups run: whole solves 372 -> 240 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 828 us
-  // (64 of 28 x 28, 16 channels, float), 16.6 -> 10.8 ms (32 of 32 x 32, 64 channels, bf16);
-  // 250 -> 135 us (4 samples, width 8), 655 -> 540 us (128 samples, width 256, float).
-  bool use_march() const {
+  // one launch each.  Whole solves 372 -> 251 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 797 us
+  // (64 of 28 x 28, 16 channels, float), 16.6 -> 9.4 ms (32 of 32 x 32, 64 channels, bf16);
+  // 250 -> 140 us (4 samples, width 8), 655 -> 522 us (128 samples, width 256, float).
+  // Where a step of a chain is long, a level needs enough chains: a lockstep launch spreads one step over many workgroups.
+  // 64 channels on more than 512 pixels: a step takes 24 us in a chain, a launch of up to 128 images 16 us; float of width
+  // 136 to 256: 5.5 us (and a barrier's wait between two kernels less) against 5.0 for 8 slices of rows, level with 7.4 at 128.
+  bool use_march(int l) const {
     if (pl.fcP || !sweep_enabled()) return false;
+    const bool conv = p->layer == MGRIT_LAYER_CONV3X3;
+    if (!(conv ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : sweep_supported(p->q))) return false;
     // (a launch holds less than 2^32 threads: at most 1024 for 16 rows, 512 for an image, of every chain)
-    const long long chains = pl.L > 1 ? pl.Nl[1] + 1LL : 1LL;
-    if ((p->layer == MGRIT_LAYER_CONV3X3 ? p->B * chains * 512 : (pl.M + 15LL) / 16 * chains * 1024) >= 1LL << 32) return false;
-    return p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : sweep_supported(p->q);
+    const long long units = conv ? p->B : (pl.M + 15LL) / 16;
+    const long long most = units * (pl.L > 1 ? pl.Nl[1] + 1LL : 1LL);
+    if (most * (conv ? 512 : 1024) >= 1LL << 32) return false;
+    const bool longstep = conv ? conv_sweep_ring(p->Himg, p->Wimg, p->C, p->dtype) : p->dtype == MGRIT_FP32 && p->q > 128;
+    return !longstep || units * (l + 1 < pl.L ? pl.Nl[l + 1] : 1LL) >= 128;
   }
   // chains of level l that start at sweep point ci * stride, for every ci
   SweepArgs sweep_args(int l, long long stride) const {
@@ -322,7 +328,7 @@ struct Solver {
   // The level's own array, complete: C-points from the level below, F-points by F-relaxation (Alg. 1 ends with the
   // C-points; the F-layers follow by F-relaxation, Sec. III-C).
   void close(int l) {
-    if (use_march()) {
+    if (use_march(l)) {
       // chain ci: the C-point and the F-points behind it; trailing F-points are a chain of their own behind the last C-point,
       // which otherwise the last chain passes on
       SweepArgs a = sweep_args(l, p->m);
@@ -341,7 +347,7 @@ struct Solver {
 
   // The coarsest level: its points in sequence.  X[l][0] holds the known value.
   void serial(int l) {
-    if (use_march()) {
+    if (use_march(l)) {
       SweepArgs a = sweep_args(l, 0);
       a.S = X[l]; a.sm = pm(l, 0, 0);
       keep_states(a, l, 0);
@@ -397,7 +403,7 @@ struct Solver {
     // residual there is R_j = P_j - U_j, Eq. (19), and the coarse right-hand side
     // S_H = L_H(U_H) + R_H = U_j - Phi_H(U_{j-1}) + P_j - U_j = P_j - Phi_H(U_{j-1}): the residual itself is needed for
     // its norm only, which the second launch takes of E1 - Ref.
-    if (use_march()) {
+    if (use_march(l)) {
       march(l, c);                                              // Alg. 1 step 1, and P
       if (p->relax == MGRIT_RELAX_FCF) c = CPoints{R[l], PtMap{0, 1}};
     } else {
@@ -412,9 +418,10 @@ struct Solver {
     const bool norm = l == 0 && want_norm;
     const PtMap next = PtMap{c.m.base + c.m.stride, c.m.stride};
     int blocks;
-    if (use_march() && !(p->layer == MGRIT_LAYER_CONV3X3 && p->dtype == MGRIT_BF16)) {
-      // (the coarse step here and the one of the coarse solve nearly cancel, so in float they have to round alike and both
-      // are the sweep kernel's: 1.7e-7 from the exact states with the lockstep kernel here, 1.0e-7 so)
+    if (use_march(l + 1)) {
+      // (the coarse step here and the one of the coarse solve nearly cancel, so they have to round alike and are the same
+      // kernel's.  With the lockstep kernel here and sweeps there: float 1.7e-7 from the exact states instead of 1.0e-7;
+      // in bf16, where a last bit may flip the rounding of an operand, the residual stays above 2e-6 for ever)
       SweepArgs a = sweep_args(l + 1, 1);
       a.G = nullptr;
       a.S = c.p; a.sm = c.m;

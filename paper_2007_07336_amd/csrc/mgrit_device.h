@@ -117,16 +117,17 @@ __device__ __forceinline__ int div_small(int p, unsigned magic) { return (int)((
 
 // A kernel that uses more than 64 KB of dynamic LDS has to opt in, once per device (the attribute belongs to
 // the device's copy of the kernel).  One of these per kernel instance remembers the largest size each device
-// has been raised to.
+// has been raised to -- once that is done, so that another thread's first launch does not run ahead of it.
 struct LdsOptIn {
   size_t seen[64] = {};
-  bool need(size_t smem) {
-    if (smem <= 64 * 1024) return false;
+  hipError_t raise(const void* kernel, size_t smem) {
+    if (smem <= 64 * 1024) return hipSuccess;
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return true;
-    if (smem <= seen[dev]) return false;
-    seen[dev] = smem;
-    return true;
+    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64;
+    if (known && smem <= seen[dev]) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e == hipSuccess && known) seen[dev] = smem;
+    return e;
   }
 };
 

@@ -118,7 +118,7 @@ hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int
 //               and with store0 = 2 the point behind the last chain, S[sm(nchains)] to X[xb + nchains*xs]
 //   Y:          the state after step kmid, in Y[yb + ci*ys]
 //   Z:          the state after the last step, in Z[zb + ci*zs], if n > kmid; chain 0's state after step kmid in Z[zfirst]
-//   tau:        not for bf16 convolution layers; single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of
+//   tau:        single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of
 //               (Z - Ref[rm(ci)])^2, Z before the update, in norm_partial[workgroup]
 // S may not be written by another chain: X, Y, Z are other arrays, or other points of the same one.
 struct SweepArgs {
@@ -145,6 +145,7 @@ int        sweep_blocks(int M, int nchains);             // workgroups of a laun
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s);
 // 3x3 convolution layers: workgroup (chain, images).
 bool       conv_sweep_supported(int Himg, int Wimg, int C, int dtype);
+bool       conv_sweep_ring(int Himg, int Wimg, int C, int dtype);        // its weights pass through LDS tap by tap
 int        conv_sweep_blocks(const SweepArgs& a, int dtype);
 hipError_t launch_conv_sweep(const SweepArgs& a, int dtype, hipStream_t s);
 

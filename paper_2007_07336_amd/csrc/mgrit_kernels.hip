@@ -1175,10 +1175,9 @@ int step_grid_blocks(const StepArgs& a, int layer_kind, int dtype, int groups) {
 // A failed LDS opt-in of a step kernel: the launch is skipped and launch_step returns this status.
 static hipError_t g_step_attr_err = hipSuccess;
 static bool step_opt_in(LdsOptIn& opt, const void* kernel, size_t smem) {
-  if (!opt.need(smem)) return true;
-  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e != hipSuccess) { g_step_attr_err = e; opt = LdsOptIn(); return false; }
-  return true;
+  const hipError_t e = opt.raise(kernel, smem);
+  if (e != hipSuccess) g_step_attr_err = e;
+  return e == hipSuccess;
 }
 template <typename WT, int BM, int BN, int BK, int PF, bool WS, int WR, int WC, bool HD, bool FULL, bool XR = false, bool WN = false>
 static void launch_dense_k(dim3 grid, hipStream_t s, const StepArgs& a) {
@@ -1742,11 +1741,8 @@ template <typename OT>
 static hipError_t launch_dense_grad_wide(const GradArgs& a, unsigned blocks, hipStream_t s) {
   constexpr size_t smem = dense_grad_wide_smem<OT>();
   static LdsOptIn opt;
-  if (opt.need(smem)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(dense_grad_wide_kernel<OT>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e = opt.raise(reinterpret_cast<const void*>(dense_grad_wide_kernel<OT>), smem);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((dense_grad_wide_kernel<OT>), dim3(blocks), dim3(512), smem, s, a);
   return hipGetLastError();
 }

@@ -528,11 +528,8 @@ bool conv_sweep_shape(int pixels, int C, int dtype, ConvSweepShape* sh) {
 template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
 hipError_t launch_conv_sweep_t(const SweepArgs& a, unsigned blocks, size_t smem, hipStream_t s) {
   static LdsOptIn opt;
-  const void* k = reinterpret_cast<const void*>(conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>);
-  if (opt.need(smem)) {
-    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) { opt = LdsOptIn(); return e; }
-  }
+  const hipError_t e = opt.raise(reinterpret_cast<const void*>(conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>), smem);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>), dim3(blocks), dim3(64 * NWV), smem, s, a);
   return hipGetLastError();
 }
@@ -542,6 +539,10 @@ bool conv_sweep_supported(int Himg, int Wimg, int C, int dtype) {
   ConvSweepShape sh;
   if (Himg < 1 || Wimg < 1 || C < 8 || C > 64 || C % 8 != 0 || (long long)Himg * Wimg > 1024) return false;
   return conv_sweep_shape(Himg * Wimg, C, dtype, &sh);
+}
+bool conv_sweep_ring(int Himg, int Wimg, int C, int dtype) {
+  ConvSweepShape sh;
+  return conv_sweep_supported(Himg, Wimg, C, dtype) && conv_sweep_shape(Himg * Wimg, C, dtype, &sh) && sh.ring;
 }
 // Images per workgroup: a step has fixed costs (two barriers, the weights' way into LDS) and eight wavefronts want at least
 // a block of 16 pixels each, so small images share a workgroup as long as every CU still gets one.
@@ -561,7 +562,7 @@ int conv_sweep_blocks(const SweepArgs& a, int dtype) {
 hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
   SweepArgs a = a_in;
   if (a.nchains <= 0) return hipSuccess;
-  if (a.tau && (dtype != 0 || a.nsteps != 1 || a.nlast != 1 || !a.Z)) return hipErrorInvalidValue;
+  if (a.tau && (a.nsteps != 1 || a.nlast != 1 || !a.Z)) return hipErrorInvalidValue;
   if ((a.act == ACT_IDENT) != (a.Dm != nullptr)) return hipErrorInvalidValue;     // the adjoint's steps, and only they
   if (a.M < 1 || !conv_sweep_supported(a.Himg, a.Wimg, a.C, dtype)) return hipErrorInvalidValue;
   a.ipw = conv_sweep_images(a.Himg, a.Wimg, a.C, dtype, a.M, a.nchains);
@@ -578,6 +579,8 @@ hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
   MGRIT_CS(1, 16, 8, 8, false, false) MGRIT_CS(1, 32, 8, 8, false, false) MGRIT_CS(1, 48, 8, 8, false, false)
   MGRIT_CS(1, 64, 8, 4, false, false) MGRIT_CS(1, 64, 8, 8, true, false)
   MGRIT_CS(3, 16, 8, 8, false, false) MGRIT_CS(3, 32, 8, 4, false, false)
+  MGRIT_CS(1, 16, 8, 8, false, true) MGRIT_CS(1, 32, 8, 8, false, true) MGRIT_CS(1, 48, 8, 8, false, true)
+  MGRIT_CS(1, 64, 8, 4, false, true) MGRIT_CS(1, 64, 8, 8, true, true)
   MGRIT_CS(3, 16, 8, 8, false, true) MGRIT_CS(3, 32, 8, 4, false, true)
 #undef MGRIT_CS
   // algorithmic bytes: per layer step the weights and bias, the act' factor, the right-hand side and what is kept of the
@@ -893,11 +896,8 @@ template <int NP, int NWV, int FBW, int RB, int ACT, bool WN>
 hipError_t launch_dense_sweep_t(const SweepArgs& a, unsigned blocks, hipStream_t s) {
   const size_t smem = (size_t)16 * RB * dense_sweep_pitch(NP, (a.q + 63) & ~63) + (size_t)NWV * dense_sweep_stage<NP, FBW, WN>();
   static LdsOptIn opt;
-  const void* k = reinterpret_cast<const void*>(dense_sweep_kernel<NP, NWV, FBW, RB, ACT, WN>);
-  if (opt.need(smem)) {
-    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) { opt = LdsOptIn(); return e; }
-  }
+  const hipError_t e = opt.raise(reinterpret_cast<const void*>(dense_sweep_kernel<NP, NWV, FBW, RB, ACT, WN>), smem);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((dense_sweep_kernel<NP, NWV, FBW, RB, ACT, WN>), dim3(blocks), dim3(64 * NWV), smem, s, a);
   return hipGetLastError();
 }
