@@ -31,6 +31,7 @@ CONV = [
     _conv(64, 16, 32, 1, 8, 4, 2, I.BF16, act=I.RELU),             # 512 pixels: the whole layer's weights in LDS
     _conv(64, 27, 19, 2, 18, 4, 3, I.BF16),                        # 513 pixels: weights tap by tap
     _conv(64, 32, 32, 1, 9, 2, 3, I.BF16, relax=I.RELAX_F, it=2),  # 1024 pixels
+    _conv(64, 27, 19, 16, 18, 2, 2, I.BF16),                       # 513 pixels, 144 workgroups: weights tap by tap
 ]
 
 
@@ -71,6 +72,7 @@ DENSE = [
     _dense(72, 16, 9, 3, 2, I.FP32, relax=I.RELAX_F),              # 72 of 128 features, the last k step short
     _dense(128, 33, 5, 4, 2, I.FP32),                              # one interval
     _dense(136, 3, 24, 2, 4, I.FP32),                              # 136 of 256
+    _dense(200, 150, 56, 4, 2, I.FP32),                            # 140 slices of 16 rows, the last of each chain short
     _dense(248, 400, 60, 4, 2, I.FP32, act=I.RELU),                # 32-row slices, the last one short
     _dense(256, 16, 8, 4, 1, I.FP32),                              # serial propagation
     _dense(264, 5, 8, 4, 2, I.FP32),                               # too wide: lockstep launches
@@ -84,3 +86,16 @@ DENSE = [
 @pytest.mark.parametrize("wl", DENSE, ids=lambda w: w.name)
 def test_dense_sweep_instances(wl):
     test_conv_sweep_instances(wl)
+
+
+@pytest.mark.parametrize("C,H,W", [(16, 8, 8), (64, 8, 8)])
+def test_bf16_convolution_residual_reaches_rounding(C, H, W):
+    """After as many cycles as there are intervals FAS is exact, and the C-points' residual is what the two roundings of
+    (P - Phi) + Phi leave: 2^-22 of the largest value per entry.  It needs both coarse steps to round alike."""
+    wl = _conv(C, H, W, 4, 32, 4, 2, I.BF16, it=9)
+    gp = GpuProblem(wl, I.generate(wl))
+    _, U, hist, _ = gp.forward()
+    sizes, _ = gp.M.mgrit_level_map(gp.p)
+    bound = 2.0 ** -22 * float(np.abs(U).max()) * np.sqrt((sizes[1] + 1) * wl.E)
+    print(hist, bound, flush=True)
+    assert hist[-1] <= bound
