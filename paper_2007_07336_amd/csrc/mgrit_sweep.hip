@@ -617,9 +617,11 @@ template <int NP, int FBW, bool WN> constexpr int dense_sweep_stage() {     // b
   return NP == 3 ? (WN ? 32 * (64 * FBW + 8) : 16 * FBW * 160) : (WN ? 32 * (32 * FBW + 32) : 16 * FBW * 96);
 }
 constexpr int dense_sweep_pitch(int np, int kp) { return np * kp * 2 + 32; }   // bytes of an operand row in LDS
+constexpr int DENSE_SWEEP_ZEROS = 512;                                      // bytes of zeros behind the staging areas
 
 template <int NP, int NWV, int FBW, int RB, int ACT, bool WN>
 __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
+  static_assert(4 * (32 * FBW + 32) + 8 <= DENSE_SWEEP_ZEROS && 64 * NWV >= DENSE_SWEEP_ZEROS / 4, "one lane's reads; its writers");
   constexpr bool HD = ACT == ACT_IDENT;                             // the adjoint: act' factors, no bias
   constexpr int NTH = 64 * NWV, R = 16 * RB;
   constexpr int STG = dense_sweep_stage<NP, FBW, WN>();
@@ -640,6 +642,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   const int n = ci == a.nchains - 1 ? a.nlast : a.nsteps;
   u8* A = smem;                                                     // operand [R][OP]
   u8* Ws = smem + R * OP + wave * STG;
+  u8* Zr = smem + R * OP + NWV * STG;
   const long long sl_off = (long long)r0 * q;
   const int f0 = wave * FBW * 16;                                   // this wavefront's first feature
   auto layer_of = [&](int k) __attribute__((always_inline)) { return a.lb + ci * a.ls + (long long)(k - 1) * a.lk; };
@@ -668,7 +671,8 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   if (n <= 0) return;                                               // the whole workgroup
 
   // ---- weights of a k step, straight into registers: whole 128-byte (bf16: 64-byte) pieces of the wavefront's rows, or
-  // rows of k.  Everything past the width is clamped to a valid address: its operand is zero, or its output is not stored.
+  // rows of k.  Everything past the width is clamped to a valid address: the lanes that hold it read zeros instead, or its
+  // output is not stored.
   const WT* Wall = reinterpret_cast<const WT*>(a.W);
   // (a k step inside the width: a uniform base and offsets that stay the same; the last ones are clamped value by value)
   unsigned wo[NL];
@@ -753,6 +757,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   load_w(w0, Wc, 0);
   load_w(w1, Wc, 1);
   load_d(1);
+  if (tid < DENSE_SWEEP_ZEROS / 4) reinterpret_cast<float*>(Zr)[tid] = 0.0f;
   write_operand();
   __syncthreads();
 
@@ -783,6 +788,9 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
       {
         stage_w(w);
         wave_sync();
+        // bf16: a lane whose eight values of k lie past the width takes zeros: its operand is zero as well, but a clamped
+        // weight may be infinite
+        const bool in = NP == 3 || 32 * s + 8 * kq < q;
 #pragma unroll
         for (int j = 0; j < FBW; ++j) {
           if constexpr (NP == 3 && WN) {
@@ -800,12 +808,12 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
             // two transposing reads: rows k = 8 kq + 0 .. 3 and + 4 .. 7 of column c of the block
             constexpr int P = 32 * FBW + 32;
             typedef __attribute__((address_space(3))) short4w* lds_s4;
-            const u8* p = Ws + (8 * kq + (c >> 2)) * P + 32 * j + 8 * (c & 3);
+            const u8* p = in ? Ws + (8 * kq + (c >> 2)) * P + 32 * j + 8 * (c & 3) : Zr;
             const short4w lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p));
             const short4w hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p + 4 * P));
             af[j][0] = __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo), __builtin_bit_cast(bf16x4, hi), 0, 1, 2, 3, 4, 5, 6, 7);
           } else {
-            af[j][0] = *reinterpret_cast<const bf16x8*>(Ws + (16 * j + c) * 96 + kq * 16);
+            af[j][0] = *reinterpret_cast<const bf16x8*>(in ? Ws + (16 * j + c) * 96 + kq * 16 : Zr);
           }
         }
         wave_sync();
@@ -894,7 +902,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
 namespace {
 template <int NP, int NWV, int FBW, int RB, int ACT, bool WN>
 hipError_t launch_dense_sweep_t(const SweepArgs& a, unsigned blocks, hipStream_t s) {
-  const size_t smem = (size_t)16 * RB * dense_sweep_pitch(NP, (a.q + 63) & ~63) + (size_t)NWV * dense_sweep_stage<NP, FBW, WN>();
+  const size_t smem = (size_t)16 * RB * dense_sweep_pitch(NP, (a.q + 63) & ~63) + (size_t)NWV * dense_sweep_stage<NP, FBW, WN>() + DENSE_SWEEP_ZEROS;
   static LdsOptIn opt;
   const hipError_t e = opt.raise(reinterpret_cast<const void*>(dense_sweep_kernel<NP, NWV, FBW, RB, ACT, WN>), smem);
   if (e != hipSuccess) return e;
