@@ -19,8 +19,7 @@ namespace mgrit {
 // NP = 1: bf16 problems.  NP = 3: float problems; state and weights are split into three bf16 numbers each, x = x1 + x2
 // + x3 (8 + 8 + 8 significant bits, so the split is exact), and the six products that reach 2^-24 are formed on the bf16
 // matrix cores with float accumulation -- 6/16 of the time of the float instructions.  The products left out are below
-// 2^-27 of the full one, less than the rounding of a single float addition.  (An infinite operand splits into inf and NaN
-// parts, so an output that would be infinite is NaN; no finite result depends on one.)
+// 2^-27 of the full one, less than the rounding of a single float addition.  (Infinite values: repeat_in_float.)
 // The weights of a layer: all in LDS (the next layer's are on their way in registers during a step), or, for 64 channels
 // on images too large for that (RING), tap by tap through three LDS slots.
 // What bounds it: 16 channels float -- the LDS reads of the operand (15 KB per 16 pixels and step against 480 cycles of
@@ -55,6 +54,132 @@ __device__ __forceinline__ void split3(F f, V& h, V& m, V& l) {               //
   }
 }
 
+// A value that rounds to an infinite bf16 number, 0x1.ffp127 = 3.396e38 or more, has no such parts: in a weight or an operand
+// it makes NaN of every sum that it enters.  Float sweeps pass NaN on through the activation, so that it stays in the state,
+// and a workgroup that ends with a state that is not finite repeats its chain with products of the float values themselves,
+// as the lockstep kernels form them.  (To look at the values where they are split, or at the sums of a step, took 1 to 7 % of
+// the sweeps of 16 channels and up to 40 % of those of width 256, in registers and branches more than in instructions; this
+// way 64 layers of 16 channels went from 810 to 817 us, 256 of width 256 from 500 to 505.)
+template <int NP, int ACT> __device__ __forceinline__ float sweep_act(float z) {
+  if constexpr (NP == 3 && ACT == ACT_RELU) return __builtin_elementwise_maximum(z, 0.0f);
+  else return act_fn_c<ACT>(z);
+}
+template <int A, int B> __device__ __forceinline__ bool any_not_finite(const floatx4 (&st)[A][B]) {   // in some lane
+  float top = 0.0f;
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) top = __builtin_elementwise_maximum(top, __builtin_fabsf(st[i][j][v]));
+  return __builtin_amdgcn_ballot_w64(!(top < __builtin_inff())) != 0;
+}
+
+// Sum over a workgroup in a fixed order over the wavefronts; valid in thread 0.
+template <int NWV> __device__ __forceinline__ float sum_workgroup(float sq, float* red, int tid) {
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) sq += __shfl_xor(sq, w, 64);
+  if ((tid & 63) == 0) red[tid >> 6] = sq;
+  __syncthreads();
+  float t = red[0];
+#pragma unroll
+  for (int w = 1; w < NWV; ++w) t += red[w];
+  return t;
+}
+
+// The repeated chain.  A workgroup's samples are `total` consecutive values of a state; a thread holds every 64 NWV-th group of
+// four of them, at most U, and the operand of a step is in LDS as it is.  Latency is all that bounds it.  It takes nothing but
+// the wavefront's number from the sweep and reads its arguments again, through a pointer that the compiler cannot follow (kept
+// in scalar registers from the sweep on, they cost 2 % of it in spills).
+template <int NWV, int U, int ACT, bool WN, bool CONV>
+__device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) {
+  constexpr int NTH = 64 * NWV;
+  typedef const unsigned __attribute__((address_space(4))) * ArgWords;
+  ArgWords words = (ArgWords)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(words));
+  const int tid = 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  SweepArgs a;
+  static_assert(sizeof(SweepArgs) % 4 == 0, "copied word by word");
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(SweepArgs) / 4; ++i) reinterpret_cast<unsigned*>(&a)[i] = words[i];
+  const int per = CONV ? a.ipw : 16 * U;                            // samples of a workgroup (dense: 16 rows per block)
+  const int size = CONV ? a.Himg * a.Wimg * a.C : a.q;              // values of a sample
+  const int nwg = (a.M + per - 1) / per, L = logical_block(), r0 = (L % nwg) * per;
+  const long long ci = L / nwg, first = (long long)r0 * size;
+  const int total = min(per, a.M - r0) * size, n = a.tau ? 1 : ci == a.nchains - 1 ? a.nlast : a.nsteps;
+  const int C = CONV ? a.C : a.q, Wd = a.Wimg, HW = CONV ? a.Himg * Wd : 1, ZP = per * HW;
+  auto at = [&](const float* base, long long point) { return const_cast<float*>(base) + point * a.E + first; };
+  auto elem = [&](int i) { return 4 * (tid + NTH * i); };
+  floatx4 st[U];
+#pragma unroll
+  for (int i = 0; i < U; ++i) {
+    st[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (elem(i) < total) st[i] = *reinterpret_cast<const floatx4*>(at(a.S, a.sm.base + ci * a.sm.stride) + elem(i));
+  }
+  if (CONV && tid < C) X[ZP * C + tid] = 0.0f;
+#pragma unroll 1
+  for (int k = 1; k <= n; ++k) {
+    const long long layer = a.lb + ci * a.ls + (long long)(k - 1) * a.lk;
+    const float* W = reinterpret_cast<const float*>(a.W) + layer * a.wsize;
+    const float* Dm = reinterpret_cast<const float*>(a.Dm);
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (elem(i) < total)
+        *reinterpret_cast<floatx4*>(X + elem(i)) = ACT == ACT_IDENT ? st[i] * *reinterpret_cast<const floatx4*>(at(Dm, layer) + elem(i)) : st[i];
+    __syncthreads();
+    // where the state is kept, as in the sweep
+    float* o1 = nullptr;
+    float* o2 = nullptr;
+    if (a.tau) {}
+    else if (a.X && a.xk) o1 = at(a.X, a.xb + ci * a.xs + (long long)k * a.xk);
+    else if (k == a.kmid) { o1 = at(a.Y, a.yb + ci * a.ys); if (ci == 0) o2 = at(a.Z, a.zfirst); }
+    else if (a.Z && k == n) o1 = at(a.Z, a.zb + ci * a.zs);
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (elem(i) < total) {
+        const int p = elem(i) / C, ch = elem(i) % C;                // pixel and channel, or row and feature
+        floatx4 z = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (a.bias) z = *reinterpret_cast<const floatx4*>(a.bias + layer * C + ch);
+        const int y = p % HW / Wd, x = p % HW % Wd;
+#pragma unroll 1
+        for (int tap = 0; tap < (CONV ? 9 : 1); ++tap) {
+          const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
+          const bool inside = yy >= 0 && yy < a.Himg && xx >= 0 && xx < Wd;
+          const float* xp = X + (CONV ? inside ? p + (yy - y) * Wd + xx - x : ZP : p) * C;
+          const float* w = W + (CONV ? (ch * 9 + tap) * C : WN ? ch : ch * C);
+          const int wv = CONV ? 9 * C : WN ? 1 : C, wt = !CONV && WN ? C : 1;
+#pragma unroll 1
+          for (int t = 0; t < C; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z[v] = __builtin_fmaf(w[v * wv + t * wt], xp[t], z[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) st[i][v] += a.hs * act_fn_c<ACT>(z[v]);
+        if (a.G) st[i] += *reinterpret_cast<const floatx4*>(at(a.G, a.gb + ci * a.gs + k) + elem(i));
+        if (o1) *reinterpret_cast<floatx4*>(o1 + elem(i)) = st[i];
+        if (o2) *reinterpret_cast<floatx4*>(o2 + elem(i)) = st[i];
+      }
+    __syncthreads();
+  }
+  if (!a.tau) return;
+  float sq = 0.0f;
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+    if (elem(i) < total) {
+      floatx4* o = reinterpret_cast<floatx4*>(at(a.Z, a.zb + ci * a.zs) + elem(i));
+      const floatx4 p = *o;
+      *o = p - st[i];
+      if (a.Ref) {
+        const floatx4 d = p - *reinterpret_cast<const floatx4*>(at(a.Ref, a.rm.base + ci * a.rm.stride) + elem(i));
+        sq += (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+      }
+    }
+  if (a.norm_partial) {
+    const float t = sum_workgroup<NWV>(sq, red, tid);
+    if (tid == 0) a.norm_partial[L] = t;
+  }
+}
+
 // LDS layouts of this file: a 16-byte read is served for lanes 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and the
 // same in the upper half (so the layouts that measured faster say), so for a fragment -- lane (c, kq) reads piece kq of
 // row c -- these sixteen should lie in different 16-byte columns of 256 bytes.  Row pitches of 2 modulo 4 columns do that;
@@ -84,12 +209,16 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   constexpr int WS = RING ? 2 : S;                              // k steps loaded together: a tap or the whole layer
   constexpr int WU = (WS * 4 * CP + NTH - 1) / NTH;             // units (8 input channels of one output channel) per thread
   constexpr int WR = NP == 3 ? 2 : 1;                           // 16-byte loads per unit
-  constexpr bool HOLD = CP == 16 || (CP == 32 && NP == 1);      // a layer's weight fragments fit in registers
+  // a layer's weight fragments fit in registers (beside the factors of the float adjoint not without spills: 1390 us for 64
+  // layers of 16 channels, 1371 when they are read from LDS)
+  constexpr bool HOLD = (CP == 16 && !(HD && NP == 3)) || (CP == 32 && NP == 1);
   constexpr bool DEARLY = !RING;                                // act' factors requested at the start of a step
   static_assert(NBW % GB == 0 && (!RING || (CP == 64 && NP == 1)), "instances");
   typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
   typedef typename DRaw<WT>::type DR;
   extern __shared__ __attribute__((aligned(16))) u8 smem[];
+  __shared__ float red[NWV];
+  __shared__ int repeat;                                        // float: a state of the chain is not finite
 
   const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -249,6 +378,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   };
   load_d(1);
   if (tid < PXB / 4) reinterpret_cast<float*>(P + (size_t)ZP * PXB)[tid] = 0.0f;
+  if (NP == 3 && tid == 0) repeat = 0;
   write_operand();
   store_w(wr, Wl, 0);
   if constexpr (RING) load_w(wr, Wc, 1);
@@ -327,7 +457,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
 #pragma unroll
         for (int i = 0; i < NV; ++i)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) st[G0 + i][cb][v] += a.hs * act_fn_c<ACT>(acc[i][cb][v]);
+          for (int v = 0; v < 4; ++v) st[G0 + i][cb][v] += a.hs * sweep_act<NP, ACT>(acc[i][cb][v]);
       }
       if (gp) {                                                     // coarse levels only
 #pragma unroll
@@ -447,6 +577,11 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     static_assert(NG <= 4, "groups");
 
     if constexpr (TAU) {                                            // coarse right-hand side: Z <- Z - state, and its norm
+      if constexpr (NP == 3) {
+        if (any_not_finite(st)) repeat = 1;
+        __syncthreads();
+        if (repeat) break;
+      }
       float* o = place(a.Z, a.zb + ci * a.zs);
       const float* ref = a.Ref ? a.Ref + (a.rm.base + ci * a.rm.stride) * a.E + img_off : nullptr;
       float sq = 0.0f;
@@ -471,27 +606,18 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
             }
         }
       }
-      if (a.norm_partial) {                                         // in a fixed order over the wavefronts
-#pragma unroll
-        for (int w = 32; w > 0; w >>= 1) sq += __shfl_xor(sq, w, 64);
-        float* red = reinterpret_cast<float*>(P);
-        __syncthreads();                                            // the operand is not needed any more
-        if (lane == 0) red[wave] = sq;
-        __syncthreads();
-        if (tid == 0) {
-          float t = red[0];
-#pragma unroll
-          for (int w = 1; w < NWV; ++w) t += red[w];
-          a.norm_partial[L] = t;
-        }
+      if (a.norm_partial) {
+        const float t = sum_workgroup<NWV>(sq, red, tid);
+        if (tid == 0) a.norm_partial[L] = t;
       }
-      break;
+      break;                                                        // (n = 1)
     }
     float* o1 = nullptr;                                            // where this step's state is kept: at most two places
     float* o2 = nullptr;
     if (a.X && a.xk) o1 = place(a.X, a.xb + ci * a.xs + (long long)k * a.xk);
     else if (k == a.kmid) { o1 = place(a.Y, a.yb + ci * a.ys); if (ci == 0) o2 = place(a.Z, a.zfirst); }
     else if (a.Z && k == n) o1 = place(a.Z, a.zb + ci * a.zs);
+    if (NP == 3 && k == n) { if (any_not_finite(st)) repeat = 1; }
     for (; o1; o1 = o2, o2 = nullptr) store_state(o1);
     if (k == n) break;
     if constexpr (!DEARLY) load_d(k + 1);
@@ -501,6 +627,10 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     if (tid < CP) bl[((k + 1) & 1) * CP + tid] = bnext;
     Wc = Wn;
     __syncthreads();
+  }
+  if constexpr (NP == 3) {
+    if constexpr (!TAU) __syncthreads();
+    if (repeat) repeat_in_float<NWV, NBW * CB, ACT, false, true>(reinterpret_cast<float*>(P), red, wave);
   }
 }
 
@@ -631,6 +761,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   typedef u32x4 LW;
   extern __shared__ __attribute__((aligned(16))) u8 smem[];
   __shared__ float red[NWV];
+  __shared__ int repeat;                                            // float: a state of the chain is not finite
 
   const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -758,6 +889,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   load_w(w1, Wc, 1);
   load_d(1);
   if (tid < DENSE_SWEEP_ZEROS / 4) reinterpret_cast<float*>(Zr)[tid] = 0.0f;
+  if (NP == 3 && tid == 0) repeat = 0;
   write_operand();
   __syncthreads();
 
@@ -789,7 +921,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
         stage_w(w);
         wave_sync();
         // bf16: a lane whose eight values of k lie past the width takes zeros: its operand is zero as well, but a clamped
-        // weight may be infinite
+        // weight may be infinite (float: such a chain is repeated)
         const bool in = NP == 3 || 32 * s + 8 * kq < q;
 #pragma unroll
         for (int j = 0; j < FBW; ++j) {
@@ -851,10 +983,15 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
         if constexpr (NP == 3) z += low[rb][j];
         if constexpr (!HD) z += bv[j];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) st[rb][j][v] += a.hs * act_fn_c<ACT>(z[v]);
+        for (int v = 0; v < 4; ++v) st[rb][j][v] += a.hs * sweep_act<NP, ACT>(z[v]);
         if (a.G) st[rb][j] += gv[rb][j];
       }
 
+    if (NP == 3 && k == n) {
+      if (any_not_finite(st)) repeat = 1;
+      __syncthreads();
+      if (repeat) break;
+    }
     if (a.tau) {                                                    // coarse right-hand side: Z <- Z - state, and its norm
       float* o = place(a.Z, a.zb + ci * a.zs);
       const float* ref = a.Ref ? place(a.Ref, a.rm.base + ci * a.rm.stride) : nullptr;
@@ -871,19 +1008,11 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
               sq += (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
             }
           }
-      if (a.norm_partial) {                                         // in a fixed order over the wavefronts
-#pragma unroll
-        for (int w = 32; w > 0; w >>= 1) sq += __shfl_xor(sq, w, 64);
-        if (lane == 0) red[wave] = sq;
-        __syncthreads();
-        if (tid == 0) {
-          float t = red[0];
-#pragma unroll
-          for (int w = 1; w < NWV; ++w) t += red[w];
-          a.norm_partial[L] = t;
-        }
+      if (a.norm_partial) {
+        const float t = sum_workgroup<NWV>(sq, red, tid);
+        if (tid == 0) a.norm_partial[L] = t;
       }
-      break;
+      break;                                                        // (n = 1)
     }
     float* o1 = nullptr;                                            // where this step's state is kept: at most two places
     float* o2 = nullptr;
@@ -896,6 +1025,9 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
     write_operand();
     Wc = Wn;
     __syncthreads();
+  }
+  if constexpr (NP == 3) {
+    if (repeat) repeat_in_float<NWV, RB * FBW, ACT, WN, false>(reinterpret_cast<float*>(A), red, wave);
   }
 }
 
