@@ -127,10 +127,6 @@ int make_plan(const mgrit_problem_t* p, Plan* pl, int fcP = 0) {
   if (pl->L > 1) {
     size_t np1 = (size_t)step_grid_blocks(a, p->layer, p->dtype, pl->Nl[1]) * pl->Nl[1];
     if (np1 > np) np = np1;
-    if (p->layer == MGRIT_LAYER_DENSE && sweep_supported(p->q)) {           // the sweep kernel's workgroups, one per slice of rows
-      np1 = (size_t)sweep_blocks(pl->M, pl->Nl[1]);
-      if (np1 > np) np = np1;
-    }
   }
   if (fcP)     // the dense launch of the fully connected groups adds its workgroups (at most 32x32 tiles of each)
     np += (size_t)((p->B + 31) / 32) * (size_t)((pl->dfc + 31) / 32) * (size_t)pl->nfc;
@@ -417,6 +413,7 @@ struct Solver {
     }
     const bool norm = l == 0 && want_norm;
     const PtMap next = PtMap{c.m.base + c.m.stride, c.m.stride};
+    float* sums = partial;                                      // one per workgroup
     int blocks;
     if (use_march(l + 1)) {
       // (the coarse step here and the one of the coarse solve nearly cancel, so they have to round alike and are the same
@@ -427,7 +424,10 @@ struct Solver {
       a.S = c.p; a.sm = c.m;
       a.nsteps = a.nlast = 1; a.nchains = Nc;
       a.tau = 1; a.Z = g[l + 1]; a.zb = 1; a.zs = 1;
-      if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = partial; }
+      // (a slice of 16 rows may be less than a lockstep tile, which `partial` is sized for; a state of every chain that nothing
+      // needs at this point holds more: the coarse solve's, or the residual's where only FCF-relaxation uses it)
+      sums = p->relax == MGRIT_RELAX_FCF ? X[l + 1] + pl.E : R[l];
+      if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = sums; }
       launch_march(a, Nc);
       blocks = p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_blocks(a, p->dtype) : sweep_blocks(a.M, Nc);
     } else {
@@ -442,7 +442,7 @@ struct Solver {
     }
     if (norm) {
       const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(Nc + 1) * (double)pl.E) : 1.0;
-      chk(launch_norm_final(partial, blocks, scale, hist_dev + iter, s));
+      chk(launch_norm_final(sums, blocks, scale, hist_dev + iter, s));
     }
     cycle(l + 1, iter, CPoints{c.p, PtMap{c.m.base, c.m.stride * m}});   // V_H, Alg. 1 steps 3 to 5
     if (l + 1 < pl.L - 1) close(l + 1);

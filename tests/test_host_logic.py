@@ -227,3 +227,14 @@ def test_bench_reads_measured_traffic_from_the_profile_tables():
     for cls in Bd.TRACE_CLASSES:                                # every traced step-kernel class has a row pattern
         if cls != "dense_grad_kernel":
             assert cls in bench.PROFILE_ROW, cls
+
+
+@pytest.mark.parametrize("q,B,N,m,tile", [(8, 15515, 88, 2, 128), (24, 18945, 24, 3, 128), (64, 116, 848, 2, 128)])
+def test_workspace_holds_the_norm_partials_of_a_lockstep_launch_and_no_more(q, B, N, m, tile):
+    """Narrow layers: the sweeps' slices of 16 or 32 rows outnumber the tiles that the workspace counts.  Their partial sums
+    go elsewhere, so that the size stays what callers and the fixed workspace of the static entry point were laid out for."""
+    p = M.make_problem(N=N, h=1 / N, m=m, max_levels=2, relax=1, max_iter=2, layer=0, act=0, dtype=0, B=B, q=q)
+    align = lambda n: -(-n // 256) * 256                                                     # noqa: E731
+    E, n1 = B * q, N // m
+    partials = -(-B // tile) * -(-q // tile) * N + min(1024, -(-E // 4096))                  # all layers, and u0 - U[0]
+    assert M.mgrit_workspace_bytes(p) == 3 * align((n1 + 1) * E * 4) + align(4 * partials) + align(3 * 8)

@@ -39,7 +39,7 @@ def _run_both(wl, **overrides):
     assert rc == rc2 == 0 and it_ref == it_new
     assert hist_ref == hist_new, (hist_ref, hist_new)
     assert torch.equal(U_ref, U_new)
-    return U_new
+    return U_new, hist_new
 
 
 def test_static_workspace_entry_point_matches_the_existing_one_twice_in_a_row():
@@ -51,6 +51,17 @@ def test_static_workspace_entry_point_matches_the_existing_one_twice_in_a_row():
     _run_both(small)
     # and a run to a tolerance (host outputs, one synchronisation per cycle) with the RMS norm
     _run_both(I.reduced(I.cfg2(30), name="static_dense_q64_tol", q=64, B=20, N=64), tol=1e-6, norm_kind=1)
+
+
+@pytest.mark.parametrize("relax", [I.RELAX_F, I.RELAX_FCF], ids=["F", "FCF"])
+def test_static_workspace_entry_point_at_its_limit(relax, monkeypatch):
+    """67 068 416 of 67 108 864 bytes, on a shape whose sweeps have more norm partials than the workspace counts: the residual
+    history is the lockstep launches' (sums of 5e6 squares in float, in another order: 1e-5)."""
+    wl = I.reduced(I.cfg2(2), name="static_dense_q8_B15515_N88", q=8, B=15515, N=88, m=2, max_levels=2, relax=relax, bias_var=0.1)
+    hist = _run_both(wl)[1]
+    monkeypatch.setenv("MGRIT_NO_SWEEP", "1")
+    ref = _run_both(wl)[1]
+    assert len(hist) == len(ref) == 2 and all(abs(a - b) <= 1e-5 * b for a, b in zip(hist, ref)), (hist, ref)
 
 
 def test_static_workspace_entry_point_refuses_what_does_not_fit():
