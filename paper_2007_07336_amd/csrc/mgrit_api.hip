@@ -463,7 +463,9 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
   // the known value, in every array that holds sweep point 0, and the initial guess of the C-points
   float* zero_pt[2 * MGRIT_MAX_LEVELS];
   int nz = 0;
-  Solver::CPoints c{first, PtMap{0, 0}};                                  // MGRIT_INIT_COPY: `first` everywhere
+  // MGRIT_INIT_COPY: the known value everywhere, from the coarsest level's copy of it (`first` may be a row of the caller's
+  // array, the last state of an earlier solve, that the relaxation writes to)
+  Solver::CPoints c{sv.X[pl.L - 1], PtMap{0, 0}};
   if (pl.L == 1) {
     zero_pt[nz++] = sv.X[0] + sv.pm(0, 0, 0).base * pl.E;
   } else {

@@ -160,3 +160,30 @@ def test_layer_step_count_of_the_benchmark_matches_the_launch_schedule(relax, le
     tr = M.mgrit_trace_end()
     units = sum(v[2] for k, v in tr.items() if k != "dense_grad_kernel")
     assert units == bench.layer_steps_per_solve(sizes, wl.m, wl.relax, cycles), (tr, sizes)
+
+
+@pytest.mark.parametrize("sweep", [True, False], ids=["sweep", "lockstep"])
+@pytest.mark.parametrize("relax", [I.RELAX_F, I.RELAX_FCF], ids=["F", "FCF"])
+@pytest.mark.parametrize("row", [0, 1, 4, 9])
+def test_known_value_inside_the_result_array(row, relax, sweep, monkeypatch):
+    """u0 (lamN) may be a row of U (Lam), as where one solve continues from the last state of another in the same array: a
+    C-point, an F-point or a trailing F-point, which the first relaxation writes to."""
+    import torch
+    import paper_2007_07336_amd as M
+    if not sweep:
+        monkeypatch.setenv("MGRIT_NO_SWEEP", "1")
+    wl = I.reduced(I.cfg5(2), name="alias", q=64, B=16, N=9, m=4, max_levels=2, min_coarse=1, dtype=I.FP32, relax=relax, head_classes=0)
+    _say(f"row {row} relax {relax} sweep {sweep}")
+    gp = GpuProblem(wl, I.generate(wl))
+    _, U, hist, _ = gp.forward()
+    gp.U.fill_(7.0)
+    gp.U[row] = gp.u0
+    _, hist2, _ = M.mgrit_fas_forward(gp.p, gp.W, gp.b, gp.U[row], gp.U, gp.ws)
+    assert np.array_equal(gp.U.cpu().numpy(), U) and hist2 == hist
+    lamN = np.random.default_rng(2).standard_normal(wl.state_shape).astype(np.float32)
+    Lam, _, _, hist, _ = gp.adjoint(U, lamN)
+    Lam2 = torch.full_like(gp.U, 7.0)
+    Lam2[row] = torch.from_numpy(lamN).cuda()
+    ws = torch.empty(M.mgrit_adjoint_workspace_bytes(gp.p), dtype=torch.uint8, device="cuda")
+    _, hist2, _ = M.mgrit_fas_adjoint(gp.p, gp.W, gp.b, gp.U, Lam2[row], Lam2, None, None, ws)
+    assert np.array_equal(Lam2.cpu().numpy(), Lam) and hist2 == hist
