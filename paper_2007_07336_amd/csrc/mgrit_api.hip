@@ -273,8 +273,14 @@ struct Solver {
   // (64 of 28 x 28, 16 channels, float), 16.6 -> 9.4 ms (32 of 32 x 32, 64 channels, bf16);
   // 250 -> 140 us (4 samples, width 8), 655 -> 522 us (128 samples, width 256, float).
   // Where a step of a chain is long, a level needs enough chains: a lockstep launch spreads one step over many workgroups.
-  // 64 channels on more than 512 pixels: a step takes 24 us in a chain, a launch of up to 128 images 16 us; float of width
-  // 136 to 256: 5.5 us (and a barrier's wait between two kernels less) against 5.0 for 8 slices of rows, level with 7.4 at 128.
+  // us per step with one chain (images, or slices of 16 rows, on as many CUs), sweep / lockstep, forward and adjoint:
+  //   64 channels on more than 512 pixels: 24.5 / 24.4 forward with 128 images, 27.9 / 45 with 256 (32 x 32); adjoint 50 / 42 with
+  //   128, 52 / 55 with 144 (32 x 32), 37.3 / 36.2 with 160 and 40 / 50 with 192 (23 x 23); 48 channels adjoint on 32 x 32 17.1 / 16.5
+  //   with 8, 20.7 / 21.2 with 32; float of width 136 to 256: 5.5 (and a barrier's wait between two kernels less) / 5.0 for 8
+  //   slices, level with 7.4 at 128.
+  // Every other instance is as fast or faster with a single image at its largest size: float 16 channels on 32 x 32 7.0 / 7.1 and
+  // 8.2 / 8.2, 32 on 16 x 32 9.9 / 16.3 and 11.4 / 17.9; bf16 32 channels on 32 x 32 8.0 / 8.9 and 9.2 / 10.3, 48 on 32 x 32
+  // 13.3 / 14.3, 64 on 16 x 32 9.9 / 13.3 and 12.8 / 14.6; dense 1.4 .. 2.5 / 4 (float to 128), 0.9 .. 3.0 / 4.4 (bf16).
   bool use_march(int l) const {
     if (pl.fcP || !sweep_enabled()) return false;
     const bool conv = p->layer == MGRIT_LAYER_CONV3X3;
@@ -283,8 +289,11 @@ struct Solver {
     const long long units = conv ? p->B : (pl.M + 15LL) / 16;
     const long long most = units * (pl.L > 1 ? pl.Nl[1] + 1LL : 1LL);
     if (most * (conv ? 512 : 1024) >= 1LL << 32) return false;
-    const bool longstep = conv ? conv_sweep_ring(p->Himg, p->Wimg, p->C, p->dtype) : p->dtype == MGRIT_FP32 && p->q > 128;
-    return !longstep || units * (l + 1 < pl.L ? pl.Nl[l + 1] : 1LL) >= 128;
+    long long need = 1;
+    if (!conv) need = p->dtype == MGRIT_FP32 && p->q > 128 ? 128 : 1;
+    else if (conv_sweep_ring(p->Himg, p->Wimg, p->C, p->dtype)) need = !adjoint ? 128 : p->Himg * p->Wimg >= 784 ? 144 : 192;
+    else if (adjoint && p->C == 48 && p->Himg * p->Wimg > 900) need = 32;
+    return units * (l + 1 < pl.L ? pl.Nl[l + 1] : 1LL) >= need;
   }
   // chains of level l that start at sweep point ci * stride, for every ci
   SweepArgs sweep_args(int l, long long stride) const {

@@ -209,10 +209,13 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   constexpr int WS = RING ? 2 : S;                              // k steps loaded together: a tap or the whole layer
   constexpr int WU = (WS * 4 * CP + NTH - 1) / NTH;             // units (8 input channels of one output channel) per thread
   constexpr int WR = NP == 3 ? 2 : 1;                           // 16-byte loads per unit
-  // a layer's weight fragments fit in registers (beside the factors of the float adjoint not without spills: 1390 us for 64
-  // layers of 16 channels, 1371 when they are read from LDS)
-  constexpr bool HOLD = (CP == 16 && !(HD && NP == 3)) || (CP == 32 && NP == 1);
-  constexpr bool DEARLY = !RING;                                // act' factors requested at the start of a step
+  // a layer's weight fragments fit in registers (beside the factors of the adjoint not without spills, except for bf16 and 16
+  // channels: 1390 us for 64 float layers of 16 channels, 1371 with fragments read from LDS; a step of 32 channels bf16 on
+  // 32 x 32 pixels 11.1 -> 9.2 us)
+  constexpr bool HOLD = (CP == 16 && !(HD && NP == 3)) || (CP == 32 && NP == 1 && !HD);
+  // act' factors requested at the start of a step (wider layers: only when it is done, for they would be spilled: a step of 48
+  // channels on 28 x 28 pixels 17.8 -> 14.1 us, of 64 on 16 x 32 14.4 -> 12.8)
+  constexpr bool DEARLY = CP <= 32;
   static_assert(NBW % GB == 0 && (!RING || (CP == 64 && NP == 1)), "instances");
   typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
   typedef typename DRaw<WT>::type DR;

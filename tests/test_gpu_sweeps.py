@@ -99,3 +99,34 @@ def test_bf16_convolution_residual_reaches_rounding(C, H, W):
     bound = 2.0 ** -22 * float(np.abs(U).max()) * np.sqrt((sizes[1] + 1) * wl.E)
     print(hist, bound, flush=True)
     assert hist[-1] <= bound
+
+
+# the smallest number of chains that a long step is worth a sweep for, and one less: serial propagation (max_levels = 1), where
+# an image or 16 rows are a chain's workgroup; one instance of every other kind with a single chain
+EDGES = [(_conv(64, 28, 28, 127, 2, 2, 1, I.BF16), "forward", False), (_conv(64, 28, 28, 128, 2, 2, 1, I.BF16), "forward", True),
+         (_conv(64, 28, 28, 143, 2, 2, 1, I.BF16), "adjoint", False), (_conv(64, 28, 28, 144, 2, 2, 1, I.BF16), "adjoint", True),
+         (_conv(64, 23, 23, 191, 2, 2, 1, I.BF16), "adjoint", False), (_conv(64, 23, 23, 192, 2, 2, 1, I.BF16), "adjoint", True),
+         (_conv(48, 31, 31, 31, 3, 2, 1, I.BF16), "adjoint", False), (_conv(48, 31, 31, 32, 3, 2, 1, I.BF16), "adjoint", True),
+         (_conv(48, 30, 30, 1, 3, 2, 1, I.BF16), "adjoint", True), (_conv(48, 32, 32, 1, 3, 2, 1, I.BF16), "forward", True),
+         (_conv(32, 20, 30, 1, 3, 2, 1, I.BF16), "adjoint", True), (_conv(24, 32, 32, 2, 3, 2, 1, I.BF16), "adjoint", True),
+         (_conv(56, 16, 32, 1, 3, 2, 1, I.BF16), "adjoint", True), (_conv(56, 19, 27, 1, 3, 2, 1, I.BF16), "forward", False),
+         (_conv(32, 16, 32, 1, 3, 2, 1, I.FP32), "adjoint", True)]
+
+
+@pytest.mark.parametrize("wl,direction,sweep", EDGES, ids=lambda v: v if isinstance(v, str) else getattr(v, "name", None))
+def test_kernel_choice_at_the_edges_of_its_rule(wl, direction, sweep, monkeypatch):
+    """Which kernel runs, and that both kernels give the same result there."""
+    print(f"\n[case] {wl.name} {direction}", flush=True)
+    data = I.generate(wl)
+    gp = GpuProblem(wl, data)
+    rng = np.random.default_rng(4)
+    U = rng.standard_normal((wl.N + 1,) + wl.state_shape).astype(np.float32)
+    lamN = rng.standard_normal(wl.state_shape).astype(np.float32)
+    run = (lambda: gp.forward()[1]) if direction == "forward" else (lambda: gp.adjoint(U, lamN, want_grad=False)[0])
+    gp.M.mgrit_trace_begin()
+    got = run()
+    tr = gp.M.mgrit_trace_end()
+    kernel = "conv_sweep_kernel" if wl.layer == I.CONV else "dense_sweep_kernel"
+    assert any(k.startswith(kernel) for k in tr) == sweep, tr
+    monkeypatch.setenv("MGRIT_NO_SWEEP", "1")
+    assert rel_l2_per_state(got, run()) <= (1e-6 if wl.dtype == I.FP32 else 1e-3)      # the same operands, sums in another order
