@@ -94,8 +94,8 @@ DENSE_CASES = [
     I.reduced(I.cfg2(1), name="dense_fp32_q16_N3_m4_too_short_to_coarsen", q=16, B=3, N=3, m=4),
 ]
 
-# widths that are multiples of 128 (the fused sweep kernel's block width) at launch sizes below its threshold:
-# these run through the lockstep launches
+# widths that are multiples of 128.  Bf16 and float of width 128 run through sweeps, the other float layers and the wider ones
+# through lockstep launches; with the sweeps switched off all of them take the lockstep launches
 CHAIN_CASES = [
     I.reduced(I.cfg2(3), name="chain_fp32_q128_B37_N64_L3_FCF", q=128, B=37, N=64),
     I.reduced(I.cfg2(2), name="chain_fp32_q256_B70_N32_L2_F", q=256, B=70, N=32, max_levels=2, relax=I.RELAX_F,
@@ -111,6 +111,16 @@ CHAIN_CASES = [
 @pytest.mark.parametrize("wl", CHAIN_CASES, ids=lambda w: w.name)
 def test_dense_forward_chain_widths(wl):
     _check_forward(wl)
+
+
+@pytest.mark.parametrize("wl", CHAIN_CASES, ids=lambda w: w.name)
+def test_dense_forward_chain_widths_lockstep(wl, monkeypatch):
+    import torch                     # noqa: F401  (before the library is loaded: both then share torch's HIP runtime)
+    import paper_2007_07336_amd as M
+    monkeypatch.setenv("MGRIT_NO_SWEEP", "1")
+    M.mgrit_trace_begin()
+    _check_forward(wl)
+    assert not any("sweep" in k for k in M.mgrit_trace_end())
 
 
 @pytest.mark.parametrize("wl", DENSE_CASES, ids=lambda w: w.name)
@@ -558,8 +568,7 @@ def test_dense_step_whole_tiles_unmasked_and_masked(wl, monkeypatch):
 
 
 # ------------------------------------------------------------------ fused F-relaxation sweeps (dense layers)
-# Shapes on which the library fuses the steps of an F-relaxation sweep into one launch (width 128 or 256;
-# at least 128 (interval, 32-row slice) workgroups; m >= 3); each also runs with the fused
+# Shapes on which the library fuses the steps of a level's relaxation into one launch; each also runs with the fused
 # launches switched off (MGRIT_NO_SWEEP=1), i.e. through the lockstep launches, and the two must agree with the
 # oracle alike.
 SWEEP_CASES = [
@@ -571,7 +580,7 @@ SWEEP_CASES = [
               head_classes=0),
     # deep enough that the middle level's sweeps are fused too: they carry the FAS right-hand side
     I.reduced(I.cfg2(1), name="sweep_fp32_q128_B37_N1024_m4_L3_rhs", q=128, B=37, N=1024, bias_var=0.1, act=I.TANH),
-    # trailing F-points: the fused launch covers the whole intervals, single-group launches the rest
+    # trailing F-points: a chain of their own in the closing launch
     # (190 -> 47, two trailing points; 1030 -> 257 -> 64, two on the fine and one on the middle level)
     I.reduced(I.cfg2(2), name="sweep_fp32_q256_B70_N190_m4_L2_trailing", q=256, B=70, N=190, max_levels=2, bias_var=0.1),
     I.reduced(I.cfg5(1), name="sweep_bf16_q128_B40_N1030_m4_L3_trailing", q=128, B=40, N=1030, m=4, max_levels=3,

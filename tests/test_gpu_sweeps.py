@@ -1,6 +1,7 @@
 """Sweep kernels (many layer steps in one launch) at the edges of their instances, against the CPU oracle: channel counts that
 fill and do not fill a block of 16, pixel counts around the multiples of 16, images that share a workgroup (the last
-workgroup short), the largest image and the one past it, one coarse interval, trailing F-points, m = 2.
+workgroup short), the largest image and the one past it, one coarse interval, trailing F-points, m = 2.  Every row says which
+kernels its forward solve runs, S sweeps and L lockstep launches (levels with few chains of long steps), and that is checked.
 Tolerances (relative L2 per state / per layer gradient): float 1e-5, bf16 operands 2e-2, as in the other parity tests."""
 import numpy as np
 import pytest
@@ -18,29 +19,35 @@ def _conv(C, H, W, B, N, m, levels, dtype, relax=I.RELAX_FCF, act=I.TANH, it=1):
 
 
 CONV = [
-    _conv(8, 3, 5, 3, 7, 2, 3, I.FP32),                            # 15 pixels, half-empty channel block, m = 2, trailing
-    _conv(16, 4, 4, 21, 97, 4, 2, I.FP32, act=I.RELU, it=2),       # 16 pixels, images share workgroups, the last one short
-    _conv(16, 32, 32, 1, 8, 4, 2, I.FP32),                         # the largest image
-    _conv(24, 11, 3, 2, 9, 3, 3, I.FP32, relax=I.RELAX_F),         # 33 pixels, 24 of 32 channels
-    _conv(32, 16, 32, 1, 5, 4, 2, I.FP32, act=I.RELU),             # 512 pixels: the largest of this instance; one interval
-    _conv(32, 19, 27, 1, 4, 2, 2, I.FP32),                         # 513 pixels: lockstep launches
-    _conv(16, 7, 9, 2, 4, 4, 2, I.BF16, it=2),                     # one interval (Nc = 1)
-    _conv(40, 5, 13, 2, 11, 4, 2, I.BF16),                         # 65 pixels, 40 of 48 channels
-    _conv(48, 31, 33, 1, 6, 3, 2, I.BF16, relax=I.RELAX_F),        # 1023 pixels
-    _conv(56, 8, 8, 2, 10, 2, 4, I.BF16),                          # 56 of 64 channels
-    _conv(64, 16, 32, 1, 8, 4, 2, I.BF16, act=I.RELU),             # 512 pixels: the whole layer's weights in LDS
-    _conv(64, 27, 19, 2, 18, 4, 3, I.BF16),                        # 513 pixels: weights tap by tap
-    _conv(64, 32, 32, 1, 9, 2, 3, I.BF16, relax=I.RELAX_F, it=2),  # 1024 pixels
-    _conv(64, 27, 19, 16, 18, 2, 2, I.BF16),                       # 513 pixels, 144 workgroups: weights tap by tap
+    ("S", _conv(8, 3, 5, 3, 7, 2, 3, I.FP32)),                           # 15 pixels, half-empty channel block, m = 2, trailing
+    ("S", _conv(16, 4, 4, 21, 97, 4, 2, I.FP32, act=I.RELU, it=2)),      # 16 pixels, images share workgroups, the last one short
+    ("S", _conv(16, 32, 32, 1, 8, 4, 2, I.FP32)),                        # the largest image
+    ("S", _conv(24, 11, 3, 2, 9, 3, 3, I.FP32, relax=I.RELAX_F)),        # 33 pixels, 24 of 32 channels
+    ("S", _conv(32, 16, 32, 1, 5, 4, 2, I.FP32, act=I.RELU)),            # 512 pixels: the largest of this instance; one interval
+    ("L", _conv(32, 19, 27, 1, 4, 2, 2, I.FP32)),                        # 513 pixels: lockstep launches
+    ("S", _conv(16, 7, 9, 2, 4, 4, 2, I.BF16, it=2)),                    # one interval (Nc = 1)
+    ("S", _conv(40, 5, 13, 2, 11, 4, 2, I.BF16)),                        # 65 pixels, 40 of 48 channels
+    ("S", _conv(48, 31, 33, 1, 6, 3, 2, I.BF16, relax=I.RELAX_F)),       # 1023 pixels
+    ("S", _conv(56, 8, 8, 2, 10, 2, 4, I.BF16)),                         # 56 of 64 channels
+    ("S", _conv(64, 16, 32, 1, 8, 4, 2, I.BF16, act=I.RELU)),            # 512 pixels: the whole layer's weights in LDS
+    ("L", _conv(64, 27, 19, 2, 18, 4, 3, I.BF16)),                       # 513 pixels, 8 chains: lockstep launches
+    ("L", _conv(64, 32, 32, 1, 9, 2, 3, I.BF16, relax=I.RELAX_F, it=2)), # 1024 pixels, 4 chains: lockstep launches
+    ("SL", _conv(64, 27, 19, 16, 18, 2, 2, I.BF16)),                     # 513 pixels, 144 workgroups: weights tap by tap on level 0
+    # 529 pixels, 384 and 192 workgroups: weights tap by tap on levels 0 and 1, level 1 with a right-hand side of its own and
+    # level 0's formed by the sweep's single steps, forward and adjoint
+    ("SL", _conv(64, 23, 23, 24, 32, 2, 3, I.BF16)),
 ]
 
 
-@pytest.mark.parametrize("wl", CONV, ids=lambda w: w.name)
-def test_conv_sweep_instances(wl):
+@pytest.mark.parametrize("kernels,wl", CONV, ids=[wl.name for _, wl in CONV])
+def test_conv_sweep_instances(kernels, wl):
     print(f"\n[case] {wl.name}", flush=True)
     data = I.generate(wl)
     gp = GpuProblem(wl, data)
+    gp.M.mgrit_trace_begin()
     _, U, hist, it = gp.forward()
+    tr = gp.M.mgrit_trace_end()
+    assert ("S" if any("sweep" in k for k in tr) else "") + ("L" if any("sweep" not in k for k in tr) else "") == kernels, tr
     Uo, hist_o, it_o = oracle_forward(wl, data)
     tol = TOL[wl.dtype]
     assert it == it_o and rel_l2_per_state(U, Uo) <= tol
@@ -67,25 +74,68 @@ def _dense(q, B, N, m, levels, dtype, relax=I.RELAX_FCF, act=I.TANH, it=1):
 
 
 DENSE = [
-    _dense(8, 1, 7, 2, 3, I.FP32, it=2),                           # one feature block, one row, trailing F-points
-    _dense(64, 17, 12, 4, 2, I.FP32),                              # the widest of the four-wavefront instance, 17 rows
-    _dense(72, 16, 9, 3, 2, I.FP32, relax=I.RELAX_F),              # 72 of 128 features, the last k step short
-    _dense(128, 33, 5, 4, 2, I.FP32),                              # one interval
-    _dense(136, 3, 24, 2, 4, I.FP32),                              # 136 of 256
-    _dense(200, 150, 56, 4, 2, I.FP32),                            # 140 slices of 16 rows, the last of each chain short
-    _dense(248, 400, 60, 4, 2, I.FP32, act=I.RELU),                # 32-row slices, the last one short
-    _dense(256, 16, 8, 4, 1, I.FP32),                              # serial propagation
-    _dense(264, 5, 8, 4, 2, I.FP32),                               # too wide: lockstep launches
-    _dense(24, 40, 13, 3, 3, I.BF16),
-    _dense(104, 500, 49, 4, 2, I.BF16, it=2),                      # 32-row slices
-    _dense(256, 15, 33, 2, 3, I.BF16, relax=I.RELAX_F),
-    _dense(200, 50, 21, 5, 2, I.BF16),
+    ("S", _dense(8, 1, 7, 2, 3, I.FP32, it=2)),                          # one feature block, one row, trailing F-points
+    ("S", _dense(64, 17, 12, 4, 2, I.FP32)),                             # the widest of the four-wavefront instance, 17 rows
+    ("S", _dense(72, 16, 9, 3, 2, I.FP32, relax=I.RELAX_F)),             # 72 of 128 features, the last k step short
+    ("S", _dense(128, 33, 5, 4, 2, I.FP32)),                             # one interval
+    ("L", _dense(136, 3, 24, 2, 4, I.FP32)),                             # few chains of a wide float layer: lockstep launches
+    ("SL", _dense(200, 150, 56, 4, 2, I.FP32)),                          # 140 slices of 16 rows, the last of each chain short
+    ("SL", _dense(248, 400, 60, 4, 2, I.FP32, act=I.RELU)),              # 32-row slices, the last one short
+    ("SL", _dense(200, 250, 32, 2, 3, I.FP32)),                          # 256 and 128 slices: level 1 too, with its right-hand side
+    ("L", _dense(256, 16, 8, 4, 1, I.FP32)),                             # serial propagation of one slice: lockstep launches
+    ("L", _dense(264, 5, 8, 4, 2, I.FP32)),                              # too wide: lockstep launches
+    ("S", _dense(24, 40, 13, 3, 3, I.BF16)),
+    ("S", _dense(104, 500, 49, 4, 2, I.BF16, it=2)),                     # 32-row slices
+    ("S", _dense(256, 15, 33, 2, 3, I.BF16, relax=I.RELAX_F)),
+    ("S", _dense(200, 50, 21, 5, 2, I.BF16)),
 ]
 
 
-@pytest.mark.parametrize("wl", DENSE, ids=lambda w: w.name)
-def test_dense_sweep_instances(wl):
-    test_conv_sweep_instances(wl)
+@pytest.mark.parametrize("kernels,wl", DENSE, ids=[wl.name for _, wl in DENSE])
+def test_dense_sweep_instances(kernels, wl):
+    test_conv_sweep_instances(kernels, wl)
+
+
+@pytest.mark.parametrize("dtype", [I.FP32, I.BF16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("q,B", [(40, 70), (40, 6130), (128, 70), (128, 6130), (168, 2040), (256, 6130)])
+def test_dense_sweep_activations_elementwise(q, B, dtype, monkeypatch):
+    """Four, eight and sixteen wavefronts with 16 and with 32 rows each: tanh, ReLU and the adjoint's identity (weights as
+    stored and transposed), every element of two steps in sequence against float64 on the same operands."""
+    gap = 0.0
+    for act in (I.TANH, I.RELU):
+        wl = _dense(q, B, 2, 2, 1, dtype, act=act)
+        data = I.generate(wl)
+        gp = GpuProblem(wl, data)
+        W, b = data["W"].astype(np.float64), data["b"].astype(np.float64)
+        operand = (lambda x: I.round_to_bf16(x.astype(np.float32)).astype(np.float64)) if dtype == I.BF16 else (lambda x: x.astype(np.float64))
+        gp.M.mgrit_trace_begin()
+        U = gp.forward()[1]
+        assert any("dense_sweep" in k for k in gp.M.mgrit_trace_end())
+        f = np.tanh if act == I.TANH else lambda z: np.maximum(z, 0.0)
+        for n in range(2):
+            ref = U[n] + wl.h * f(operand(U[n]) @ W[n].T + b[n])
+            gap = max(gap, float(np.abs(U[n + 1] - ref).max()))
+        lamN = np.random.default_rng(1).standard_normal(wl.state_shape).astype(np.float32)
+        Uz = I.round_to_bf16(U)
+        for copy in ("0", "1"):
+            monkeypatch.setenv("MGRIT_ADJ_TRANSPOSED", copy)
+            gp.M.mgrit_trace_begin()
+            Lam = gp.adjoint(Uz, lamN, want_grad=False)[0]
+            assert any("dense_sweep" in k for k in gp.M.mgrit_trace_end())
+            for n in (1, 0):
+                z = Uz[n].astype(np.float64) @ W[n].T + b[n]
+                d = 1.0 - np.tanh(z) ** 2 if act == I.TANH else np.where(np.abs(z) < 1e-4, np.nan, (z > 0).astype(np.float64))
+                if dtype == I.BF16:                                  # the cached factor and the operand are rounded
+                    d = operand(d)
+                x = operand((d * Lam[n + 1]).astype(np.float32)) if dtype == I.BF16 else d * Lam[n + 1]
+                ref = Lam[n + 1] + wl.h * (x @ W[n])
+                row = ~np.isnan(ref).any(axis=1)                     # a ReLU' decision near zero spoils its row
+                assert row.mean() > 0.5
+                gap = max(gap, float(np.abs(Lam[n] - ref)[row].max()))
+    # float: sums of q products around 1/sqrt(q) and a state below 8, rounded to 24 bits a few times: 4e-6.  bf16: besides that
+    # a rounding decided the other way, 2^-9 of one product of a weight up to 4/sqrt(q) and a value up to 4, times h
+    print(f"q {q} B {B}: largest difference {gap:.2e}", flush=True)
+    assert gap <= (4e-6 if dtype == I.FP32 else 0.5 / np.sqrt(q) * 4 * 4 * 2.0 ** -9 + 4e-6)
 
 
 @pytest.mark.parametrize("C,H,W", [(16, 8, 8), (64, 8, 8)])
