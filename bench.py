@@ -242,9 +242,12 @@ class Workbench:
         if self.mixed and dom.startswith("dense"):      # the fully connected layers' launches dominate
             flops_per_unit = 2.0 * wl.B * wl.d_fc * wl.d_fc
             bytes_per_unit = wl.d_fc * wl.d_fc * (4 if wl.dtype == I.FP32 else 2) + 2 * wl.E * 4
-        peak_mfma = PEAK["fp32_mfma"] if wl.dtype == I.FP32 else PEAK["bf16_mfma"]
+        # float sweeps form their products on the bf16 matrix cores, six for one: that unit's rate is their roof
+        peak_mfma = PEAK["bf16_mfma"] if wl.dtype != I.FP32 else PEAK["bf16_mfma"] / 6 if "sweep" in dom else PEAK["fp32_mfma"]
         avg_us = ms_tot * 1e3 / launches
         tflops = units * flops_per_unit / (ms_tot * 1e-3) / 1e12
+        # (units of a sweep are the layer steps of the lockstep schedule that it stands for; it skips the repeated sweep of the
+        # first interval and the trailing F-points of a visit, about 1 % of them)
         # algorithmic bytes: the library's launch trace sums, per layer step, weights and bias, the input state, every
         # fused epilogue operand (residual and right-hand-side launches read one or two more states), the act' factor
         # of the adjoint and the output, each once; bytes_per_unit is the bare step (weights, state in, state out)
@@ -254,7 +257,7 @@ class Workbench:
         hbm_bound = alg_bytes / (PEAK["hbm_GBps"] * 1e9) > units * flops_per_unit / (peak_mfma * 1e12)
         return {"bound": "hbm" if hbm_bound else "mfma", "kernel": dom,
                 "achieved": round(gbps if hbm_bound else tflops, 3),
-                "peak": PEAK["hbm_GBps"] if hbm_bound else peak_mfma,
+                "peak": PEAK["hbm_GBps"] if hbm_bound else round(peak_mfma, 1),
                 "unit": "GB/s" if hbm_bound else "TFLOP/s",
                 "frac": round(gbps / PEAK["hbm_GBps"] if hbm_bound else tflops / peak_mfma, 5),
                 "traffic": measured_traffic_bytes(self.name, dom),

@@ -25,8 +25,11 @@
  *
  * Environment (diagnostic switches, read at every call; results agree with the default path to rounding).
  * MGRIT_NO_SWEEP=1 makes the library use one launch per layer step also where it would fuse many steps
- * into one launch (dense layers of width at most 256; convolution layers whose images fit on a compute unit: at most
- * 1024 pixels, in float at most 16 channels, or 32 and 512 pixels).  MGRIT_GRAD_NARROW=1 keeps the
+ * into one launch: dense layers of width at most 256, and convolution layers whose images fit on a compute unit
+ * (in float at most 16 channels and 1024 pixels or 32 and 512; in bf16 at most 48 channels or exactly 64 and 1024
+ * pixels, 56 and 512; no stacks with fully connected layers).  A level with few samples and intervals takes one launch
+ * per step all the same where that is faster (float of width 136 to 256, 64 channels on more than 512 pixels, the
+ * adjoint of 48 channels on more than 900).  MGRIT_GRAD_NARROW=1 keeps the
  * parameter gradient of dense layers of width 512 and more on the 128x128 tiles of narrower layers.
  * MGRIT_MASKED_STEP=1 sends dense layer steps whose batch, width and contraction length are whole multiples of
  * the tile through the bounds-masked loop that ragged shapes use.
@@ -229,8 +232,9 @@ int32_t mgrit_residual_norm_mixed(const mgrit_problem_t* p, const mgrit_fc_layer
 /* Diagnostic launch tracing, off by default and the one piece of state the library keeps: between
  * mgrit_trace_begin() and mgrit_trace_end() every layer-step and gradient launch is bracketed by a
  * pair of HIP events on its stream.  mgrit_trace_end synchronises on the last event and returns,
- * per kernel class (MGRIT_TRACE_*), the summed elapsed milliseconds, the number of launches, the
- * number of layer steps (groups) they processed and (bytes, may be NULL) their algorithmic bytes --
+ * per kernel class (MGRIT_TRACE_*; CONV_SWEEP_F32 counts sweeps of both types), the summed elapsed milliseconds,
+ * the number of launches, the number of layer steps (groups) they processed -- a fused launch: the layer steps of the
+ * one-launch-per-step schedule that it stands for -- and (bytes, may be NULL) their algorithmic bytes --
  * per layer step the layer's weights and bias, the input state, every fused epilogue operand, the
  * act' factor and the output, each moved once; arrays of n_classes entries, host.  Not thread
  * safe; meant for the benchmark's roofline figures (Sec. IV-B reports such a timeline). */

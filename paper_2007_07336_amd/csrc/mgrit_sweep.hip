@@ -17,9 +17,11 @@ namespace mgrit {
 //     neighbours on the same banks.
 //   - The contraction runs over k = (tap, input channel) in steps of 32, four 8-channel pieces per step.
 // NP = 1: bf16 problems.  NP = 3: float problems; state and weights are split into three bf16 numbers each, x = x1 + x2
-// + x3 (8 + 8 + 8 significant bits, so the split is exact), and the six products that reach 2^-24 are formed on the bf16
-// matrix cores with float accumulation -- 6/16 of the time of the float instructions.  The products left out are below
-// 2^-27 of the full one, less than the rounding of a single float addition.  (Infinite values: repeat_in_float.)
+// + x3 (8 + 8 + 8 significant bits, so the split is exact for values above about 2^-110; below, x3 and then x2 leave bf16's
+// range), and the six products that reach 2^-24 are formed on the bf16 matrix cores with float accumulation -- 6/16 of the time
+// of the float instructions.  Two of the products left out, x2 y3 and x3 y2, can reach 2^-25 of the full one each (|x2| <= 2^-8,
+// |x3| <= 2^-17 for x near 1), together one rounding of a float addition in the worst case; typically they are 2^-29.
+// (Infinite values: repeat_in_float.)
 // The weights of a layer: all in LDS (the next layer's are on their way in registers during a step), or, for 64 channels
 // on images too large for that (RING), tap by tap through three LDS slots.
 // What bounds it: 16 channels float -- the LDS reads of the operand (15 KB per 16 pixels and step against 480 cycles of
@@ -180,11 +182,13 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
   }
 }
 
-// LDS layouts of this file: a 16-byte read is served for lanes 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and the
-// same in the upper half (so the layouts that measured faster say), so for a fragment -- lane (c, kq) reads piece kq of
-// row c -- these sixteen should lie in different 16-byte columns of 256 bytes.  Row pitches of 2 modulo 4 columns do that;
-// elsewhere the pieces are permuted, by -kq & 3 rather than kq for the weights: two-way conflicts before, 823 -> 797 us
-// for 64 layers of 16 channels float, 9.71 -> 9.44 ms for 512 of 64 channels bf16, 531 -> 522 us for 256 of width 256.
+// LDS layouts of this file suppose that a 16-byte read is served for lanes 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31,
+// and the same in the upper half (inferred: the layouts made for it measured faster), so for a fragment -- lane (c, kq) reads
+// piece kq of row c -- these sixteen should lie in different 16-byte columns of 256 bytes.  Row pitches of 2 modulo 4 columns do
+// that; elsewhere the pieces are permuted, by -kq & 3 rather than kq for the weights: 823 -> 797 us for 64 layers of 16 channels
+// float, 9.71 -> 9.44 ms for 512 of 64 channels bf16, 531 -> 522 us for 256 of width 256.  Conflicts are left all the same: the
+// counters still show about two conflict cycles per LDS cycle in the convolution sweeps and 0.9 in the adjoint dense sweep,
+// whose 8-byte staging stores at a pitch of 72 bytes put rows r and r + 4 on the same banks (forward: 0.2 to 0.4).
 template <int NP, int CP>
 __device__ __forceinline__ int conv_sweep_swz(int p) {          // permutation of a pixel's 16-byte pieces
   if (CP == 64 && NP == 1) return p & 7;                        // pitch 128 bytes
