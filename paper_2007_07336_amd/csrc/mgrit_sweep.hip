@@ -77,6 +77,9 @@ template <int A, int B> __device__ __forceinline__ bool any_not_finite(const flo
   return __builtin_amdgcn_ballot_w64(!(top < __builtin_inff())) != 0;
 }
 
+// A barrier for what is in LDS: the stores of the last states stay in flight (waiting for them is 1 % of the sweeps of width 256).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Sum over a workgroup in a fixed order over the wavefronts; valid in thread 0.
 template <int NWV> __device__ __forceinline__ float sum_workgroup(float sq, float* red, int tid) {
 #pragma unroll
@@ -112,6 +115,7 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
   const int C = CONV ? a.C : a.q, Wd = a.Wimg, HW = CONV ? a.Himg * Wd : 1, ZP = per * HW;
   auto at = [&](const float* base, long long point) { return const_cast<float*>(base) + point * a.E + first; };
   auto elem = [&](int i) { return 4 * (tid + NTH * i); };
+  __syncthreads();                                                  // the sweep's stores are done: the same places are written again
   floatx4 st[U];
 #pragma unroll
   for (int i = 0; i < U; ++i) {
@@ -586,7 +590,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     if constexpr (TAU) {                                            // coarse right-hand side: Z <- Z - state, and its norm
       if constexpr (NP == 3) {
         if (any_not_finite(st)) repeat = 1;
-        __syncthreads();
+        lds_barrier();
         if (repeat) break;
       }
       float* o = place(a.Z, a.zb + ci * a.zs);
@@ -636,7 +640,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     __syncthreads();
   }
   if constexpr (NP == 3) {
-    if constexpr (!TAU) __syncthreads();
+    if constexpr (!TAU) lds_barrier();
     if (repeat) repeat_in_float<NWV, NBW * CB, ACT, false, true>(reinterpret_cast<float*>(P), red, wave);
   }
 }
@@ -994,12 +998,12 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
         if (a.G) st[rb][j] += gv[rb][j];
       }
 
-    if (NP == 3 && k == n) {
-      if (any_not_finite(st)) repeat = 1;
-      __syncthreads();
-      if (repeat) break;
-    }
     if (a.tau) {                                                    // coarse right-hand side: Z <- Z - state, and its norm
+      if constexpr (NP == 3) {
+        if (any_not_finite(st)) repeat = 1;
+        lds_barrier();
+        if (repeat) break;
+      }
       float* o = place(a.Z, a.zb + ci * a.zs);
       const float* ref = a.Ref ? place(a.Ref, a.rm.base + ci * a.rm.stride) : nullptr;
       float sq = 0.0f;
@@ -1034,6 +1038,10 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
     __syncthreads();
   }
   if constexpr (NP == 3) {
+    if (!a.tau) {
+      if (any_not_finite(st)) repeat = 1;
+      lds_barrier();
+    }
     if (repeat) repeat_in_float<NWV, RB * FBW, ACT, WN, false>(reinterpret_cast<float*>(A), red, wave);
   }
 }
