@@ -61,7 +61,7 @@ __device__ __forceinline__ void split3(F f, V& h, V& m, V& l) {               //
 // and a workgroup that ends with a state that is not finite repeats its chain with products of the float values themselves,
 // as the lockstep kernels form them.  (To look at the values where they are split, or at the sums of a step, took 1 to 7 % of
 // the sweeps of 16 channels and up to 40 % of those of width 256, in registers and branches more than in instructions; this
-// way 64 layers of 16 channels went from 810 to 817 us, 256 of width 256 from 500 to 505.)
+// way 64 layers of 16 channels take 805 us as before, 256 of width 256 went from 500 to 504.)
 template <int NP, int ACT> __device__ __forceinline__ float sweep_act(float z) {
   if constexpr (NP == 3 && ACT == ACT_RELU) return __builtin_elementwise_maximum(z, 0.0f);
   else return act_fn_c<ACT>(z);
@@ -191,8 +191,8 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
 // piece kq of row c -- these sixteen should lie in different 16-byte columns of 256 bytes.  Row pitches of 2 modulo 4 columns do
 // that; elsewhere the pieces are permuted, by -kq & 3 rather than kq for the weights: 823 -> 797 us for 64 layers of 16 channels
 // float, 9.71 -> 9.44 ms for 512 of 64 channels bf16, 531 -> 522 us for 256 of width 256.  Conflicts are left all the same: the
-// counters still show about two conflict cycles per LDS cycle in the convolution sweeps and 0.9 in the adjoint dense sweep,
-// whose 8-byte staging stores at a pitch of 72 bytes put rows r and r + 4 on the same banks (forward: 0.2 to 0.4).
+// counters still show 1.4 to 1.8 conflict cycles per LDS cycle in the sweeps of 16 channels, 0.75 in those of 64 and 0.9 in the
+// adjoint dense sweep, whose 8-byte staging stores at a pitch of 72 bytes put rows r and r + 4 on the same banks (forward: 0.2 to 0.4).
 template <int NP, int CP>
 __device__ __forceinline__ int conv_sweep_swz(int p) {          // permutation of a pixel's 16-byte pieces
   if (CP == 64 && NP == 1) return p & 7;                        // pitch 128 bytes
@@ -628,7 +628,6 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     if (a.X && a.xk) o1 = place(a.X, a.xb + ci * a.xs + (long long)k * a.xk);
     else if (k == a.kmid) { o1 = place(a.Y, a.yb + ci * a.ys); if (ci == 0) o2 = place(a.Z, a.zfirst); }
     else if (a.Z && k == n) o1 = place(a.Z, a.zb + ci * a.zs);
-    if (NP == 3 && k == n) { if (any_not_finite(st)) repeat = 1; }
     for (; o1; o1 = o2, o2 = nullptr) store_state(o1);
     if (k == n) break;
     if constexpr (!DEARLY) load_d(k + 1);
@@ -640,7 +639,10 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
     __syncthreads();
   }
   if constexpr (NP == 3) {
-    if constexpr (!TAU) lds_barrier();
+    if constexpr (!TAU) {
+      if (any_not_finite(st)) repeat = 1;
+      lds_barrier();
+    }
     if (repeat) repeat_in_float<NWV, NBW * CB, ACT, false, true>(reinterpret_cast<float*>(P), red, wave);
   }
 }
