@@ -92,12 +92,14 @@ template <int NWV> __device__ __forceinline__ float sum_workgroup(float sq, floa
   return t;
 }
 
-// The repeated chain.  A workgroup's samples are `total` consecutive values of a state; a thread holds every 64 NWV-th group of
-// four of them, at most U, and the operand of a step is in LDS as it is.  Latency is all that bounds it.  It takes nothing but
-// the wavefront's number from the sweep and reads its arguments again, through a pointer that the compiler cannot follow (kept
-// in scalar registers from the sweep on, they cost 2 % of it in spills).
+// The repeated chain.  A thread holds U groups of four neighbouring values -- channels of a pixel, features of a row, the lanes
+// of a wavefront at most eight different ones, so that they share weights -- and the operand of a step is in LDS as it is.
+// What bounds it are LDS reads (convolution: the weights too, put there at the start of a step) and weight loads.  With NaN in
+// every state a solve of 64 layers of 16 channels takes 7.1 ms (lockstep: 1.4), one of 256 layers of width 256 2.4 ms (0.7); 29
+// and 34 ms with the weights loaded value by value.  It takes nothing but the wavefront's number from the sweep and reads its arguments again,
+// through a pointer that the compiler cannot follow (kept in scalar registers from the sweep on, they cost 2 % of it in spills).
 template <int NWV, int U, int ACT, bool WN, bool CONV>
-__device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) {
+__device__ __forceinline__ void repeat_in_float(float* X, float* Wl, float* red, int wave) {
   constexpr int NTH = 64 * NWV;
   typedef const unsigned __attribute__((address_space(4))) * ArgWords;
   ArgWords words = (ArgWords)__builtin_amdgcn_kernarg_segment_ptr();
@@ -111,16 +113,20 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
   const int size = CONV ? a.Himg * a.Wimg * a.C : a.q;              // values of a sample
   const int nwg = (a.M + per - 1) / per, L = logical_block(), r0 = (L % nwg) * per;
   const long long ci = L / nwg, first = (long long)r0 * size;
-  const int total = min(per, a.M - r0) * size, n = a.tau ? 1 : ci == a.nchains - 1 ? a.nlast : a.nsteps;
-  const int C = CONV ? a.C : a.q, Wd = a.Wimg, HW = CONV ? a.Himg * Wd : 1, ZP = per * HW;
+  const int rows = min(per, a.M - r0), n = a.tau ? 1 : ci == a.nchains - 1 ? a.nlast : a.nsteps;
+  const int C = CONV ? a.C : a.q, Wd = a.Wimg, HW = CONV ? a.Himg * Wd : 1, npx = rows * HW, ZP = per * HW;
+  const int PX = CONV ? C : C + 4;                                  // floats of a pixel or row in LDS
   auto at = [&](const float* base, long long point) { return const_cast<float*>(base) + point * a.E + first; };
-  auto elem = [&](int i) { return 4 * (tid + NTH * i); };
+  auto pixel = [&](int i) { const int u = tid + NTH * i; return CONV ? u / (C / 4) : u % (16 * U); };
+  auto chan = [&](int i) { const int u = tid + NTH * i; return 4 * (CONV ? u % (C / 4) : u / (16 * U)); };
+  auto mine = [&](int i) { return pixel(i) < npx && chan(i) < C; };
+  auto elem = [&](int i) { return pixel(i) * C + chan(i); };
   __syncthreads();                                                  // the sweep's stores are done: the same places are written again
   floatx4 st[U];
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     st[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (elem(i) < total) st[i] = *reinterpret_cast<const floatx4*>(at(a.S, a.sm.base + ci * a.sm.stride) + elem(i));
+    if (mine(i)) st[i] = *reinterpret_cast<const floatx4*>(at(a.S, a.sm.base + ci * a.sm.stride) + elem(i));
   }
   if (CONV && tid < C) X[ZP * C + tid] = 0.0f;
 #pragma unroll 1
@@ -130,8 +136,10 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
     const float* Dm = reinterpret_cast<const float*>(a.Dm);
 #pragma unroll
     for (int i = 0; i < U; ++i)
-      if (elem(i) < total)
-        *reinterpret_cast<floatx4*>(X + elem(i)) = ACT == ACT_IDENT ? st[i] * *reinterpret_cast<const floatx4*>(at(Dm, layer) + elem(i)) : st[i];
+      if (mine(i))
+        *reinterpret_cast<floatx4*>(X + pixel(i) * PX + chan(i)) = ACT == ACT_IDENT ? st[i] * *reinterpret_cast<const floatx4*>(at(Dm, layer) + elem(i)) : st[i];
+    if (CONV)                                                       // a layer's weights, 9 C^2 floats, to LDS
+      for (int e = 4 * tid; e < 9 * C * C; e += 4 * NTH) *reinterpret_cast<floatx4*>(Wl + e) = *reinterpret_cast<const floatx4*>(W + e);
     __syncthreads();
     // where the state is kept, as in the sweep
     float* o1 = nullptr;
@@ -142,8 +150,8 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
     else if (a.Z && k == n) o1 = at(a.Z, a.zb + ci * a.zs);
 #pragma unroll
     for (int i = 0; i < U; ++i)
-      if (elem(i) < total) {
-        const int p = elem(i) / C, ch = elem(i) % C;                // pixel and channel, or row and feature
+      if (mine(i)) {
+        const int p = pixel(i), ch = chan(i);
         floatx4 z = floatx4{0.f, 0.f, 0.f, 0.f};
         if (a.bias) z = *reinterpret_cast<const floatx4*>(a.bias + layer * C + ch);
         const int y = p % HW / Wd, x = p % HW % Wd;
@@ -151,13 +159,20 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
         for (int tap = 0; tap < (CONV ? 9 : 1); ++tap) {
           const int yy = y + tap / 3 - 1, xx = x + tap % 3 - 1;
           const bool inside = yy >= 0 && yy < a.Himg && xx >= 0 && xx < Wd;
-          const float* xp = X + (CONV ? inside ? p + (yy - y) * Wd + xx - x : ZP : p) * C;
-          const float* w = W + (CONV ? (ch * 9 + tap) * C : WN ? ch : ch * C);
-          const int wv = CONV ? 9 * C : WN ? 1 : C, wt = !CONV && WN ? C : 1;
-#pragma unroll 1
-          for (int t = 0; t < C; ++t)
+          const float* xp = X + (CONV ? inside ? p + (yy - y) * Wd + xx - x : ZP : p) * PX;
+          const float* w = CONV ? Wl + (ch * 9 + tap) * C : W + (WN ? ch : ch * C);
+          const int next = CONV ? 9 * C : C;                        // from one output's weights, or one k's, to the next
+#pragma unroll 2
+          for (int t = 0; t < C; t += 4) {
+            const floatx4 xv = *reinterpret_cast<const floatx4*>(xp + t);
+            floatx4 wv[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) z[v] = __builtin_fmaf(w[v * wv + t * wt], xp[t], z[v]);
+            for (int r = 0; r < 4; ++r) wv[r] = *reinterpret_cast<const floatx4*>(WN ? w + (t + r) * next : w + r * next + t);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) z[v] = __builtin_fmaf(WN ? wv[r][v] : wv[v][r], xv[r], z[v]);
+          }
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) st[i][v] += a.hs * act_fn_c<ACT>(z[v]);
@@ -171,7 +186,7 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* red, int wave) 
   float sq = 0.0f;
 #pragma unroll
   for (int i = 0; i < U; ++i)
-    if (elem(i) < total) {
+    if (mine(i)) {
       floatx4* o = reinterpret_cast<floatx4*>(at(a.Z, a.zb + ci * a.zs) + elem(i));
       const floatx4 p = *o;
       *o = p - st[i];
@@ -204,6 +219,7 @@ template <int NP, int CP> constexpr int conv_sweep_ksteps() { return (9 * (CP / 
 template <int NP, int CP, bool RING> constexpr size_t conv_sweep_wbytes() {
   return (size_t)(RING ? 3 * 2 : conv_sweep_ksteps<NP, CP>()) * 4 * NP * CP * 16;
 }
+static_assert(conv_sweep_wbytes<3, 16, false>() >= 9 * 16 * 16 * 4 && conv_sweep_wbytes<3, 32, false>() >= 9 * 32 * 32 * 4, "repeat_in_float");
 
 // TAU: the coarse right-hand side, single steps (its epilogue beside the others would cost the sweep registers)
 template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
@@ -643,7 +659,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       if (any_not_finite(st)) repeat = 1;
       lds_barrier();
     }
-    if (repeat) repeat_in_float<NWV, NBW * CB, ACT, false, true>(reinterpret_cast<float*>(P), red, wave);
+    if (repeat) repeat_in_float<NWV, NBW * CB, ACT, false, true>(reinterpret_cast<float*>(P), reinterpret_cast<float*>(Wl), red, wave);
   }
 }
 
@@ -1044,7 +1060,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
       if (any_not_finite(st)) repeat = 1;
       lds_barrier();
     }
-    if (repeat) repeat_in_float<NWV, RB * FBW, ACT, WN, false>(reinterpret_cast<float*>(A), red, wave);
+    if (repeat) repeat_in_float<NWV, RB * FBW, ACT, WN, false>(reinterpret_cast<float*>(A), nullptr, red, wave);
   }
 }
 
