@@ -72,7 +72,8 @@ def measured_traffic_bytes(workload, kernel_class):
 
 def layer_steps_per_solve(sizes, m, relax, iters):
     """Layer-step evaluations (one u + h F(u) for the whole batch at one point of one level) that
-    a solve of `iters` V-cycles performs -- mirrors the launch schedule exactly."""
+    a solve of `iters` V-cycles performs -- mirrors the schedule of one launch per layer step exactly (a
+    sweep leaves out the steps that change nothing, about 1 %)."""
     L = len(sizes)
     if L == 1:
         return sizes[0]

@@ -23,8 +23,8 @@ inline bool adjoint_transposed_copy() {
 }
 inline bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % ALIGN) == 0; }
 
-// The fused F-relaxation sweep (one launch per sweep instead of one per step) can be switched off with
-// MGRIT_NO_SWEEP=1 in the environment; the tests run both ways.
+// Sweeps (one launch for many layer steps) can be switched off with MGRIT_NO_SWEEP=1 in the environment; the tests run
+// both ways.
 inline bool sweep_enabled() {
   const char* e = getenv("MGRIT_NO_SWEEP");
   return !(e && e[0] == '1');
@@ -269,9 +269,9 @@ struct Solver {
   }
   // Layers whose state fits on a CU -- convolution layers on images of at most 1024 pixels, dense layers of width at most
   // 256: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
-  // one launch each.  Whole solves 372 -> 251 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 797 us
-  // (64 of 28 x 28, 16 channels, float), 16.6 -> 9.4 ms (32 of 32 x 32, 64 channels, bf16);
-  // 250 -> 140 us (4 samples, width 8), 655 -> 505 us (128 samples, width 256, float).
+  // one launch each.  Whole solves 372 -> 226 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 797 us
+  // (64 of 28 x 28, 16 channels, float), 16.6 -> 9.3 ms (32 of 32 x 32, 64 channels, bf16);
+  // 250 -> 140 us (4 samples, width 8), 655 -> 521 us (128 samples, width 256, float).
   // Where a step of a chain is long, a level needs enough chains: a lockstep launch spreads one step over many workgroups.
   // us per step with one chain (images, or slices of 16 rows, on as many CUs), sweep / lockstep, forward and adjoint:
   //   64 channels on more than 512 pixels: 24.5 / 24.4 forward with 128 images, 27.9 / 45 with 256 (32 x 32); adjoint 50 / 42 with

@@ -85,7 +85,7 @@ struct ConvGradGeom {
 ConvGradGeom conv_grad_geom(int B, int Himg, int Wimg, int C, int dtype, int layers);
 size_t     conv_grad_partial_bytes(int B, int Himg, int Wimg, int C, int dtype, int layers);
 
-// ---- launch wrappers (defined in mgrit_kernels.hip); all enqueue on `s` and return the HIP status
+// ---- launch wrappers (defined in mgrit_kernels.hip, those of sweeps in mgrit_sweep.hip); all enqueue on `s` and return the HIP status
 hipError_t launch_step(const StepArgs& a, int layer_kind, int dtype, int groups, hipStream_t s);
 int        step_grid_blocks(const StepArgs& a, int layer_kind, int dtype, int groups);  // workgroups per group
 int        conv_tile_rows(int Himg, int Wimg, int C, int dtype);            // TH, or 0 if unsupported
