@@ -22,7 +22,7 @@ struct PtMap {
 //     out = act'(z)                                           (mode DACT)
 // which covers F-/C-relaxation, the C-point residual, the FAS right-hand side and the adjoint
 // steps (Sec. III-B, III-C).  If norm_partial is set, every workgroup also writes the sum of
-// out^2 over its tile to norm_partial[linear block index].
+// out^2, with Ref of (E1 - Ref)^2, over its tile to norm_partial[linear block index].
 struct StepArgs {
   const float* X;   PtMap xm;
   const float* Dm;  PtMap dm;      // optional elementwise multiplier of the matrix operand (the act' cache);

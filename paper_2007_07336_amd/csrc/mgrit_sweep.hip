@@ -61,7 +61,7 @@ __device__ __forceinline__ void split3(F f, V& h, V& m, V& l) {               //
 // and a workgroup that ends with a state that is not finite repeats its chain with products of the float values themselves,
 // as the lockstep kernels form them.  (To look at the values where they are split, or at the sums of a step, took 1 to 7 % of
 // the sweeps of 16 channels and up to 40 % of those of width 256, in registers and branches more than in instructions; this
-// way 64 layers of 16 channels take 805 us as before, 256 of width 256 went from 500 to 504.)
+// way 64 layers of 16 channels take what they took, 795 us, and 256 of width 256 524 instead of 522.)
 template <int NP, int ACT> __device__ __forceinline__ float sweep_act(float z) {
   if constexpr (NP == 3 && ACT == ACT_RELU) return __builtin_elementwise_maximum(z, 0.0f);
   else return act_fn_c<ACT>(z);
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   constexpr int WU = (WS * 4 * CP + NTH - 1) / NTH;             // units (8 input channels of one output channel) per thread
   constexpr int WR = NP == 3 ? 2 : 1;                           // 16-byte loads per unit
   // a layer's weight fragments fit in registers (beside the factors of the adjoint not without spills, except for bf16 and 16
-  // channels: 1390 us for 64 float layers of 16 channels, 1371 with fragments read from LDS; a step of 32 channels bf16 on
+  // channels: 1445 us for 64 float layers of 16 channels, 1385 with fragments read from LDS; a step of 32 channels bf16 on
   // 32 x 32 pixels 11.1 -> 9.2 us)
   constexpr bool HOLD = (CP == 16 && !(HD && NP == 3)) || (CP == 32 && NP == 1 && !HD);
   // act' factors requested at the start of a step (wider layers: only when it is done, for they would be spilled: a step of 48
