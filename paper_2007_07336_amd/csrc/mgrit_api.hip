@@ -21,6 +21,11 @@ inline bool adjoint_transposed_copy() {
   const char* e = getenv("MGRIT_ADJ_TRANSPOSED");
   return e && e[0] == '1';
 }
+// MGRIT_ACT_VALUES=1 in the environment: the act' factors of ReLU stacks are stored as values, like tanh's (diagnostic)
+inline bool act_factors_as_values() {
+  const char* e = getenv("MGRIT_ACT_VALUES");
+  return e && e[0] == '1';
+}
 inline bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % ALIGN) == 0; }
 
 // Sweeps (one launch for many layer steps) can be switched off with MGRIT_NO_SWEEP=1 in the environment; the tests run
@@ -169,6 +174,7 @@ struct Solver {
   int wn = 0, wn_fc = 0;               // adjoint on the caller's dense / fully connected weights as stored: W[k][n]
   const float* bias;
   const float* Dm;
+  int dbits = 0;                       // the act' factors (input and output) are bits: ReLU's
   const void* Wfc = nullptr;           // fully connected layers of a mixed stack (their transposes in the adjoint)
   const float* bfc = nullptr;
   int act;
@@ -195,7 +201,7 @@ struct Solver {
     a.sp = 1.0f; a.hs = pl.hl[l]; a.mode = MODE_PHI; a.act = act;
     a.M = pl.M; a.Nf = pl.Nf; a.K = pl.K; a.Himg = p->Himg; a.Wimg = p->Wimg; a.TH = pl.TH;
     a.E = pl.E; a.wsize = pl.wsize;
-    a.dbf16 = p->dtype == MGRIT_BF16 ? 1 : 0;
+    a.dbf16 = p->dtype == MGRIT_BF16 ? 1 : 0; a.dbits = dbits;
     // weights that a level touches: above 128 MB they are streamed past the caches, else later sweeps of the
     // same cycle find them in the last-level cache (a coarse level re-reads its few layers several times per cycle)
     a.wstream = (double)pl.Nl[l] * (double)pl.wsize * (double)pl.esize > 128.0 * 1024.0 * 1024.0 ? 1 : 0;
@@ -304,7 +310,7 @@ struct Solver {
     a.W = W; a.wn = wn; a.bias = bias; a.Dm = Dm;
     if (adjoint) { a.lb = p->N - mp; a.ls = -stride * mp; a.lk = -mp; }
     else         { a.lb = 0;         a.ls = stride * mp;  a.lk = mp; }
-    a.hs = pl.hl[l]; a.act = act;
+    a.hs = pl.hl[l]; a.act = act == ACT_IDENT && dbits ? ACT_MASK : act;
     a.M = pl.M; a.q = pl.Nf; a.E = pl.E; a.wsize = pl.wsize;
     if (p->layer == MGRIT_LAYER_CONV3X3) { a.M = pl.B; a.Himg = p->Himg; a.Wimg = p->Wimg; a.C = p->C; }
     return a;
@@ -607,6 +613,7 @@ int adjoint_impl(const mgrit_problem_t* p, const mgrit_fc_layers_t* fc, const vo
   if (fc && copy_dense) sv.chk(launch_transpose_weights(fc->Wfc, Wfct, MGRIT_LAYER_DENSE, p->dtype, pl.nfc, (int)pl.dfc, sv.s));
   {
     sv.W = W; sv.bias = b; sv.Dm = nullptr; sv.act = p->act;
+    sv.dbits = p->act == MGRIT_ACT_RELU && !act_factors_as_values();
     if (fc) { sv.Wfc = fc->Wfc; sv.bfc = fc->bfc; }
     StepArgs a = sv.base_args(0, 1, 1);
     a.wm = PtMap{0, 1};
@@ -628,7 +635,7 @@ int adjoint_impl(const mgrit_problem_t* p, const mgrit_fc_layers_t* fc, const vo
     memset(&ga, 0, sizeof(ga));
     ga.U = U; ga.um = PtMap{0, 1};
     ga.Lam = Lam; ga.lm = PtMap{1, 1};
-    ga.Dm = D; ga.dm = PtMap{0, 1};
+    ga.Dm = D; ga.dm = PtMap{0, 1}; ga.dbits = sv.dbits;
     ga.dW = dW; ga.db = db; ga.hs = p->h;
     ga.M = pl.M; ga.Nf = pl.Nf; ga.K = pl.K; ga.Himg = p->Himg; ga.Wimg = p->Wimg; ga.B = p->B;
     ga.E = pl.E; ga.wsize = pl.wsize;
@@ -644,7 +651,7 @@ int adjoint_impl(const mgrit_problem_t* p, const mgrit_fc_layers_t* fc, const vo
       memset(&gd, 0, sizeof(gd));
       gd.U = U; gd.um = PtMap{0, P};
       gd.Lam = Lam; gd.lm = PtMap{1, P};
-      gd.Dm = D; gd.dm = PtMap{0, P};
+      gd.Dm = D; gd.dm = PtMap{0, P}; gd.dbits = sv.dbits;
       gd.dW = dW ? fc->dWfc : nullptr; gd.db = db ? fc->dbfc : nullptr; gd.hs = p->h;
       gd.M = p->B; gd.Nf = (int)pl.dfc; gd.K = (int)pl.dfc; gd.B = p->B;
       gd.E = pl.E; gd.wsize = pl.wsize_fc;

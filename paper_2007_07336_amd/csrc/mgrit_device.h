@@ -3,6 +3,8 @@
 #pragma once
 #include "mgrit_internal.h"
 
+#include <type_traits>
+
 namespace mgrit {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
@@ -43,16 +45,45 @@ __device__ __forceinline__ uint4 ld_weights(const T* p) {
 // bf16 when the matrix-core operands are bf16 anyway (half the bytes of its many reads).  Four consecutive
 // values are loaded raw -- no conversion next to the load, which would make the compiler wait for it -- and
 // widened when they are used.
-__device__ __forceinline__ float4 ld_d4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ uint2 ld_d4(const __bf16* p) { return *reinterpret_cast<const uint2*>(p); }
-__device__ __forceinline__ float4 d4_to_f4(float4 r) { return r; }
-__device__ __forceinline__ float4 d4_to_f4(uint2 r) {
-  return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
-                     __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
+// ReLU's are 0 or 1 and are stored as bits, value i of a state in bit i % 8 of byte i / 8 (a state has a multiple of 8 values):
+// Fac<Bit>.  A wide adjoint sweep spends a third to a half of its memory traffic on the factors, the gradient a fifth.
+struct Bit {};
+template <typename T> struct Fac {                                  // T = float or __bf16
+  typedef const T* Ptr;                                             // of a layer's factors
+  typedef typename std::conditional<sizeof(T) == 4, float4, uint2>::type Raw;
+  static __device__ __forceinline__ Ptr at(const void* base, long long value) { return reinterpret_cast<const T*>(base) + value; }
+  static __device__ __forceinline__ Raw load(Ptr p, unsigned off) { return *reinterpret_cast<const Raw*>(p + off); }   // four, off % 4 == 0
+  // (byte offsets from a uniform base, as the unmasked kernels address memory)
+  static __device__ __forceinline__ Raw load_bytes(const char* p, unsigned off) { return *reinterpret_cast<const Raw*>(p + (unsigned)sizeof(T) * off); }
+  // the four as floats; off: their offset again, any number of eights left out
+  static __device__ __forceinline__ float4 f4(float4 r, unsigned) { return r; }
+  static __device__ __forceinline__ float4 f4(uint2 r, unsigned) {
+    return make_float4(__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xffff0000u),
+                       __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u));
+  }
+};
+// bit i of n as a factor 0 or 1
+__device__ __forceinline__ float bit_factor(unsigned n, int i) {
+  return __uint_as_float((unsigned)((int)(n << (31 - i)) >> 31) & 0x3f800000u);
 }
-template <typename T> struct DRaw;
-template <> struct DRaw<float>  { typedef float4 type; };
-template <> struct DRaw<__bf16> { typedef uint2 type; };
+template <> struct Fac<Bit> {
+  typedef const unsigned char* Ptr;
+  typedef unsigned Raw;
+  static __device__ __forceinline__ Ptr at(const void* base, long long value) { return reinterpret_cast<Ptr>(base) + (value >> 3); }
+  static __device__ __forceinline__ Raw load(Ptr p, unsigned off) { return p[off >> 3]; }
+  static __device__ __forceinline__ Raw load_bytes(const char* p, unsigned off) { return reinterpret_cast<Ptr>(p)[off >> 3]; }
+  static __device__ __forceinline__ float4 f4(Raw r, unsigned off) {
+    const unsigned n = r >> (off & 4u);
+    return make_float4(bit_factor(n, 0), bit_factor(n, 1), bit_factor(n, 2), bit_factor(n, 3));
+  }
+};
+// The byte of the factors of this lane's four values o and of its odd or even neighbour's (lanes 2 i and 2 i + 1 hold eight
+// consecutive ones); both lanes get it.
+__device__ __forceinline__ unsigned char factor_byte(float4 o, int lane) {
+  const unsigned n = (o.x != 0.0f ? 1u : 0u) | (o.y != 0.0f ? 2u : 0u) | (o.z != 0.0f ? 4u : 0u) | (o.w != 0.0f ? 8u : 0u);
+  const unsigned other = (unsigned)__builtin_amdgcn_mov_dpp((int)n, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
+  return (unsigned char)((lane & 1) ? (n << 4) | other : n | (other << 4));
+}
 __device__ __forceinline__ void cvt_store4(float* dst, float4 v) { *reinterpret_cast<float4*>(dst) = v; }
 __device__ __forceinline__ void cvt_store4(__bf16* dst, float4 v) {
   bf16x4 o;

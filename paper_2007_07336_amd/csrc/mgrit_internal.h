@@ -26,7 +26,7 @@ struct PtMap {
 struct StepArgs {
   const float* X;   PtMap xm;
   const float* Dm;  PtMap dm;      // optional elementwise multiplier of the matrix operand (the act' cache);
-                                   // its storage type is the weights' type: float, or bf16 when dbf16 is set
+                                   // its storage type is the weights' type: float, or bf16 when dbf16 is set; bits with dbits
   const void*  W;   PtMap wm;      // weights of layer wm(gi); element type = template parameter
   int wn;                          // dense only, 1: W holds W[k][n] (contraction index slowest), as the adjoint reads the
                                    // caller's weights without a transposed copy; 0: W[n][k].  Needs K == Nf and Dm.
@@ -45,6 +45,7 @@ struct StepArgs {
   unsigned wmagic;                 // conv only: ceil(2^20 / Wimg), filled in by the launch wrapper
   int tiles;                       // workgroups per group (filled in by the launch wrapper)
   int dbf16;                       // 1: Dm (input) and the output of MODE_DACT are bf16 arrays
+  int dbits;                       // 1: ... are bits (the factors of ReLU, 0 or 1), whatever dbf16 says
   int wstream;                     // 1: all layers' weights together exceed the last-level cache, load them
                                    // non-temporally; 0: they fit and later launches of the solve find them there
   int skip0, skipper;              // conv only, skipper > 0: groups skip0, skip0 + skipper, ... do nothing (their
@@ -55,14 +56,15 @@ struct StepArgs {
 };
 
 enum { MODE_PHI = 0, MODE_DACT = 1 };
-enum { ACT_TANH = 0, ACT_RELU = 1, ACT_IDENT = 2 };
+enum { ACT_TANH = 0, ACT_RELU = 1, ACT_IDENT = 2, ACT_MASK = 3 };   // ACT_MASK: identity, the sweep's Dm as bits
 
 // Parameter gradient launch (one group per layer n):
 //   G = Dm[n] .* Lam[n+1];  dW[n] = hs * G^T (*) U[n];  db[n] = hs * sum G
 struct GradArgs {
   const float* U;   PtMap um;
   const float* Lam; PtMap lm;
-  const float* Dm;  PtMap dm;        // act' cache in the weights' type (float, or bf16 for a bf16 problem)
+  const float* Dm;  PtMap dm;        // act' cache in the weights' type (float, or bf16 for a bf16 problem), or bits
+  int dbits;
   float* dW;                        // [layers][Nf][K] float
   float* db;                        // [layers][Nf] or null
   float hs;
@@ -130,7 +132,7 @@ struct SweepArgs {
   const float* G;  long long gb, gs;     // optional right-hand side (null: none)
   const void* W;  const float* bias;     // weights in the problem's type; bias may be null
   int wn;                                // dense sweep, 1: W holds W[k][n] (the adjoint on the caller's weights)
-  const void* Dm;                        // optional act' factors in the weights' type, [layers][E]
+  const void* Dm;                        // optional act' factors in the weights' type, [layers][E]; bits with ACT_MASK
   long long lb, ls, lk;
   float hs;
   int act, nsteps, nlast, nchains, M, q;

@@ -272,8 +272,12 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
       for (int i = 0; i < HB; ++i) {
         const int rl = (h0 + i) * RPI + lrow;
         const long long row = row0[tm] + rl;
+        unsigned char fb = 0;
+        if (dact && a.dbits) fb = factor_byte(xv[i], lane);
         if (colok && row < row_end) {
-          if (dact && a.dbf16) {                     // act' cache of a bf16 problem: 4 x bf16
+          if (dact && a.dbits) {
+            if (!(lane & 1)) reinterpret_cast<unsigned char*>(a.Out)[((a.om.base + gi * a.om.stride) * a.E + (unsigned)(row * a.Nf + col)) >> 3] = fb;
+          } else if (dact && a.dbf16) {              // act' cache of a bf16 problem: 4 x bf16
             __bf16* ob = reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E;
             cvt_store4(ob + (unsigned)(row * a.Nf + col), xv[i]);
           } else if (e.Op_) {
@@ -332,7 +336,7 @@ __device__ __forceinline__ void epilogue(const StepArgs& a, int gi, long long la
 // each 64-column half), so the state is read from memory once per step instead of twice.
 // WN: the weights are read as stored, W[k][n] (the adjoint's product, Out = G W): the slab sits k-major in LDS
 // and the fragments come from mma_step_wn; otherwise W[n][k] with k fastest (the forward product, Out = X W^T).
-template <typename WT, int BM, int BN, int WR, int WC, int BK, int PF, bool WS, bool HD = true, bool FULL = false, bool XR = false, bool WN = false>
+template <typename WT, int BM, int BN, int WR, int WC, int BK, int PF, bool WS, bool HD = true, bool FULL = false, bool XR = false, bool WN = false, typename DT = WT>
 __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1) void dense_step_kernel(StepArgs a) {
   constexpr int NTH = 64 * WR * WC;
   constexpr int ST = BK + Op<WT>::PAD, VEC = Op<WT>::VEC, KSTEP = Op<WT>::KSTEP;
@@ -354,10 +358,10 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
   const long long layer = a.wm.base + gi * a.wm.stride;
   const float* Xp = a.X + (a.xm.base + gi * a.xm.stride) * a.E;
-  const WT* Dp = HD && a.Dm ? reinterpret_cast<const WT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E : nullptr;
+  const typename Fac<DT>::Ptr Dp = HD && a.Dm ? Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E) : nullptr;
   const WT* Wp = reinterpret_cast<const WT*>(a.W) + layer * a.wsize;
   const int K = a.K;
-  typedef typename DRaw<WT>::type DR;
+  typedef typename Fac<DT>::Raw DR;
 
   // PF register sets hold the slabs in flight from global memory.  Loads are unconditional (a
   // predicated load makes the compiler wait for it right away, which serialises the whole slab):
@@ -386,7 +390,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
       for (int i = 0; i < AP; ++i) {
         const unsigned off = aoff0 + (unsigned)i * astep + (unsigned)k0;
         ar[i] = *reinterpret_cast<const float4*>(Xc + 4u * off);
-        if (HD) dr[HD ? i : 0] = ld_d4(reinterpret_cast<const WT*>(Dc + (unsigned)sizeof(WT) * off));
+        if (HD) dr[HD ? i : 0] = Fac<DT>::load_bytes(Dc, off);
       }
 #pragma unroll
       for (int i = 0; i < BP; ++i) {
@@ -403,7 +407,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
       const unsigned off = ok ? (unsigned)((m0 + row) * K + k0 + kc) : 0u;
       am |= ok ? (1u << i) : 0u;
       ar[i] = *reinterpret_cast<const float4*>(Xp + off);
-      if (HD && Dp) dr[HD ? i : 0] = ld_d4(Dp + off);
+      if (HD && Dp) dr[HD ? i : 0] = Fac<DT>::load(Dp, off);
     }
 #pragma unroll
     for (int i = 0; i < BP; ++i) {
@@ -420,7 +424,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
     for (int i = 0; i < AP; ++i) {
       const int p = tid + NTH * i, row = p / (BK / 4), kc = (p % (BK / 4)) * 4;
       float4 v = ar[i];
-      if (HD && (FULL || Dp)) { const float4 d = d4_to_f4(dr[HD ? i : 0]); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
+      if (HD && (FULL || Dp)) { const float4 d = Fac<DT>::f4(dr[HD ? i : 0], kc); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
       if (!FULL && !((am >> i) & 1u)) v = make_float4(0.f, 0.f, 0.f, 0.f);
       cvt_store4(&As[row * ST + kc], v);
     }
@@ -515,8 +519,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
           stage[(wm0 + i * 32 + 8 * (r >> 2) + 4 * g + (r & 3)) * SWF + wn0 + jn * 32 + c] = acc[i][jn][r];
     __syncthreads();
     const EpiPtrs e = epi_ptrs(a, gi, layer);
-    const int rq = tid / (BK / 4), cq = (tid % (BK / 4)) * 4;
-    const bool dact = a.mode == MODE_DACT;
+    const int rq = tid / (BK / 4), cq = (tid % (BK / 4)) * 4;      // (never MODE_DACT: dense_xr)
     float sq = 0.0f;
     auto tile_rows = [&](auto actc) {
     constexpr int ACT = decltype(actc)::value;
@@ -553,21 +556,11 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
         for (int u = 0; u < 4; ++u) {
           const float4 xv = xown[half][XR ? h0 + u : 0];
           float4 o;
-          if (dact) {
-            o.x = act_prime_c<ACT>(z[u].x + bv.x); o.y = act_prime_c<ACT>(z[u].y + bv.y);
-            o.z = act_prime_c<ACT>(z[u].z + bv.z); o.w = act_prime_c<ACT>(z[u].w + bv.w);
-          } else {
-            o.x = a.sp * (xv.x + a.hs * act_fn_c<ACT>(z[u].x + bv.x)) + a.c1 * e1[u].x;
-            o.y = a.sp * (xv.y + a.hs * act_fn_c<ACT>(z[u].y + bv.y)) + a.c1 * e1[u].y;
-            o.z = a.sp * (xv.z + a.hs * act_fn_c<ACT>(z[u].z + bv.z)) + a.c1 * e1[u].z;
-            o.w = a.sp * (xv.w + a.hs * act_fn_c<ACT>(z[u].w + bv.w)) + a.c1 * e1[u].w;
-          }
-          if (dact && a.dbf16) {
-            __bf16* ob = reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E;
-            cvt_store4(ob + off[u], o);
-          } else if (e.Op_) {
-            *reinterpret_cast<float4*>(e.Op_ + off[u]) = o;
-          }
+          o.x = a.sp * (xv.x + a.hs * act_fn_c<ACT>(z[u].x + bv.x)) + a.c1 * e1[u].x;
+          o.y = a.sp * (xv.y + a.hs * act_fn_c<ACT>(z[u].y + bv.y)) + a.c1 * e1[u].y;
+          o.z = a.sp * (xv.z + a.hs * act_fn_c<ACT>(z[u].z + bv.z)) + a.c1 * e1[u].z;
+          o.w = a.sp * (xv.w + a.hs * act_fn_c<ACT>(z[u].w + bv.w)) + a.c1 * e1[u].w;
+          if (e.Op_) *reinterpret_cast<float4*>(e.Op_ + off[u]) = o;
           sq += e.Rp ? sq_diff(e1[u], rf[u]) : sq_norm(o);
         }
       }
@@ -625,7 +618,7 @@ template <typename WT> constexpr size_t ksplit_smem(int nw) {
   return (size_t)nw * 2 * 32 * (KsOp<WT>::KC / 2 + Op<WT>::PAD) * sizeof(WT);
 }
 
-template <typename WT, bool WS, int NW, bool WN = false>
+template <typename WT, bool WS, int NW, bool WN = false, typename DT = WT>
 __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
   static_assert(NW == 4 || NW == 8, "four or eight wavefronts");
   constexpr int KC = KsOp<WT>::KC;
@@ -642,10 +635,10 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
   const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
   const long long layer = a.wm.base + gi * a.wm.stride;
   const float* Xp = a.X + (a.xm.base + gi * a.xm.stride) * a.E;
-  const WT* Dp = a.Dm ? reinterpret_cast<const WT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E : nullptr;
+  const typename Fac<DT>::Ptr Dp = a.Dm ? Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E) : nullptr;
   const WT* Wp = reinterpret_cast<const WT*>(a.W) + layer * a.wsize;
   const int K = a.K;
-  typedef typename DRaw<WT>::type DR;
+  typedef typename Fac<DT>::Raw DR;
   const EpiPtrs e = epi_ptrs(a, gi, layer);
 
   // ---- epilogue operands first (one float4 per thread of the first four wavefronts: row tid/8, columns
@@ -713,7 +706,7 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
         const unsigned off = ok ? (unsigned)(row * K + k) : 0u;
         am |= ok ? (1u << i) : 0u;
         x[i] = *reinterpret_cast<const float4*>(Xp + off);
-        if (Dp) d[i] = ld_d4(Dp + off);
+        if (Dp) d[i] = Fac<DT>::load(Dp, off);
       }
     };
     // one piece: registers -> this wavefront's LDS area -> MFMA fragments.  The area belongs to this wavefront
@@ -736,7 +729,7 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
 #pragma unroll
       for (int i = 0; i < AI; ++i) {
         float4 v = x[i];
-        if (Dp) { const float4 dd = d4_to_f4(d[i]); v.x *= dd.x; v.y *= dd.y; v.z *= dd.z; v.w *= dd.w; }
+        if (Dp) { const float4 dd = Fac<DT>::f4(d[i], akc); v.x *= dd.x; v.y *= dd.y; v.z *= dd.z; v.w *= dd.w; }
         if (!((am >> i) & 1u)) v = zero;
         cvt_store4(&Al[(ARI * i + arl) * LST + akc], v);
       }
@@ -795,8 +788,11 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
     o.w = a.sp * (xv.w + a.hs * act_fn(z.w + bv.w, a.act)) + a.c1 * e1.w;
   }
   float sq = 0.0f;
+  unsigned char fb = 0;
+  if (dact && a.dbits) fb = factor_byte(o, lane);
   if (eok) {
-    if (dact && a.dbf16) cvt_store4(reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E + eoff, o);
+    if (dact && a.dbits) { if (!(lane & 1)) reinterpret_cast<unsigned char*>(a.Out)[((a.om.base + gi * a.om.stride) * a.E + eoff) >> 3] = fb; }
+    else if (dact && a.dbf16) cvt_store4(reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E + eoff, o);
     else if (e.Op_) *reinterpret_cast<float4*>(e.Op_ + eoff) = o;
     sq = e.Rp ? sq_diff(e1, rf) : sq_norm(o);
   }
@@ -819,7 +815,7 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
 // workgroup's output columns), so the tap loop unrolls with its LDS reads ahead of the matrix instructions and
 // the weight pieces need neither masks nor divisions -- with bf16 matrix instructions a tap is 16 of them per
 // wavefront, and a rolled k loop that waits for every fragment read takes several times as long.
-template <typename WT, int TN, bool N16 = false, int CFIX = 0>
+template <typename WT, int TN, bool N16 = false, int CFIX = 0, typename DT = WT>
 __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two workgroups per CU: at most 256 registers
   static_assert(!N16 || (sizeof(WT) == 4 && TN == 1), "the 16-wide variant is float only");
   static_assert(CFIX == 0 || (!N16 && CFIX == 32 * TN && CFIX % Op<WT>::KSTEP == 0), "fixed channel count = output columns");
@@ -849,9 +845,9 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
   const int bimg = tile / tiles_per_img, y0 = (tile % tiles_per_img) * TH;
   const long long layer = a.wm.base + gi * a.wm.stride;
   const float* Xp = a.X + (a.xm.base + gi * a.xm.stride) * a.E;
-  const WT* Dp = a.Dm ? reinterpret_cast<const WT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E : nullptr;
+  const typename Fac<DT>::Ptr Dp = a.Dm ? Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E) : nullptr;
   const WT* Wp = reinterpret_cast<const WT*>(a.W) + layer * a.wsize;
-  typedef typename DRaw<WT>::type DR;
+  typedef typename Fac<DT>::Raw DR;
 
   // 16-wide variant: the nine [C_out][C_in] slices are 9 x 16 x 16 floats in all.  They are requested first (their
   // latency hides behind the patch loads), written to LDS once, and the taps run without a weight ring and
@@ -909,7 +905,7 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
         const unsigned off = ok ? (unsigned)((((long long)bimg * H + gy) * Wd + gx) * C + c4) : 0u;
         hm |= ok ? (1u << u) : 0u;
         v[u] = *reinterpret_cast<const float4*>(Xp + off);
-        if (Dp) d[u] = ld_d4(Dp + off);
+        if (Dp) d[u] = Fac<DT>::load(Dp, off);
       }
 #pragma unroll
       for (int u = 0; u < HU; ++u) {
@@ -918,7 +914,7 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
           const int pp = p / cq, c4 = (p % cq) * 4;
           const int prow = pp < Wd ? 0 : TH + 1, gx = pp < Wd ? pp : pp - Wd;
           float4 w = v[u];
-          if (Dp) { const float4 dd = d4_to_f4(d[u]); w.x *= dd.x; w.y *= dd.y; w.z *= dd.z; w.w *= dd.w; }
+          if (Dp) { const float4 dd = Fac<DT>::f4(d[u], c4); w.x *= dd.x; w.y *= dd.y; w.z *= dd.z; w.w *= dd.w; }
           if (!((hm >> u) & 1u)) w = make_float4(0.f, 0.f, 0.f, 0.f);
           cvt_store4(&patch[(prow * PW + gx + 1) * CS + c4], w);
         }
@@ -941,7 +937,7 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
           const int p = (wave * TM + tm) * 32 + h * RPI + lrow;
           const bool ok = (okm >> (tm * NIT + h)) & 1u;
           const unsigned off = ok ? (unsigned)((((long long)bimg * H + y0) * Wd + p) * C + colq) : 0u;
-          dreg[h] = ld_d4(Dp + off);
+          dreg[h] = Fac<DT>::load(Dp, off);
         }
       }
 #pragma unroll
@@ -950,7 +946,7 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
         const int p = (wave * TM + tm) * 32 + h * RPI + lrow;
         if (p < TH * Wd && colq < Cp) {
           float4 w = xreg[i];
-          if (Dp) { const float4 dd = d4_to_f4(dreg[h]); w.x *= dd.x; w.y *= dd.y; w.z *= dd.z; w.w *= dd.w; }
+          if (Dp) { const float4 dd = Fac<DT>::f4(dreg[h], colq); w.x *= dd.x; w.y *= dd.y; w.z *= dd.z; w.w *= dd.w; }
           if (!((okm >> i) & 1u)) w = make_float4(0.f, 0.f, 0.f, 0.f);
           const int py = div_small(p, a.wmagic);           // p / Wd without the division sequence
           cvt_store4(&patch[((py + 1) * PW + (p - py * Wd) + 1) * CS + colq], w);
@@ -1179,16 +1175,18 @@ static bool step_opt_in(LdsOptIn& opt, const void* kernel, size_t smem) {
   if (e != hipSuccess) g_step_attr_err = e;
   return e == hipSuccess;
 }
-template <typename WT, int BM, int BN, int BK, int PF, bool WS, int WR, int WC, bool HD, bool FULL, bool XR = false, bool WN = false>
+template <typename WT, int BM, int BN, int BK, int PF, bool WS, int WR, int WC, bool HD, bool FULL, bool XR = false, bool WN = false, typename DT = WT>
 static void launch_dense_k(dim3 grid, hipStream_t s, const StepArgs& a) {
+  if constexpr (HD && std::is_same<DT, WT>::value)
+    if (a.dbits && a.Dm) return launch_dense_k<WT, BM, BN, BK, PF, WS, WR, WC, HD, FULL, XR, WN, Bit>(grid, s, a);
   constexpr size_t bn_rows = (size_t)BN * (BK + Op<WT>::PAD), bk_rows = (size_t)BK * (BN + (sizeof(WT) == 2 ? 16 : 4));
   constexpr size_t tiles_b = ((size_t)BM * (BK + Op<WT>::PAD) + (WN ? bk_rows : bn_rows)) * sizeof(WT);
   constexpr size_t stage_b = XR ? (size_t)BM * (BN + 4) * sizeof(float)                   // whole-tile epilogue staging
                                 : (size_t)(WR * WC) * 32 * (BN / WC + 4) * sizeof(float);  // per-wavefront staging
   constexpr size_t smem = tiles_b > stage_b ? tiles_b : stage_b;
   static LdsOptIn opt;
-  if (!step_opt_in(opt, reinterpret_cast<const void*>(dense_step_kernel<WT, BM, BN, WR, WC, BK, PF, WS, HD, FULL, XR, WN>), smem)) return;
-  hipLaunchKernelGGL((dense_step_kernel<WT, BM, BN, WR, WC, BK, PF, WS, HD, FULL, XR, WN>), grid, dim3(64 * WR * WC), smem, s, a);
+  if (!step_opt_in(opt, reinterpret_cast<const void*>(dense_step_kernel<WT, BM, BN, WR, WC, BK, PF, WS, HD, FULL, XR, WN, DT>), smem)) return;
+  hipLaunchKernelGGL((dense_step_kernel<WT, BM, BN, WR, WC, BK, PF, WS, HD, FULL, XR, WN, DT>), grid, dim3(64 * WR * WC), smem, s, a);
 }
 // Whole tiles and 32-bit byte offsets within one group's operands: the kernel's unmasked path.
 template <typename WT, int BM, int BN, int BK>
@@ -1232,17 +1230,19 @@ static void launch_dense(dim3 grid, hipStream_t s, const StepArgs& a) {
   if (a.wstream) launch_dense_ws<WT, BM, BN, BK, PF, true, WR, WC>(grid, s, a);
   else           launch_dense_ws<WT, BM, BN, BK, PF, false, WR, WC>(grid, s, a);
 }
-template <typename WT, bool WS, int NW>
+template <typename WT, bool WS, int NW, typename DT = WT>
 static void launch_ksplit_nw(dim3 grid, hipStream_t s, const StepArgs& a) {
+  if constexpr (std::is_same<DT, WT>::value)
+    if (a.dbits && a.Dm) return launch_ksplit_nw<WT, WS, NW, Bit>(grid, s, a);
   constexpr size_t smem = ksplit_smem<WT>(NW);
   static LdsOptIn opt, optn;
   if (a.wn) {
-    if (!step_opt_in(optn, reinterpret_cast<const void*>(dense_ksplit_kernel<WT, WS, NW, true>), smem)) return;
-    hipLaunchKernelGGL((dense_ksplit_kernel<WT, WS, NW, true>), grid, dim3(NW * 64), smem, s, a);
+    if (!step_opt_in(optn, reinterpret_cast<const void*>(dense_ksplit_kernel<WT, WS, NW, true, DT>), smem)) return;
+    hipLaunchKernelGGL((dense_ksplit_kernel<WT, WS, NW, true, DT>), grid, dim3(NW * 64), smem, s, a);
     return;
   }
-  if (!step_opt_in(opt, reinterpret_cast<const void*>(dense_ksplit_kernel<WT, WS, NW>), smem)) return;
-  hipLaunchKernelGGL((dense_ksplit_kernel<WT, WS, NW>), grid, dim3(NW * 64), smem, s, a);
+  if (!step_opt_in(opt, reinterpret_cast<const void*>(dense_ksplit_kernel<WT, WS, NW, false, DT>), smem)) return;
+  hipLaunchKernelGGL((dense_ksplit_kernel<WT, WS, NW, false, DT>), grid, dim3(NW * 64), smem, s, a);
 }
 template <typename WT>
 static void launch_ksplit(dim3 grid, hipStream_t s, const StepArgs& a) {
@@ -1251,11 +1251,13 @@ static void launch_ksplit(dim3 grid, hipStream_t s, const StepArgs& a) {
   else           { if (wide) launch_ksplit_nw<WT, false, 8>(grid, s, a); else launch_ksplit_nw<WT, false, 4>(grid, s, a); }
 }
 
-template <typename WT, int TN, bool N16 = false, int CFIX = 0>
+template <typename WT, int TN, bool N16 = false, int CFIX = 0, typename DT = WT>
 static void launch_conv(dim3 grid, size_t smem, hipStream_t s, const StepArgs& a) {
+  if constexpr (std::is_same<DT, WT>::value)
+    if (a.dbits && a.Dm) return launch_conv<WT, TN, N16, CFIX, Bit>(grid, smem, s, a);
   static LdsOptIn opt;
-  if (!step_opt_in(opt, reinterpret_cast<const void*>(conv_step_kernel<WT, TN, N16, CFIX>), smem)) return;
-  hipLaunchKernelGGL((conv_step_kernel<WT, TN, N16, CFIX>), grid, dim3(NT), smem, s, a);
+  if (!step_opt_in(opt, reinterpret_cast<const void*>(conv_step_kernel<WT, TN, N16, CFIX, DT>), smem)) return;
+  hipLaunchKernelGGL((conv_step_kernel<WT, TN, N16, CFIX, DT>), grid, dim3(NT), smem, s, a);
 }
 // MGRIT_CONV_GENERIC=1 in the environment keeps 64-channel bf16 layers on the kernel with a run-time channel count
 static bool conv_fixed_channels(const StepArgs& a, int dtype) {
@@ -1315,8 +1317,9 @@ hipError_t launch_step(const StepArgs& a_in, int layer_kind, int dtype, int grou
   double per = (double)a.wsize * es + (a.bias ? 4.0 * a.Nf : 0.0) + 4.0 * (double)a.E;
   if (a.E1 && a.c1 != 0.0f) per += 4.0 * (double)a.E;
   if (a.Ref) per += 4.0 * (double)a.E;
-  if (a.Dm) per += es * (double)a.E;
-  if (a.Out) per += (a.mode == MODE_DACT ? es : 4.0) * (double)a.E;
+  const double ds = a.dbits ? 0.125 : es;          // bytes of an act' factor
+  if (a.Dm) per += ds * (double)a.E;
+  if (a.Out) per += (a.mode == MODE_DACT ? ds : 4.0) * (double)a.E;
   trace_after(s, cls, worked, per * worked);
   return e;
 }
@@ -1487,7 +1490,7 @@ hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int
 // column add up the unrounded G values that pass through their threads (fixed order: a thread's rows in
 // sequence, then the eight threads of a column group by a butterfly).
 // ------------------------------------------------------------------------------------------
-template <typename OT>
+template <typename OT, typename DT>
 __global__ __launch_bounds__(NT) void dense_grad_kernel(GradArgs a) {
   constexpr int BKR = 32, ST = BKR + Op<OT>::PAD, KSTEP = Op<OT>::KSTEP;
   constexpr int BM = 128, BN = 128, TM = 2, TN = 2;
@@ -1505,9 +1508,9 @@ __global__ __launch_bounds__(NT) void dense_grad_kernel(GradArgs a) {
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
   const float* Up = a.U + (a.um.base + gi * a.um.stride) * a.E;
   const float* Lp = a.Lam + (a.lm.base + gi * a.lm.stride) * a.E;
-  const OT* Dp = reinterpret_cast<const OT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E;
+  const typename Fac<DT>::Ptr Dp = Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E);
   float* dWp = a.dW ? a.dW + (long long)gi * a.wsize : nullptr;
-  typedef typename DRaw<OT>::type DR;
+  typedef typename Fac<DT>::Raw DR;
 
   const int rb = tid & 7, cb = tid >> 3;             // 4 batch rows x 4 columns per thread
   const bool aok = m0 + 4 * cb < q, bok = n0 + 4 * cb < q;      // q % 4 == 0: a float4 is in or out as a whole
@@ -1526,7 +1529,7 @@ __global__ __launch_bounds__(NT) void dense_grad_kernel(GradArgs a) {
       rmask |= rok ? (1u << rr) : 0u;
       const unsigned offa = (rok && aok) ? (unsigned)(row * q + m0 + 4 * cb) : 0u;
       const unsigned offb = (rok && bok) ? (unsigned)(row * q + n0 + 4 * cb) : 0u;
-      dv[rr] = ld_d4(Dp + offa);
+      dv[rr] = Fac<DT>::load(Dp, offa);
       lv[rr] = *reinterpret_cast<const float4*>(Lp + offa);
       uv[rr] = *reinterpret_cast<const float4*>(Up + offb);
     }
@@ -1537,7 +1540,7 @@ __global__ __launch_bounds__(NT) void dense_grad_kernel(GradArgs a) {
     for (int rr = 0; rr < 4; ++rr) {
       const bool rok = (rmask >> rr) & 1u;
       const float ga = (rok && aok) ? 1.0f : 0.0f, ub = (rok && bok) ? 1.0f : 0.0f;
-      const float4 dd = d4_to_f4(dv[rr]);
+      const float4 dd = Fac<DT>::f4(dv[rr], 4 * cb);
       gk[0][rr] = ga * dd.x * lv[rr].x; gk[1][rr] = ga * dd.y * lv[rr].y;
       gk[2][rr] = ga * dd.z * lv[rr].z; gk[3][rr] = ga * dd.w * lv[rr].w;
       uk[0][rr] = ub * uv[rr].x; uk[1][rr] = ub * uv[rr].y; uk[2][rr] = ub * uv[rr].z; uk[3][rr] = ub * uv[rr].w;
@@ -1614,7 +1617,7 @@ __global__ __launch_bounds__(NT) void dense_grad_kernel(GradArgs a) {
 // halves it.  The bias gradient db[o] = hs * sum over the batch of G[.][o] rides along: the column tiles with
 // n0 == 0 sum the float G values they stage anyway (per thread over its rows, then over the eight row lanes in a
 // fixed order), which spares the separate pass over Dm and Lam.
-template <typename OT>
+template <typename OT, typename DT>
 __global__ __launch_bounds__(512) void dense_grad_wide_kernel(GradArgs a) {
   constexpr int BKR = 32, ST = BKR + Op<OT>::PAD, KSTEP = Op<OT>::KSTEP;
   constexpr int BM = 256, BN = 256, TM = 4, TN = 2, NTH = 512;
@@ -1630,9 +1633,9 @@ __global__ __launch_bounds__(512) void dense_grad_wide_kernel(GradArgs a) {
   const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
   const float* Up = a.U + (a.um.base + gi * a.um.stride) * a.E;
   const float* Lp = a.Lam + (a.lm.base + gi * a.lm.stride) * a.E;
-  const OT* Dp = reinterpret_cast<const OT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E;
+  const typename Fac<DT>::Ptr Dp = Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E);
   float* dWp = a.dW ? a.dW + (long long)gi * a.wsize : nullptr;
-  typedef typename DRaw<OT>::type DR;
+  typedef typename Fac<DT>::Raw DR;
   const bool want_db = a.db != nullptr && n0 == 0;
 
   const int rb = tid & 7, cb = tid >> 3;             // 4 batch rows x 4 columns per thread, of G and of U
@@ -1650,7 +1653,7 @@ __global__ __launch_bounds__(512) void dense_grad_wide_kernel(GradArgs a) {
       rmask |= rok ? (1u << rr) : 0u;
       const unsigned offa = (rok && aok) ? (unsigned)(row * q + m0 + 4 * cb) : 0u;
       const unsigned offb = (rok && bok) ? (unsigned)(row * q + n0 + 4 * cb) : 0u;
-      dv[rr] = ld_d4(Dp + offa);
+      dv[rr] = Fac<DT>::load(Dp, offa);
       lv[rr] = *reinterpret_cast<const float4*>(Lp + offa);
       uv[rr] = *reinterpret_cast<const float4*>(Up + offb);
     }
@@ -1661,7 +1664,7 @@ __global__ __launch_bounds__(512) void dense_grad_wide_kernel(GradArgs a) {
     for (int rr = 0; rr < 4; ++rr) {
       const bool rok = (rmask >> rr) & 1u;
       const float ga = (rok && aok) ? 1.0f : 0.0f, ub = (rok && bok) ? 1.0f : 0.0f;
-      const float4 dd = d4_to_f4(dv[rr]);
+      const float4 dd = Fac<DT>::f4(dv[rr], 4 * cb);
       gk[0][rr] = ga * dd.x * lv[rr].x; gk[1][rr] = ga * dd.y * lv[rr].y;
       gk[2][rr] = ga * dd.z * lv[rr].z; gk[3][rr] = ga * dd.w * lv[rr].w;
       uk[0][rr] = ub * uv[rr].x; uk[1][rr] = ub * uv[rr].y; uk[2][rr] = ub * uv[rr].z; uk[3][rr] = ub * uv[rr].w;
@@ -1737,14 +1740,19 @@ template <typename OT> constexpr size_t dense_grad_wide_smem() {
   constexpr size_t tiles = (size_t)512 * (32 + Op<OT>::PAD) * sizeof(OT), stage = (size_t)8 * 32 * 68 * sizeof(float);
   return tiles > stage ? tiles : stage;
 }
-template <typename OT>
-static hipError_t launch_dense_grad_wide(const GradArgs& a, unsigned blocks, hipStream_t s) {
+template <typename OT, typename DT>
+static hipError_t launch_dense_grad_wide_t(const GradArgs& a, unsigned blocks, hipStream_t s) {
   constexpr size_t smem = dense_grad_wide_smem<OT>();
   static LdsOptIn opt;
-  const hipError_t e = opt.raise(reinterpret_cast<const void*>(dense_grad_wide_kernel<OT>), smem);
+  const hipError_t e = opt.raise(reinterpret_cast<const void*>(dense_grad_wide_kernel<OT, DT>), smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dense_grad_wide_kernel<OT>), dim3(blocks), dim3(512), smem, s, a);
+  hipLaunchKernelGGL((dense_grad_wide_kernel<OT, DT>), dim3(blocks), dim3(512), smem, s, a);
   return hipGetLastError();
+}
+
+template <typename OT>
+static hipError_t launch_dense_grad_wide(const GradArgs& a, unsigned blocks, hipStream_t s) {
+  return a.dbits ? launch_dense_grad_wide_t<OT, Bit>(a, blocks, s) : launch_dense_grad_wide_t<OT, OT>(a, blocks, s);
 }
 
 // Parameter gradient (3x3 conv): dK[n][o][dy][dx][i] = hs * sum over pixels of G[b,y,x,o] *
@@ -1752,7 +1760,7 @@ static hipError_t launch_dense_grad_wide(const GradArgs& a, unsigned blocks, hip
 // a C x C output tile (C <= 64), contraction over all B*H*W pixels in slabs of 32, operands
 // transposed in registers as in the dense kernel.  Every tap re-reads the whole layer, so this form is
 // kept only for image rows too wide for the all-taps kernel below.
-template <typename OT>
+template <typename OT, typename DT>
 __global__ __launch_bounds__(NT) void conv_grad_tap_kernel(GradArgs a) {
   constexpr int BKR = 32, ST = BKR + Op<OT>::PAD, KSTEP = Op<OT>::KSTEP;
   __shared__ __attribute__((aligned(16))) OT As[64 * ST];
@@ -1764,9 +1772,9 @@ __global__ __launch_bounds__(NT) void conv_grad_tap_kernel(GradArgs a) {
   const int dy = tap / 3 - 1, dx = tap % 3 - 1;
   const float* Up = a.U + (a.um.base + gi * a.um.stride) * a.E;
   const float* Lp = a.Lam + (a.lm.base + gi * a.lm.stride) * a.E;
-  const OT* Dp = reinterpret_cast<const OT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E;
+  const typename Fac<DT>::Ptr Dp = Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E);
   float* dKp = a.dW + (long long)gi * a.wsize;
-  typedef typename DRaw<OT>::type DR;
+  typedef typename Fac<DT>::Raw DR;
 
   const int rb = tid & 7, cb = (tid >> 3) & 15;      // 4 pixels x 4 channels per thread; threads 128.. idle
   const bool cok = tid < 128 && 4 * cb < C;
@@ -1785,7 +1793,7 @@ __global__ __launch_bounds__(NT) void conv_grad_tap_kernel(GradArgs a) {
       umask |= sok ? (1u << rr) : 0u;
       const unsigned og = pok ? (unsigned)(px * C + 4 * cb) : 0u;
       const unsigned ou = sok ? (unsigned)((px + dy * Wd + dx) * C + 4 * cb) : 0u;
-      dv[rr] = ld_d4(Dp + og);
+      dv[rr] = Fac<DT>::load(Dp, og);
       lv[rr] = *reinterpret_cast<const float4*>(Lp + og);
       uv[rr] = *reinterpret_cast<const float4*>(Up + ou);
     }
@@ -1796,7 +1804,7 @@ __global__ __launch_bounds__(NT) void conv_grad_tap_kernel(GradArgs a) {
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const float ga = ((gmask >> rr) & 1u) ? 1.0f : 0.0f, ub = ((umask >> rr) & 1u) ? 1.0f : 0.0f;
-      const float4 dd = d4_to_f4(dv[rr]);
+      const float4 dd = Fac<DT>::f4(dv[rr], 4 * cb);
       gk[0][rr] = ga * dd.x * lv[rr].x; gk[1][rr] = ga * dd.y * lv[rr].y;
       gk[2][rr] = ga * dd.z * lv[rr].z; gk[3][rr] = ga * dd.w * lv[rr].w;
       uk[0][rr] = ub * uv[rr].x; uk[1][rr] = ub * uv[rr].y; uk[2][rr] = ub * uv[rr].z; uk[3][rr] = ub * uv[rr].w;
@@ -1849,7 +1857,7 @@ __global__ __launch_bounds__(NT) void conv_grad_tap_kernel(GradArgs a) {
 // NWV wavefronts: 4, or 8 for more than 32 channels -- there the accumulators of four wavefronts (2 x 5 blocks
 // each) leave room for one workgroup per CU anyway, and with eight the transposing stores of a slab, which
 // take longer than its matrix instructions, are spread over twice the threads.
-template <typename OT, int TM, int TN, bool N16 = false, int NWV = 4>
+template <typename OT, typename DT, int TM, int TN, bool N16 = false, int NWV = 4>
 __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
   constexpr int NTH = 64 * NWV;
   constexpr int UB = NWV == 8 ? 2 : 3;                  // 4x4 blocks of the U patch per thread, at most
@@ -1866,8 +1874,8 @@ __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
   const int gi = L / a.gchunks, ch = L % a.gchunks;
   const float* Up = a.U + (a.um.base + gi * a.um.stride) * a.E;
   const float* Lp = a.Lam + (a.lm.base + gi * a.lm.stride) * a.E;
-  const OT* Dp = reinterpret_cast<const OT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E;
-  typedef typename DRaw<OT>::type DR;
+  const typename Fac<DT>::Ptr Dp = Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E);
+  typedef typename Fac<DT>::Raw DR;
 
   {
     const int n16 = (int)(((size_t)3 * C * PU + (size_t)C * PG) * sizeof(OT) / 16);
@@ -1908,7 +1916,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
         const bool ok = rok && x < Wd;
         gmask |= ok ? (1u << j) : 0u;
         const unsigned off = ok ? (unsigned)((((long long)b * H + y) * Wd + x) * C + 4 * g_cg) : 0u;
-        dv[j] = ld_d4(Dp + off);
+        dv[j] = Fac<DT>::load(Dp, off);
         lv[j] = *reinterpret_cast<const float4*>(Lp + off);
       }
     }
@@ -1934,7 +1942,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const bool ok = (gmask >> j) & 1u;
-        const float4 dd = d4_to_f4(dv[j]);
+        const float4 dd = Fac<DT>::f4(dv[j], 4 * g_cg);
         gk[0][j] = ok ? dd.x * lv[j].x : 0.0f; gk[1][j] = ok ? dd.y * lv[j].y : 0.0f;
         gk[2][j] = ok ? dd.z * lv[j].z : 0.0f; gk[3][j] = ok ? dd.w * lv[j].w : 0.0f;
       }
@@ -2103,19 +2111,19 @@ __global__ __launch_bounds__(NT) void conv_grad_reduce_kernel(const float* parti
 
 // db[n][o] = hs * sum over rows of Dm .* Lam (fixed order).  64 columns per workgroup: 16 lanes of
 // float4 across, 16 row lanes down, then a fixed-order LDS reduction over the row lanes.
-template <typename OT>
+template <typename OT, typename DT>
 __global__ __launch_bounds__(NT) void bias_grad_kernel(GradArgs a) {
   __shared__ float4 part[16][17];
   const int gi = blockIdx.y;
   const float* Lp = a.Lam + (a.lm.base + gi * a.lm.stride) * a.E;
-  const OT* Dp = reinterpret_cast<const OT*>(a.Dm) + (a.dm.base + gi * a.dm.stride) * a.E;
+  const typename Fac<DT>::Ptr Dp = Fac<DT>::at(a.Dm, (a.dm.base + gi * a.dm.stride) * a.E);
   const int cx = threadIdx.x & 15, ry = threadIdx.x >> 4;
   const int col = blockIdx.x * 64 + 4 * cx;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (col < a.Nf) {
     for (int r = ry; r < a.M; r += 16) {
       const unsigned off = (unsigned)(r * a.Nf + col);
-      const float4 d = d4_to_f4(ld_d4(Dp + off)), l = *reinterpret_cast<const float4*>(Lp + off);
+      const float4 d = Fac<DT>::f4(Fac<DT>::load(Dp, off), 4 * cx), l = *reinterpret_cast<const float4*>(Lp + off);
       s.x += d.x * l.x; s.y += d.y * l.y; s.z += d.z * l.z; s.w += d.w * l.w;
     }
   }
@@ -2180,19 +2188,29 @@ size_t conv_grad_partial_bytes(int B, int Himg, int Wimg, int C, int dtype, int 
   if (!gm.ok || gm.chunks <= 1) return 0;
   return (size_t)gm.chunks * layers * (9 * C * C + C) * sizeof(float);
 }
+// a gradient kernel by the types of operands and act' factors
+#define MGRIT_BY_FACTORS(KERNEL, GRID)                                                                                    \
+  if (a.dbits) {                                                                                                          \
+    if (dtype == 0) hipLaunchKernelGGL((KERNEL<float, Bit>), GRID, dim3(NT), 0, s, a);                                    \
+    else            hipLaunchKernelGGL((KERNEL<__bf16, Bit>), GRID, dim3(NT), 0, s, a);                                   \
+  } else {                                                                                                                \
+    if (dtype == 0) hipLaunchKernelGGL((KERNEL<float, float>), GRID, dim3(NT), 0, s, a);                                  \
+    else            hipLaunchKernelGGL((KERNEL<__bf16, __bf16>), GRID, dim3(NT), 0, s, a);                                \
+  }
 static void launch_bias_grad(const GradArgs& a, int dtype, int groups, hipStream_t s) {
   const dim3 grid((a.Nf + 63) / 64, groups);
-  if (dtype == 0) hipLaunchKernelGGL((bias_grad_kernel<float>), grid, dim3(NT), 0, s, a);
-  else            hipLaunchKernelGGL((bias_grad_kernel<__bf16>), grid, dim3(NT), 0, s, a);
+  MGRIT_BY_FACTORS(bias_grad_kernel, grid)
 }
-template <typename OT, int TM, int TN, bool N16 = false, int NWV = 4>
+template <typename OT, int TM, int TN, bool N16 = false, int NWV = 4, typename DT = OT>
 static hipError_t launch_conv_grad(const GradArgs& a, unsigned blocks, size_t smem, hipStream_t s) {
+  if constexpr (std::is_same<DT, OT>::value)
+    if (a.dbits) return launch_conv_grad<OT, TM, TN, N16, NWV, Bit>(a, blocks, smem, s);
   if (smem > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_grad_kernel<OT, TM, TN, N16, NWV>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_grad_kernel<OT, DT, TM, TN, N16, NWV>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((conv_grad_kernel<OT, TM, TN, N16, NWV>), dim3(blocks), dim3(64 * NWV), smem, s, a);
+  hipLaunchKernelGGL((conv_grad_kernel<OT, DT, TM, TN, N16, NWV>), dim3(blocks), dim3(64 * NWV), smem, s, a);
   return hipGetLastError();
 }
 
@@ -2220,8 +2238,7 @@ hipError_t launch_grad(const GradArgs& a_in, int layer_kind, int dtype, int grou
     a.tiles = ((a.Nf + 127) / 128) * ((a.Nf + 127) / 128);
     if (a.dW || a.db) {                                    // the bias gradient, if wanted, in the same launch
       dim3 grid((unsigned)a.tiles * (unsigned)groups);
-      if (dtype == 0) hipLaunchKernelGGL((dense_grad_kernel<float>), grid, dim3(NT), 0, s, a);
-      else            hipLaunchKernelGGL((dense_grad_kernel<__bf16>), grid, dim3(NT), 0, s, a);
+      MGRIT_BY_FACTORS(dense_grad_kernel, grid)
       db_done = true;
     }
   } else if (a.dW || a.db) {
@@ -2230,8 +2247,7 @@ hipError_t launch_grad(const GradArgs& a_in, int layer_kind, int dtype, int grou
       a.tiles = 9;
       if (a.dW) {
         dim3 grid(9u * (unsigned)groups);
-        if (dtype == 0) hipLaunchKernelGGL((conv_grad_tap_kernel<float>), grid, dim3(NT), 0, s, a);
-        else            hipLaunchKernelGGL((conv_grad_tap_kernel<__bf16>), grid, dim3(NT), 0, s, a);
+        MGRIT_BY_FACTORS(conv_grad_tap_kernel, grid)
       }
       if (a.db) launch_bias_grad(a, dtype, groups, s);
     } else {                                               // all taps and the bias gradient in one kernel
@@ -2273,7 +2289,7 @@ hipError_t launch_grad(const GradArgs& a_in, int layer_kind, int dtype, int grou
   if (a.db && layer_kind == 0 && !db_done) launch_bias_grad(a, dtype, groups, s);
   const hipError_t e = hipGetLastError();
   // algorithmic bytes of a layer's gradient: U, Lam and the act' factors in, dW and db out
-  const double ges = dtype == 0 ? 4.0 : 2.0;
+  const double ges = a.dbits ? 0.125 : dtype == 0 ? 4.0 : 2.0;
   trace_after(s, TRACE_GRAD, groups,
               (double)groups * ((8.0 + ges) * (double)a.E + (a.dW ? 4.0 * (double)a.wsize : 0.0) + (a.db ? 4.0 * a.Nf : 0.0)));
   return e;

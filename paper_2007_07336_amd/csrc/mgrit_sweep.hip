@@ -2,8 +2,6 @@
 // coarse interval and keeps their state on chip from step to step.
 #include "mgrit_device.h"
 
-#include <type_traits>
-
 namespace mgrit {
 
 // ------------------------------------------------------------------------------------------
@@ -133,11 +131,17 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* Wl, float* red,
   for (int k = 1; k <= n; ++k) {
     const long long layer = a.lb + ci * a.ls + (long long)(k - 1) * a.lk;
     const float* W = reinterpret_cast<const float*>(a.W) + layer * a.wsize;
-    const float* Dm = reinterpret_cast<const float*>(a.Dm);
 #pragma unroll
     for (int i = 0; i < U; ++i)
-      if (mine(i))
-        *reinterpret_cast<floatx4*>(X + pixel(i) * PX + chan(i)) = ACT == ACT_IDENT ? st[i] * *reinterpret_cast<const floatx4*>(at(Dm, layer) + elem(i)) : st[i];
+      if (mine(i)) {
+        floatx4 v = st[i];
+        if constexpr (ACT == ACT_IDENT || ACT == ACT_MASK) {
+          typedef Fac<typename std::conditional<ACT == ACT_MASK, Bit, float>::type> F;
+          const float4 d = F::f4(F::load(F::at(a.Dm, layer * a.E + first), elem(i)), elem(i));
+          v *= floatx4{d.x, d.y, d.z, d.w};
+        }
+        *reinterpret_cast<floatx4*>(X + pixel(i) * PX + chan(i)) = v;
+      }
     if (CONV)                                                       // a layer's weights, 9 C^2 floats, to LDS
       for (int e = 4 * tid; e < 9 * C * C; e += 4 * NTH) *reinterpret_cast<floatx4*>(Wl + e) = *reinterpret_cast<const floatx4*>(W + e);
     __syncthreads();
@@ -224,7 +228,8 @@ static_assert(conv_sweep_wbytes<3, 16, false>() >= 9 * 16 * 16 * 4 && conv_sweep
 // TAU: the coarse right-hand side, single steps (its epilogue beside the others would cost the sweep registers)
 template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
 __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
-  constexpr bool HD = ACT == ACT_IDENT;                         // the adjoint: act' factors, no bias
+  constexpr bool HD = ACT == ACT_IDENT || ACT == ACT_MASK;      // the adjoint: act' factors, no bias
+  constexpr bool MASK = ACT == ACT_MASK;                        // ... as bits
   constexpr int NTH = 64 * NWV;
   constexpr int CB = CP / 16, PPT = CP / 8, NPC = 9 * PPT, S = conv_sweep_ksteps<NP, CP>();
   constexpr int PLB = CP * 2, PXB = NP * PLB;                   // LDS bytes of one part of a pixel, of a pixel
@@ -233,16 +238,18 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   constexpr int WS = RING ? 2 : S;                              // k steps loaded together: a tap or the whole layer
   constexpr int WU = (WS * 4 * CP + NTH - 1) / NTH;             // units (8 input channels of one output channel) per thread
   constexpr int WR = NP == 3 ? 2 : 1;                           // 16-byte loads per unit
-  // a layer's weight fragments fit in registers (beside the factors of the adjoint not without spills, except for bf16 and 16
+  // a layer's weight fragments fit in registers (beside factors stored as values not without spills, except for bf16 and 16
   // channels: 1445 us for 64 float layers of 16 channels, 1385 with fragments read from LDS; a step of 32 channels bf16 on
-  // 32 x 32 pixels 11.1 -> 9.2 us)
-  constexpr bool HOLD = (CP == 16 && !(HD && NP == 3)) || (CP == 32 && NP == 1 && !HD);
-  // act' factors requested at the start of a step (wider layers: only when it is done, for they would be spilled: a step of 48
-  // channels on 28 x 28 pixels 17.8 -> 14.1 us, of 64 on 16 x 32 14.4 -> 12.8)
-  constexpr bool DEARLY = CP <= 32;
+  // 32 x 32 pixels 11.1 -> 9.2 us.  Beside bits they do: 64 float layers of 16 channels, adjoint and gradient, 1370 -> 1304 us)
+  constexpr bool HOLD = (CP == 16 && !(HD && !MASK && NP == 3)) || (CP == 32 && NP == 1 && (!HD || MASK));
+  // act' factors requested at the start of a step (values of wider layers: only when it is done, for they would be spilled: a step
+  // of 48 channels on 28 x 28 pixels 17.8 -> 14.1 us, of 64 on 16 x 32 14.4 -> 12.8).  Bits instead of bf16 values, requested
+  // early: 512 layers of 64 channels on 32 x 32 pixels, 32 images, adjoint and gradient, 17.1 -> 15.1 ms
+  constexpr bool DEARLY = CP <= 32 || MASK;
   static_assert(NBW % GB == 0 && (!RING || (CP == 64 && NP == 1)), "instances");
   typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
-  typedef typename DRaw<WT>::type DR;
+  typedef Fac<WT> F;
+  typedef typename F::Raw DR;
   extern __shared__ __attribute__((aligned(16))) u8 smem[];
   __shared__ float red[NWV];
   __shared__ int repeat;                                        // float: a state of the chain is not finite
@@ -366,14 +373,28 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   load_bias(1);
 
   // ---- operand of a step: act' .* state, to LDS (a pixel's padded channels are zero)
-  DR dr[HD ? NBW : 1][HD ? CB : 1];
+  // (bits: all of a pixel's channels in one load of up to eight bytes, wherever they start; it may reach into the next pixel,
+  // and behind the last layer's factors into the cache's unused part.  Up to 32 channels a lane loads those of its own pixels;
+  // above, the four lanes of a pixel load those of a quarter of the blocks each and exchange them when the operand is written:
+  // four registers from the start of a step on, not sixteen)
+  constexpr bool DSHARE = CB > 2;
+  constexpr int NDB = DSHARE ? NBW / 4 : NBW;
+  typedef typename std::conditional<CB == 1, unsigned short, typename std::conditional<CB == 2, unsigned, u32x2>::type>::type BW;
+  struct __attribute__((packed)) PixelBits { BW w; };
+  BW db[MASK ? NDB : 1];
+  DR dr[HD && !MASK ? NBW : 1][HD && !MASK ? CB : 1];
   auto load_d = [&](int k) __attribute__((always_inline)) {
-    if constexpr (HD) {
-      const WT* dp = reinterpret_cast<const WT*>(a.Dm) + layer_of(k) * a.E + img_off;
+    if constexpr (MASK) {
+      const u8* dp = Fac<Bit>::at(a.Dm, layer_of(k) * a.E + img_off);
+#pragma unroll
+      for (int i = 0; i < NDB; ++i)
+        db[i] = reinterpret_cast<const PixelBits*>(dp + (unsigned)(min(px(DSHARE ? NDB * kq + i : i), npx - 1) * C) / 8u)->w;
+    } else if constexpr (HD) {
+      const typename F::Ptr dp = F::at(a.Dm, layer_of(k) * a.E + img_off);
 #pragma unroll
       for (int b = 0; b < NBW; ++b)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) dr[b][cb] = ld_d4(dp + off(b, cb));
+        for (int cb = 0; cb < CB; ++cb) dr[b][cb] = F::load(dp, off(b, cb));
     }
   };
   auto piece = [&](int p, int pc) __attribute__((always_inline)) { return (unsigned)(p * PXB + ((pc ^ conv_sweep_swz<NP, CP>(p)) << 4)); };
@@ -381,11 +402,20 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
 #pragma unroll
     for (int b = 0; b < NBW; ++b) {
       const int p = px(b);
+      unsigned bits[2];                                             // channels 32 i + 4 kq and on
+      if constexpr (MASK && DSHARE) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) bits[i] = (unsigned)__builtin_amdgcn_ds_bpermute(4 * (c + 16 * (b / NDB)), (int)db[b % NDB][i]) >> (4 * kq);
+      } else if constexpr (MASK) bits[0] = (unsigned)db[b] >> (4 * kq);
       if (p < npx) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
           float4 v = make_float4(st[b][cb][0], st[b][cb][1], st[b][cb][2], st[b][cb][3]);
-          if constexpr (HD) { const float4 d = d4_to_f4(dr[b][cb]); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
+          if constexpr (MASK) {
+            const unsigned w = bits[cb >> 1];
+            const int at = 16 * (cb & 1);
+            v.x *= bit_factor(w, at); v.y *= bit_factor(w, at + 1); v.z *= bit_factor(w, at + 2); v.w *= bit_factor(w, at + 3);
+          } else if constexpr (HD) { const float4 d = F::f4(dr[b][cb], 0); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
           if (cb == CB - 1 && !last_ok) v = make_float4(0.f, 0.f, 0.f, 0.f);
           // (the permutation of a pixel's pieces repeats every 16 pixels at most: it depends on the lane alone)
           u8* q = P + p * PXB + (((2 * cb + (kq >> 1)) ^ conv_sweep_swz<NP, CP>(cpx)) << 4) + (kq & 1) * 8;
@@ -722,7 +752,7 @@ hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
   SweepArgs a = a_in;
   if (a.nchains <= 0) return hipSuccess;
   if (a.tau && (a.nsteps != 1 || a.nlast != 1 || !a.Z)) return hipErrorInvalidValue;
-  if ((a.act == ACT_IDENT) != (a.Dm != nullptr)) return hipErrorInvalidValue;     // the adjoint's steps, and only they
+  if ((a.act == ACT_IDENT || a.act == ACT_MASK) != (a.Dm != nullptr)) return hipErrorInvalidValue;     // the adjoint's steps, and only they
   if (a.M < 1 || !conv_sweep_supported(a.Himg, a.Wimg, a.C, dtype)) return hipErrorInvalidValue;
   a.ipw = conv_sweep_images(a.Himg, a.Wimg, a.C, dtype, a.M, a.nchains);
   ConvSweepShape sh;
@@ -734,6 +764,7 @@ hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
   if (sh.np == NP_ && sh.cp == CP_ && sh.nwv == NWV_ && sh.nbw == NBW_ && sh.ring == RING_ && (a.tau != 0) == TAU_)    \
     e = a.act == ACT_TANH   ? launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_TANH, TAU_>(a, blocks, sh.smem, s)  \
         : a.act == ACT_RELU ? launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_RELU, TAU_>(a, blocks, sh.smem, s)  \
+        : a.act == ACT_MASK ? launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_MASK, TAU_>(a, blocks, sh.smem, s)  \
                             : launch_conv_sweep_t<NP_, CP_, NWV_, NBW_, RING_, ACT_IDENT, TAU_>(a, blocks, sh.smem, s);
   MGRIT_CS(1, 16, 8, 8, false, false) MGRIT_CS(1, 32, 8, 8, false, false) MGRIT_CS(1, 48, 8, 8, false, false)
   MGRIT_CS(1, 64, 8, 4, false, false) MGRIT_CS(1, 64, 8, 8, true, false)
@@ -746,7 +777,7 @@ hipError_t launch_conv_sweep(const SweepArgs& a_in, int dtype, hipStream_t s) {
   // state; the start state once per chain
   const double es = dtype == 0 ? 4.0 : 2.0, E4 = 4.0 * (double)a.E;
   const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
-  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.C : 0.0) + (a.Dm ? es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
+  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.C : 0.0) + (a.Dm ? a.act == ACT_MASK ? 0.125 : es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
                      (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
   trace_after(s, TRACE_CONV_SWEEP_F32, a.units,
               steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0)));
@@ -781,12 +812,13 @@ constexpr int DENSE_SWEEP_ZEROS = 512;                                      // b
 template <int NP, int NWV, int FBW, int RB, int ACT, bool WN>
 __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   static_assert(4 * (32 * FBW + 32) + 8 <= DENSE_SWEEP_ZEROS && 64 * NWV >= DENSE_SWEEP_ZEROS / 4, "one lane's reads; its writers");
-  constexpr bool HD = ACT == ACT_IDENT;                             // the adjoint: act' factors, no bias
+  constexpr bool HD = ACT == ACT_IDENT || ACT == ACT_MASK;          // the adjoint: act' factors, no bias
   constexpr int NTH = 64 * NWV, R = 16 * RB;
   constexpr int STG = dense_sweep_stage<NP, FBW, WN>();
   constexpr int NL = NP == 3 ? 2 * FBW : FBW;                       // 16-byte loads of a k step per lane
   typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
-  typedef typename DRaw<WT>::type DR;
+  typedef Fac<typename std::conditional<ACT == ACT_MASK, Bit, WT>::type> F;
+  typedef typename F::Raw DR;
   typedef u32x4 LW;
   extern __shared__ __attribute__((aligned(16))) u8 smem[];
   __shared__ float red[NWV];
@@ -883,11 +915,11 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
   DR dr[RB][FBW];
   auto load_d = [&](int k) __attribute__((always_inline)) {
     if constexpr (HD) {
-      const WT* dp = reinterpret_cast<const WT*>(a.Dm) + layer_of(k) * a.E + sl_off;
+      const typename F::Ptr dp = F::at(a.Dm, layer_of(k) * a.E + sl_off);
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int j = 0; j < FBW; ++j) dr[rb][j] = ld_d4(dp + off(rb, j));
+        for (int j = 0; j < FBW; ++j) dr[rb][j] = F::load(dp, off(rb, j));
     }
   };
   auto write_operand = [&]() __attribute__((always_inline)) {
@@ -897,7 +929,7 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
       for (int j = 0; j < FBW; ++j)
         if (feat(j) < KP) {
           float4 v = make_float4(st[rb][j][0], st[rb][j][1], st[rb][j][2], st[rb][j][3]);
-          if constexpr (HD) { const float4 d = d4_to_f4(dr[rb][j]); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
+          if constexpr (HD) { const float4 d = F::f4(dr[rb][j], 4 * kq); v.x *= d.x; v.y *= d.y; v.z *= d.z; v.w *= d.w; }
           if (feat(j) >= q) v = make_float4(0.f, 0.f, 0.f, 0.f);
           u8* p = A + (16 * rb + c) * OP + feat(j) * 2;
           if constexpr (NP == 1) {
@@ -1086,7 +1118,7 @@ int sweep_blocks(int M, int nchains) { const int r = sweep_rows(M, nchains); ret
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
   if (a.nchains <= 0) return hipSuccess;
   if (a.M < 1 || !sweep_supported(a.q)) return hipErrorInvalidValue;
-  if ((a.act == ACT_IDENT) != (a.Dm != nullptr) || (a.Dm == nullptr && (a.wn || !a.bias))) return hipErrorInvalidValue;  // the adjoint's steps, and only they
+  if ((a.act == ACT_IDENT || a.act == ACT_MASK) != (a.Dm != nullptr) || (a.Dm == nullptr && (a.wn || !a.bias))) return hipErrorInvalidValue;  // the adjoint's steps, and only they
   if (a.tau && (a.nsteps != 1 || a.nlast != 1 || !a.Z)) return hipErrorInvalidValue;
   const int rows = sweep_rows(a.M, a.nchains);
   const unsigned blocks = (unsigned)sweep_blocks(a.M, a.nchains);
@@ -1095,6 +1127,8 @@ hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
 #define MGRIT_DS_RB(NP_, NWV_, FBW_, RB_)                                                                     \
   e = a.act == ACT_TANH   ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_TANH, false>(a, blocks, s)         \
       : a.act == ACT_RELU ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_RELU, false>(a, blocks, s)         \
+      : a.act == ACT_MASK ? (a.wn ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_MASK, true>(a, blocks, s)  \
+                                  : launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_MASK, false>(a, blocks, s)) \
       : a.wn              ? launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_IDENT, true>(a, blocks, s)         \
                           : launch_dense_sweep_t<NP_, NWV_, FBW_, RB_, ACT_IDENT, false>(a, blocks, s)
 #define MGRIT_DS(NP_, NWV_, FBW_) { if (rows == 32) MGRIT_DS_RB(NP_, NWV_, FBW_, 2); else MGRIT_DS_RB(NP_, NWV_, FBW_, 1); }
@@ -1105,7 +1139,7 @@ hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
 #undef MGRIT_DS_RB
   const double es = dtype == 0 ? 4.0 : 2.0, E4 = 4.0 * (double)a.E;
   const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
-  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.q : 0.0) + (a.Dm ? es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
+  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.q : 0.0) + (a.Dm ? a.act == ACT_MASK ? 0.125 : es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
                      (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
   trace_after(s, dtype == 0 ? TRACE_SWEEP_F32 : TRACE_SWEEP_BF16, a.units,
               steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0)));
