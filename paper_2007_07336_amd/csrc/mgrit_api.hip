@@ -180,6 +180,13 @@ struct Solver {
   int act;
   float* partial;
   double* hist_dev;
+  // Narrow dense stacks (wave): sweeps that follow one another are collected and launched together (flush).
+  bool wave = false;
+  WaveProgram prog;
+  long long prog_units = 0;
+  double prog_bytes = 0.0;
+  bool prog_by_slice = false;          // it has norm partials laid out for one workgroup per slice
+  int late_norms = 0;                  // > 0: norm partials per cycle that wait in `partial`, cycle by cycle, for one summation
   hipError_t err = hipSuccess;
 
   void chk(hipError_t e) { if (err == hipSuccess && e != hipSuccess) err = e; }
@@ -248,6 +255,7 @@ struct Solver {
     return nb;
   }
   void launch(const StepArgs& a, int groups) {
+    flush();
     if (err != hipSuccess) return;
     if (!pl.fcP) { chk(launch_step(a, p->layer, p->dtype, groups, s)); return; }
     // mixed stack: the convolution kernel passes over the fully connected groups, a dense launch serves them
@@ -319,9 +327,48 @@ struct Solver {
     const PtMap unit = pm(l, 0, 1);                                 // storage index of sweep point js = base + js * stride
     a.X = X[l]; a.xb = unit.base; a.xs = unit.stride * stride; a.xk = unit.stride;
   }
+  // A sweep joins the ones before it in one launch if a slice's workgroup is done with it before a launch of its own would be:
+  // us, measured -- a step takes 0.25 and, with many chains on one CU, 0.08 for each of them; a dependent launch 4 more, spread
+  // over the CUs 0.3 a step.
+  bool joins(const SweepArgs& a) const {
+    const double step = 0.08 * a.nchains > 0.25 * wave_workgroups(a.nchains) ? 0.08 * a.nchains : 0.25 * wave_workgroups(a.nchains);
+    return wave && 0.5 + step * a.nsteps <= 4.0 + 0.3 * a.nsteps;
+  }
+  void flush() {
+    if (prog.nops == 0) return;
+    // (a sweep that stayed alone gets all the workgroups it can use)
+    const int per = prog.nops == 1 && !prog_by_slice ? wave_workgroups(prog.op[0].nchains) : 1;
+    if (err == hipSuccess) chk(launch_wave(prog, per, p->dtype, prog_units, prog_bytes, s));
+    prog.nops = 0; prog_units = 0; prog_bytes = 0.0; prog_by_slice = false;
+  }
+  void collect(const SweepArgs& a) {
+    const bool join = joins(a);
+    if (!join || prog.nops == WAVE_OPS) flush();
+    prog.M = a.M; prog.q = a.q; prog.act = a.act; prog.wn = a.wn;
+    prog.W = a.W; prog.bias = a.bias; prog.Dm = a.Dm; prog.E = a.E; prog.wsize = a.wsize;
+    WaveOp& o = prog.op[prog.nops++];
+    o.S = a.S; o.X = a.X; o.Y = a.Y; o.Z = a.Z; o.Ref = a.Ref; o.G = a.G; o.norm_partial = a.norm_partial;
+    o.sb = (int)a.sm.base; o.ss = (int)a.sm.stride;
+    o.xb = (int)a.xb; o.xs = (int)a.xs; o.xk = (int)a.xk; o.store0 = a.store0;
+    o.yb = (int)a.yb; o.ys = (int)a.ys; o.kmid = a.kmid;
+    o.zb = (int)a.zb; o.zs = (int)a.zs; o.zfirst = (int)a.zfirst; o.tau = a.tau;
+    o.rb = (int)a.rm.base; o.rs = (int)a.rm.stride; o.gb = (int)a.gb; o.gs = (int)a.gs;
+    o.lb = (int)a.lb; o.ls = (int)a.ls; o.lk = (int)a.lk;
+    o.nsteps = a.nsteps; o.nlast = a.nlast; o.nchains = a.nchains; o.hs = a.hs;
+    prog_by_slice |= join && a.norm_partial;
+    prog_units += a.units;
+    prog_bytes += sweep_bytes(a, p->dtype);
+    if (!join) flush();
+  }
+  // workgroups (= norm partials) of the launch of a
+  int march_blocks(const SweepArgs& a) const {
+    if (wave) return wave_slices(a.M) * (joins(a) ? 1 : wave_workgroups(a.nchains));
+    return p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_blocks(a, p->dtype) : sweep_blocks(a.M, a.nchains);
+  }
   void launch_march(SweepArgs& a, long long units) {
     a.units = units;
     if (err != hipSuccess) return;
+    if (wave) { collect(a); return; }
     chk(p->layer == MGRIT_LAYER_CONV3X3 ? launch_conv_sweep(a, p->dtype, s) : launch_sweep(a, p->dtype, s));
   }
   // Where the current values of a level's C-points 0, m, 2m, .. are: point js = j m at p[m.base + j m.stride].
@@ -352,6 +399,7 @@ struct Solver {
       launch_march(a, pl.Nl[l] - Nc);
       return;
     }
+    flush();
     chk(launch_copy_points(X[l], pm(l, 0, p->m), X[l + 1], PtMap{0, 1}, pl.E, pl.Nl[l + 1] + 1, s));
     f_relax(l, CPoints{X[l + 1], PtMap{0, 1}});
   }
@@ -404,6 +452,10 @@ struct Solver {
     plain_rhs = false;
   }
 
+  double norm_scale() const {          // of the C-point residual of the fine level
+    return p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(pl.Nl[1] + 1) * (double)pl.E) : 1.0;
+  }
+
   // One visit of level l, up to the new values of its C-points in X[l + 1] (of all its points on the coarsest level).
   // c: the C-points' current values (unused on the coarsest level).
   void cycle(int l, int iter, CPoints c) {
@@ -442,9 +494,12 @@ struct Solver {
       // (a slice of 16 rows may be less than a lockstep tile, which `partial` is sized for; a state of every chain that nothing
       // needs at this point holds more: the coarse solve's, or the residual's where only FCF-relaxation uses it)
       sums = p->relax == MGRIT_RELAX_FCF ? X[l + 1] + pl.E : R[l];
+      if (norm && iter == 0 && p->tol <= 0.0f && joins(a) && (size_t)wave_slices(pl.M) * p->max_iter <= pl.n_partial)
+        late_norms = wave_slices(pl.M);
+      if (norm && late_norms) sums = partial + (size_t)iter * late_norms;
       if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = sums; }
+      blocks = march_blocks(a);
       launch_march(a, Nc);
-      blocks = p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_blocks(a, p->dtype) : sweep_blocks(a.M, Nc);
     } else {
       StepArgs a = base_args(l + 1, 1, 1);
       a.X = c.p; a.xm = c.m;
@@ -455,9 +510,9 @@ struct Solver {
       launch(a, Nc);
       blocks = launch_blocks(a, Nc);
     }
-    if (norm) {
-      const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(Nc + 1) * (double)pl.E) : 1.0;
-      chk(launch_norm_final(sums, blocks, scale, hist_dev + iter, s));
+    if (norm && !late_norms) {
+      flush();
+      chk(launch_norm_final(sums, blocks, norm_scale(), hist_dev + iter, 1, s));
     }
     cycle(l + 1, iter, CPoints{c.p, PtMap{c.m.base, c.m.stride * m}});   // V_H, Alg. 1 steps 3 to 5
     if (l + 1 < pl.L - 1) close(l + 1);
@@ -476,6 +531,8 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
   const Plan& pl = sv.pl;
   const int m = p->m;
   // the known value, in every array that holds sweep point 0, and the initial guess of the C-points
+  sv.wave = p->layer == MGRIT_LAYER_DENSE && !pl.fcP && wave_supported(p->q) && sv.use_march(0) && sv.use_march(pl.L - 1);
+  sv.want_norm = p->tol > 0.0f || resnorm_hist;
   float* zero_pt[2 * MGRIT_MAX_LEVELS];
   int nz = 0;
   // MGRIT_INIT_COPY: the known value everywhere, from the coarsest level's copy of it (`first` may be a row of the caller's
@@ -491,19 +548,32 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
       zero_pt[nz++] = sv.X[0] + c.m.base * pl.E;
     }
   }
-  sv.chk(launch_spread_state(zero_pt, nz, first, pl.E, sv.s));
-  if (pl.L > 1 && p->init == MGRIT_INIT_ZERO)
+  if (sv.wave) {
+    for (int i = 0; i < nz; ++i) {                              // chains of no steps
+      SweepArgs a = sv.sweep_args(0, 0);
+      a.G = nullptr;
+      a.S = first; a.sm = PtMap{0, 0};
+      a.X = zero_pt[i]; a.store0 = 1;
+      a.nchains = 1;
+      sv.launch_march(a, 0);
+    }
+  } else {
+    sv.chk(launch_spread_state(zero_pt, nz, first, pl.E, sv.s));
+  }
+  if (pl.L > 1 && p->init == MGRIT_INIT_ZERO) {
+    sv.flush();
     sv.chk(launch_zero_points(sv.X[0], sv.pm(0, m, m), pl.E, pl.Nl[1], sv.s));
+  }
   if (pl.L > 1 && p->init == MGRIT_INIT_NESTED) {
     sv.nested_start();
     c = Solver::CPoints{sv.X[1], PtMap{0, 1}};
   }
-  sv.want_norm = p->tol > 0.0f || resnorm_hist;
 
   int iters = 0;
   int rc = MGRIT_OK;
   if (pl.L == 1) {
     sv.cycle(0, 0, c);
+    sv.flush();
     iters = 1;
     if (resnorm_hist) resnorm_hist[0] = 0.0;
     if (sv.err == hipSuccess && (resnorm_hist || iters_done)) sv.chk(hipStreamSynchronize(sv.s));
@@ -514,6 +584,7 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
       ++iters;
       if (p->tol > 0.0f) {
         double v = 0.0;
+        sv.flush();
         sv.chk(hipMemcpyAsync(&v, sv.hist_dev + k, sizeof(double), hipMemcpyDeviceToHost, sv.s));
         sv.chk(hipStreamSynchronize(sv.s));
         if (sv.err != hipSuccess) break;
@@ -523,6 +594,9 @@ int run_solver(Solver& sv, const float* first, double* resnorm_hist, int32_t* it
       }
     }
     if (sv.err == hipSuccess) sv.close(0);
+    sv.flush();
+    if (sv.late_norms && sv.err == hipSuccess)
+      sv.chk(launch_norm_final(sv.partial, sv.late_norms, sv.norm_scale(), sv.hist_dev, iters, sv.s));
     if (!(p->tol > 0.0f) && resnorm_hist && sv.err == hipSuccess) {
       sv.chk(hipMemcpyAsync(resnorm_hist, sv.hist_dev, sizeof(double) * iters, hipMemcpyDeviceToHost, sv.s));
       sv.chk(hipStreamSynchronize(sv.s));
@@ -692,7 +766,7 @@ int residual_norm_impl(const mgrit_problem_t* p, const mgrit_fc_layers_t* fc, co
   int nb0 = 0;
   sv.chk(launch_diff_sq(u0, U, pl.E, sv.partial + nb, &nb0, sv.s));
   const double scale = p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(p->N + 1) * (double)pl.E) : 1.0;
-  sv.chk(launch_norm_final(sv.partial, nb + nb0, scale, sv.hist_dev, sv.s));
+  sv.chk(launch_norm_final(sv.partial, nb + nb0, scale, sv.hist_dev, 1, sv.s));
   double v = 0.0;
   sv.chk(hipMemcpyAsync(&v, sv.hist_dev, sizeof(double), hipMemcpyDeviceToHost, sv.s));
   sv.chk(hipStreamSynchronize(sv.s));

@@ -12,6 +12,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // Operand traits.  Matrix-core operands live in LDS as rows of KSTEP-multiples, k fastest.
 //   float : v_mfma_f32_32x32x2_f32, a lane feeds 4 consecutive k over 4 instructions

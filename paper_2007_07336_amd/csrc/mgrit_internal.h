@@ -2,6 +2,7 @@
 // library.  Not part of the public C ABI.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace mgrit {
@@ -104,8 +105,8 @@ hipError_t launch_zero_points(float* out, PtMap om, long long E, int groups, hip
 hipError_t launch_diff_sq(const float* a, const float* b, long long n, float* partial, int* blocks_used,
                           hipStream_t s);
 int        diff_sq_blocks(long long n);
-// out[0] = sqrt(sum_{i<n} partial[i]) * scale, summed in a fixed order in double
-hipError_t launch_norm_final(const float* partial, int n, double scale, double* out, hipStream_t s);
+// out[j] = sqrt(sum_{i<n} partial[j n + i]) * scale for j < count, summed in a fixed order in double
+hipError_t launch_norm_final(const float* partial, int n, double scale, double* out, int count, hipStream_t s);
 // transposed parameter copies for the adjoint: dense Wt[n][i][o] = W[n][o][i];
 // conv Kt[n][i][2-dy][2-dx][o] = K[n][o][dy][dx][i]
 hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int dtype, int layers, int Nf,
@@ -144,7 +145,27 @@ struct SweepArgs {
 // Dense layers of width at most 256: workgroup (chain, slice of batch rows).
 bool       sweep_supported(int q);
 int        sweep_blocks(int M, int nchains);             // workgroups of a launch
+double     sweep_bytes(const SweepArgs& a, int dtype);   // algorithmic bytes of a launch
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s);
+// Dense layers of width at most 16: one wavefront per (chain, slice of 16 batch rows), and up to WAVE_OPS sweeps that follow one
+// another in one launch.  The fields of a sweep are SweepArgs's; what all of them share is stated once.
+struct WaveOp {
+  const float* S;  float* X;  float* Y;  float* Z;  const float* Ref;  const float* G;  float* norm_partial;
+  int sb, ss;  int xb, xs, xk, store0;  int yb, ys, kmid;  int zb, zs, zfirst, tau;  int rb, rs;  int gb, gs;
+  int lb, ls, lk;  int nsteps, nlast, nchains;  float hs;
+};
+enum { WAVE_OPS = 20 };
+struct WaveProgram {
+  int nops = 0, nsl, per, M, q, act, wn;       // nsl slices, per workgroups for each (both filled in by the launch wrapper)
+  const void* W;  const float* bias;  const void* Dm;
+  long long E, wsize;
+  WaveOp op[WAVE_OPS];
+};
+bool       wave_supported(int q);
+int        wave_slices(int M);
+int        wave_workgroups(int nchains);                 // workgroups of a slice that hold all chains of a sweep at once
+// (norm_partial: one per workgroup; `per` workgroups for each slice, 1 if there is more than one sweep)
+hipError_t launch_wave(const WaveProgram& p, int per, int dtype, long long units, double bytes, hipStream_t s);
 // 3x3 convolution layers: workgroup (chain, images).
 bool       conv_sweep_supported(int Himg, int Wimg, int C, int dtype);
 bool       conv_sweep_ring(int Himg, int Wimg, int C, int dtype);        // its weights pass through LDS tap by tap

@@ -107,7 +107,6 @@ __device__ __forceinline__ void mma_step(const __bf16* const (&ap)[TM], const __
 //   bf16  : two LDS transpose reads per fragment.  Within each group of 16 lanes, ds_read_b64_tr_b16 hands lane i
 //           element i % 4 of the 8-byte pieces addressed by lanes i / 4, 4 + i / 4, 8 + i / 4, 12 + i / 4; with lane
 //           l of a group pointing at row l / 4, columns 4 (l % 4) .. + 3, lane i receives rows 0..3 of column i.
-typedef short short4v __attribute__((ext_vector_type(4)));
 template <int TM, int TN>
 __device__ __forceinline__ void mma_step_wn(const float* const (&ap)[TM], const float* bk, int BNP, const int (&bcol)[TN],
                                             floatx16 (&acc)[TM][TN], int g) {
@@ -1403,6 +1402,7 @@ hipError_t launch_diff_sq(const float* a, const float* b, long long n, float* pa
   return hipGetLastError();
 }
 __global__ __launch_bounds__(NT) void norm_final_kernel(const float* partial, int n, double scale, double* out) {
+  partial += (size_t)blockIdx.x * n;
   __shared__ double red[NT];
   double s = 0.0;
   for (int i = threadIdx.x; i < n; i += NT) s += (double)partial[i];
@@ -1412,10 +1412,10 @@ __global__ __launch_bounds__(NT) void norm_final_kernel(const float* partial, in
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = sqrt(red[0]) * scale;
+  if (threadIdx.x == 0) out[blockIdx.x] = sqrt(red[0]) * scale;
 }
-hipError_t launch_norm_final(const float* partial, int n, double scale, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(norm_final_kernel, dim3(1), dim3(NT), 0, s, partial, n, scale, out);
+hipError_t launch_norm_final(const float* partial, int n, double scale, double* out, int count, hipStream_t s) {
+  hipLaunchKernelGGL(norm_final_kernel, dim3((unsigned)count), dim3(NT), 0, s, partial, n, scale, out);
   return hipGetLastError();
 }
 

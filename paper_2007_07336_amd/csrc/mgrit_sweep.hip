@@ -27,8 +27,6 @@ namespace mgrit {
 // 8 KB of fragments for 16 instructions).  Global memory sees only what a caller keeps of the states.
 // ------------------------------------------------------------------------------------------
 typedef unsigned char u8;
-typedef short short4w __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // x = h + m + l, each representable in bf16 (rounded to nearest each time; exact, since a float has 24 significant
 // bits), for a vector of floats: two values per conversion instruction.
@@ -1000,10 +998,10 @@ __global__ __launch_bounds__(64 * NWV) void dense_sweep_kernel(SweepArgs a) {
           } else if constexpr (WN) {
             // two transposing reads: rows k = 8 kq + 0 .. 3 and + 4 .. 7 of column c of the block
             constexpr int P = 32 * FBW + 32;
-            typedef __attribute__((address_space(3))) short4w* lds_s4;
+            typedef __attribute__((address_space(3))) short4v* lds_s4;
             const u8* p = in ? Ws + (8 * kq + (c >> 2)) * P + 32 * j + 8 * (c & 3) : Zr;
-            const short4w lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p));
-            const short4w hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p + 4 * P));
+            const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p));
+            const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(p + 4 * P));
             af[j][0] = __builtin_shufflevector(__builtin_bit_cast(bf16x4, lo), __builtin_bit_cast(bf16x4, hi), 0, 1, 2, 3, 4, 5, 6, 7);
           } else {
             af[j][0] = *reinterpret_cast<const bf16x8*>(in ? Ws + (16 * j + c) * 96 + kq * 16 : Zr);
@@ -1115,6 +1113,15 @@ int sweep_rows(int M, int nchains) { return (long long)((M + 31) / 32) * nchains
 bool sweep_supported(int q) { return q >= 8 && q <= 256 && q % 8 == 0; }
 int sweep_blocks(int M, int nchains) { const int r = sweep_rows(M, nchains); return (M + r - 1) / r * nchains; }
 
+// Algorithmic bytes: per layer step the weights and bias, the act' factor, the right-hand side and what is kept of the state; the
+// start state once per chain.
+double sweep_bytes(const SweepArgs& a, int dtype) {
+  const double es = dtype == 0 ? 4.0 : 2.0, E4 = 4.0 * (double)a.E;
+  const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
+  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.q : 0.0) + (a.Dm ? a.act == ACT_MASK ? 0.125 : es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
+                     (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
+  return steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0));
+}
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
   if (a.nchains <= 0) return hipSuccess;
   if (a.M < 1 || !sweep_supported(a.q)) return hipErrorInvalidValue;
@@ -1137,12 +1144,7 @@ hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s) {
   else            { if (a.q <= 64) MGRIT_DS(1, 4, 1) else if (a.q <= 128) MGRIT_DS(1, 8, 1) else MGRIT_DS(1, 16, 1) }
 #undef MGRIT_DS
 #undef MGRIT_DS_RB
-  const double es = dtype == 0 ? 4.0 : 2.0, E4 = 4.0 * (double)a.E;
-  const double steps = (double)(a.nchains - 1) * a.nsteps + a.nlast;
-  const double per = es * (double)a.wsize + (a.bias ? 4.0 * a.q : 0.0) + (a.Dm ? a.act == ACT_MASK ? 0.125 : es : 0.0) * (double)a.E + (a.G ? E4 : 0.0) +
-                     (a.X && a.xk ? E4 : 0.0) + (a.tau ? E4 : 0.0) + (a.Ref ? E4 : 0.0);
-  trace_after(s, dtype == 0 ? TRACE_SWEEP_F32 : TRACE_SWEEP_BF16, a.units,
-              steps * per + (double)a.nchains * E4 * (1.0 + (a.Y ? 1.0 : 0.0) + (a.Z ? 1.0 : 0.0) + (a.store0 ? 1.0 : 0.0)));
+  trace_after(s, dtype == 0 ? TRACE_SWEEP_F32 : TRACE_SWEEP_BF16, a.units, sweep_bytes(a, dtype));
   return e;
 }
 
