@@ -282,7 +282,7 @@ struct Solver {
     step(l, js0, jstride, groups, X[l], pm(l, js0 - 1, jstride), X[l], pm(l, js0, jstride));
   }
   // Layers whose state fits on a CU -- convolution layers on images of at most 1024 pixels, dense layers of width at most
-  // 256: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
+  // 256, in bf16 1024: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
   // one launch each.  Whole solves 372 -> 226 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 797 us
   // (64 of 28 x 28, 16 channels, float), 16.6 -> 9.3 ms (32 of 32 x 32, 64 channels, bf16);
   // 250 -> 140 us (4 samples, width 8), 655 -> 521 us (128 samples, width 256, float).
@@ -292,19 +292,24 @@ struct Solver {
   //   128, 52 / 55 with 144 (32 x 32), 37.3 / 36.2 with 160 and 40 / 50 with 192 (23 x 23); 48 channels adjoint on 32 x 32 17.1 / 16.5
   //   with 8, 20.7 / 21.2 with 32; float of width 136 to 256: 5.5 (and a barrier's wait between two kernels less) / 5.0 for 8
   //   slices, level with 7.4 at 128.
+  // bf16 of width 264 to 1024, a whole solve with its gradient where there is one, lockstep / sweep: 64 rows and 64 chains 1.15 at
+  // width 272, 1.22 (adjoint 1.00) at 512, 1.07 (0.96) at 640, 0.99 (0.90) at 768; 256 rows and 16, 32, 40 chains 0.91, 1.26, 1.33 at 512,
+  // 0.92, 1.02, 1.06 at 768, 0.66, 0.85, 1.15 at 1024 (adjoint 1.05 with 40); 64 chains 1.33, 1.47 and 1.23 (adjoint 1.21, 1.21, 1.10).
   // Every other instance is as fast or faster with a single image at its largest size: float 16 channels on 32 x 32 7.0 / 7.1 and
   // 8.2 / 8.2, 32 on 16 x 32 9.9 / 16.3 and 11.4 / 17.9; bf16 32 channels on 32 x 32 8.0 / 8.9 and 9.2 / 10.3, 48 on 32 x 32
   // 13.3 / 14.3, 64 on 16 x 32 9.9 / 13.3 and 12.8 / 14.6; dense 1.4 .. 2.5 / 4 (float to 128), 0.9 .. 3.0 / 4.4 (bf16).
   bool use_march(int l) const {
     if (pl.fcP || !sweep_enabled()) return false;
     const bool conv = p->layer == MGRIT_LAYER_CONV3X3;
-    if (!(conv ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : sweep_supported(p->q))) return false;
-    // (a launch holds less than 2^32 threads: at most 1024 for 16 rows, 512 for an image, of every chain)
-    const long long units = conv ? p->B : (pl.M + 15LL) / 16;
+    const bool wide = !conv && wide_supported(p->q, p->dtype);
+    if (!(conv ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : wide || sweep_supported(p->q))) return false;
+    // (a launch holds less than 2^32 threads: at most 1024 for 16 rows, 512 for an image or 64 rows, of every chain)
+    const long long units = conv ? p->B : wide ? wide_blocks(pl.M, 1) : (pl.M + 15LL) / 16;
     const long long most = units * (pl.L > 1 ? pl.Nl[1] + 1LL : 1LL);
     if (most * (conv ? 512 : 1024) >= 1LL << 32) return false;
     long long need = 1;
-    if (!conv) need = p->dtype == MGRIT_FP32 && p->q > 128 ? 128 : 1;
+    if (wide) need = p->q > 768 ? 160 : p->q > 640 ? 144 : p->q > 512 ? 96 : 72;
+    else if (!conv) need = p->dtype == MGRIT_FP32 && p->q > 128 ? 128 : 1;
     else if (conv_sweep_ring(p->Himg, p->Wimg, p->C, p->dtype)) need = !adjoint ? 128 : p->Himg * p->Wimg >= 784 ? 144 : 192;
     else if (adjoint && p->C == 48 && p->Himg * p->Wimg > 900) need = 32;
     return units * (l + 1 < pl.L ? pl.Nl[l + 1] : 1LL) >= need;
@@ -363,13 +368,16 @@ struct Solver {
   // workgroups (= norm partials) of the launch of a
   int march_blocks(const SweepArgs& a) const {
     if (wave) return wave_slices(a.M) * (joins(a) ? 1 : wave_workgroups(a.nchains));
+    if (wide_supported(p->q, p->dtype)) return wide_blocks(a.M, a.nchains);
     return p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_blocks(a, p->dtype) : sweep_blocks(a.M, a.nchains);
   }
   void launch_march(SweepArgs& a, long long units) {
     a.units = units;
     if (err != hipSuccess) return;
     if (wave) { collect(a); return; }
-    chk(p->layer == MGRIT_LAYER_CONV3X3 ? launch_conv_sweep(a, p->dtype, s) : launch_sweep(a, p->dtype, s));
+    chk(p->layer == MGRIT_LAYER_CONV3X3     ? launch_conv_sweep(a, p->dtype, s)
+        : wide_supported(p->q, p->dtype) ? launch_wide(a, p->dtype, s)
+                                         : launch_sweep(a, p->dtype, s));
   }
   // Where the current values of a level's C-points 0, m, 2m, .. are: point js = j m at p[m.base + j m.stride].
   // They do not live in the level's own array: the relaxation leaves them in R[l], the coarse solve in X[l + 1]

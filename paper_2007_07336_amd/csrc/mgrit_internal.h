@@ -147,6 +147,10 @@ bool       sweep_supported(int q);
 int        sweep_blocks(int M, int nchains);             // workgroups of a launch
 double     sweep_bytes(const SweepArgs& a, int dtype);   // algorithmic bytes of a launch
 hipError_t launch_sweep(const SweepArgs& a, int dtype, hipStream_t s);
+// Dense layers of width 257 to 1024, bf16: workgroup (chain, 64 batch rows).
+bool       wide_supported(int q, int dtype);
+int        wide_blocks(int M, int nchains);
+hipError_t launch_wide(const SweepArgs& a, int dtype, hipStream_t s);
 // Dense layers of width at most 16: one wavefront per (chain, slice of 16 batch rows), and up to WAVE_OPS sweeps that follow one
 // another in one launch.  The fields of a sweep are SweepArgs's; what all of them share is stated once.
 struct WaveOp {
