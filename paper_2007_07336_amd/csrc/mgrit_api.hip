@@ -299,8 +299,12 @@ struct Solver {
   // 8.2 / 8.2, 32 on 16 x 32 9.9 / 16.3 and 11.4 / 17.9; bf16 32 channels on 32 x 32 8.0 / 8.9 and 9.2 / 10.3, 48 on 32 x 32
   // 13.3 / 14.3, 64 on 16 x 32 9.9 / 13.3 and 12.8 / 14.6; dense 1.4 .. 2.5 / 4 (float to 128), 0.9 .. 3.0 / 4.4 (bf16).
   bool use_march(int l) const {
-    if (pl.fcP || !sweep_enabled()) return false;
+    if (!sweep_enabled()) return false;
     const bool conv = p->layer == MGRIT_LAYER_CONV3X3;
+    // Mixed stacks, forward: where the fully connected layers of a level open intervals (and on the coarsest level wherever they
+    // are) they are launches of their own between sweeps over the convolution layers.  256 layers of 16 channels on 16 x 16
+    // pixels, 32 images, one in 64 fully connected: the convolutions' lockstep launches took 1180 of 2300 us.
+    if (pl.fcP && (adjoint || (l + 1 < pl.L && pl.fcP % (pl.mpow[l] * p->m) != 0))) return false;
     const bool wide = !conv && wide_supported(p->q, p->dtype);
     if (!(conv ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : wide || sweep_supported(p->q))) return false;
     // (a launch holds less than 2^32 threads: at most 1024 for 16 rows, 512 for an image or 64 rows, of every chain)
@@ -327,6 +331,26 @@ struct Solver {
     a.M = pl.M; a.q = pl.Nf; a.E = pl.E; a.wsize = pl.wsize;
     if (p->layer == MGRIT_LAYER_CONV3X3) { a.M = pl.B; a.Himg = p->Himg; a.Wimg = p->Wimg; a.C = p->C; }
     return a;
+  }
+  // the same, steps from + 1, from + 2, .. of the chains
+  void start_behind(SweepArgs& a, int from) const {
+    a.lb += from * a.lk;
+    if (a.G) a.gb += from;
+    if (a.X) a.xb += from * a.xk;
+  }
+  // Mixed stacks: the chains of a, groups of them, whose first layer is fully connected.  That step of theirs as one launch, into
+  // out[om]; the sweep then goes on from there.
+  void first_steps(SweepArgs& a, int l, long long js0, long long jstride, int groups, float* out, PtMap om) {
+    if (!pl.fcP) return;
+    StepArgs s1 = base_args(l, js0, jstride);
+    long long g0, per; int cnt;
+    fc_subset(s1.wm, groups, &g0, &per, &cnt);
+    if (!cnt) return;
+    s1.X = a.S; s1.xm = a.sm;
+    s1.Out = out; s1.om = om;
+    if (a.G) { s1.E1 = a.G; s1.e1m = PtMap{js0, jstride}; s1.c1 = 1.0f; }
+    if (err == hipSuccess) chk(launch_step(fc_args(s1, g0, per), MGRIT_LAYER_DENSE, p->dtype, cnt, s));
+    a.alt0 = (int)g0; a.altper = (int)per; a.Alt = out; a.am = om;
   }
   void keep_states(SweepArgs& a, int l, long long stride) const {   // into the level's own array
     const PtMap unit = pm(l, 0, 1);                                 // storage index of sweep point js = base + js * stride
@@ -404,6 +428,7 @@ struct Solver {
       const int tail = pl.Nl[l] - Nc * p->m;
       a.store0 = tail > 0 ? 1 : 2;
       a.nsteps = p->m - 1; a.nlast = tail > 0 ? tail : p->m - 1; a.nchains = Nc + (tail > 0 ? 1 : 0);
+      first_steps(a, l, 1, p->m, a.nchains, X[l], pm(l, 1, p->m));
       launch_march(a, pl.Nl[l] - Nc);
       return;
     }
@@ -415,11 +440,20 @@ struct Solver {
   // The coarsest level: its points in sequence.  X[l][0] holds the known value.
   void serial(int l) {
     if (use_march(l)) {
-      SweepArgs a = sweep_args(l, 0);
-      a.S = X[l]; a.sm = pm(l, 0, 0);
-      keep_states(a, l, 0);
-      a.nsteps = a.nlast = pl.Nl[l]; a.nchains = 1;
-      launch_march(a, pl.Nl[l]);
+      for (int j = 0; j < pl.Nl[l];) {                          // (one run, in a mixed stack those between fully connected layers)
+        auto fc = [&](int i) { return pl.fcP && layer_map(l, i + 1, 1).base % pl.fcP == 0; };     // step i + 1
+        int end = j;
+        while (end < pl.Nl[l] && !fc(end)) ++end;
+        if (end > j) {
+          SweepArgs a = sweep_args(l, 0);
+          a.S = X[l]; a.sm = pm(l, j, 0);
+          keep_states(a, l, 0);
+          start_behind(a, j);
+          a.nsteps = a.nlast = end - j; a.nchains = 1;
+          launch_march(a, end - j);
+        }
+        for (j = end; j < pl.Nl[l] && fc(j); ++j) propagate(l, j + 1, 1, 1);
+      }
       return;
     }
     for (int j = 1; j <= pl.Nl[l]; ++j) propagate(l, j, 1, 1);
@@ -436,6 +470,25 @@ struct Solver {
     a.S = c.p; a.sm = c.m;
     a.nchains = Nc;
     a.Z = g[l + 1];
+    if (pl.fcP) {
+      // Mixed stack: fully connected layers open intervals, so a chain has them in step 1 and, under FCF-relaxation, in step
+      // m + 1: two sweeps.  The states behind those steps wait where Z will be: of an interval's own C-point in the first
+      // sweep, which writes Z of chain 0 alone, of the chain itself in the second.
+      first_steps(a, l, 1, m, Nc, g[l + 1], PtMap{1, 1});
+      a.nsteps = a.nlast = m;
+      a.zb = 1; a.zs = 1;
+      if (p->relax == MGRIT_RELAX_FCF) { a.Y = R[l]; a.yb = 1; a.ys = 1; a.kmid = m; a.zfirst = 1; }
+      launch_march(a, pl.Nl[l]);
+      if (p->relax != MGRIT_RELAX_FCF || Nc < 2) return;
+      SweepArgs b = sweep_args(l, m);
+      start_behind(b, m);
+      b.S = R[l]; b.sm = PtMap{1, 1};
+      b.nsteps = b.nlast = m; b.nchains = Nc - 1;
+      b.Z = g[l + 1]; b.zb = 2; b.zs = 1;
+      first_steps(b, l, m + 1, m, Nc - 1, g[l + 1], PtMap{2, 1});
+      launch_march(b, pl.Nl[l]);
+      return;
+    }
     if (p->relax == MGRIT_RELAX_FCF) {
       a.Y = R[l]; a.yb = 1; a.ys = 1; a.kmid = m;
       a.zb = 2; a.zs = 1; a.zfirst = 1;
@@ -460,6 +513,15 @@ struct Solver {
     plain_rhs = false;
   }
 
+  // the coarse right-hand side of level l as lockstep steps: S_H = P - Phi_H, P in place
+  StepArgs rhs_args(int l, const CPoints& c) const {
+    StepArgs a = base_args(l + 1, 1, 1);
+    a.X = c.p; a.xm = c.m;
+    a.Out = g[l + 1]; a.om = PtMap{1, 1};
+    a.sp = -1.0f;
+    a.E1 = g[l + 1]; a.e1m = PtMap{1, 1}; a.c1 = 1.0f;          // in place, element by element
+    return a;
+  }
   double norm_scale() const {          // of the C-point residual of the fine level
     return p->norm_kind == MGRIT_NORM_RMS ? 1.0 / sqrt((double)(pl.Nl[1] + 1) * (double)pl.E) : 1.0;
   }
@@ -507,13 +569,24 @@ struct Solver {
       if (norm && late_norms) sums = partial + (size_t)iter * late_norms;
       if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = sums; }
       blocks = march_blocks(a);
+      if (pl.fcP) {                                             // the coarse steps of fully connected layers by themselves
+        StepArgs d = rhs_args(l, c);
+        long long g0, per; int cnt;
+        fc_subset(d.wm, Nc, &g0, &per, &cnt);
+        if (cnt) {
+          a.alt0 = (int)g0; a.altper = (int)per;
+          d = fc_args(d, g0, per);
+          if (norm) {
+            const PtMap rn{next.base + g0 * next.stride, next.stride * per};
+            d.Ref = c.p; d.rm = rn; d.norm_partial = sums + blocks;
+            blocks += step_grid_blocks(d, MGRIT_LAYER_DENSE, p->dtype, cnt) * cnt;
+          }
+          if (err == hipSuccess) chk(launch_step(d, MGRIT_LAYER_DENSE, p->dtype, cnt, s));
+        }
+      }
       launch_march(a, Nc);
     } else {
-      StepArgs a = base_args(l + 1, 1, 1);
-      a.X = c.p; a.xm = c.m;
-      a.Out = g[l + 1]; a.om = PtMap{1, 1};
-      a.sp = -1.0f;
-      a.E1 = g[l + 1]; a.e1m = PtMap{1, 1}; a.c1 = 1.0f;        // in place, element by element
+      StepArgs a = rhs_args(l, c);
       if (norm) { a.Ref = c.p; a.rm = next; a.norm_partial = partial; }
       launch(a, Nc);
       blocks = launch_blocks(a, Nc);

@@ -123,7 +123,9 @@ hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int
 //   Z:          the state after the last step, in Z[zb + ci*zs], if n > kmid; chain 0's state after step kmid in Z[zfirst]
 //   tau:        single steps (n = 1): Z[zb + ci*zs] <- Z[zb + ci*zs] - state, and with Ref the sum over a workgroup of
 //               (Z - Ref[rm(ci)])^2, Z before the update, in norm_partial[workgroup]
-// S may not be written by another chain: X, Y, Z are other arrays, or other points of the same one.
+//   alt:        chains alt0, alt0 + altper, .. (convolution sweep, altper > 0) have a first layer of another kind: they go on from
+//               Alt[am(ci)], the state behind their first step, or with tau do nothing but write 0 to their norm partials
+// S and Alt may not be written by another chain: X, Y, Z are other arrays, or other points of the same one.
 struct SweepArgs {
   const float* S;  PtMap sm;
   float* X;  long long xb, xs, xk;  int store0;
@@ -139,6 +141,7 @@ struct SweepArgs {
   int act, nsteps, nlast, nchains, M, q;
   long long units;                       // layer steps of the schedule that the launch stands for (launch trace)
   long long E, wsize;
+  int alt0, altper;  const float* Alt;  PtMap am;
   int Himg, Wimg, C;                     // convolution sweep only (then M = images per state)
   int ipw;                               // ... images per workgroup (filled in by the launch wrapper)
 };

@@ -117,16 +117,17 @@ __device__ __forceinline__ void repeat_in_float(float* X, float* Wl, float* red,
   auto chan = [&](int i) { const int u = tid + NTH * i; return 4 * (CONV ? u % (C / 4) : u / (16 * U)); };
   auto mine = [&](int i) { return pixel(i) < npx && chan(i) < C; };
   auto elem = [&](int i) { return pixel(i) * C + chan(i); };
+  const bool alt = CONV && a.altper > 0 && ci >= a.alt0 && (ci - a.alt0) % a.altper == 0;
   __syncthreads();                                                  // the sweep's stores are done: the same places are written again
   floatx4 st[U];
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     st[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (mine(i)) st[i] = *reinterpret_cast<const floatx4*>(at(a.S, a.sm.base + ci * a.sm.stride) + elem(i));
+    if (mine(i)) st[i] = *reinterpret_cast<const floatx4*>((alt ? at(a.Alt, a.am.base + ci * a.am.stride) : at(a.S, a.sm.base + ci * a.sm.stride)) + elem(i));
   }
   if (CONV && tid < C) X[ZP * C + tid] = 0.0f;
 #pragma unroll 1
-  for (int k = 1; k <= n; ++k) {
+  for (int k = alt ? 2 : 1; k <= n; ++k) {
     const long long layer = a.lb + ci * a.ls + (long long)(k - 1) * a.lk;
     const float* W = reinterpret_cast<const float*>(a.W) + layer * a.wsize;
 #pragma unroll
@@ -223,8 +224,9 @@ template <int NP, int CP, bool RING> constexpr size_t conv_sweep_wbytes() {
 }
 static_assert(conv_sweep_wbytes<3, 16, false>() >= 9 * 16 * 16 * 4 && conv_sweep_wbytes<3, 32, false>() >= 9 * 32 * 32 * 4, "repeat_in_float");
 
-// TAU: the coarse right-hand side, single steps (its epilogue beside the others would cost the sweep registers)
-template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
+// TAU: the coarse right-hand side, single steps (its epilogue beside the others would cost the sweep registers).  ALT: some chains have
+// a first layer of another kind (in every instance: 64 layers of 16 channels 805 -> 830 us)
+template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU, bool ALT>
 __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   constexpr bool HD = ACT == ACT_IDENT || ACT == ACT_MASK;      // the adjoint: act' factors, no bias
   constexpr bool MASK = ACT == ACT_MASK;                        // ... as bits
@@ -264,6 +266,12 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   const int nbw = nblk > wave ? (nblk - wave + NWV - 1) / NWV : 0;     // blocks wave, wave + 8, .. of this wavefront
   const int ngr = ((nblk + NWV - 1) / NWV + GB - 1) / GB;       // groups of the wavefront with the most blocks
   const int n = TAU ? 1 : ci == a.nchains - 1 ? a.nlast : a.nsteps;
+  const bool alt = ALT && ci >= a.alt0 && (ci - a.alt0) % a.altper == 0;
+  const int k1 = alt ? 2 : 1;                                   // the first step
+  if (TAU && alt) {                                             // the whole workgroup
+    if (a.norm_partial && tid == 0) a.norm_partial[L] = 0.0f;
+    return;
+  }
   const int ZP = a.ipw * HW;                                    // the pixel of zeros
   u8* P = smem;
   u8* Wl = smem + ((size_t)(ZP + 1) * PXB + 255) / 256 * 256;
@@ -314,7 +322,14 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       for (int cb = 0; cb < CB; ++cb) st[b][cb] = *reinterpret_cast<const floatx4*>(sp + off(b, cb));
     if (a.store0) store_state(place(a.X, a.xb + (ci + t) * a.xs));
   }
-  if (n <= 0) return;                                           // the whole workgroup
+  if (n < k1) return;                                           // the whole workgroup
+  if (alt) {
+    const float* sp = a.Alt + (a.am.base + ci * a.am.stride) * a.E + img_off;
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) st[b][cb] = *reinterpret_cast<const floatx4*>(sp + off(b, cb));
+  }
 
   // ---- weights: unit u = (k step, output channel, piece of the step)
   const WT* Wall = reinterpret_cast<const WT*>(a.W);
@@ -364,11 +379,11 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       }
     }
   };
-  const WT* Wc = Wall + layer_of(1) * a.wsize;
+  const WT* Wc = Wall + layer_of(k1) * a.wsize;
   load_w(wr, Wc, 0);
   float bnext = 0.0f;
   auto load_bias = [&](int k) __attribute__((always_inline)) { if (a.bias && tid < CP && tid < C) bnext = a.bias[layer_of(k) * C + tid]; };
-  load_bias(1);
+  load_bias(k1);
 
   // ---- operand of a step: act' .* state, to LDS (a pixel's padded channels are zero)
   // (bits: all of a pixel's channels in one load of up to eight bytes, wherever they start; it may reach into the next pixel,
@@ -431,17 +446,17 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       }
     }
   };
-  load_d(1);
+  load_d(k1);
   if (tid < PXB / 4) reinterpret_cast<float*>(P + (size_t)ZP * PXB)[tid] = 0.0f;
   if (NP == 3 && tid == 0) repeat = 0;
   write_operand();
   store_w(wr, Wl, 0);
   if constexpr (RING) load_w(wr, Wc, 1);
-  if (tid < CP) bl[CP + tid] = bnext;
+  if (tid < CP) bl[(k1 & 1) * CP + tid] = bnext;
   __syncthreads();
 
   const unsigned alane = (unsigned)(((kq * NP) * CP + (c ^ (4 * (-kq & 3)))) * 16);      // this lane's row of a weight fragment
-  for (int k = 1; k <= n; ++k) {
+  for (int k = k1; k <= n; ++k) {
     asm volatile("" : "+v"(cpx));
 #pragma unroll
     for (int b = 0; b < NBW; ++b) asm volatile("" : "+v"(mask[b]));
@@ -712,12 +727,15 @@ bool conv_sweep_shape(int pixels, int C, int dtype, ConvSweepShape* sh) {
   sh->smem = conv_sweep_smem(sh->np, sh->cp, sh->ring, pixels);
   return pixels <= sh->nwv * sh->nbw * 16 && sh->smem <= cap;
 }
-template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU>
+template <int NP, int CP, int NWV, int NBW, bool RING, int ACT, bool TAU, bool ALT = false>
 hipError_t launch_conv_sweep_t(const SweepArgs& a, unsigned blocks, size_t smem, hipStream_t s) {
+  if constexpr (!ALT && (ACT == ACT_TANH || ACT == ACT_RELU))
+    if (a.altper > 0) return launch_conv_sweep_t<NP, CP, NWV, NBW, RING, ACT, TAU, true>(a, blocks, smem, s);
+  if (!ALT && a.altper > 0) return hipErrorInvalidValue;        // forward solves only
   static LdsOptIn opt;
-  const hipError_t e = opt.raise(reinterpret_cast<const void*>(conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>), smem);
+  const hipError_t e = opt.raise(reinterpret_cast<const void*>(conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU, ALT>), smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU>), dim3(blocks), dim3(64 * NWV), smem, s, a);
+  hipLaunchKernelGGL((conv_sweep_kernel<NP, CP, NWV, NBW, RING, ACT, TAU, ALT>), dim3(blocks), dim3(64 * NWV), smem, s, a);
   return hipGetLastError();
 }
 }  // namespace
