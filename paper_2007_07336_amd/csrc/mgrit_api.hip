@@ -21,10 +21,14 @@ inline bool adjoint_transposed_copy() {
   const char* e = getenv("MGRIT_ADJ_TRANSPOSED");
   return e && e[0] == '1';
 }
-// MGRIT_ACT_VALUES=1 in the environment: the act' factors of ReLU stacks are stored as values, like tanh's (diagnostic)
-inline bool act_factors_as_values() {
+// Whether ReLU's act' factors are stored as bits.  Narrow stacks whose factors are few bytes as values lose 2 % on taking bits apart
+// (4 MB of width 64: 175 us with values, 178 with bits; 6 MB of 8 channels 235, 240); elsewhere bits gain: 6 MB of 16 channels 257 and
+// 252 us, 2 MB of 24 channels 275 and 260, 32 MB of width 256 652 and 626, 256 MB of width 1024 6.75 and 6.28 ms, 512 MB of 64 channels
+// 5.57 and 5.01.  MGRIT_ACT_VALUES=1 / 0 in the environment: values / bits whatever the size (diagnostic).
+inline bool act_factor_bits(double bytes_as_values, bool narrow) {
   const char* e = getenv("MGRIT_ACT_VALUES");
-  return e && e[0] == '1';
+  if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '0';
+  return !(narrow && bytes_as_values < 8.0 * 1024.0 * 1024.0);
 }
 inline bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % ALIGN) == 0; }
 
@@ -768,7 +772,8 @@ int adjoint_impl(const mgrit_problem_t* p, const mgrit_fc_layers_t* fc, const vo
   if (fc && copy_dense) sv.chk(launch_transpose_weights(fc->Wfc, Wfct, MGRIT_LAYER_DENSE, p->dtype, pl.nfc, (int)pl.dfc, sv.s));
   {
     sv.W = W; sv.bias = b; sv.Dm = nullptr; sv.act = p->act;
-    sv.dbits = p->act == MGRIT_ACT_RELU && !act_factors_as_values();
+    sv.dbits = p->act == MGRIT_ACT_RELU &&
+               act_factor_bits((double)p->N * (double)pl.E * (double)pl.esize, p->layer == MGRIT_LAYER_DENSE || p->C == 8);
     if (fc) { sv.Wfc = fc->Wfc; sv.bfc = fc->bfc; }
     StepArgs a = sv.base_args(0, 1, 1);
     a.wm = PtMap{0, 1};

@@ -1,4 +1,4 @@
-"""The act' factors of ReLU stacks, stored as bits, against the same factors stored as values (MGRIT_ACT_VALUES=1): every kernel
+"""The act' factors of ReLU stacks, stored as bits (MGRIT_ACT_VALUES=0), against the same factors stored as values (=1): every kernel
 that writes or reads them, at widths and channel counts whose rows end inside a byte group of another row, at images whose last
 block of pixels is short.  The arithmetic is the same, so states and gradients agree bit for bit, infinities (0 times one is
 NaN) included."""
@@ -34,6 +34,7 @@ CASES = [
 
 
 def _same(monkeypatch, run):
+    monkeypatch.setenv("MGRIT_ACT_VALUES", "0")
     got = run()
     monkeypatch.setenv("MGRIT_ACT_VALUES", "1")
     ref = run()
