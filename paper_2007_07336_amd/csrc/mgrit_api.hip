@@ -21,14 +21,20 @@ inline bool adjoint_transposed_copy() {
   const char* e = getenv("MGRIT_ADJ_TRANSPOSED");
   return e && e[0] == '1';
 }
-// Whether ReLU's act' factors are stored as bits.  Narrow stacks whose factors are few bytes as values lose 2 % on taking bits apart
-// (4 MB of width 64: 175 us with values, 178 with bits; 6 MB of 8 channels 235, 240); elsewhere bits gain: 6 MB of 16 channels 257 and
-// 252 us, 2 MB of 24 channels 275 and 260, 32 MB of width 256 652 and 626, 256 MB of width 1024 6.75 and 6.28 ms, 512 MB of 64 channels
-// 5.57 and 5.01.  MGRIT_ACT_VALUES=1 / 0 in the environment: values / bits whatever the size (diagnostic).
-inline bool act_factor_bits(double bytes_as_values, bool narrow) {
+// Whether ReLU's act' factors are stored as bits.  They are where their bytes count; taking bits apart costs more than it saves where
+// the factors are few bytes as values, most of all in float layers wider than 128, whose lockstep launches wait for the epilogue's
+// loads anyway, and in layers of 8 or 16 features and of 8 channels, whose threads have few factors each.  us with values / with bits,
+// adjoint with gradient: float width 256, 8 MB of factors 513 / 529, 32 MB 644 / 648, 64 MB 1135 / 1121; float width 64, 4 MB
+// 181 / 183, 32 MB 372 / 358; bf16 width 64, 2 MB 128 / 124; width 8, 1 MB 113 / 117; bf16 8 channels, 16 MB 322 / 333, 128 MB
+// 1620 / 1599; 16 channels, 1 MB 181 / 177; bf16 24 channels, 2 MB 260 / 244; bf16 64 channels, 2 GB 17093 / 15100.
+// MGRIT_ACT_VALUES=1 / 0 in the environment: values / bits whatever the size (diagnostic).
+inline bool act_factor_bits(const mgrit_problem_t* p, double bytes_as_values) {
   const char* e = getenv("MGRIT_ACT_VALUES");
   if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '0';
-  return !(narrow && bytes_as_values < 8.0 * 1024.0 * 1024.0);
+  const double mb = bytes_as_values / (1024.0 * 1024.0);
+  if (p->layer == MGRIT_LAYER_CONV3X3) return !(p->C <= 8 && mb < 64.0);
+  if (p->dtype == MGRIT_FP32) return mb >= (p->q > 128 ? 40.0 : 8.0);
+  return !(p->q <= 16 && mb < 8.0);
 }
 inline bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % ALIGN) == 0; }
 
@@ -773,7 +779,7 @@ int adjoint_impl(const mgrit_problem_t* p, const mgrit_fc_layers_t* fc, const vo
   {
     sv.W = W; sv.bias = b; sv.Dm = nullptr; sv.act = p->act;
     sv.dbits = p->act == MGRIT_ACT_RELU &&
-               act_factor_bits((double)p->N * (double)pl.E * (double)pl.esize, p->layer == MGRIT_LAYER_DENSE || p->C == 8);
+               act_factor_bits(p, (double)p->N * (double)pl.E * (double)pl.esize);
     if (fc) { sv.Wfc = fc->Wfc; sv.bfc = fc->bfc; }
     StepArgs a = sv.base_args(0, 1, 1);
     a.wm = PtMap{0, 1};
