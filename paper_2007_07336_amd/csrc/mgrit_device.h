@@ -96,6 +96,30 @@ __device__ __forceinline__ void cvt_store4(__bf16* dst, float4 v) {
   *reinterpret_cast<bf16x4*>(dst) = o;
 }
 
+// x = h + m + l, each representable in bf16 (rounded to nearest each time; exact, since a float has 24 significant
+// bits), for a vector of floats: two values per conversion instruction.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ floatx2 widen2(bf16x2 v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  return floatx2{__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u)};
+}
+template <int N, typename F, typename V>
+__device__ __forceinline__ void split3(F f, V& h, V& m, V& l) {               // f(i) = value i
+#pragma unroll
+  for (int i = 0; i < N; i += 2) {
+    const floatx2 x = floatx2{f(i), f(i + 1)};
+    const bf16x2 a = __builtin_convertvector(x, bf16x2);
+    const floatx2 wa = widen2(a), r = floatx2{x[0] - wa[0], x[1] - wa[1]};
+    const bf16x2 b = __builtin_convertvector(r, bf16x2);
+    const floatx2 wb = widen2(b);
+    const bf16x2 c = __builtin_convertvector((floatx2{r[0] - wb[0], r[1] - wb[1]}), bf16x2);
+    h[i] = a[0]; h[i + 1] = a[1];
+    m[i] = b[0]; m[i + 1] = b[1];
+    l[i] = c[0]; l[i + 1] = c[1];
+  }
+}
+
 __device__ __forceinline__ floatx16 zero16() {
   floatx16 z;
 #pragma unroll

@@ -86,6 +86,10 @@ struct ConvGradGeom {
   bool ok;                          // false: image row too wide for this kernel (one workgroup per tap is used)
 };
 ConvGradGeom conv_grad_geom(int B, int Himg, int Wimg, int C, int dtype, int layers);
+// Float layers of at most 32 channels on the bf16 matrix cores: the slab's geometry (false: not these), and the launch, with
+// `layers`, `gchunks` and what the geometry gives filled in.
+bool       conv_grad_split_geom(int B, int Himg, int Wimg, int C, bool bits, ConvGradGeom* gm);
+hipError_t launch_conv_grad_split(const GradArgs& a, size_t smem, hipStream_t s);
 size_t     conv_grad_partial_bytes(int B, int Himg, int Wimg, int C, int dtype, int layers);
 
 // ---- launch wrappers (defined in mgrit_kernels.hip, those of sweeps in mgrit_sweep.hip); all enqueue on `s` and return the HIP status

@@ -1851,18 +1851,15 @@ __global__ __launch_bounds__(NT) void conv_grad_tap_kernel(GradArgs a) {
 // LDS is cleared once; slots that are never written (row padding, the column left of x = 0 in the
 // dx = -1 copy, ...) stay zero, rows outside the image are written as zeros every slab.
 // With few layers the slabs of a layer are split over `gchunks` workgroups that write partial sums.
-// N16 (float, at most 16 channels): 16x16x4 blocks, so the output-channel side carries no padding rows (a 32-row
-// block would be half empty at 16 channels, and this kernel is bound by the matrix cores); wavefront w then owns the
-// 16-column blocks w, w+4, ..
+// (Float layers of at most 32 channels: conv_grad_split_kernel.)
 // NWV wavefronts: 4, or 8 for more than 32 channels -- there the accumulators of four wavefronts (2 x 5 blocks
 // each) leave room for one workgroup per CU anyway, and with eight the transposing stores of a slab, which
 // take longer than its matrix instructions, are spread over twice the threads.
-template <typename OT, typename DT, int TM, int TN, bool N16 = false, int NWV = 4>
+template <typename OT, typename DT, int TM, int TN, int NWV = 4>
 __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
   constexpr int NTH = 64 * NWV;
   constexpr int UB = NWV == 8 ? 2 : 3;                  // 4x4 blocks of the U patch per thread, at most
-  static_assert(!N16 || (sizeof(OT) == 4 && TM == 1), "the 16-wide variant is float only");
-  constexpr int KSTEP = N16 ? 16 : Op<OT>::KSTEP;
+  constexpr int KSTEP = Op<OT>::KSTEP;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, c = lane & 31;
   const int C = a.Nf, H = a.Himg, Wd = a.Wimg;
@@ -2000,27 +1997,21 @@ __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
   // this lane's operand rows: output channel o for A, column n = tap * C + i for B; column 9C multiplies G by
   // ones, which sums it over the pixels (the bias gradient).  Clamped: blocks past the end compute values
   // that are never stored.
-  constexpr int BW = N16 ? 16 : 32;                     // block width: rows of A and columns of B per block
-  const int bl = N16 ? (lane & 15) : c;                 // this lane's row / column inside a block
-  const int kq = lane >> 4;                             // 16-wide blocks: the lane's quarter of a k step
   const OT* arow[TM];
   const OT* brow[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) arow[i] = Gt + min(BW * i + bl, C - 1) * PG;
+  for (int i = 0; i < TM; ++i) arow[i] = Gt + min(32 * i + c, C - 1) * PG;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    const int n = min(BW * (wave + NWV * j) + bl, 9 * C);
+    const int n = min(32 * (wave + NWV * j) + c, 9 * C);
     const int tap = n / C, ii = n % C;
     brow[j] = n == 9 * C ? ones : Ut + ((tap % 3) * C + ii) * PU + (tap / 3) * Wp;
   }
   floatx16 acc[TM][TN];
-  floatx4 acc16[TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = zero16();
-#pragma unroll
-  for (int j = 0; j < TN; ++j) acc16[j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   const int s_begin = ch * a.gspc, s_end = min(s_begin + a.gspc, a.gslabs);
   if (s_begin < s_end) load_slab(s_begin);
@@ -2030,26 +2021,13 @@ __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
     __syncthreads();
     if (sl + 1 < s_end) load_slab(sl + 1);
     for (int ks = 0; ks < KL; ks += KSTEP) {
-      if constexpr (N16) {
-        // lane (bl, kq) feeds k = ks + 4 kq .. + 3, one value per instruction
-        const float4 af = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(arow[0]) + ks + 4 * kq);
+      const OT* ap[TM];
+      const OT* bp[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const float4 bf = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(brow[j]) + ks + 4 * kq);
-          acc16[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.x, bf.x, acc16[j], 0, 0, 0);
-          acc16[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.y, bf.y, acc16[j], 0, 0, 0);
-          acc16[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.z, bf.z, acc16[j], 0, 0, 0);
-          acc16[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af.w, bf.w, acc16[j], 0, 0, 0);
-        }
-      } else {
-        const OT* ap[TM];
-        const OT* bp[TN];
+      for (int i = 0; i < TM; ++i) ap[i] = arow[i] + ks;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) ap[i] = arow[i] + ks;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bp[j] = brow[j] + ks;
-        mma_step<TM, TN>(ap, bp, acc, g);
-      }
+      for (int j = 0; j < TN; ++j) bp[j] = brow[j] + ks;
+      mma_step<TM, TN>(ap, bp, acc, g);
     }
   }
   const bool direct = a.gchunks == 1;
@@ -2060,36 +2038,20 @@ __global__ __launch_bounds__(64 * NWV) void conv_grad_kernel(GradArgs a) {
   float* dbd = direct ? (a.db ? a.db + (long long)gi * C : nullptr)
                       : a.partial + ((long long)ch * a.layers + gi) * pstride + a.wsize;
   const float scale = direct ? a.hs : 1.0f;
-  if constexpr (N16) {
-    // register v of lane (bl, kq) holds row o = 4 kq + v, column n = 16 (wave + 4 j) + bl of the block
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int n = 16 * (wave + NWV * j) + bl;
+      const int n = 32 * (wave + NWV * j) + c;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int o = 4 * kq + v;
+      for (int r = 0; r < 16; ++r) {
+        const int o = 32 * i + 8 * (r >> 2) + 4 * g + (r & 3);
         if (o < C) {
-          if (n < NC) { if (dKd) dKd[(long long)o * NC + n] = scale * acc16[j][v]; }
-          else if (n == NC) { if (dbd) dbd[o] = scale * acc16[j][v]; }
+          if (n < NC) { if (dKd) dKd[(long long)o * NC + n] = scale * acc[i][j][r]; }
+          else if (n == NC) { if (dbd) dbd[o] = scale * acc[i][j][r]; }
         }
       }
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = 32 * (wave + NWV * j) + c;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int o = 32 * i + 8 * (r >> 2) + 4 * g + (r & 3);
-          if (o < C) {
-            if (n < NC) { if (dKd) dKd[(long long)o * NC + n] = scale * acc[i][j][r]; }
-            else if (n == NC) { if (dbd) dbd[o] = scale * acc[i][j][r]; }
-          }
-        }
-      }
-  }
 }
 // dK and db = hs * (sum of the chunk partial sums, in chunk order).  A record holds wsize values of dK and C of db.
 __global__ __launch_bounds__(NT) void conv_grad_reduce_kernel(const float* partial, float* dW, float* db, int layers,
@@ -2147,7 +2109,8 @@ ConvGradGeom conv_grad_geom(int B, int Himg, int Wimg, int C, int dtype, int lay
   ConvGradGeom gm = {};
   const int nth = 64 * conv_grad_waves(C);
   const int es = dtype == 0 ? 4 : 2, pad = dtype == 0 ? Op<float>::PAD : Op<__bf16>::PAD;
-  const int kstep = (dtype == 0 && C <= 16) ? 16 : dtype == 0 ? Op<float>::KSTEP : Op<__bf16>::KSTEP;   // as conv_grad_n16
+  // (float layers of at most 32 channels have slabs of their own and take only the number of chunks from here)
+  const int kstep = (dtype == 0 && C <= 16) ? 16 : dtype == 0 ? Op<float>::KSTEP : Op<__bf16>::KSTEP;
   gm.Wp = (Wimg + 7) & ~7;
   // Image rows per slab.  A thread transposes at most one 4x4 block of G and three of the U patch per slab, so
   // R * blocks_per_row <= 256 and (R + 2) * blocks_per_row <= 768; 64 / Wp rows always satisfy that (64 channels,
@@ -2201,16 +2164,16 @@ static void launch_bias_grad(const GradArgs& a, int dtype, int groups, hipStream
   const dim3 grid((a.Nf + 63) / 64, groups);
   MGRIT_BY_FACTORS(bias_grad_kernel, grid)
 }
-template <typename OT, int TM, int TN, bool N16 = false, int NWV = 4, typename DT = OT>
+template <typename OT, int TM, int TN, int NWV = 4, typename DT = OT>
 static hipError_t launch_conv_grad(const GradArgs& a, unsigned blocks, size_t smem, hipStream_t s) {
   if constexpr (std::is_same<DT, OT>::value)
-    if (a.dbits) return launch_conv_grad<OT, TM, TN, N16, NWV, Bit>(a, blocks, smem, s);
+    if (a.dbits) return launch_conv_grad<OT, TM, TN, NWV, Bit>(a, blocks, smem, s);
   if (smem > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_grad_kernel<OT, DT, TM, TN, N16, NWV>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_grad_kernel<OT, DT, TM, TN, NWV>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((conv_grad_kernel<OT, DT, TM, TN, N16, NWV>), dim3(blocks), dim3(64 * NWV), smem, s, a);
+  hipLaunchKernelGGL((conv_grad_kernel<OT, DT, TM, TN, NWV>), dim3(blocks), dim3(64 * NWV), smem, s, a);
   return hipGetLastError();
 }
 
@@ -2242,7 +2205,12 @@ hipError_t launch_grad(const GradArgs& a_in, int layer_kind, int dtype, int grou
       db_done = true;
     }
   } else if (a.dW || a.db) {
-    const ConvGradGeom gm = conv_grad_geom(a.B, a.Himg, a.Wimg, a.Nf, dtype, groups);
+    ConvGradGeom gm = conv_grad_geom(a.B, a.Himg, a.Wimg, a.Nf, dtype, groups);
+    const bool split = dtype == 0 && gm.ok && conv_grad_split_geom(a.B, a.Himg, a.Wimg, a.Nf, a.dbits != 0, &gm);
+    if (split) {                                           // its own slabs, in at most as many chunks: the partial sums fit
+      gm.spc = (gm.slabs + gm.chunks - 1) / gm.chunks;
+      gm.chunks = (gm.slabs + gm.spc - 1) / gm.spc;
+    }
     if (!gm.ok) {                                          // wide image rows: one workgroup per (layer, tap)
       a.tiles = 9;
       if (a.dW) {
@@ -2255,26 +2223,25 @@ hipError_t launch_grad(const GradArgs& a_in, int layer_kind, int dtype, int grou
       a.gWp = gm.Wp; a.gR = gm.R; a.gKL = gm.KL; a.gPU = gm.PU; a.gPG = gm.PG;
       a.gspi = gm.spi; a.gslabs = gm.slabs; a.gchunks = gm.chunks; a.gspc = gm.spc;
       a.tiles = gm.chunks;
-      const bool n16 = dtype == 0 && a.Nf <= 16;            // 16x16x4 blocks (8 or 16 float channels)
       const int nwv = conv_grad_waves(a.Nf);
-      const int tm = a.Nf > 32 ? 2 : 1, tn = n16 ? ((9 * a.Nf + 1 + 15) / 16 + 3) / 4 : ((9 * a.Nf + 1 + 31) / 32 + nwv - 1) / nwv;
+      const int tm = a.Nf > 32 ? 2 : 1, tn = ((9 * a.Nf + 1 + 31) / 32 + nwv - 1) / nwv;
       hipError_t e = hipErrorInvalidValue;                 // also the result if the partial-sum buffer is missing
       const unsigned blocks = (unsigned)gm.chunks * (unsigned)groups;
       const bool have_buf = gm.chunks == 1 || a.partial != nullptr;
-      if (have_buf && n16 && tn == 2) e = launch_conv_grad<float, 1, 2, true>(a, blocks, gm.smem, s);      // 8 channels: 73 columns
-      else if (have_buf && n16 && tn == 3) e = launch_conv_grad<float, 1, 3, true>(a, blocks, gm.smem, s); // 16 channels: 145 columns
+      if (have_buf && split) e = launch_conv_grad_split(a, gm.smem, s);
       else {
-#define MGRIT_CG(TM_, TN_)                                                                                     \
-      if (have_buf && tm == TM_ && tn == TN_)                                                                   \
-        e = dtype == 0 ? launch_conv_grad<float, TM_, TN_>(a, blocks, gm.smem, s)                               \
-                       : launch_conv_grad<__bf16, TM_, TN_>(a, blocks, gm.smem, s);
-      if (nwv == 4) { MGRIT_CG(1, 1) MGRIT_CG(1, 2) MGRIT_CG(1, 3) MGRIT_CG(2, 3) MGRIT_CG(2, 4) MGRIT_CG(2, 5) }
+#define MGRIT_CG(OT_, TM_, TN_)                                                                                \
+      if (have_buf && dtype == (sizeof(OT_) == 4 ? 0 : 1) && tm == TM_ && tn == TN_) e = launch_conv_grad<OT_, TM_, TN_>(a, blocks, gm.smem, s);
+      if (nwv == 4) {
+        MGRIT_CG(__bf16, 1, 1) MGRIT_CG(__bf16, 1, 2) MGRIT_CG(__bf16, 1, 3) MGRIT_CG(__bf16, 2, 3) MGRIT_CG(__bf16, 2, 4) MGRIT_CG(__bf16, 2, 5)
+        MGRIT_CG(float, 2, 3) MGRIT_CG(float, 2, 4) MGRIT_CG(float, 2, 5)
+      }
 #undef MGRIT_CG
       // eight wavefronts (33 .. 64 channels: 10 .. 19 column blocks of 32, two or three per wavefront)
       if (have_buf && nwv == 8 && tn == 2)
-        e = dtype == 0 ? launch_conv_grad<float, 2, 2, false, 8>(a, blocks, gm.smem, s) : launch_conv_grad<__bf16, 2, 2, false, 8>(a, blocks, gm.smem, s);
+        e = dtype == 0 ? launch_conv_grad<float, 2, 2, 8>(a, blocks, gm.smem, s) : launch_conv_grad<__bf16, 2, 2, 8>(a, blocks, gm.smem, s);
       if (have_buf && nwv == 8 && tn == 3)
-        e = dtype == 0 ? launch_conv_grad<float, 2, 3, false, 8>(a, blocks, gm.smem, s) : launch_conv_grad<__bf16, 2, 3, false, 8>(a, blocks, gm.smem, s);
+        e = dtype == 0 ? launch_conv_grad<float, 2, 3, 8>(a, blocks, gm.smem, s) : launch_conv_grad<__bf16, 2, 3, 8>(a, blocks, gm.smem, s);
       }
       if (e != hipSuccess) { trace_after(s, TRACE_GRAD, groups, 0.0); return e; }
       if (gm.chunks > 1) {

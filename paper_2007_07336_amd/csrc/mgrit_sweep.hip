@@ -28,30 +28,6 @@ namespace mgrit {
 // ------------------------------------------------------------------------------------------
 typedef unsigned char u8;
 
-// x = h + m + l, each representable in bf16 (rounded to nearest each time; exact, since a float has 24 significant
-// bits), for a vector of floats: two values per conversion instruction.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ floatx2 widen2(bf16x2 v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  return floatx2{__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u)};
-}
-template <int N, typename F, typename V>
-__device__ __forceinline__ void split3(F f, V& h, V& m, V& l) {               // f(i) = value i
-#pragma unroll
-  for (int i = 0; i < N; i += 2) {
-    const floatx2 x = floatx2{f(i), f(i + 1)};
-    const bf16x2 a = __builtin_convertvector(x, bf16x2);
-    const floatx2 wa = widen2(a), r = floatx2{x[0] - wa[0], x[1] - wa[1]};
-    const bf16x2 b = __builtin_convertvector(r, bf16x2);
-    const floatx2 wb = widen2(b);
-    const bf16x2 c = __builtin_convertvector((floatx2{r[0] - wb[0], r[1] - wb[1]}), bf16x2);
-    h[i] = a[0]; h[i + 1] = a[1];
-    m[i] = b[0]; m[i + 1] = b[1];
-    l[i] = c[0]; l[i + 1] = c[1];
-  }
-}
-
 // A value that rounds to an infinite bf16 number, 0x1.ffp127 = 3.396e38 or more, has no such parts: in a weight or an operand
 // it makes NaN of every sum that it enters.  Float sweeps pass NaN on through the activation, so that it stays in the state,
 // and a workgroup that ends with a state that is not finite repeats its chain with products of the float values themselves,
