@@ -38,8 +38,8 @@ PROFILE_ROW = {
     "dense_step_kernel<bf16,128,128>": r"dense_step_kernel<__bf16, 128, 128,",
     "conv_step_kernel<float>": r"conv_step_kernel<float,",
     "conv_step_kernel<bf16>": r"conv_step_kernel<__bf16,",
-    "dense_sweep_kernel<float>": r"dense_sweep_kernel<3,",
-    "dense_sweep_kernel<bf16>": r"dense_sweep_kernel<1,",
+    "dense_sweep_kernel<float>": r"dense_(?:sweep_kernel<3|wave_kernel<float),",
+    "dense_sweep_kernel<bf16>": r"(?:dense_sweep_kernel<1,|dense_wave_kernel<__bf16,|wide_sweep_kernel<)",
     "dense_ksplit_kernel<float,8>": r"dense_ksplit_kernel<float, (?:false|true), 8[,>]",
     "dense_ksplit_kernel<float,4>": r"dense_ksplit_kernel<float, (?:false|true), 4[,>]",
     "dense_ksplit_kernel<bf16,4>": r"dense_ksplit_kernel<__bf16, (?:false|true), 4[,>]",
