@@ -482,9 +482,9 @@ struct Solver {
     a.Z = g[l + 1];
     if (pl.fcP) {
       // Mixed stack: fully connected layers open intervals, so a chain has them in step 1 and, under FCF-relaxation, in step
-      // m + 1: two sweeps.  The states behind those steps wait where Z will be: of an interval's own C-point in the first
-      // sweep, which writes Z of chain 0 alone, of the chain itself in the second.
-      first_steps(a, l, 1, m, Nc, g[l + 1], PtMap{1, 1});
+      // m + 1: two sweeps.  The states behind those steps wait at their F-points in the level's own array, where lockstep
+      // relaxation has them too and which no sweep writes before the level is closed.
+      first_steps(a, l, 1, m, Nc, X[l], pm(l, 1, m));
       a.nsteps = a.nlast = m;
       a.zb = 1; a.zs = 1;
       if (p->relax == MGRIT_RELAX_FCF) { a.Y = R[l]; a.yb = 1; a.ys = 1; a.kmid = m; a.zfirst = 1; }
@@ -495,7 +495,7 @@ struct Solver {
       b.S = R[l]; b.sm = PtMap{1, 1};
       b.nsteps = b.nlast = m; b.nchains = Nc - 1;
       b.Z = g[l + 1]; b.zb = 2; b.zs = 1;
-      first_steps(b, l, m + 1, m, Nc - 1, g[l + 1], PtMap{2, 1});
+      first_steps(b, l, m + 1, m, Nc - 1, X[l], pm(l, m + 1, m));
       launch_march(b, pl.Nl[l]);
       return;
     }

@@ -129,7 +129,8 @@ hipError_t launch_transpose_weights(const void* W, void* Wt, int layer_kind, int
 //               (Z - Ref[rm(ci)])^2, Z before the update, in norm_partial[workgroup]
 //   alt:        chains alt0, alt0 + altper, .. (convolution sweep, altper > 0) have a first layer of another kind: they go on from
 //               Alt[am(ci)], the state behind their first step, or with tau do nothing but write 0 to their norm partials
-// S and Alt may not be written by another chain: X, Y, Z are other arrays, or other points of the same one.
+// The launch may not write what it reads of S and Alt, by whichever chain: X, Y, Z are other arrays, or other points of the same
+// one.  (A float sweep that meets a value that is not finite starts its chain from them once more, after its stores.)
 struct SweepArgs {
   const float* S;  PtMap sm;
   float* X;  long long xb, xs, xk;  int store0;
