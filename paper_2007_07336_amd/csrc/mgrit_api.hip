@@ -291,6 +291,8 @@ struct Solver {
   void propagate(int l, long long js0, long long jstride, int groups) {
     step(l, js0, jstride, groups, X[l], pm(l, js0 - 1, jstride), X[l], pm(l, js0, jstride));
   }
+  // dense layers of the wide sweep (q says nothing of other layers)
+  bool wide_layers() const { return p->layer == MGRIT_LAYER_DENSE && wide_supported(p->q, p->dtype); }
   // Layers whose state fits on a CU -- convolution layers on images of at most 1024 pixels, dense layers of width at most
   // 256, in bf16 1024: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
   // one launch each.  Whole solves 372 -> 226 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 797 us
@@ -315,7 +317,7 @@ struct Solver {
     // are) they are launches of their own between sweeps over the convolution layers.  256 layers of 16 channels on 16 x 16
     // pixels, 32 images, one in 64 fully connected: the convolutions' lockstep launches took 1180 of 2300 us.
     if (pl.fcP && (adjoint || (l + 1 < pl.L && pl.fcP % (pl.mpow[l] * p->m) != 0))) return false;
-    const bool wide = !conv && wide_supported(p->q, p->dtype);
+    const bool wide = wide_layers();
     if (!(conv ? conv_sweep_supported(p->Himg, p->Wimg, p->C, p->dtype) : wide || sweep_supported(p->q))) return false;
     // (a launch holds less than 2^32 threads: at most 1024 for 16 rows, 512 for an image or 64 rows, of every chain)
     const long long units = conv ? p->B : wide ? wide_blocks(pl.M, 1) : (pl.M + 15LL) / 16;
@@ -402,16 +404,16 @@ struct Solver {
   // workgroups (= norm partials) of the launch of a
   int march_blocks(const SweepArgs& a) const {
     if (wave) return wave_slices(a.M) * (joins(a) ? 1 : wave_workgroups(a.nchains));
-    if (wide_supported(p->q, p->dtype)) return wide_blocks(a.M, a.nchains);
+    if (wide_layers()) return wide_blocks(a.M, a.nchains);
     return p->layer == MGRIT_LAYER_CONV3X3 ? conv_sweep_blocks(a, p->dtype) : sweep_blocks(a.M, a.nchains);
   }
   void launch_march(SweepArgs& a, long long units) {
     a.units = units;
     if (err != hipSuccess) return;
     if (wave) { collect(a); return; }
-    chk(p->layer == MGRIT_LAYER_CONV3X3     ? launch_conv_sweep(a, p->dtype, s)
-        : wide_supported(p->q, p->dtype) ? launch_wide(a, p->dtype, s)
-                                         : launch_sweep(a, p->dtype, s));
+    chk(p->layer == MGRIT_LAYER_CONV3X3 ? launch_conv_sweep(a, p->dtype, s)
+        : wide_layers()                 ? launch_wide(a, p->dtype, s)
+                                        : launch_sweep(a, p->dtype, s));
   }
   // Where the current values of a level's C-points 0, m, 2m, .. are: point js = j m at p[m.base + j m.stride].
   // They do not live in the level's own array: the relaxation leaves them in R[l], the coarse solve in X[l + 1]

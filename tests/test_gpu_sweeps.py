@@ -180,3 +180,16 @@ def test_kernel_choice_at_the_edges_of_its_rule(wl, direction, sweep, monkeypatc
     assert any(k.startswith(kernel) for k in tr) == sweep, tr
     monkeypatch.setenv("MGRIT_NO_SWEEP", "1")
     assert rel_l2_per_state(got, run()) <= (1e-6 if wl.dtype == I.FP32 else 1e-3)      # the same operands, sums in another order
+
+
+@pytest.mark.parametrize("relax", [I.RELAX_F, I.RELAX_FCF], ids=["F", "FCF"])
+def test_a_convolution_stack_has_no_width(relax):
+    """q is the width of dense stacks alone: with a value that the wide sweep takes, a convolution stack's states and history are the
+    same ones."""
+    wl = I.reduced(I.cfg4(2), name="conv_with_q", C=16, Himg=9, Wimg=7, B=70, N=24, m=2, max_levels=3, relax=relax)
+    data, res = I.generate(wl), []
+    for q in (0, 512):
+        _, U, hist, _ = GpuProblem(wl, data, q=q).forward()
+        res.append((U, hist))
+    assert res[0][1] == res[1][1]
+    assert not (res[0][0] != res[1][0]).any()
