@@ -15,10 +15,13 @@ namespace mgrit {
 // LDS is full (128 KB + 32 KB at width 1024), so nothing is padded: 16-byte pieces of the operand's rows and of the staging rows are
 // permuted instead, such that the lanes that are served together (0-3, 12-15, 20-27, then the others) find different banks.
 // What bounds it at width 1024: the contraction alone takes 31 us a step (LDS: 8 MB a step; the matrix instructions 14), with its
-// weights, 2 MB a step and workgroup from L2, 50 (adjoint 62): a quarter of them are misses that only two pairs of pieces can be
-// requested ahead of.  A lockstep launch takes 73 (97) us, reads the weights once per 128 rows and the state in and out.  1024 layers
-// of width 1024, 256 samples: forward solve 7.2 -> 5.65 ms, adjoint with gradient 13.0 -> 10.6.  Four pieces in flight without regard
-// to lines 6.13, all slices at the same k 6.5, one wavefront in turn touching the lines of a later group 6.0.
+// weights, 2 MB a step and workgroup from L2, 55 (adjoint 67): the first of a chain's slices to ask for a line waits for memory, the
+// others with it, and only two pairs of pieces can be requested ahead.  A lockstep launch takes 73 (97) us, reads the weights once per
+// 128 rows and the state in and out.  1024 layers of width 1024, 256 samples: forward solve 7.36 -> 6.00 ms, adjoint with gradient
+// 13.1 -> 11.2.  Tried: four pieces in flight 6.13; a load per group of pairs that touches the lines of the next group, each
+// slice another quarter, 6.4.
+// The instances for width 769 to 1024 use all 256 registers and spill (forward 86, adjoint 61 to 64): before and behind the
+// loop over k, which is free of spills, in the writing of the operand, the end of a step and the coarse right-hand side.
 // ------------------------------------------------------------------------------------------
 constexpr int WIDE_NWV = 8, WIDE_RB = 4, WIDE_ROWS = 16 * WIDE_RB, WIDE_STG = 2 * 2048;     // staging bytes of a wavefront, two pieces
 constexpr int wide_kp(int q) { return (q + 127) / 128 * 128; }
@@ -89,13 +92,12 @@ __global__ __launch_bounds__(64 * WIDE_NWV) void wide_sweep_kernel(SweepArgs a) 
     wo[i] = 2u * (unsigned)(WN ? row * q + 32 * wave + pc : (32 * wave + row) * q + pc + 32 * (lane >> 5));
   }
   const unsigned wlast = 2u * (unsigned)(q * q - 8);
-  // (Up to four slices of a chain go through every 256 values of k in a different order: each fetches another quarter of the weights
-  // first and finds the others' in the XCD's L2.  In the same order all would wait for the same lines from memory, with too few
-  // bytes in flight; over a whole pass, what eight chains fetch would not stay in the L2.)
-  const int turns = KS % 8 == 0 ? 3 : 1, slice = L % nsl;
-  auto turn = [&](int d) __attribute__((always_inline)) { return (d & ~turns) | ((d + slice) & turns); };
+  // (All slices of a chain take k in the same order, so that a sample's result does not depend on its place in the batch.  With each
+  // slice fetching another quarter of every 256 values of k first and finding the others' in the XCD's L2 the forward solve took 5.55
+  // ms instead of 5.94, the adjoint 10.7 instead of 11.1.)
   auto load_w = [&](LW (&w)[4], const __bf16* Wp, int p, int d) __attribute__((always_inline)) {
-    const int s = 2 * turn(d);
+    int s = 2 * d;
+    asm volatile("" : "+s"(s));                                     // (or every load gets an address register that counts along)
     const unsigned add = 2u * (unsigned)(WN ? 32 * s * q + 256 * p : 256 * p * q + 32 * s);
     const char* base = reinterpret_cast<const char*>(Wp);
 #pragma unroll
@@ -200,7 +202,8 @@ __global__ __launch_bounds__(64 * WIDE_NWV) void wide_sweep_kernel(SweepArgs a) 
       // the request for the pair after the next, then the matrix instructions (the other wavefront of the SIMD covers the reads)
       auto kstep = [&](LW (&w0)[4], LW (&w1)[4], int i, auto oddc) __attribute__((always_inline)) {
         constexpr int odd = decltype(oddc)::value, half = 2048 * odd;
-        const int s = 2 * turn(i >> 1) + odd;
+        int s = i;
+        asm volatile("" : "+s"(s));
         __builtin_amdgcn_sched_barrier(0);
         bf16x8 af[FB], bf[RB];
 #pragma unroll

@@ -92,3 +92,26 @@ def test_infinite_weights_past_the_width(monkeypatch):
         res.append(U)
     assert bool((res[0][1, :, 0] == 0).all())
     assert torch.equal(res[0].isnan(), res[1].isnan()) and torch.equal(res[0].nan_to_num(), res[1].nan_to_num())
+
+
+@pytest.mark.parametrize("q,m,N,relu", [(512, 2, 80, True), (640, 2, 100, False), (1000, 2, 100, False), (1024, 3, 150, True)])
+def test_a_sample_ends_the_same_wherever_it_is_in_the_batch(q, m, N, relu):
+    """Four slices of 64 rows with the same samples: the same states and multipliers, bit for bit, as in lockstep launches."""
+    import torch
+    import paper_2007_07336_amd as M
+    g = torch.Generator(device="cuda").manual_seed(q)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")                                     # noqa: E731
+    p = M.make_problem(N=N, h=1.0 / N, m=m, max_levels=2, min_coarse=1, relax=1, max_iter=1, layer=0, act=1 if relu else 0, dtype=1, B=256, q=q)
+    W, b = (rnd(N, q, q) / q ** 0.5).bfloat16(), 0.3 * rnd(N, q)
+    u0, lam = rnd(64, q).repeat(4, 1), rnd(64, q).repeat(4, 1)
+    ws = torch.empty(M.mgrit_adjoint_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    U, Lam = torch.empty(N + 1, 256, q, device="cuda"), torch.empty(N + 1, 256, q, device="cuda")
+    M.mgrit_trace_begin()
+    M.mgrit_fas_forward(p, W, b, u0, U, ws)
+    M.mgrit_fas_adjoint(p, W, b, U, lam, Lam, None, None, ws)
+    torch.cuda.synchronize()
+    tr = M.mgrit_trace_end()
+    assert any("sweep" in k for k in tr), tr
+    for x in (U, Lam):
+        for i in range(1, 4):
+            assert not bool((x[:, 64 * i:64 * i + 64] != x[:, :64]).any())
