@@ -199,7 +199,9 @@ __device__ __forceinline__ EpiPtrs epi_ptrs(const StepArgs& a, int gi, long long
 // loads its input tile in exactly this arrangement).
 // `stage_block(tm, stage)` writes the wavefront's accumulators of block row tm (32 rows x CW columns) to
 // `stage` with row stride CW + 4; it is the only part that depends on the MFMA shape.
-template <int ACT, int TM, int CW, bool XREG, int NX, typename StageFn>
+// BITS: MODE_DACT stores bits.  Instances of their own do that (those with DT = Bit): the test and the packing beside every other
+// launch's stores cost the float adjoint of width 256, whose factors are values, 0.6 % (642 against 638 us).
+template <bool BITS, int ACT, int TM, int CW, bool XREG, int NX, typename StageFn>
 __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, long long layer, StageFn stage_block,
                                               const long long (&row0)[TM], long long row_end, int colbase, int L,
                                               float* red, float* stage_all, const float4 (&xreg)[NX]) {
@@ -272,9 +274,9 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
         const int rl = (h0 + i) * RPI + lrow;
         const long long row = row0[tm] + rl;
         unsigned char fb = 0;
-        if (dact && a.dbits) fb = factor_byte(xv[i], lane);
+        if (BITS && dact) fb = factor_byte(xv[i], lane);
         if (colok && row < row_end) {
-          if (dact && a.dbits) {
+          if (BITS && dact) {
             if (!(lane & 1)) reinterpret_cast<unsigned char*>(a.Out)[((a.om.base + gi * a.om.stride) * a.E + (unsigned)(row * a.Nf + col)) >> 3] = fb;
           } else if (dact && a.dbf16) {              // act' cache of a bf16 problem: 4 x bf16
             __bf16* ob = reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E;
@@ -293,17 +295,17 @@ __device__ __forceinline__ void epilogue_rows_act(const StepArgs& a, int gi, lon
   }
 }
 
-template <int TM, int CW, bool XREG, int NX, typename StageFn>
+template <bool BITS, int TM, int CW, bool XREG, int NX, typename StageFn>
 __device__ __forceinline__ void epilogue_rows(const StepArgs& a, int gi, long long layer, StageFn stage_block,
                                               const long long (&row0)[TM], long long row_end, int colbase, int L,
                                               float* red, float* stage_all, const float4 (&xreg)[NX]) {
-  if (a.act == ACT_TANH)      epilogue_rows_act<ACT_TANH, TM, CW, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
-  else if (a.act == ACT_RELU) epilogue_rows_act<ACT_RELU, TM, CW, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
-  else                        epilogue_rows_act<ACT_IDENT, TM, CW, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
+  if (a.act == ACT_TANH)      epilogue_rows_act<BITS, ACT_TANH, TM, CW, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
+  else if (a.act == ACT_RELU) epilogue_rows_act<BITS, ACT_RELU, TM, CW, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
+  else                        epilogue_rows_act<BITS, ACT_IDENT, TM, CW, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
 }
 
 // 32x32 MFMA blocks: register r of a lane holds row 8 (r / 4) + 4 g + r % 4, column c of the block
-template <int TM, int TN, bool XREG = false, int NX = 1>
+template <bool BITS, int TM, int TN, bool XREG = false, int NX = 1>
 __device__ __forceinline__ void epilogue(const StepArgs& a, int gi, long long layer, floatx16 (&acc)[TM][TN],
                                          const long long (&row0)[TM], long long row_end, int colbase, int L,
                                          float* red, float* stage_all, const float4 (&xreg)[NX]) {
@@ -314,14 +316,14 @@ __device__ __forceinline__ void epilogue(const StepArgs& a, int gi, long long la
 #pragma unroll
       for (int r = 0; r < 16; ++r) stage[(8 * (r >> 2) + 4 * g + (r & 3)) * (TN * 32 + 4) + tn * 32 + c] = acc[tm][tn][r];
   };
-  epilogue_rows<TM, TN * 32, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
+  epilogue_rows<BITS, TM, TN * 32, XREG, NX>(a, gi, layer, stage_block, row0, row_end, colbase, L, red, stage_all, xreg);
 }
-template <int TM, int TN>
+template <bool BITS, int TM, int TN>
 __device__ __forceinline__ void epilogue(const StepArgs& a, int gi, long long layer, floatx16 (&acc)[TM][TN],
                                          const long long (&row0)[TM], long long row_end, int colbase, int L,
                                          float* red, float* stage_all) {
   const float4 none[1] = {make_float4(0.f, 0.f, 0.f, 0.f)};
-  epilogue<TM, TN, false, 1>(a, gi, layer, acc, row0, row_end, colbase, L, red, stage_all, none);
+  epilogue<BITS, TM, TN, false, 1>(a, gi, layer, acc, row0, row_end, colbase, L, red, stage_all, none);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -577,7 +579,7 @@ __global__ __launch_bounds__(64 * WR * WC, WR * WC == 8 ? 4 : (XR && WN) ? 2 : 1
   long long row0[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) row0[i] = m0 + wm0 + i * 32;
-  epilogue<TM, TN>(a, gi, layer, acc, row0, (long long)a.M, n0 + wn0, L, red, reinterpret_cast<float*>(smem_raw));
+  epilogue<std::is_same<DT, Bit>::value && !WN, TM, TN>(a, gi, layer, acc, row0, (long long)a.M, n0 + wn0, L, red, reinterpret_cast<float*>(smem_raw));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -621,7 +623,7 @@ template <typename WT, bool WS, int NW, bool WN = false, typename DT = WT>
 __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
   static_assert(NW == 4 || NW == 8, "four or eight wavefronts");
   constexpr int KC = KsOp<WT>::KC;
-  constexpr bool BF = sizeof(WT) == 2;
+  constexpr bool BF = sizeof(WT) == 2, BITS = std::is_same<DT, Bit>::value && !WN;       // (epilogue_rows_act)
   constexpr int KL = BF ? 8 : 4;                    // consecutive k a lane feeds per piece
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // the wavefronts' staging areas
   static_assert(ksplit_smem<WT>(NW) >= sizeof(float) * NW * 32 * 36, "the partial tiles reuse the staging areas");
@@ -788,9 +790,9 @@ __global__ __launch_bounds__(NW * 64) void dense_ksplit_kernel(StepArgs a) {
   }
   float sq = 0.0f;
   unsigned char fb = 0;
-  if (dact && a.dbits) fb = factor_byte(o, lane);
+  if (BITS && dact) fb = factor_byte(o, lane);
   if (eok) {
-    if (dact && a.dbits) { if (!(lane & 1)) reinterpret_cast<unsigned char*>(a.Out)[((a.om.base + gi * a.om.stride) * a.E + eoff) >> 3] = fb; }
+    if (BITS && dact) { if (!(lane & 1)) reinterpret_cast<unsigned char*>(a.Out)[((a.om.base + gi * a.om.stride) * a.E + eoff) >> 3] = fb; }
     else if (dact && a.dbf16) cvt_store4(reinterpret_cast<__bf16*>(a.Out) + (a.om.base + gi * a.om.stride) * a.E + eoff, o);
     else if (e.Op_) *reinterpret_cast<float4*>(e.Op_ + eoff) = o;
     sq = e.Rp ? sq_diff(e1, rf) : sq_norm(o);
@@ -1107,10 +1109,10 @@ __global__ __launch_bounds__(NT, 2) void conv_step_kernel(StepArgs a) {   // two
 #pragma unroll
         for (int v = 0; v < 4; ++v) stage[(16 * b + 4 * kq + v) * (CW + 4) + r16] = acc16[2 * tm + b][v];
     };
-    epilogue_rows<TM, CW, true, NX>(a, gi, layer, stage_block, row0, img_row0 + npx, 0, L, red,
+    epilogue_rows<std::is_same<DT, Bit>::value, TM, CW, true, NX>(a, gi, layer, stage_block, row0, img_row0 + npx, 0, L, red,
                                     reinterpret_cast<float*>(smem_raw), xreg);
   } else {
-    epilogue<TM, TN, true, NX>(a, gi, layer, acc, row0, img_row0 + npx, 0, L, red, reinterpret_cast<float*>(smem_raw), xreg);
+    epilogue<std::is_same<DT, Bit>::value, TM, TN, true, NX>(a, gi, layer, acc, row0, img_row0 + npx, 0, L, red, reinterpret_cast<float*>(smem_raw), xreg);
   }
 }
 
@@ -1174,10 +1176,12 @@ static bool step_opt_in(LdsOptIn& opt, const void* kernel, size_t smem) {
   if (e != hipSuccess) g_step_attr_err = e;
   return e == hipSuccess;
 }
+// act' factors as bits, read or written: the instances with DT = Bit
+static bool uses_bits(const StepArgs& a) { return a.dbits && (a.Dm || a.mode == MODE_DACT); }
 template <typename WT, int BM, int BN, int BK, int PF, bool WS, int WR, int WC, bool HD, bool FULL, bool XR = false, bool WN = false, typename DT = WT>
 static void launch_dense_k(dim3 grid, hipStream_t s, const StepArgs& a) {
-  if constexpr (HD && std::is_same<DT, WT>::value)
-    if (a.dbits && a.Dm) return launch_dense_k<WT, BM, BN, BK, PF, WS, WR, WC, HD, FULL, XR, WN, Bit>(grid, s, a);
+  if constexpr (std::is_same<DT, WT>::value && (HD || !XR))
+    if (uses_bits(a)) return launch_dense_k<WT, BM, BN, BK, PF, WS, WR, WC, HD, FULL, XR, WN, Bit>(grid, s, a);
   constexpr size_t bn_rows = (size_t)BN * (BK + Op<WT>::PAD), bk_rows = (size_t)BK * (BN + (sizeof(WT) == 2 ? 16 : 4));
   constexpr size_t tiles_b = ((size_t)BM * (BK + Op<WT>::PAD) + (WN ? bk_rows : bn_rows)) * sizeof(WT);
   constexpr size_t stage_b = XR ? (size_t)BM * (BN + 4) * sizeof(float)                   // whole-tile epilogue staging
@@ -1232,7 +1236,7 @@ static void launch_dense(dim3 grid, hipStream_t s, const StepArgs& a) {
 template <typename WT, bool WS, int NW, typename DT = WT>
 static void launch_ksplit_nw(dim3 grid, hipStream_t s, const StepArgs& a) {
   if constexpr (std::is_same<DT, WT>::value)
-    if (a.dbits && a.Dm) return launch_ksplit_nw<WT, WS, NW, Bit>(grid, s, a);
+    if (uses_bits(a)) return launch_ksplit_nw<WT, WS, NW, Bit>(grid, s, a);
   constexpr size_t smem = ksplit_smem<WT>(NW);
   static LdsOptIn opt, optn;
   if (a.wn) {
@@ -1253,7 +1257,7 @@ static void launch_ksplit(dim3 grid, hipStream_t s, const StepArgs& a) {
 template <typename WT, int TN, bool N16 = false, int CFIX = 0, typename DT = WT>
 static void launch_conv(dim3 grid, size_t smem, hipStream_t s, const StepArgs& a) {
   if constexpr (std::is_same<DT, WT>::value)
-    if (a.dbits && a.Dm) return launch_conv<WT, TN, N16, CFIX, Bit>(grid, smem, s, a);
+    if (uses_bits(a)) return launch_conv<WT, TN, N16, CFIX, Bit>(grid, smem, s, a);
   static LdsOptIn opt;
   if (!step_opt_in(opt, reinterpret_cast<const void*>(conv_step_kernel<WT, TN, N16, CFIX, DT>), smem)) return;
   hipLaunchKernelGGL((conv_step_kernel<WT, TN, N16, CFIX, DT>), grid, dim3(NT), smem, s, a);

@@ -25,6 +25,7 @@ def _conv(C, H, W, B, N, dtype, m=4, levels=2):
 CASES = [
     _dense(8, 3, 9, I.FP32), _dense(72, 33, 10, I.FP32), _dense(136, 130, 40, I.FP32), _dense(256, 64, 64, I.FP32),   # sweeps, lockstep
     _dense(24, 17, 9, I.BF16), _dense(200, 35, 12, I.BF16),
+    _dense(128, 128, 256, I.FP32, m=2),
     _dense(264, 70, 12, I.FP32), _dense(520, 96, 16, I.BF16), _dense(512, 256, 64, I.BF16, m=2), _dense(2056, 5, 4, I.FP32, m=2),  # tiled, whole tiles, k-split
     _conv(8, 3, 5, 3, 8, I.FP32), _conv(16, 13, 11, 3, 8, I.FP32), _conv(32, 9, 7, 2, 8, I.FP32), _conv(24, 11, 3, 2, 9, I.FP32),
     _conv(48, 9, 9, 2, 6, I.FP32), _conv(16, 40, 70, 1, 4, I.FP32, m=2),                                               # lockstep; a workgroup per tap
@@ -53,7 +54,7 @@ def test_bits_and_values_agree(wl, monkeypatch):
     _same(monkeypatch, lambda: gp.adjoint(U, lam))
 
 
-@pytest.mark.parametrize("wl", [CASES[1], CASES[11], CASES[17]], ids=lambda w: w.name)
+@pytest.mark.parametrize("wl", [CASES[1], CASES[12], CASES[18]], ids=lambda w: w.name)
 def test_infinite_values(wl, monkeypatch):
     data = I.generate(wl)
     gp = GpuProblem(wl, data)
