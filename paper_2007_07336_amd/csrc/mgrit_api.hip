@@ -21,20 +21,25 @@ inline bool adjoint_transposed_copy() {
   const char* e = getenv("MGRIT_ADJ_TRANSPOSED");
   return e && e[0] == '1';
 }
-// Whether ReLU's act' factors are stored as bits.  They are where their bytes count; taking bits apart costs more than it saves where
-// the factors are few bytes as values, most of all in float layers wider than 128, whose lockstep launches wait for the epilogue's
-// loads anyway, and in layers of 8 or 16 features and of 8 channels, whose threads have few factors each.  us with values / with bits,
-// adjoint with gradient: float width 256, 8 MB of factors 513 / 529, 32 MB 644 / 648, 64 MB 1135 / 1121; float width 64, 4 MB
-// 181 / 183, 32 MB 372 / 358; bf16 width 64, 2 MB 128 / 124; width 8, 1 MB 113 / 117; bf16 8 channels, 16 MB 322 / 333, 128 MB
-// 1620 / 1599; 16 channels, 1 MB 181 / 177; bf16 24 channels, 2 MB 260 / 244; bf16 64 channels, 2 GB 17093 / 15100.
+// Whether ReLU's act' factors are stored as bits.  They are where their bytes count; taking bits apart costs more than it saves
+//   - in dense layers of 8 or 16 features, whose lanes have four factors each;
+//   - in float layers wider than 128 that have few of them, and in the widest, whose weights are most of the bytes;
+//   - in layers of 8 channels that have few.
+// us with values / with bits, adjoint with gradient: float width 8, 8 MB of factors as values 260 / 277, 32 MB 812 / 832; width 16,
+// 16 MB 264 / 284, 64 MB 827 / 833; bf16 width 16, 8 MB 192 / 194, 32 MB 525 / 536; float width 24, 3 MB 185 / 182, 96 MB 1954 / 1912;
+// width 64, 2 MB 143 / 143, 64 MB 651 / 629; width 136, 2 MB 316 / 323, 68 MB 1405 / 1371; width 256, 1 MB 315 / 317, 16 MB
+// 547 / 546, 32 MB 668 / 652, 128 MB 1854 / 1766; width 448, 28 MB 1759 / 1774, 56 MB 2105 / 2061; width 512, 32 MB 1911 / 1940, 128 MB
+// 3420 / 3404; width 896, 112 MB 5513 / 5567, 448 MB 18586 / 18473; width 1024, 64 MB 5580 / 5598, 512 MB 22539 / 22636; bf16 width 64,
+// 2 MB 112 / 107; 8 channels, 12 MB 316 / 330, 49 MB 702 / 728, 128 MB 1603 / 1573; bf16 24 channels, 2 MB 272 / 259; bf16 64
+// channels, 2 GB 17093 / 15100.
 // MGRIT_ACT_VALUES=1 / 0 in the environment: values / bits whatever the size (diagnostic).
 inline bool act_factor_bits(const mgrit_problem_t* p, double bytes_as_values) {
   const char* e = getenv("MGRIT_ACT_VALUES");
   if (e && (e[0] == '0' || e[0] == '1')) return e[0] == '0';
   const double mb = bytes_as_values / (1024.0 * 1024.0);
-  if (p->layer == MGRIT_LAYER_CONV3X3) return !(p->C <= 8 && mb < 64.0);
-  if (p->dtype == MGRIT_FP32) return mb >= (p->q > 128 ? 40.0 : 8.0);
-  return !(p->q <= 16 && mb < 8.0);
+  if (p->layer == MGRIT_LAYER_CONV3X3) return p->C > 8 || mb >= 64.0;
+  if (p->q <= 16) return false;
+  return p->dtype == MGRIT_BF16 || p->q <= 128 || (p->q <= 896 && mb >= (p->q <= 448 ? 24.0 : 128.0));
 }
 inline bool aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) % ALIGN) == 0; }
 

@@ -73,8 +73,8 @@ template <> struct Fac<Bit> {
   typedef unsigned Raw;
   static __device__ __forceinline__ Ptr at(const void* base, long long value) { return reinterpret_cast<Ptr>(base) + (value >> 3); }
   // (four bytes, of which the first counts and the others may lie past the last layer's factors, in the cache's unused part: a byte
-  // that waits in a register until it is used is masked right behind its load, and the wavefront waits for it there.  Float width 64, 32 layers on 16384 samples, adjoint with
-  // gradient: 2170 us with bytes, 1887 so, 1950 with values)
+  // that waits in a register until it is used is masked right behind its load, and the wavefront waits for it there.  Float width
+  // 64, 32 layers on 16384 samples, adjoint with gradient: 2170 us with bytes, 1887 so, 1950 with values)
   struct __attribute__((packed)) Word { unsigned w; };
   static __device__ __forceinline__ Raw load(Ptr p, unsigned off) { return reinterpret_cast<const Word*>(p + (off >> 3))->w; }
   static __device__ __forceinline__ Raw load_bytes(const char* p, unsigned off) { return load(reinterpret_cast<Ptr>(p), off); }
