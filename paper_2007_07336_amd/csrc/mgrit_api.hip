@@ -309,9 +309,22 @@ struct Solver {
   //   128, 52 / 55 with 144 (32 x 32), 37.3 / 36.2 with 160 and 40 / 50 with 192 (23 x 23); 48 channels adjoint on 32 x 32 17.1 / 16.5
   //   with 8, 20.7 / 21.2 with 32; float of width 136 to 256: 5.5 (and a barrier's wait between two kernels less) / 5.0 for 8
   //   slices, level with 7.4 at 128.
-  // bf16 of width 264 to 1024, a whole solve with its gradient where there is one, lockstep / sweep: 64 rows and 64 chains 1.15 at
-  // width 272, 1.22 (adjoint 1.00) at 512, 1.07 (0.96) at 640, 0.99 (0.90) at 768; 256 rows and 16, 32, 40 chains 0.91, 1.26, 1.33 at 512,
-  // 0.92, 1.02, 1.06 at 768, 0.66, 0.85, 1.15 at 1024 (adjoint 1.05 with 40); 64 chains 1.33, 1.47 and 1.23 (adjoint 1.21, 1.21, 1.10).
+  // bf16 of width 264 to 1024: a workgroup has a CU to itself, so a sweep goes in rounds of 256 of them.  Time of a level's
+  // relaxation, lockstep / sweep, forward (adjoint), mean over m = 2, 4 and 16, at widths 1024, 768, 640 and 512, 256 rows:
+  //   80 workgroups  0.62 (0.64)   0.93 (1.01)   1.08 (1.11)   1.08 (1.24)
+  //   160            1.01 (0.95)   0.96 (1.01)   1.11 (1.15)   1.30 (1.39)
+  //   208            1.14 (1.10)   1.44 (1.43)   1.65 (1.57)   1.42 (1.51)
+  //   256            1.12 (1.14)   1.59 (1.45)   1.69 (1.56)   1.46 (1.51)
+  //   260            0.80 (0.74)   0.93 (0.93)   0.99 (0.93)   1.21 (1.11)
+  //   320            0.86 (0.79)   0.97 (0.97)   1.11 (1.08)   1.23 (1.17)
+  //   352            0.88 (0.90)   1.20 (1.12)   1.14 (1.12)   1.22 (1.24)
+  //   416            1.08 (1.04)   1.28 (1.18)   1.41 (1.27)   1.35 (1.40)
+  //   516            0.96 (0.90)   1.12 (1.05)   1.10 (1.07)   1.27 (1.25)
+  //   640            1.09 (1.04)   1.27 (1.30)   1.33 (1.28)   1.33 (1.33)
+  // and 772 of them, the fourth round begun, 1.10 (1.05) at width 1024, 1.24 (1.19) at 768.  A second or third round is therefore
+  // taken up where it is full enough.  64 rows, for which a lockstep launch reads every weight and uses half a tile, lose in the
+  // first round alone: 80 workgroups 1.15 (0.89) and 1.01 (0.86) at 1024 and 768, 160 1.39 (1.23) and 1.55 (1.40), 257 1.13 (1.06)
+  // and 1.33 (1.20).
   // Every other instance is as fast or faster with a single image at its largest size: float 16 channels on 32 x 32 7.0 / 7.1 and
   // 8.2 / 8.2, 32 on 16 x 32 9.9 / 16.3 and 11.4 / 17.9; bf16 32 channels on 32 x 32 8.0 / 8.9 and 9.2 / 10.3, 48 on 32 x 32
   // 13.3 / 14.3, 64 on 16 x 32 9.9 / 13.3 and 12.8 / 14.6; dense 1.4 .. 2.5 / 4 (float to 128), 0.9 .. 3.0 / 4.4 (bf16).
@@ -329,11 +342,16 @@ struct Solver {
     const long long most = units * (pl.L > 1 ? pl.Nl[1] + 1LL : 1LL);
     if (most * (conv ? 512 : 1024) >= 1LL << 32) return false;
     long long need = 1;
-    if (wide) need = p->q > 768 ? 160 : p->q > 640 ? 144 : p->q > 512 ? 96 : 72;
-    else if (!conv) need = p->dtype == MGRIT_FP32 && p->q > 128 ? 128 : 1;
+    const long long wgs = units * (l + 1 < pl.L ? pl.Nl[l + 1] : 1LL);
+    if (wide) {
+      const long long rounds = (wgs + 255) / 256;
+      need = p->q > 768 ? 160 : p->q > 640 ? 144 : p->q > 512 ? 96 : 72;
+      if (units > 1 && adjoint && p->q > 896) need = 200;
+      if (units > 1 && p->q > 512 && (rounds == 2 || rounds == 3)) need = rounds * (p->q > 768 ? 200 : p->q > 640 ? 172 : 144);
+    } else if (!conv) need = p->dtype == MGRIT_FP32 && p->q > 128 ? 128 : 1;
     else if (conv_sweep_ring(p->Himg, p->Wimg, p->C, p->dtype)) need = !adjoint ? 128 : p->Himg * p->Wimg >= 784 ? 144 : 192;
     else if (adjoint && p->C == 48 && p->Himg * p->Wimg > 900) need = 32;
-    return units * (l + 1 < pl.L ? pl.Nl[l + 1] : 1LL) >= need;
+    return wgs >= need;
   }
   // chains of level l that start at sweep point ci * stride, for every ci
   SweepArgs sweep_args(int l, long long stride) const {

@@ -115,3 +115,36 @@ def test_a_sample_ends_the_same_wherever_it_is_in_the_batch(q, m, N, relu):
     for x in (U, Lam):
         for i in range(1, 4):
             assert not bool((x[:, 64 * i:64 * i + 64] != x[:, :64]).any())
+
+
+# rows, chains: workgroups of 64 rows, 256 to a round
+@pytest.mark.parametrize("q,B,chains,direction,sweep", [
+    (776, 128, 79, "forward", False), (776, 128, 80, "forward", True), (776, 128, 128, "forward", True), (776, 128, 129, "forward", False),
+    (776, 128, 199, "adjoint", False), (776, 128, 200, "adjoint", True), (776, 70, 299, "forward", False), (776, 70, 300, "forward", True),
+    (776, 256, 193, "adjoint", True), (776, 64, 257, "forward", True), (904, 128, 99, "adjoint", False), (904, 128, 100, "adjoint", True),
+    (904, 128, 99, "forward", True), (648, 128, 171, "forward", False), (648, 128, 172, "forward", True), (520, 128, 143, "adjoint", False),
+    (520, 128, 144, "adjoint", True), (512, 128, 129, "forward", True)])
+def test_kernel_choice_where_a_round_of_workgroups_begins(q, B, chains, direction, sweep, monkeypatch):
+    """Which kernel relaxes the fine level, and that both give the same result there."""
+    import torch
+    import paper_2007_07336_amd as M
+    print(f"\n[case] q{q} B{B} {chains} chains {direction}", flush=True)
+    N = 2 * chains
+    g = torch.Generator(device="cuda").manual_seed(q)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")                                     # noqa: E731
+    p = M.make_problem(N=N, h=1.0 / N, m=2, max_levels=2, min_coarse=1, relax=0, max_iter=1, layer=0, act=0, dtype=1, B=B, q=q)
+    W, b, U, first = (rnd(N, q, q) / q ** 0.5).bfloat16(), 0.3 * rnd(N, q), rnd(N + 1, B, q), rnd(B, q)
+    ws, res = torch.empty(M.mgrit_adjoint_workspace_bytes(p), dtype=torch.uint8, device="cuda"), []
+    for off in (False, True):
+        if off:
+            monkeypatch.setenv("MGRIT_NO_SWEEP", "1")
+        X = torch.full_like(U, float("nan"))
+        M.mgrit_trace_begin()
+        if direction == "forward":
+            M.mgrit_fas_forward(p, W, b, first, X, ws, want_hist=False)
+        else:
+            M.mgrit_fas_adjoint(p, W, b, U, first, X, None, None, ws, want_hist=False)
+        torch.cuda.synchronize()
+        assert any("sweep" in k for k in M.mgrit_trace_end()) == (sweep and not off)
+        res.append(X)
+    assert float((res[0] - res[1]).norm()) <= 1e-3 * float(res[1].norm())
