@@ -339,18 +339,16 @@ bool conv_grad_split_geom(int B, int Himg, int Wimg, int C, bool bits, ConvGradG
   return best != 0.0;
 }
 
-template <int NB> static hipError_t launch_split(const GradArgs& a, size_t smem, hipStream_t s) {
-  const dim3 grid((unsigned)a.gchunks * (unsigned)a.layers);
-  const auto kernel = a.dbits ? &conv_grad_split_kernel<Bit, NB> : &conv_grad_split_kernel<float, NB>;
-  if (smem > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kernel, grid, dim3(CGS_NTH), smem, s, a);
+template <typename DT, int NB> static hipError_t launch_split(const GradArgs& a, size_t smem, hipStream_t s) {
+  static LdsOptIn opt;
+  const hipError_t e = opt.raise(reinterpret_cast<const void*>(conv_grad_split_kernel<DT, NB>), smem);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((conv_grad_split_kernel<DT, NB>), dim3((unsigned)a.gchunks * (unsigned)a.layers), dim3(CGS_NTH), smem, s, a);
   return hipGetLastError();
 }
 hipError_t launch_conv_grad_split(const GradArgs& a, size_t smem, hipStream_t s) {
-  return a.Nf > 16 ? launch_split<2>(a, smem, s) : launch_split<1>(a, smem, s);
+  if (a.dbits) return a.Nf > 16 ? launch_split<Bit, 2>(a, smem, s) : launch_split<Bit, 1>(a, smem, s);
+  return a.Nf > 16 ? launch_split<float, 2>(a, smem, s) : launch_split<float, 1>(a, smem, s);
 }
 
 }  // namespace mgrit
