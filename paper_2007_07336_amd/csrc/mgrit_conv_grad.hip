@@ -21,7 +21,8 @@ namespace mgrit {
 // Infinite values (and finite ones of 3.396e38 or more) have no such parts and make NaN of the sums they enter: a workgroup that
 // ends with a sum that is not finite forms its sums again from the float values.  The gradient above with a NaN in every layer 168 ->
 // 870 us (25.7 ms with a thread per output that walked the pixels in global memory), 32 channels on 16 images of 32 x 32 148 -> 1040
-// (26.8 ms).
+// (26.8 ms).  So does one that ends with sums of less than 2^-90 and not zero, whose operands may be so small, below about 1e-34, that
+// their lower parts are no bf16 numbers any more: at 1e-37 the error would be 3e-4 of the result instead of 2e-7.
 // ------------------------------------------------------------------------------------------
 constexpr int CGS_NTH = 256;
 // 4 x 4 blocks of U per thread, at most (two, and the factors as values, spill beside the sums of NB = 1)
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(CGS_NTH, 2) void conv_grad_split_kernel(GradArgs a)
       else if (bl == 0 && dbd) dbd[o] = scale * acc[j][v];
     }
   }
-  if (!(top < __builtin_inff())) bad = 1;
+  if (!(top < __builtin_inff()) || (top > 0.0f && top < 0x1p-90f)) bad = 1;
   __syncthreads();                                                  // (and the stores above before those below)
   if (!bad) return;
   // The sums from the float values: slab by slab through LDS, [pixel][channel], a thread per pair of channels (o, i) with its nine

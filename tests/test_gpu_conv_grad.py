@@ -73,6 +73,22 @@ def test_against_64_bits(wl):
         assert (np.abs(got.reshape(r.shape) - r) <= tol * m + 1e-30).all()
 
 
+@pytest.mark.parametrize("su,sl", [(1.0, 1e-34), (1.0, 1e-36), (1.0, 1e-37), (1e-37, 1.0), (1e-18, 1e-18), (0.0, 1.0)])
+@pytest.mark.parametrize("wl", [CASES[1], CASES[3], CASES[9], CASES[12]], ids=lambda w: w.name)
+def test_values_whose_lower_parts_are_too_small(wl, su, sl):
+    """States or multipliers so small that bf16 has no numbers for their lower parts: the same accuracy, but for sums that are
+    themselves rounded to multiples of 2^-149."""
+    data = I.generate(wl)
+    U, lam = _inputs(wl, 5)
+    Lam, dW, db = _raw(GpuProblem(wl, data), U * np.float32(su), lam * np.float32(sl))
+    ref, mag = _exact(wl, data, U * np.float32(su), Lam)
+    n = wl.B * wl.Himg * wl.Wimg
+    steps = -(-wl.B * wl.Himg * ((wl.Wimg + 7) & ~7) // 32) + 2 * wl.B * wl.Himg
+    tol = 2.0 ** -24 * (8 + steps) + (1e-6 if wl.act == I.TANH else 0.0)
+    for got, r, m in zip((dW, db), ref, mag):
+        assert (np.abs(got.reshape(r.shape) - r) <= tol * m + 4 * n * 2.0 ** -149).all()
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38], ids=["inf", "-inf", "nan", "3.4e38"])
 @pytest.mark.parametrize("wl", [CASES[2], CASES[3], CASES[5], CASES[7], CASES[9], CASES[10], CASES[12]], ids=lambda w: w.name)
 def test_values_without_parts(wl, value, monkeypatch):
