@@ -30,8 +30,8 @@ inline bool adjoint_transposed_copy() {
 // width 64, 2 MB 143 / 143, 64 MB 651 / 629; width 136, 2 MB 316 / 323, 68 MB 1405 / 1371; width 256, 1 MB 315 / 317, 16 MB
 // 547 / 546, 32 MB 668 / 652, 128 MB 1854 / 1766; width 448, 28 MB 1759 / 1774, 56 MB 2105 / 2061; width 512, 32 MB 1911 / 1940, 128 MB
 // 3420 / 3404; width 896, 112 MB 5513 / 5567, 448 MB 18586 / 18473; width 1024, 64 MB 5580 / 5598, 512 MB 22539 / 22636; bf16 width 64,
-// 2 MB 112 / 107; 8 channels, 12 MB 316 / 330, 49 MB 702 / 728, 128 MB 1603 / 1573; bf16 24 channels, 2 MB 272 / 259; bf16 64
-// channels, 2 GB 17093 / 15100.
+// 2 MB 112 / 107; 8 channels, 12 MB 316 / 330, 49 MB 702 / 728, 128 MB 1603 / 1573; bf16 24 channels, 2 MB 272 / 259; bf16 40
+// channels, 2 MB 446 / 349; bf16 64 channels, 0.4 MB 296 / 296, 2 MB 615 / 601, 2 GB 17093 / 14817.
 // MGRIT_ACT_VALUES=1 / 0 in the environment: values / bits whatever the size (diagnostic).
 inline bool act_factor_bits(const mgrit_problem_t* p, double bytes_as_values) {
   const char* e = getenv("MGRIT_ACT_VALUES");

@@ -220,7 +220,9 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
   constexpr bool HOLD = (CP == 16 && !(HD && !MASK && NP == 3)) || (CP == 32 && NP == 1 && (!HD || MASK));
   // act' factors requested at the start of a step (values of wider layers: only when it is done, for they would be spilled: a step
   // of 48 channels on 28 x 28 pixels 17.8 -> 14.1 us, of 64 on 16 x 32 14.4 -> 12.8).  Bits instead of bf16 values, requested
-  // early: 512 layers of 64 channels on 32 x 32 pixels, 32 images, adjoint and gradient, 17.1 -> 15.1 ms
+  // early: 512 layers of 64 channels on 32 x 32 pixels, 32 images, adjoint and gradient, 17.1 -> 14.8 ms; 64 layers on 2 images of 5 x 5
+  // 299 -> 296 us.  Above 32 channels registers are short (spilled: 48 channels 14, 64 channels 16 above 512 pixels, else 1), so
+  // what write_operand exchanges is addressed by the opaque pixel: 11 to 23 registers spilled otherwise, and those two 310 us, 15.0 ms
   constexpr bool DEARLY = CP <= 32 || MASK;
   static_assert(NBW % GB == 0 && (!RING || (CP == 64 && NP == 1)), "instances");
   typedef typename std::conditional<NP == 3, float, __bf16>::type WT;
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(64 * NWV) void conv_sweep_kernel(SweepArgs a) {
       unsigned bits[2];                                             // channels 32 i + 4 kq and on
       if constexpr (MASK && DSHARE) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) bits[i] = (unsigned)__builtin_amdgcn_ds_bpermute(4 * (c + 16 * (b / NDB)), (int)db[b % NDB][i]) >> (4 * kq);
+        for (int i = 0; i < 2; ++i) bits[i] = (unsigned)__builtin_amdgcn_ds_bpermute(4 * (cpx + 16 * (b / NDB)), (int)db[b % NDB][i]) >> (4 * kq);
       } else if constexpr (MASK) bits[0] = (unsigned)db[b] >> (4 * kq);
       if (p < npx) {
 #pragma unroll
