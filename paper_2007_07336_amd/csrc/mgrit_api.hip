@@ -1,7 +1,7 @@
 // Host side of the MGRIT-FAS library: argument checks, the level hierarchy, the workspace
 // layout and the launch schedule of the FAS V-cycle (forward and adjoint).  Every arithmetic
-// step of the method runs in the HIP kernels of mgrit_kernels.hip and mgrit_sweep.hip; this file only decides
-// which launch comes next.
+// step of the method runs in the HIP kernels of mgrit_kernels.hip, mgrit_conv_grad.hip and the three files of sweeps
+// (mgrit_sweep.hip, mgrit_wave.hip, mgrit_wide.hip); this file only decides which launch comes next.
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -302,7 +302,7 @@ struct Solver {
   // 256, in bf16 1024: all relaxation of a level's visit is one launch (march), the closing F-relaxation and the coarsest solve are
   // one launch each.  Whole solves 372 -> 226 us (5 images of 13 x 17 pixels, 24 channels, bf16), 1405 -> 797 us
   // (64 of 28 x 28, 16 channels, float), 16.6 -> 9.3 ms (32 of 32 x 32, 64 channels, bf16);
-  // 250 -> 140 us (4 samples, width 8), 655 -> 521 us (128 samples, width 256, float).
+  // 655 -> 521 us (128 samples, width 256, float); width 8 and 16, where launches are saved as well, 250 -> 67 us (4 samples, width 8).
   // Where a step of a chain is long, a level needs enough chains: a lockstep launch spreads one step over many workgroups.
   // us per step with one chain (images, or slices of 16 rows, on as many CUs), sweep / lockstep, forward and adjoint:
   //   64 channels on more than 512 pixels: 24.5 / 24.4 forward with 128 images, 27.9 / 45 with 256 (32 x 32); adjoint 50 / 42 with

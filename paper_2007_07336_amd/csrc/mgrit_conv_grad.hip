@@ -14,7 +14,7 @@ namespace mgrit {
 //   - NB = 1: each of the four wavefronts has all nine taps and the bias of every fourth step of 32 slots, and their sums are
 //     added in wavefront order at the end; NB = 2: a wavefront per pair of channel blocks.
 // 64 layers of 16 channels, 64 images of 28 x 28: 174 us (281 on the float matrix instructions, whose 143 it spent in matrix cores and
-// the rest in three shifted copies of U), errors against 64 bits 1e-7 instead of 1e-6.  Of the 174 the matrix instructions take 43,
+// the rest in three shifted copies of U), errors against 64 bits 2e-7 instead of 1e-6.  Of the 174 the matrix instructions take 43,
 // the vector instructions that split and shift 78, the bytes 103 at the copy rate; what bounds it is that a slab's load, split and
 // product follow one another with two workgroups per CU to overlap them (the sums take 80 registers).  Tried: the neighbours read
 // from the rows, with four-way bank conflicts, 179; pixels instead of channel groups along the lanes of a load 179.

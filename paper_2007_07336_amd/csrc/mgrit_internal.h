@@ -92,7 +92,8 @@ bool       conv_grad_split_geom(int B, int Himg, int Wimg, int C, bool bits, Con
 hipError_t launch_conv_grad_split(const GradArgs& a, size_t smem, hipStream_t s);
 size_t     conv_grad_partial_bytes(int B, int Himg, int Wimg, int C, int dtype, int layers);
 
-// ---- launch wrappers (defined in mgrit_kernels.hip, those of sweeps in mgrit_sweep.hip); all enqueue on `s` and return the HIP status
+// ---- launch wrappers (defined in mgrit_kernels.hip, those of sweeps in mgrit_sweep.hip, mgrit_wave.hip and mgrit_wide.hip); all
+// enqueue on `s` and return the HIP status
 hipError_t launch_step(const StepArgs& a, int layer_kind, int dtype, int groups, hipStream_t s);
 int        step_grid_blocks(const StepArgs& a, int layer_kind, int dtype, int groups);  // workgroups per group
 int        conv_tile_rows(int Himg, int Wimg, int C, int dtype);            // TH, or 0 if unsupported

@@ -19,7 +19,8 @@ namespace mgrit {
 // What bounds it is latency, and with many wavefronts on a CU the addresses: a lane's 16 bytes lie 64 from its neighbour's, and
 // such an access takes the CU 64 cycles.  (That is why it ends at width 16: with two blocks of features a layer's weights are four
 // such accesses, and 64 layers of width 32 took 138 us, as sweeps of four wavefronts 100.)
-// 16 layers of width 8, four cycles with the residual history 140 -> 64 us; 1024 layers on 256 samples 292 -> 157 us.
+// 16 layers of width 8, 4 samples, four cycles with the residual history, against sweeps of four wavefronts and a launch each: 141 -> 67
+// us; 1024 layers on 256 samples, two cycles, three levels with m = 4: 359 -> 127 us forward, 536 -> 255 adjoint and gradient.
 // ------------------------------------------------------------------------------------------
 constexpr int WAVE_NW = 8;                                          // wavefronts of a workgroup
 

@@ -20,8 +20,9 @@ namespace mgrit {
 // 128 rows and the state in and out.  1024 layers of width 1024, 256 samples: forward solve 7.36 -> 6.00 ms, adjoint with gradient
 // 13.1 -> 11.2.  Tried: four pieces in flight 6.13; a load per group of pairs that touches the lines of the next group, each
 // slice another quarter, 6.4.
-// The instances for width 769 to 1024 use all 256 registers and spill (forward 86, adjoint 61 to 64): before and behind the
-// loop over k, which is free of spills, in the writing of the operand, the end of a step and the coarse right-hand side.
+// The instances for width 769 to 1024 use all 256 registers and spill (forward 86, adjoint 61 to 64; up to 768 the adjoint about factors
+// as values 6 to 8): before and behind the loop over k, which is free of spills, in the writing of the operand, the end of a step and the
+// coarse right-hand side.  About 30 of the spilled ones are read in a step, 60 KB of a workgroup's 2 MB.
 // ------------------------------------------------------------------------------------------
 constexpr int WIDE_NWV = 8, WIDE_RB = 4, WIDE_ROWS = 16 * WIDE_RB, WIDE_STG = 2 * 2048;     // staging bytes of a wavefront, two pieces
 constexpr int wide_kp(int q) { return (q + 127) / 128 * 128; }
