@@ -25,11 +25,13 @@
  *
  * Environment (diagnostic switches, read at every call; results agree with the default path to rounding).
  * MGRIT_NO_SWEEP=1 makes the library use one launch per layer step also where it would fuse many steps
- * into one launch: dense layers of width at most 256, and convolution layers whose images fit on a compute unit
+ * into one launch: dense layers of width at most 256, in bf16 1024, and convolution layers whose images fit on a compute unit
  * (in float at most 16 channels and 1024 pixels or 32 and 512; in bf16 at most 48 channels or exactly 64 and 1024
- * pixels, 56 and 512; no stacks with fully connected layers).  A level with few samples and intervals takes one launch
- * per step all the same where that is faster (float of width 136 to 256, 64 channels on more than 512 pixels, the
- * adjoint of 48 channels on more than 900).  MGRIT_GRAD_NARROW=1 keeps the
+ * pixels, 56 and 512; of stacks with fully connected layers the forward solve's levels in which those open intervals).  A level
+ * with few samples and intervals takes one launch per step all the same where that is faster (float of width 136 to 256, bf16 wider
+ * than 256, 64 channels on more than 512 pixels, the adjoint of 48 channels on more than 900).
+ * MGRIT_ACT_VALUES=1 / 0 stores the act' factors of ReLU layers as values / as bits whatever their number.
+ * MGRIT_GRAD_NARROW=1 keeps the
  * parameter gradient of dense layers of width 512 and more on the 128x128 tiles of narrower layers.
  * MGRIT_MASKED_STEP=1 sends dense layer steps whose batch, width and contraction length are whole multiples of
  * the tile through the bounds-masked loop that ragged shapes use.
