@@ -17,8 +17,8 @@ namespace mgrit {
 // What bounds it at width 1024: the contraction alone takes 31 us a step (LDS: 8 MB a step; the matrix instructions 14), with its
 // weights, 2 MB a step and workgroup from L2, 55 (adjoint 67): the first of a chain's slices to ask for a line waits for memory, the
 // others with it, and only two pairs of pieces can be requested ahead.  A lockstep launch takes 73 (97) us, reads the weights once per
-// 128 rows and the state in and out.  1024 layers of width 1024, 256 samples: forward solve 7.36 -> 6.00 ms, adjoint with gradient
-// 13.1 -> 11.2.  Tried: four pieces in flight 6.13; a load per group of pairs that touches the lines of the next group, each
+// 128 rows and the state in and out.  1024 layers of width 1024, 256 samples: forward solve 7.21 -> 5.95 ms, adjoint with gradient
+// 13.0 -> 11.1.  Tried: four pieces in flight 6.13; a load per group of pairs that touches the lines of the next group, each
 // slice another quarter, 6.4.
 // The instances for width 769 to 1024 use all 256 registers and spill (forward 86, adjoint 61 to 64; up to 768 the adjoint about factors
 // as values 6 to 8): before and behind the loop over k, which is free of spills, in the writing of the operand, the end of a step and the
